@@ -287,7 +287,7 @@ hipError_t wave_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hi
 }  // namespace
 
 namespace {
-// Products that fill 256 x 128 tiles reasonably go to the split-bf16 kernel (gemm_split.hpp).
+// Products that fill 256 x 128 tiles reasonably go to the split-fp16 kernel (gemm_split.hpp).
 bool split_gemm_eligible(const GemmJob &j)
 {
     if (!tuning().use_split_gemm || (j.mode != kStore && j.mode != kSubLowerSkip && j.mode != kSubRect && j.mode != kAddRect))
@@ -306,6 +306,8 @@ bool split_gemm_eligible(const GemmJob &j)
     if ((long)j.K * j.lda * 4 > 0x7fffffffl || (long)j.K * j.ldb * 4 > 0x7fffffffl) return false;
     if ((long)j.M * j.ldc * 4 > 0x7fffffffl) return false;
     if (((uintptr_t)j.A) % 4 || ((uintptr_t)j.B) % 4) return false;
+    // the epilogue decides about four columns of a pivot band at a time
+    if (j.mode != kStore && (j.p0 % 4 != 0 || (j.p1 % 4 != 0 && j.p1 < j.N))) return false;
     if (j.mode == kSubLowerSkip) return j.M == j.N;
     return true;
 }
@@ -314,13 +316,29 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
 {
     GemmSTable tab;
     tab.count = 0;
-    tab.debug = (int)tuning().wave_debug;
     long blocks = 0;
     double flops = 0.0;
     auto flush = [&]() -> hipError_t {
         if (tab.count == 0) return hipSuccess;
-        KFAC_LAUNCH(KFAC_K_GEMM_SPLIT, s, gemm_split_kernel, dim3((unsigned)blocks), dim3(256), 0, tab);
-        timing_work(flops, 6.0 * flops);
+        // tile ranges of the XCDs, of equal cost: the K stages of a tile and about twelve more for its start and end
+        double total = 0.0;
+        auto cost = [&](const GemmSProb &p) { return (p.K + S_KT - 1) / S_KT + 12.0; };
+        for (int k = 0; k < tab.count; ++k)
+            total += cost(tab.p[k]) * ((k + 1 < tab.count ? tab.p[k + 1].blk_start : (int)blocks) - tab.p[k].blk_start);
+        int most = 1, x = 1;
+        double before = 0.0;
+        tab.xcd[0] = 0;
+        tab.xcd[8] = (int)blocks;
+        for (int k = 0; k < tab.count; ++k) {
+            const int first = tab.p[k].blk_start, n = (k + 1 < tab.count ? tab.p[k + 1].blk_start : (int)blocks) - first;
+            const double c = cost(tab.p[k]);
+            for (; x < 8 && total * x / 8 <= before + c * n; ++x) tab.xcd[x] = first + (int)((total * x / 8 - before) / c);
+            before += c * n;
+        }
+        for (; x < 8; ++x) tab.xcd[x] = (int)blocks;
+        for (int k = 0; k < 8; ++k) most = std::max(most, tab.xcd[k + 1] - tab.xcd[k]);
+        KFAC_LAUNCH(KFAC_K_GEMM_SPLIT, s, gemm_split_kernel<4>, dim3((unsigned)(8 * most)), dim3(256), 0, tab);
+        timing_work(flops, 3.0 * flops);
         tab.count = 0;
         blocks = 0;
         flops = 0.0;
@@ -337,9 +355,10 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         p.mode = j.mode; p.p0 = j.p0; p.p1 = j.p1;
         p.doff = (int)std::min<long>(j.doff, 1l << 30);
         if (j.mode == kSubLowerSkip) p.doff = 0;
+        p.krow = j.krow;
         p.gate = j.gate; p.gate_cond = j.gate_cond;
         p.blk_start = (int)blocks;
-        for (int I = 0; I < p.tI; ++I) blocks += split_row_len(p.mode, p.tJ, p.doff, I);
+        for (int I = 0; I < p.tI; ++I) blocks += split_row_len(p.mode, p.tJ, p.doff, I, S_BM);
         if (!j.gate) flops += gemm_job_flops(j);       // a gated product may be skipped on the device: not counted
         if (tab.count == kMaxProblems) {
             hipError_t e = flush();
@@ -450,7 +469,8 @@ hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work, si
             t.A = j.A + k0 * j.lda;
             t.B = j.B + k0 * j.ldb;
             t.K = (int)std::min<long>(per, j.K - k0);
-            t.wide_tiles = true;            // a slice stays on the split-bf16 kernel whatever its depth
+            t.krow = (int)k0;
+            t.wide_tiles = true;            // a slice stays on the split-fp16 kernel whatever its depth
             if (made > 0) {
                 t.C = part + (size_t)(made - 1) * stride;
                 t.ldc = j.N;

@@ -1,30 +1,10 @@
-// C = A^T B for fp32 operands (both K-major) on the bf16 MFMA units, at fp32 accuracy.
+// C = A^T B for fp32 operands (both K-major) on the fp16 MFMA units, at fp32 accuracy: the split-fp16 core of
+// split_common.hpp with the epilogues of the preconditioning (Eq. 5 of the DP-KFAC paper) and of the blocked
+// inversion's rank-k updates and panel products (section 5.2).
 //
-// MI355X multiplies bf16 matrices sixteen times faster than fp32 ones (2.5 PFLOP/s against 157 TFLOP/s),
-// so an fp32 product is cheaper as several bf16 products.  Every fp32 operand element is cut into three bf16
-// pieces, x = x1 + x2 + x3 (x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2): 3 x 8 significant bits,
-// the sum is exact), and the product keeps the six piece products down to 2^-16 of the leading one,
-//     a b  ~  a1 b1 + a1 b2 + a2 b1 + a1 b3 + a3 b1 + a2 b2,
-// each exact in the fp32 accumulator of v_mfma_f32_32x32x16_bf16.  The terms left out (a2 b3, a3 b2, a3 b3)
-// are below 2^-24 |a b|, the size of the rounding of an fp32 product: the result is as accurate as an fp32
-// MFMA product, for 6/16 of its MFMA time.
-//
-// Used for the preconditioning products (Eq. 5 of the DP-KFAC paper) and for the rank-k updates and panel
-// products of the blocked inversion (section 5.2).
-//
-// A workgroup of four wavefronts owns a 256 x 128 tile of C (256 columns of A, 128 of B); wave (wm, wn) owns
-// 128 x 64 of it: 4 x 2 MFMA tiles, 128 accumulator registers.  K is walked in stages of 16 rows = one MFMA
-// step.  The fp32 panels [16 k][256 | 128 columns] are copied from global memory straight into LDS by
-// buffer_load_dwordx4 ... lds (no staging registers) in a ring of three stage buffers, two stages in flight:
-// a stage waits for loads issued two stages earlier, which is what hides the latency of the loads behind the
-// 48 MFMAs of a stage (with the panels fetched through registers one stage ahead, the kernel spent three
-// quarters of its time waiting for them).  A lane reads the eight k of its row of an operand tile from the
-// panel (lanes along the columns: conflict-free), cuts them into the three pieces in registers and feeds the
-// MFMAs; the conversions (5.5 VALU operations per element) are issued in the shadow of the MFMAs.  Three stage
-// buffers take 72 KB: two workgroups share a CU, so the epilogue of one runs beside the MFMAs of the other.
-//
-// Rows past K lie outside the buffer range and arrive as zeros.  Columns past M (or N) may hold neighbouring
-// data (a 16-byte piece is not split); they only feed outputs that are never stored.
+// Bound: fp16 MFMA, three products per fp32 product (2.5 PFLOP/s / 3 = 830 TFLOP/s in flops of the definition;
+// v_mfma_f32_32x32x16_f16 reaches 2.1 of the 2.5 when fed from registers).  Two workgroups share a CU, so the
+// prologue and the read-modify-write epilogue of one run beside the MFMAs of the other.
 #pragma once
 
 #include "split_common.hpp"
@@ -42,37 +22,44 @@ struct GemmSProb {
     int mode;        // kStore, kSubLowerSkip, kSubRect or kAddRect
     int p0, p1;
     int doff;        // the subtracting modes touch n <= m + doff (0 for kSubLowerSkip)
+    int krow;        // first row of the operands inside the matrices they are slices of
     const int *gate; // null, or two float bit patterns: leave C alone unless their product exceeds gate_cond
     float gate_cond;
 };
 
 struct GemmSTable {
     int count;
-    int debug;       // measurement only (results are wrong): 8 no epilogue
+    int xcd[9];      // XCD x takes the tiles xcd[x] .. xcd[x + 1] - 1
     GemmSProb p[kMaxProblems];
 };
 
-// column tiles of tile row i: all of them, or those that reach the line n = m + doff
-__host__ __device__ inline int split_row_len(int mode, int tJ, int doff, int i)
+// column tiles of tile row i (of bm rows): all of them, or those that reach the line n = m + doff
+__host__ __device__ inline int split_row_len(int mode, int tJ, int doff, int i, int bm)
 {
     if (mode == kStore) return tJ;
-    const long last = ((long)i * S_BM + S_BM - 1 + doff) / S_BN + 1;
+    const long last = ((long)i * bm + bm - 1 + doff) / S_BN + 1;
     return (int)(last < tJ ? last : tJ);
 }
 
+template <int NTI>
 __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab)
 {
-    __shared__ __attribute__((aligned(16))) float lds[S_LDS_FLOATS];
+    constexpr int BM = 64 * NTI;
+    __shared__ __attribute__((aligned(16))) SplitLds<NTI> L;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = w >> 1, wn = w & 1;
 
-    // Every XCD takes a contiguous range of tile numbers (its L2 then sees few operand panels), and the tiles of
-    // a product are numbered in groups of four tile rows, column by column inside a group: the tiles that run
-    // at the same time share their A panels (four per group) and their B panels (one per four tiles).
-    const int bid = xcd_block_id();
+    // Every XCD (workgroup i runs on XCD i mod 8) takes a contiguous range of tile numbers, so that its L2 sees few
+    // operand panels; the ranges are of equal K stages, not of equal tiles (with equal tiles the XCDs that got the
+    // deep products of a mixed launch worked twice as long as the others).  The tiles of a product are numbered in
+    // groups of four tile rows, column by column inside a group: the tiles that run at the same time share their A
+    // panels (four per group) and their B panels (one per four tiles).
+    const int x = blockIdx.x & 7;
+    const int bid = tab.xcd[x] + (int)(blockIdx.x >> 3);
+    if (bid >= tab.xcd[x + 1]) return;
     int pi = 0;
     while (pi + 1 < tab.count && bid >= tab.p[pi + 1].blk_start) ++pi;
     const GemmSProb &pr = tab.p[pi];
@@ -84,7 +71,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const bool rows_skip = pr.mode == kSubLowerSkip;
     const bool add = pr.mode == kAddRect;
     {
-        auto row_len = [&](int i) { return i >= pr.tI ? 0 : split_row_len(pr.mode, pr.tJ, pr.doff, i); };
+        auto row_len = [&](int i) { return i >= pr.tI ? 0 : split_row_len(pr.mode, pr.tJ, pr.doff, i, BM); };
         int g = 0;
         for (;;) {
             const int c = row_len(4 * g) + row_len(4 * g + 1) + row_len(4 * g + 2) + row_len(4 * g + 3);
@@ -112,214 +99,130 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
         }
         I = 4 * g + i;
     }
-    const int m0 = I * S_BM, n0 = J * S_BN;
+    const int m0 = I * BM, n0 = J * S_BN;
     if (lower) {
         // tiles wholly inside the pivot rows or columns are left untouched
-        const int m1 = min(m0 + S_BM, pr.M), n1 = min(n0 + S_BN, pr.N);
+        const int m1 = min(m0 + BM, pr.M), n1 = min(n0 + S_BN, pr.N);
         if ((rows_skip && m0 >= pr.p0 && m1 <= pr.p1) || (n0 >= pr.p0 && n1 <= pr.p1)) return;
     }
 
-    const int lda = pr.lda, ldb = pr.ldb;
-    const int nstages = (pr.K + S_KT - 1) / S_KT;
-    int4v rsrcA, rsrcB;
+    const long lda = pr.lda, ldb = pr.ldb;
+    SplitSrc<NTI, kRows> src;
     {
-        const unsigned long ba = (unsigned long)pr.A, bb = (unsigned long)pr.B;
-        const long na = (long)pr.K * lda * 4, nb = (long)pr.K * ldb * 4;
-        rsrcA.x = (int)(unsigned)ba; rsrcA.y = (int)(unsigned)(ba >> 32);
-        rsrcA.z = na > 0x7fffffffl ? 0x7fffffff : (int)na; rsrcA.w = 0x00020000;
-        rsrcB.x = (int)(unsigned)bb; rsrcB.y = (int)(unsigned)(bb >> 32);
-        rsrcB.z = nb > 0x7fffffffl ? 0x7fffffff : (int)nb; rsrcB.w = 0x00020000;
+        const long na = (long)pr.K * lda * 4, nb = (long)pr.K * ldb * 4;      // the host checked: below 2 GiB
+        src.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A), 0, (int)na, 0x00020000);
+        src.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.B), 0, (int)nb, 0x00020000);
+        src.lda4 = (unsigned)lda * 4u;
+        src.ldb4 = (unsigned)ldb * 4u;
+        src.nstages = (pr.K + S_KT - 1) / S_KT;
+        src.init_thread(tid);
+        src.lim_a = pr.M - m0;
+        src.lim_b = pr.N - n0;
+        src.rows = pr.K;
+        src.diag_a = m0 - pr.krow;
+        src.diag_b = n0 - pr.krow;
+        src.off_a = 4u * (unsigned)m0;
+        src.off_b = 4u * (unsigned)n0;
+        const int ca = m0 + src.col_a(0), cb = n0 + src.col_b(0);
+        src.va[0] = ca < pr.M ? (unsigned)ca * 4u + 4u * (unsigned)src.kq * src.lda4 : W_OOB;
+        src.vb[0] = cb < pr.N ? (unsigned)cb * 4u + 4u * (unsigned)src.kq * src.ldb4 : W_OOB;
     }
-    // this wave's copies of a stage: rows 4 w .. 4 w + 3 of the A panel (one instruction per row: 64 lanes x
-    // 4 columns) and of the B panel (one instruction per two rows: 32 lanes x 4 columns each)
-    const unsigned lds_base = (unsigned)(unsigned long)(__attribute__((address_space(3))) float *)lds;
-    const int ca = m0 + 4 * lane, cb = n0 + 4 * (lane & 31);
-    const unsigned voa = ca < pr.M ? (unsigned)(ca * 4) : W_OOB;
-    const unsigned vob = cb < pr.N ? (unsigned)(((lane >> 5) * ldb + cb) * 4) : W_OOB;
-    const unsigned rowa = (unsigned)lda * 4u, rowb = (unsigned)ldb * 4u;
-    const int dbg = tab.debug;
-    auto issue = [&](int g) {
-        const bool live_stage = g < nstages;
-        const unsigned buf = lds_base + (unsigned)((g % S_NSTAGE) * S_STAGE * 4);
-        const unsigned k0 = (unsigned)(g * S_KT + 4 * w);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            dma16(buf + (unsigned)((4 * w + r) * S_BM * 4), live_stage ? voa : W_OOB, rsrcA,
-                  live_stage ? (k0 + r) * rowa : 0u);
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-            dma16(buf + (unsigned)((S_PANEL_A + (4 * w + 2 * r) * S_BN) * 4), live_stage ? vob : W_OOB, rsrcB,
-                  live_stage ? (k0 + 2 * r) * rowb : 0u);
-    };
-
-    floatx16 acc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-
     const int lr = lane & 31, lg = lane >> 5;
-    // a wave whose 128 x 64 part lies wholly above the line n = m + doff has nothing to compute
-    const bool idle = lower && (n0 + wn * 64 > m0 + wm * 128 + 127 + pr.doff);
-    const int fa = 8 * lg * S_BM + wm * 128 + lr;                    // + e * S_BM (k) + t * 32 (tile)
-    const int fb = S_PANEL_A + 8 * lg * S_BN + wn * 64 + lr;
+    // row tiles this wavefront has to compute: none above the line n = m + doff or past the edges
+    const int mleft = pr.M - (m0 + wm * (BM / 2));
+    const bool idle = (lower && (n0 + wn * 64 > m0 + wm * (BM / 2) + BM / 2 - 1 + pr.doff)) || mleft <= 0 ||
+                      n0 + wn * 64 >= pr.N;
+    const int rows = idle ? 0 : (mleft + 31) / 32;
+    floatx16 acc[2 * NTI];
+    float none[NTI];
+    split_tile<NTI, kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid);
+    __syncthreads();
+    if (idle) return;
 
-    issue(0);
-    issue(1);
-    asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
-    for (int g = 0; g < nstages; ++g) {
-        issue(g + 2);        // into the buffer every wave left at the last barrier (stages past the end: zeros)
-        if (!idle) {
-            const float *buf = lds + (g % S_NSTAGE) * S_STAGE;
-            suint4 b1[2], b2[2], b3[2];
-            float xa[8], xn[8];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                float x[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) x[e] = buf[fb + e * S_BN + t * 32];
-                if (t == 0) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) xa[e] = buf[fa + e * S_BM];
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) xn[e] = buf[fa + e * S_BM + 32];
-                }
-                split_pieces(x, b1[t], b2[t], b3[t]);
-            }
-            suint4 c1, c2, c3;          // pieces of the A tile being multiplied
-            split_pieces(xa, c1, c2, c3);
-            __builtin_amdgcn_sched_barrier(0);
-            // Tile ti: its twelve products, with the conversions of tile ti + 1 (and the panel reads of tile
-            // ti + 2) issued between them, four VALU operations in the shadow of every MFMA.
-#pragma unroll
-            for (int ti = 0; ti < 4; ++ti) {
-                suint4 n1, n2, n3;
-                if (ti + 1 < 4) split_pieces(xn, n1, n2, n3);
-                if (ti + 2 < 4) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) xn[e] = buf[fa + e * S_BM + (ti + 2) * 32];
-                }
-                const sbf16x8 A1 = __builtin_bit_cast(sbf16x8, c1), A2 = __builtin_bit_cast(sbf16x8, c2),
-                              A3 = __builtin_bit_cast(sbf16x8, c3);
-                {
-                    // Smallest terms first.  The two column tiles alternate: an MFMA that accumulates into the result of the one
-                    // just before it waits for that result (a single chain reaches 67 % of the rate of two, measured), and the
-                    // order of the six terms of each accumulator is what fixes the bits, not the interleaving.
-                    const sbf16x8 P1 = __builtin_bit_cast(sbf16x8, b1[0]), P2 = __builtin_bit_cast(sbf16x8, b2[0]),
-                                  P3 = __builtin_bit_cast(sbf16x8, b3[0]);
-                    const sbf16x8 Q1 = __builtin_bit_cast(sbf16x8, b1[1]), Q2 = __builtin_bit_cast(sbf16x8, b2[1]),
-                                  Q3 = __builtin_bit_cast(sbf16x8, b3[1]);
-                    floatx16 c = acc[ti * 2], d = acc[ti * 2 + 1];
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2, P2, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2, Q2, d, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A3, P1, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A3, Q1, d, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, P3, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Q3, d, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2, P1, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A2, Q1, d, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, P2, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Q2, d, 0, 0, 0);
-                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, P1, c, 0, 0, 0);
-                    d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A1, Q1, d, 0, 0, 0);
-                    acc[ti * 2] = c;
-                    acc[ti * 2 + 1] = d;
-                }
-                if (ti + 1 < 4) {
-#pragma unroll
-                    for (int k = 0; k < 12; ++k) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-                        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // four VALU
-                        if (ti + 2 < 4 && k < 8) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-                    }
-                    c1 = n1; c2 = n2; c3 = n3;
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-        // at most the copies of the stage issued last are still on their way, then meet the other waves
-        asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
-    }
-    // the zero-filling copies of the stages past the end may still be landing
-    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-    if (idle || (dbg & 8)) return;
-
-    // ---- epilogue: acc[ti*2 + tj][v] = C[m0 + wm*128 + ti*32 + 8*(v>>2) + 4*lg + (v&3)][n0 + wn*64 + tj*32 + lr]
+    // ---- epilogue: acc[ti*2 + tj][v] = C[m0 + wm*BM/2 + ti*32 + 8*(v>>2) + 4*lg + (v&3)][n0 + wn*64 + tj*32 + lr]
     // A lane of the MFMA result holds single elements of many rows: written or updated from there, every memory
     // instruction moves 4 bytes per lane.  Instead each wavefront passes its part through LDS (the ring is free
-    // now: 18 KB per wavefront), 32 rows x 64 columns at a time, and reads it back with 16 lanes along a row, four
-    // columns each: the accesses to C are 16 bytes per lane and 256 contiguous bytes per row.  (C need not be
-    // 16-byte aligned: the vector type below asks for 4.)  A chunk that the bounds of the product, the line
-    // n = m + doff or the pivot rows and columns cut through takes the element-wise path further down.
-    const int mw = m0 + wm * 128, nw = n0 + wn * 64;
-    const long ldc = pr.ldc;
-    const int p0 = pr.p0, p1 = pr.p1, doff = pr.doff;
-    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    // now), 32 rows x 64 columns at a time, and reads it back with 16 lanes along a row, four columns each: the
+    // accesses to C are 16 bytes per lane and 256 contiguous bytes per row.  (C need not be 16-byte aligned: buffer
+    // accesses ask for 4.)
+    // Loads and stores share one counter and complete in order: a load issued after a store is not seen before that
+    // store has been acknowledged.  So the old values are fetched in two batches of two chunks, the results stay in
+    // registers, and all stores come last.
+    // What limits this code is its size: it runs once per workgroup, and every line of it that is not in the
+    // instruction cache is fetched from memory while the wavefront waits.  An unrolled element-wise path for the
+    // chunks that the bounds, the line n = m + doff or the pivot rows and columns cut through (100 KB of code) made the
+    // epilogue take 40 us whatever K, more than half of a rank-256 update.  Such a chunk is now read like any other, and
+    // stored with a 16-byte access by the lanes whose four columns are all wanted and up to three 4-byte accesses by
+    // the others; what must not be written gets an offset outside the buffer.
+    const int mw = m0 + wm * (BM / 2), nw = n0 + wn * 64;
+    const int ldc = pr.ldc;
     constexpr int EP = 68;                                   // LDS row pitch of a chunk (floats)
-    float *wl = lds + w * (S_LDS_FLOATS / 4);
+    float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
     const int rr = lane >> 4, c4 = (lane & 15) * 4;
-    const unsigned lane_off = (unsigned)(4 * lg) * (unsigned)pr.ldc + (unsigned)lr;
-    auto row_ptr = [&](int t, int r) { return pr.C + ((long)(mw + (t >> 1) * 32 + r) * ldc + nw + (t & 1) * 32); };
-    auto live = [&](int m, int n) {
-        if (!lower) return m < pr.M && n < pr.N;
-        return m < pr.M && n < pr.N && n <= m + doff && !(rows_skip && m >= p0 && m < p1) && !(n >= p0 && n < p1);
-    };
+    // the host checked that M rows of C are below 2 GiB
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.C, 0, (int)((long)pr.M * ldc * 4), 0x00020000);
+    const unsigned vo = (unsigned)(rr * ldc + c4) * 4u;
+    const float sign = (lower && !add) ? -1.f : 1.f;
+    auto row_off = [&](int ti, int q) { return (unsigned)((mw + ti * 32 + 4 * q) * ldc + nw) * 4u; };
+    floatx4 out[NTI][8];
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti) {
-        const int mr0 = mw + ti * 32;
-        bool whole = mr0 + 32 <= pr.M && nw + 64 <= pr.N;                    // uniform over the wavefront
-        if (lower)
-            whole = whole && nw + 63 <= mr0 + doff && !(rows_skip && mr0 < p1 && mr0 + 32 > p0) &&
-                    !(nw < p1 && nw + 64 > p0);
-        if (whole) {
+    for (int t0 = 0; t0 < NTI; t0 += 2) {
 #pragma unroll
-            for (int tj = 0; tj < 2; ++tj)
+        for (int ti = t0; ti < t0 + 2; ++ti)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                out[ti][q] = floatx4{0.f, 0.f, 0.f, 0.f};
+                if (lower) {
+                    const sint4 v = __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rc, vo + row_off(ti, q), 0, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) out[ti][q][e] = __int_as_float(v[e]);
+                }
+            }
+#pragma unroll
+        for (int ti = t0; ti < t0 + 2; ++ti) {
+#pragma unroll
+            for (int tj = 0; tj < 2; ++tj) {
+                split_unscale<NTI>(acc[2 * ti + tj], L, wm * (BM / 2) + ti * 32, wn * 64 + tj * 32 + lr, lg);
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     wl[(8 * (v >> 2) + 4 * lg + (v & 3)) * EP + tj * 32 + lr] = acc[ti * 2 + tj][v];
+            }
             // (LDS operations of one wavefront complete in order: no barrier between these writes and the reads)
-            float *crow = pr.C + ((long)(mr0 + rr) * ldc + nw + c4);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                f4u val[4], old[4];
+            for (int q = 0; q < 8; ++q) {
+                const floatx4 val = *reinterpret_cast<const floatx4 *>(wl + (4 * q + rr) * EP + c4);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = 4 * (4 * h + q);      // + rr, in crow and below
-                    val[q] = *reinterpret_cast<const f4u *>(wl + (row + rr) * EP + c4);
-                    if (lower) old[q] = *reinterpret_cast<const f4u *>(crow + (long)row * ldc);
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int row = 4 * (4 * h + q);
-                    f4u out = val[q];
-                    if (lower) out = add ? old[q] + val[q] : old[q] - val[q];
-                    *reinterpret_cast<f4u *>(crow + (long)row * ldc) = out;
-                }
-            }
-            continue;
-        }
-        // element-wise: the 16 loads of a tile are issued together
-#pragma unroll
-        for (int tj = 0; tj < 2; ++tj) {
-            const int t = ti * 2 + tj;
-            const int n = nw + tj * 32 + lr;
-            float old[16];
-            if (lower) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int r = 8 * (v >> 2) + (v & 3);
-                    old[v] = live(mr0 + r + 4 * lg, n) ? row_ptr(t, r)[lane_off] : 0.f;
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int r = 8 * (v >> 2) + (v & 3);
-                if (!live(mr0 + r + 4 * lg, n)) continue;
-                row_ptr(t, r)[lane_off] = !lower ? acc[t][v] : (add ? old[v] + acc[t][v] : old[v] - acc[t][v]);
+                for (int e = 0; e < 4; ++e) out[ti][q][e] = __builtin_fmaf(sign, val[e], out[ti][q][e]);
             }
         }
+        __builtin_amdgcn_sched_barrier(0);
     }
+    // (The whole offset of an access sits in its vector register: the range check looks at that one alone; and with an
+    // offset in a scalar register the compiler takes it that a wide store has read its data at once, where on this chip
+    // the instruction behind it could still change the last lanes' last word, seen in the results.)
+    // Columns n .. n + 3 of row m are wanted as far as wanted(m) says; p0 and p1 are multiples of 4 (or p1 is past the
+    // edge), so a pivot band takes a lane's columns whole.
+    const int n = nw + c4;
+    const bool pcol = lower && n >= pr.p0 && n < pr.p1;
+    auto wanted = [&](int m) {
+        const bool skip = m >= pr.M || pcol || (rows_skip && m >= pr.p0 && m < pr.p1);
+        const int limit = lower ? min(pr.N, m + pr.doff + 1) : pr.N;
+        return skip ? 0 : limit - n;
+    };
+#pragma unroll
+    for (int ti = 0; ti < NTI; ++ti)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int have = wanted(mw + ti * 32 + 4 * q + rr);
+            const unsigned o = vo + row_off(ti, q);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, out[ti][q]), rc, have >= 4 ? o : W_OOB, 0, 0);
+            if (__any(have > 0 && have < 4)) {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(out[ti][q][e]), rc,
+                                                          have < 4 && e < have ? o + 4u * (unsigned)e : W_OOB, 0, 0);
+            }
+        }
 }
 
 }  // namespace kfac

@@ -16,7 +16,7 @@
 //   syrk_conv3_kernel      : 3x3 convolution inputs, patch matrix never built (syrk_conv3.hpp)
 //   syrk_small_nchw_kernel : narrow NCHW fp32, no LDS staging (syrk_small.hpp)
 //   syrk_bf16_kernel       : bf16 inputs on the bf16 MFMA units (syrk_bf16.hpp)
-//   syrk_split_kernel      : wide fp32 inputs as three bf16 pieces on the bf16 MFMA units (syrk_split.hpp)
+//   syrk_split_kernel      : wide fp32 inputs as two fp16 pieces on the fp16 MFMA units (syrk_split.hpp)
 //   syrk_reduce_kernel     : sums the slices in a fixed order (deterministic), applies scale and
 //                            the running average, writes both triangles.
 // The planner below picks the kernel and the split of K per factor and groups
@@ -684,11 +684,10 @@ void plan_group(const FactorJob *jobs, const std::vector<int> &idx, std::vector<
                 tpb_j = std::max<long>(1, std::min<long>(tpb_j, 0x7fffffffl / (64 * jobs[j].ld) - 1));
             if (p.cfg == kBf16Cfg && jobs[j].layout == kRows)
                 tpb_j = std::max<long>(1, std::min<long>(tpb_j, 0x7fffffffl / (2 * H_KT * jobs[j].ld) - 1));
-            // The bf16 MFMA adds its sixteen products to the accumulator with the low bits of the aligned addends cut
-            // off: on non-negative inputs (post-ReLU activations) every stage biases the sum down by about a
-            // quarter of an ulp, measured -1.6e-8 per stage relative to the result (-3e-6 over 200 stages, where
-            // the fp32 MFMA kernels stay at 2.5e-7).  Slices are therefore kept short; the reduction adds them in
-            // fp32 with round-to-nearest.
+            // The MFMA adds its sixteen products to the accumulator with the low bits of the aligned addends cut off: on
+            // non-negative inputs (post-ReLU activations) every instruction biases the sum down a little (measured
+            // -9e-8 of the result over 256 stages of three products).  Slices are kept short; the reduction adds them
+            // in fp32 with round-to-nearest.
             if (p.cfg == kSplitCfg) tpb_j = std::max<long>(1, std::min<long>(tpb_j, tu.split_syrk_max_stages));
             p.splits = (int)((ktiles + tpb_j - 1) / tpb_j);
             // every element of the block-tile kernels' partials is summed serially over the splits by one
@@ -1031,11 +1030,15 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
                 break;
             }
             case kSplitCfg: {
+                bool ragged = false;
+                for (int k = 0; k < tab.count; ++k) ragged |= tab.p[k].hw % 4 != 0;
                 if (layout == kRows)
-                    KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, syrk_split_kernel<kRows>, dim3(blocks), dim3(256), 0, tab);
+                    KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, (syrk_split_kernel<kRows, false>), dim3(blocks), dim3(256), 0, tab);
+                else if (ragged)
+                    KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, (syrk_split_kernel<kNCHW, true>), dim3(blocks), dim3(256), 0, tab);
                 else
-                    KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, syrk_split_kernel<kNCHW>, dim3(blocks), dim3(256), 0, tab);
-                timing_work(flops, 6.0 * flops);
+                    KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, (syrk_split_kernel<kNCHW, false>), dim3(blocks), dim3(256), 0, tab);
+                timing_work(flops, 3.0 * flops);
                 e = hipGetLastError();
                 break;
             }
