@@ -357,7 +357,8 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // classes of equal order, in sequences of at most kMaxInvClasses
+    // classes of equal numbers of pivot blocks, in sequences of at most kMaxInvClasses (up to order 1280 there are 20:
+    // one sequence)
     int c0 = 0;
     while (c0 < total) {
         InvSeq q;
@@ -367,21 +368,24 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
         q.refine_cond = tuning().invert_refine ? (float)tuning().invert_fused_refine_cond : -1.f;
         int c = c0;
         while (c < total && q.nclass < kMaxInvClasses) {
+            const int nblk = (jobs[idx[c]].n + FNB - 1) / FNB;
             int e = c;
-            while (e < total && jobs[idx[e]].n == jobs[idx[c]].n) ++e;
+            while (e < total && (jobs[idx[e]].n + FNB - 1) / FNB == nblk) ++e;
             InvClass &k = q.c[q.nclass++];
-            k.first = c; k.count = e - c; k.n = jobs[idx[c]].n; k.nblk = (k.n + FNB - 1) / FNB;
+            k.first = c; k.count = e - c; k.nblk = nblk;
             k.per = 0; k.blk_start = 0;
             c = e;
         }
         c0 = c;
         auto lay_out = [&](InvSeq &t, int nclass, auto per_fn) {
-            long blocks = 0;
             t.nclass = nclass;
+            t.nprob = t.c[nclass - 1].first + t.c[nclass - 1].count - t.c[0].first;
+            t.heads = (t.nprob + 7) & ~7;
+            long blocks = t.heads;
             for (int k = 0; k < nclass; ++k) {
                 t.c[k].per = per_fn(t.c[k]);
                 t.c[k].blk_start = (int)blocks;
-                blocks += (long)t.c[k].per * seq_slots(t.c[k].count);
+                blocks += seq_class_blocks(t.c[k].count, t.c[k].per);
             }
             return blocks;
         };
@@ -403,7 +407,7 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
             KFAC_LAUNCH(KFAC_K_INV_STEP, s, fsweep_step_kernel, dim3((unsigned)blocks), dim3(256), 0, q);
             {   // a rank-64 update of the triangle, n^2 * 64 flops per matrix; every tile also forms its own W = V P
                 double fl = 0.0;
-                for (int k = 0; k < active; ++k) fl += (double)q.c[k].count * q.c[k].n * q.c[k].n * FNB;
+                for (int k = q.c[0].first; k < q.c[0].first + q.nprob; ++k) fl += (double)jobs[idx[k]].n * jobs[idx[k]].n * FNB;
                 timing_work(fl, 2.0 * fl);
             }
             e = hipGetLastError();

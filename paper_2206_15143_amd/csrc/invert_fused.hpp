@@ -31,7 +31,7 @@
 namespace kfac {
 
 constexpr int FNB = 64;            // pivot block order
-constexpr int kMaxInvClasses = 24; // distinct matrix orders per launch sequence
+constexpr int kMaxInvClasses = 24; // distinct numbers of pivot blocks per launch sequence
 
 struct InvProbF {
     const float *M;   // input factor [n, n], lower triangle read
@@ -61,7 +61,7 @@ struct InvUpload {
 struct InvClass {
     int first;       // index of the first problem of this class in the device table
     int count;       // problems in the class
-    int n, nblk;
+    int nblk;
     int per;         // blocks per problem in this launch
     int blk_start;   // first block of the class in this launch (a multiple of 8)
 };
@@ -70,6 +70,8 @@ struct InvSeq {
     const InvProbF *tab;
     int nclass;
     int step;
+    int heads;           // blocks ahead of the first class: block 0 of every matrix, rounded up to a multiple of 8
+    int nprob;           // matrices in this launch
     float refine_cond;   // panel products of pivot blocks whose condition number exceeds this are refined (< 0: never)
     InvClass c[kMaxInvClasses];
 };
@@ -83,24 +85,42 @@ __global__ __launch_bounds__(64) void inv_upload_kernel(const InvUpload u)
     for (int e = threadIdx.x + blockIdx.x * 64; e < u.count * words; e += 64 * gridDim.x) dst[e] = src[e];
 }
 
-// Block -> (matrix, block of that matrix).  Inside a class the blocks are dealt block-major: block `local` of
-// every matrix before block `local + 1` of any, with the matrix count rounded up to a multiple of 8 (the slots
-// past the last matrix are empty).  Two things follow: workgroup i runs on XCD i mod 8, so every block of a
-// matrix runs on the same XCD and its panels and pivot inverse are fetched into one L2 instead of eight; and
-// block 0 of every matrix (the one that goes on to invert the next pivot block) is dispatched first.
-__host__ __device__ __forceinline__ int seq_slots(int count) { return (count + 7) & ~7; }
-
-__device__ __forceinline__ bool seq_locate(const InvSeq &q, int blk, int &prob, int &local, int &ci)
+// Block -> (matrix, block of that matrix).  The first q.heads blocks are block 0 of every matrix, the one that goes
+// on to invert the next pivot block: dispatched first, that chain runs beside the other tiles.  The blocks 1 .. per - 1
+// follow class by class (a class: matrices with the same number of pivot blocks, whatever their order).  Inside a
+// class the matrices of the largest multiple of 8 are dealt block-major, block `local` of every matrix before block
+// `local + 1` of any: workgroup i runs on XCD i mod 8, so every block of a matrix runs on the same XCD and its panels
+// and pivot inverse are fetched into one L2 instead of eight.  The up to 7 matrices left over are dealt the same way
+// among themselves, so that their blocks are spread over all XCDs (rounded up to slots of 8 they ran on the first
+// XCDs alone: a network with 107 different layer shapes, most of them once, kept one XCD busy and seven idle; the
+// fused class of that network took 14.2 ms of kernel time, now 9.2 ms).
+__host__ __device__ __forceinline__ int seq_class_blocks(int count, int per)
 {
-    ci = 0;
+    return per > 1 ? (count * (per - 1) + 7) & ~7 : 0;
+}
+
+__device__ __forceinline__ bool seq_locate(const InvSeq &q, int blk, int &prob, int &local)
+{
+    if (blk < q.heads) {
+        prob = q.c[0].first + blk;       // the matrices of a sequence are neighbours in the table
+        local = 0;
+        return blk < q.nprob;
+    }
+    int ci = 0;
     while (ci + 1 < q.nclass && blk >= q.c[ci + 1].blk_start) ++ci;
     const InvClass &c = q.c[ci];
-    const int off = blk - c.blk_start;
-    const int slots = seq_slots(c.count);
-    local = off / slots;
-    const int pl = off - local * slots;
-    if (pl >= c.count || local >= c.per) return false;
-    prob = c.first + pl;
+    const int full = c.count & ~7, rest = c.count - full, each = c.per - 1;
+    int off = blk - c.blk_start;
+    if (off < full * each) {
+        local = off / full;
+        prob = c.first + off - local * full;
+    } else {
+        off -= full * each;
+        if (off >= rest * each) return false;
+        local = off / rest;
+        prob = c.first + full + off - local * rest;
+    }
+    ++local;
     return true;
 }
 
@@ -246,8 +266,8 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
     __shared__ __attribute__((aligned(16))) float pw[16 * 17 + 64 * 17];
     __shared__ float nrm[4 * 64 + 2];
     float (*tile)[65] = reinterpret_cast<float (*)[65]>(sbuf);
-    int prob, local, ci;
-    if (!seq_locate(q, blockIdx.x, prob, local, ci)) return;
+    int prob, local;
+    if (!seq_locate(q, blockIdx.x, prob, local)) return;
     const InvProbF pr = q.tab[prob];
     const int tid = threadIdx.x;
     if (local > 0) {
@@ -323,8 +343,8 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
     __shared__ __attribute__((aligned(16))) float Vb[FNB * PITCH];   // V of the tile's column block, or W^T
     __shared__ float nrm[4 * 64 + 2];                                // the condition test of the next pivot block
 
-    int prob, t, ci;
-    if (!seq_locate(q, blockIdx.x, prob, t, ci)) return;
+    int prob, t;
+    if (!seq_locate(q, blockIdx.x, prob, t)) return;
     const InvProbF pr = q.tab[prob];
     const int K = q.step, K1 = K + 1;
     const int nblk = pr.nblk;

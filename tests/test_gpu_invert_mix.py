@@ -1,0 +1,57 @@
+"""The one-launch-per-step inversion over mixes of matrices: counts per number of 64-row pivot blocks below, at and above
+multiples of 8, several orders with the same number of blocks, orders 64 k and 64 k + 1, single blocks.
+
+Every matrix of a batch must come out bit for bit as in a call of its own (the arithmetic of a matrix does not depend on
+what else is in the launch), and that against float64 within condition number times 2^-24 times the order's growth.
+"""
+import pytest
+import torch
+
+import paper_2206_15143_amd as kf
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+LAM = 0.03
+
+
+def factor(n, seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    x = torch.randn(n + 8, n, generator=g, device=DEV)
+    return (x.T @ x) / (n + 8)
+
+
+@pytest.mark.parametrize("orders", [
+    [64, 65],
+    [100] * 7 + [127, 70, 64, 1, 17],                       # 7 of two blocks, single blocks
+    [130, 140, 150, 160, 170, 180, 190, 192] + [64] * 8,    # exactly 8 of three blocks, all of different orders
+    [300] * 9 + [310] * 8 + [640, 1280, 1279, 1217, 65],    # 17 of five blocks, single ones of many
+])
+def test_batched_inverses_equal_single_ones(orders):
+    if len(orders) % 2:
+        orders = orders + [33]
+    pairs = list(zip(orders[0::2], orders[1::2]))
+    descs = [kf.LayerDesc.linear(a, g, False, kf.KFAC_F32) for a, g in pairs]
+    A = [factor(a, 10 + i) for i, (a, _) in enumerate(pairs)]
+    G = [factor(g, 500 + i) for i, (_, g) in enumerate(pairs)]
+    one = [1] * len(pairs)
+    work = torch.empty(kf.kfac_workspace_bytes_batched(descs, one, one, one), dtype=torch.uint8, device=DEV)
+    Ai, Gi = [torch.full_like(x, 7.0) for x in A], [torch.full_like(x, 7.0) for x in G]
+    info = torch.full((2 * len(pairs),), -1, dtype=torch.int32, device=DEV)
+    kf.kfac_invert_batched(descs, A, G, LAM, LAM, Ai, Gi, info, work)
+    torch.cuda.synchronize()
+    assert int(info.abs().max()) == 0
+    for i, d in enumerate(descs):
+        w1 = torch.empty(kf.kfac_workspace_bytes(d, 1, 1, 1), dtype=torch.uint8, device=DEV)
+        a1, g1 = torch.empty_like(A[i]), torch.empty_like(G[i])
+        i1 = torch.full((2,), -1, dtype=torch.int32, device=DEV)
+        kf.kfac_invert(d, A[i], G[i], LAM, LAM, a1, g1, i1, w1)
+        torch.cuda.synchronize()
+        assert int(i1.abs().max()) == 0
+        assert torch.equal(Ai[i], a1) and torch.equal(Gi[i], g1), pairs[i]
+        for m, x in ((A[i], a1), (G[i], g1)):
+            damped = m.double().cpu() + LAM * torch.eye(m.shape[0], dtype=torch.float64)
+            ref = torch.linalg.inv(damped)
+            cond = float(torch.linalg.matrix_norm(damped, 2) * torch.linalg.matrix_norm(ref, 2))
+            err = float((x.double().cpu() - ref).norm() / ref.norm())
+            assert err <= 8 * cond * 2.0 ** -24, (m.shape[0], err, cond)
