@@ -50,6 +50,28 @@ struct InvProbF {
     const float *dptr; // device-side damping (overrides `damping` when not null)
 };
 
+// The same with pointers that are known to point to device memory.  Of a pointer read from memory the compiler cannot
+// tell: it uses flat accesses, which count as LDS accesses too and make every wait for LDS one for all of memory.
+typedef __attribute__((address_space(1))) float gfloat;
+typedef __attribute__((address_space(1))) int gint;
+typedef __attribute__((address_space(1))) floatx4 gfloatx4;
+typedef float ufloatx4 __attribute__((ext_vector_type(4), aligned(4)));    // rows of a matrix of any order
+typedef __attribute__((address_space(1))) ufloatx4 gufloatx4;
+struct InvProbG {
+    const gfloat *M;
+    gfloat *W, *P, *Vt, *S;
+    gint *gate, *info;
+    const gfloat *dptr;
+    int n, ldv, nblk, ldm, ldw;
+    float damping;
+};
+__device__ __forceinline__ InvProbG load_prob(const InvProbF *tab, int i)
+{
+    const InvProbF p = tab[i];
+    return InvProbG{(const gfloat *)p.M, (gfloat *)p.W, (gfloat *)p.P, (gfloat *)p.Vt, (gfloat *)p.S, (gint *)p.gate,
+                    (gint *)p.info, (const gfloat *)p.dptr, p.n, p.ldv, p.nblk, p.ldm, p.ldw, p.damping};
+}
+
 constexpr int kInvUploadMax = 224;   // descriptors per upload launch (a 20 KB kernel argument)
 
 struct InvUpload {
@@ -268,7 +290,7 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
     float (*tile)[65] = reinterpret_cast<float (*)[65]>(sbuf);
     int prob, local;
     if (!seq_locate(q, blockIdx.x, prob, local)) return;
-    const InvProbF pr = q.tab[prob];
+    const InvProbG pr = load_prob(q.tab, prob);
     const int tid = threadIdx.x;
     if (local > 0) {
         const int g0 = local * FNB;
@@ -333,19 +355,31 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
 }
 
 // One step of the sweep for every tile of every active matrix (see the header of this file).
-__global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
+//
+// Per tile and wavefront 128 fp32 MFMAs (4096 cycles of its SIMD) against the memory instructions, which cost the
+// address unit that the four SIMDs share about 16 cycles each whatever their width.  So lanes move 16 bytes: the
+// contraction index of MFMA step s and lane group lk is fold_k(s, lk) = 16 (s / 4) + 4 lk + s mod 4 on both operands,
+// with which the values of P that a lane needs are four neighbours of a row (P is symmetric), and the second product
+// has its operands swapped, so that a lane's four accumulators are neighbours of a row of the matrix.  24 memory
+// instructions per wavefront and tile instead of 72; the pitch of 68 keeps both LDS operand reads (rows 4 apart)
+// free of conflicts and makes room for four workgroups per CU.
+// All steps of the matrices up to order 1280 of a DenseNet-201-shaped network 9.2 -> 7.1 ms of kernel time, of 24
+// transformer blocks of width 1024 (144 matrices of order 1024 and pivot blocks beside other kernels) 20.8 -> 11.9 ms.
+__device__ __forceinline__ int fold_k(int s4, int lk) { return 16 * (s4 >> 2) + 4 * lk + (s4 & 3); }
+
+__global__ __launch_bounds__(256, 4) void fsweep_step_kernel(const InvSeq q)
 {
     typedef Tile<2, 2> T;
-    constexpr int PITCH = T::PITCH;   // 80
-    // two operand buffers (40 KB: three workgroups per CU; the pivot-block sweep reuses them).  P is
-    // not staged: every lane keeps its 32 operand values of P in registers.
+    constexpr int PITCH = SW_PITCH;
+    // two operand buffers (the pivot-block sweep reuses them).  P is not staged: every lane keeps its 32 operand
+    // values of P in registers.
     __shared__ __attribute__((aligned(16))) float Va[FNB * PITCH];   // V of the tile's row block (or the panel block)
     __shared__ __attribute__((aligned(16))) float Vb[FNB * PITCH];   // V of the tile's column block, or W^T
     __shared__ float nrm[4 * 64 + 2];                                // the condition test of the next pivot block
 
     int prob, t;
     if (!seq_locate(q, blockIdx.x, prob, t)) return;
-    const InvProbF pr = q.tab[prob];
+    const InvProbG pr = load_prob(q.tab, prob);
     const int K = q.step, K1 = K + 1;
     const int nblk = pr.nblk;
     if (K >= nblk) return;
@@ -381,72 +415,75 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
     const int p0 = K * FNB, p1 = K1 * FNB;
     const int bs = min(FNB, n - p0);
     const int bs1 = min(FNB, n - p1);              // <= 0 when there is no next block
-    const float *Pk = pr.P + (K & 1) * FNB * FNB;
-    const float *Vk = pr.Vt + (long)(K & 1) * FNB * ldv;
-    float *Pn = pr.P + (K1 & 1) * FNB * FNB;
-    float *Sn = pr.S + (K1 & 1) * FNB * FNB;
-    const float *Sk = pr.S + (K & 1) * FNB * FNB;
+    const gfloat *Pk = pr.P + (K & 1) * FNB * FNB;
+    const gfloat *Vk = pr.Vt + (long)(K & 1) * FNB * ldv;
+    gfloat *Pn = pr.P + (K1 & 1) * FNB * FNB;
+    gfloat *Sn = pr.S + (K1 & 1) * FNB * FNB;
+    const gfloat *Sk = pr.S + (K & 1) * FNB * FNB;
     const bool refine = q.refine_cond >= 0.f && pr.gate[K & 1] != 0;      // uniform over the workgroup
-    float *Vn = pr.Vt + (long)(K1 & 1) * FNB * ldv;
+    gfloat *Vn = pr.Vt + (long)(K1 & 1) * FNB * ldv;
     const bool panel = (bi == K) != (bj == K);
     const int ra = panel ? (bi == K ? bj : bi) : bi;   // block whose V goes to Va
     const int rb = bj;
 
-    // the tile's current values: fetched now, needed after the two products
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int lr = lane & 15, lk = lane >> 4;
     const bool diag = (bi == bj);
-    float oldc[T::WT][T::WT][4];
+    // V of the row block and of the column block (unconditional loads, from clamped addresses), P, the tile's current
+    // values (needed last): all in flight together
+    const bool two = !panel && !diag;
+    floatx4 sta[4], stb[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int k = (tid >> 4) + 16 * e, c4 = (tid & 15) * 4;
+        const long row = (long)(k < bs ? k : 0) * ldv;
+        const int ga = ra * FNB + c4, gb = rb * FNB + c4;
+        sta[e] = *(const gfloatx4 *)(Vk + row + (ga < ldv ? ga : 0));
+        stb[e] = *(const gfloatx4 *)(Vk + row + (two && gb < ldv ? gb : 0));
+    }
+    // ---- P operand values of this lane: P[m = (wm*2 + t)*16 + lr][k = fold_k(s, lk)] ----
+    floatx4 pa[FNB / 16][T::WT];
+#pragma unroll
+    for (int s = 0; s < FNB / 16; ++s)
+#pragma unroll
+        for (int t2 = 0; t2 < T::WT; ++t2)
+            pa[s][t2] = *(const gfloatx4 *)(Pk + ((wm * T::WT + t2) * 16 + lr) * FNB + 16 * s + 4 * lk);
+    // oldc[ti][tj][v]: row (wm*2 + ti)*16 + lr, column (wn*2 + tj)*16 + 4*lk + v of the tile
+    const bool whole = !diag && (bi + 1) * FNB <= n;      // (bj < bi: its columns exist too)
+    floatx4 oldc[T::WT][T::WT];
     if (!panel) {
+        const gfloat *from = first ? pr.M : pr.W;
+        const long ldf = first ? ldm : ldw;
 #pragma unroll
         for (int ti = 0; ti < T::WT; ++ti)
 #pragma unroll
             for (int tj = 0; tj < T::WT; ++tj) {
-                const int gb = bj * FNB + (wn * T::WT + tj) * 16 + lr;
+                const int ga = bi * FNB + (wm * T::WT + ti) * 16 + lr, gb = bj * FNB + (wn * T::WT + tj) * 16 + 4 * lk;
+                if (whole) {
+                    oldc[ti][tj] = *(const gufloatx4 *)(from + (long)ga * ldf + gb);
+                } else {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int ga = bi * FNB + (wm * T::WT + ti) * 16 + 4 * lk + v;
-                    const bool ok = (ga < n && gb < n && (!diag || gb <= ga));
-                    float o = 0.f;
-                    if (ok)
-                        o = first ? pr.M[(long)ga * ldm + gb] + (ga == gb ? damping : 0.f)
-                                  : pr.W[(long)ga * ldw + gb];
-                    oldc[ti][tj][v] = o;
+                    for (int v = 0; v < 4; ++v) {
+                        const bool ok = ga < n && gb + v < n && (!diag || gb + v <= ga);
+                        float o = 0.f;
+                        if (ok) o = from[(long)ga * ldf + gb + v] + (first && ga == gb + v ? damping : 0.f);
+                        oldc[ti][tj][v] = o;
+                    }
                 }
             }
     }
-
-    // ---- P operand values of this lane: P[k = 4s + lk][m = (wm*2 + t)*16 + lr] ----
-    float pa[FNB / 4][T::WT];
 #pragma unroll
-    for (int s4 = 0; s4 < FNB / 4; ++s4)
+    for (int e = 0; e < 4; ++e) {
+        const int k = (tid >> 4) + 16 * e, c4 = (tid & 15) * 4;
+        const int na = k < bs ? n - ra * FNB - c4 : 0, nb = k < bs ? n - rb * FNB - c4 : 0;   // elements that exist
 #pragma unroll
-        for (int t2 = 0; t2 < T::WT; ++t2) pa[s4][t2] = Pk[(4 * s4 + lk) * FNB + (wm * T::WT + t2) * 16 + lr];
-
-    // ---- stage V_a (and V_b) ----
-    for (int e = tid; e < FNB * FNB / 4; e += 256) {
-        const int k = e >> 4, c4 = (e & 15) * 4;
-        const int ga = ra * FNB + c4;
-        floatx4 va = {0.f, 0.f, 0.f, 0.f};
-        if (ga < ldv && k < bs) {
-            va = *reinterpret_cast<const floatx4 *>(Vk + (long)k * ldv + ga);
-            if (ga + 1 >= n) va.y = 0.f;
-            if (ga + 2 >= n) va.z = 0.f;
-            if (ga + 3 >= n) va.w = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            sta[e][i] = i < na ? sta[e][i] : 0.f;
+            stb[e][i] = i < nb ? stb[e][i] : 0.f;
         }
-        *reinterpret_cast<floatx4 *>(Va + k * PITCH + c4) = va;
-        if (!panel && rb != ra) {
-            const int gb = rb * FNB + c4;
-            floatx4 vb = {0.f, 0.f, 0.f, 0.f};
-            if (gb < ldv && k < bs) {
-                vb = *reinterpret_cast<const floatx4 *>(Vk + (long)k * ldv + gb);
-                if (gb + 1 >= n) vb.y = 0.f;
-                if (gb + 2 >= n) vb.z = 0.f;
-                if (gb + 3 >= n) vb.w = 0.f;
-            }
-            *reinterpret_cast<floatx4 *>(Vb + k * PITCH + c4) = vb;
-        }
+        *reinterpret_cast<floatx4 *>(Va + k * PITCH + c4) = sta[e];
+        if (two) *reinterpret_cast<floatx4 *>(Vb + k * PITCH + c4) = stb[e];
     }
     __syncthreads();
 
@@ -460,12 +497,12 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
     for (int s4 = 0; s4 < FNB / 4; ++s4) {
         float b[T::WT];
 #pragma unroll
-        for (int t2 = 0; t2 < T::WT; ++t2) b[t2] = Va[(4 * s4 + lk) * PITCH + (wn * T::WT + t2) * 16 + lr];
+        for (int t2 = 0; t2 < T::WT; ++t2) b[t2] = Va[fold_k(s4, lk) * PITCH + (wn * T::WT + t2) * 16 + lr];
 #pragma unroll
         for (int ti = 0; ti < T::WT; ++ti)
 #pragma unroll
             for (int tj = 0; tj < T::WT; ++tj)
-                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[s4][ti], b[tj], acc[ti][tj], 0, 0, 0);
+                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa[s4 >> 2][ti][s4 & 3], b[tj], acc[ti][tj], 0, 0, 0);
     }
 
     if (refine) {
@@ -503,14 +540,14 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
                 float b[T::WT], sop[T::WT];     // the operand values of S are read as they are used: this path is rare
 #pragma unroll
                 for (int t2 = 0; t2 < T::WT; ++t2) {
-                    b[t2] = X[(4 * s4 + lk) * PITCH + (wn * T::WT + t2) * 16 + lr];
-                    sop[t2] = pass == 0 ? Sk[(4 * s4 + lk) * FNB + (wm * T::WT + t2) * 16 + lr] : 0.f;
+                    b[t2] = X[fold_k(s4, lk) * PITCH + (wn * T::WT + t2) * 16 + lr];
+                    sop[t2] = pass == 0 ? Sk[fold_k(s4, lk) * FNB + (wm * T::WT + t2) * 16 + lr] : 0.f;
                 }
 #pragma unroll
                 for (int ti = 0; ti < T::WT; ++ti)
 #pragma unroll
                     for (int tj = 0; tj < T::WT; ++tj)
-                        r2[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(pass == 0 ? sop[ti] : pa[s4][ti], b[tj],
+                        r2[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(pass == 0 ? sop[ti] : pa[s4 >> 2][ti][s4 & 3], b[tj],
                                                                           r2[ti][tj], 0, 0, 0);
             }
             __syncthreads();   // every wave is done reading X
@@ -542,21 +579,28 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
             for (int tj = 0; tj < T::WT; ++tj) {
                 const int c = (wn * T::WT + tj) * 16 + lr;
                 const int gc = ra * FNB + c;
+                const int m0 = (wm * T::WT + ti) * 16 + 4 * lk;
+                if (below) {      // the pivot block has all its 64 rows: others follow it
+                    if (gc < n) *(gufloatx4 *)(pr.W + (long)gc * ldw + p0 + m0) = acc[ti][tj];
+                    // V'[kk = c][column p0 + m] = M[p1 + c][p0 + m]; rows kk >= bs1 are zero
+                    if (next) {
+                        floatx4 w = acc[ti][tj];
+                        if (gc >= n) w = floatx4{0.f, 0.f, 0.f, 0.f};
+                        *(gfloatx4 *)(Vn + (long)c * ldv + p0 + m0) = w;
+                    }
+                    continue;
+                }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int m = (wm * T::WT + ti) * 16 + 4 * lk + v;
+                    const int m = m0 + v;
                     const float w = acc[ti][tj][v];
-                    const bool ok = (gc < n && m < bs);
-                    if (ok) {
-                        if (below) pr.W[(long)gc * ldw + p0 + m] = w;
-                        else if (!last) pr.W[(long)(p0 + m) * ldw + gc] = w;
+                    if (gc < n && m < bs) {
+                        if (!last) pr.W[(long)(p0 + m) * ldw + gc] = w;
                         else {   // last step: the row panel is final
                             pr.W[(long)(p0 + m) * ldw + gc] = -w;
                             pr.W[(long)gc * ldw + p0 + m] = -w;
                         }
                     }
-                    // V'[kk = c][column p0 + m] = M[p1 + c][p0 + m]; rows kk >= bs1 are zero
-                    if (next && m < bs) Vn[(long)c * ldv + p0 + m] = ok ? w : 0.f;
                 }
             }
         return;
@@ -585,24 +629,57 @@ __global__ __launch_bounds__(256) void fsweep_step_kernel(const InvSeq q)
 #pragma unroll
         for (int b = 0; b < T::WT; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int s4 = 0; s4 < FNB / T::KT; ++s4)
-        mma_stage<T, kRows, kRows, false>(Ws + s4 * T::KT * PITCH, Vj + s4 * T::KT * PITCH, wm, wn, lane, acc);
+    for (int s4 = 0; s4 < FNB / 4; ++s4) {
+        float a[T::WT], b[T::WT];
+#pragma unroll
+        for (int t2 = 0; t2 < T::WT; ++t2) {
+            a[t2] = Ws[fold_k(s4, lk) * PITCH + (wm * T::WT + t2) * 16 + lr];
+            b[t2] = Vj[fold_k(s4, lk) * PITCH + (wn * T::WT + t2) * 16 + lr];
+        }
+#pragma unroll
+        for (int ti = 0; ti < T::WT; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < T::WT; ++tj)
+                acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x4f32(b[tj], a[ti], acc[ti][tj], 0, 0, 0);
+    }
 
-    // acc[ti][tj][v] = (W_i V_j^T)[a][b], a = (wm*2+ti)*16 + 4*lk + v, b = (wn*2+tj)*16 + lr
+    // acc[ti][tj][v] = (W_i V_j^T)[a][b], a = (wm*2+ti)*16 + lr, b = (wn*2+tj)*16 + 4*lk + v
     const bool next_col = (bj == K1 && bi > K1);    // column panel of the next pivot: V'[b][ga]
     const bool next_row = (bi == K1 && bj < K1);    // row panel of the next pivot: V'[a][gb]
     const bool next_piv = (bi == K1 && bj == K1);
+    if (whole) {     // not on the diagonal: never the next pivot
+#pragma unroll
+        for (int ti = 0; ti < T::WT; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < T::WT; ++tj) {
+                const int a = (wm * T::WT + ti) * 16 + lr, b = (wn * T::WT + tj) * 16 + 4 * lk;
+                const int ga = bi * FNB + a, gb = bj * FNB + b;
+                floatx4 c;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    c[v] = oldc[ti][tj][v] - acc[ti][tj][v];
+                    if (next_col) Vn[(long)(b + v) * ldv + ga] = c[v];
+                    if (last) {
+                        c[v] = -c[v];
+                        pr.W[(long)(gb + v) * ldw + ga] = c[v];
+                    }
+                }
+                if (next_row) *(gfloatx4 *)(Vn + (long)a * ldv + gb) = c;
+                *(gufloatx4 *)(pr.W + (long)ga * ldw + gb) = c;
+            }
+        return;
+    }
     __syncthreads();   // Va is reused below when this tile is the next pivot
 #pragma unroll
     for (int ti = 0; ti < T::WT; ++ti)
 #pragma unroll
         for (int tj = 0; tj < T::WT; ++tj) {
-            const int b = (wn * T::WT + tj) * 16 + lr;
-            const int gb = bj * FNB + b;
+            const int a = (wm * T::WT + ti) * 16 + lr;
+            const int ga = bi * FNB + a;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int a = (wm * T::WT + ti) * 16 + 4 * lk + v;
-                const int ga = bi * FNB + a;
+                const int b = (wn * T::WT + tj) * 16 + 4 * lk + v;
+                const int gb = bj * FNB + b;
                 const bool ok = (ga < n && gb < n && (!diag || gb <= ga));
                 float c = 0.f;
                 if (ok) {
