@@ -161,10 +161,11 @@ struct Tuning {
     long split_syrk_fill_nchw = 40;  // ... NCHW inputs (tile fill x share of real positions in the K stages)
     long split_syrk_max_stages = 32; // ... K stages (of 16 rows) per slice at most: bounds the accumulation chain
     long use_split_gemm = 1;         // large A^T B products as three fp16 MFMA products of the operands' fp16 pieces
-    long split_gemm_min_m = 192;     // ... from this many output rows on
-    long split_gemm_min_k = 1024;     // ... and this depth (stores only)
-    long split_gemm_min_fill = 60;   // ... when the product fills at least this percentage of its 256 x 128 tiles
-    long gemm_kslice_stages = 75;    // ... deep stores of a call with few tiles: K slices of about this many stages (0 = never)
+    long split_gemm_min_m = 128;     // ... stores: from this many output rows on
+    long split_gemm_min_k = 128;     // ... and this depth
+    long split_gemm_min_fill = 40;   // ... when the product fills at least this percentage of its 256 x 128 tiles
+    long gemm_kslice_stages = 40;    // ... deep stores of a call with few tiles: K slices of at least this many stages (0 = never)
+    long gemm_kslice_groups = 400;   // ... and as many more as leave about this many workgroups
     long use_small_kernel = 1;       // direct MFMA kernel for narrow NCHW operands (d <= 64)
     long fuse_conv3 = 1;             // 3x3/s1/p1 fp32 convs: build A straight from the NCHW input
     long fuse_conv3_max_c = 64;      // ... up to this many input channels (wider ones: patch matrix + split-fp16 kernel)

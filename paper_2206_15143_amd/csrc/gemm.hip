@@ -288,20 +288,28 @@ hipError_t wave_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hi
 
 namespace {
 // Products that fill 256 x 128 tiles reasonably go to the split-fp16 kernel (gemm_split.hpp).
-bool split_gemm_eligible(const GemmJob &j)
+bool split_gemm_eligible(const GemmJob &j, bool wide)
 {
     if (!tuning().use_split_gemm || (j.mode != kStore && j.mode != kSubLowerSkip && j.mode != kSubRect && j.mode != kAddRect))
         return false;
-    if (j.M < tuning().split_gemm_min_m || j.N < 64 || j.K < 16) return false;
+    const long min_m = wide && j.mode == kStore ? tuning().split_gemm_min_m : 192;
+    if (j.M < min_m || j.N < 64 || j.K < 16) return false;
     // a product of a tile or two is bound by the latency of one tile's K loop and read-modify-write (55 us at
     // K = 256): the 64-wide tiles of the block-tile kernel spread it over many CUs and finish in 10-15 us
     if ((long)j.M * j.N < 4l * S_BM * S_BN) return false;
     if (j.mode == kStore && !j.wide_tiles) {
-        if (j.K < tuning().split_gemm_min_k) return false;
-        // 256 x 128 tiles: products that fill them badly (a 257-row or 65-column operand) stay with the 144-wide
-        // tiles of the fp32 kernel
+        if (j.K < (wide ? tuning().split_gemm_min_k : 1024)) return false;
+        // 256 x 128 tiles: products that fill less than 40 % of them stay with the other kernels.  The split kernel does
+        // a multiply-add of the definition in a fifth of the fp32 MFMA's time, so that it wins with over half of a
+        // tile empty and with few K stages.  Preconditioning, lines M >= 192, K >= 1024, fill 60 % -> M >= 128,
+        // K >= 128, 40 % (together with the K slices below): twelve 768-wide transformer blocks 4.23 -> 2.77 ms,
+        // ResNet-50-shaped 1.09 -> 0.88, DenseNet-201-shaped 1.30 -> 1.05, one 700 x 500 layer 0.23 -> 0.08,
+        // a 256-channel 3x3 layer 0.17 -> 0.10 ms; fill 50 %: 0.99 and 1.24 ms on the two networks.
+        // The narrow lines stay for calls whose work is mostly in products too small for either: another launch
+        // for one or two products of the call costs more than they gain (an update with one of seven products moved
+        // 0.92 -> 0.97 ms).
         const double tiles = (double)((j.M + S_BM - 1) / S_BM) * ((j.N + S_BN - 1) / S_BN);
-        if ((double)j.M * j.N < 0.01 * tuning().split_gemm_min_fill * tiles * S_BM * S_BN) return false;
+        if ((double)j.M * j.N < 0.01 * (wide ? tuning().split_gemm_min_fill : 60) * tiles * S_BM * S_BN) return false;
     }
     if ((long)j.K * j.lda * 4 > 0x7fffffffl || (long)j.K * j.ldb * 4 > 0x7fffffffl) return false;
     if ((long)j.M * j.ldc * 4 > 0x7fffffffl) return false;
@@ -310,6 +318,18 @@ bool split_gemm_eligible(const GemmJob &j)
     if (j.mode != kStore && (j.p0 % 4 != 0 || (j.p1 % 4 != 0 && j.p1 < j.N))) return false;
     if (j.mode == kSubLowerSkip) return j.M == j.N;
     return true;
+}
+
+// whether a call takes the wide lines: with them the split kernel has at least half of the call's work.  (The K slices
+// of a product count as the product does.)
+bool split_gemm_wide(const GemmJob *jobs, int n)
+{
+    double split = 0.0, rest = 0.0;
+    for (int i = 0; i < n; ++i) {
+        if (!(jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0)) continue;
+        (split_gemm_eligible(jobs[i], true) ? split : rest) += (double)jobs[i].M * jobs[i].N * jobs[i].K;
+    }
+    return split >= rest;
 }
 
 hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hipStream_t s)
@@ -374,12 +394,15 @@ namespace {
 // compute units with one long workgroup and nothing to pack beside it (three 512 x 4609 x 4609 products: 222 tiles
 // of 289 stages on 256 units).  Such a product is cut into K slices: slice 0 stores into C, the others into
 // partial matrices in the workspace, and a reduction adds them to C in slice order (a fixed order: the result
-// does not depend on the schedule).  The partials are M x N, small beside the K x N operand that is read.
+// does not depend on the schedule).  The partials are M x N, small beside the K x N operand that is read.  The slices
+// of a call are as deep as leaves about 400 workgroups of equal depth (two fit a compute unit), between 40 and 150
+// stages: one depth for every call is too long for a single layer and too short for a network (preconditioning with
+// slices of 75 and of 150 stages: ResNet-50-shaped 1.09 and 0.96 ms, a 2048 x 1024 layer 0.135 and 0.163 ms; with
+// this rule 0.88 and 0.127 ms), no slices at all cost a 1024-wide transformer block 1.10 ms instead of 0.45.
 constexpr int kMaxKSlices = 8;
 
-int kslice_count(const GemmJob &j, long split_tiles)
+int kslice_count(const GemmJob &j, long split_tiles, long cap)
 {
-    const long cap = tuning().gemm_kslice_stages;
     if (cap <= 0 || split_tiles >= 1024) return 1;     // enough tiles to keep every unit busy as it is
     if (j.mode != kStore || j.gate || j.wide_tiles) return 1;
     const long stages = (j.K + S_KT - 1) / S_KT;
@@ -391,14 +414,21 @@ int kslice_count(const GemmJob &j, long split_tiles)
 size_t plan_kslices(const GemmJob *jobs, int n, std::vector<int> &ks)
 {
     ks.assign(n, 1);
+    const bool wide = split_gemm_wide(jobs, n);
     long tiles = 0;
+    double stages = 0.0;
     for (int i = 0; i < n; ++i)
-        if (jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0 && split_gemm_eligible(jobs[i]))
-            tiles += (long)((jobs[i].M + S_BM - 1) / S_BM) * ((jobs[i].N + S_BN - 1) / S_BN);
+        if (jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0 && split_gemm_eligible(jobs[i], wide)) {
+            const long t = (long)((jobs[i].M + S_BM - 1) / S_BM) * ((jobs[i].N + S_BN - 1) / S_BN);
+            tiles += t;
+            stages += (double)t * ((jobs[i].K + S_KT - 1) / S_KT);
+        }
+    const long least = tuning().gemm_kslice_stages;
+    const long cap = least <= 0 ? 0 : std::max(least, (long)std::min(stages / tuning().gemm_kslice_groups, 150.0));
     size_t floats = 0;
     for (int i = 0; i < n; ++i) {
-        if (!(jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0) || !split_gemm_eligible(jobs[i])) continue;
-        ks[i] = kslice_count(jobs[i], tiles);
+        if (!(jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0) || !split_gemm_eligible(jobs[i], wide)) continue;
+        ks[i] = kslice_count(jobs[i], tiles, cap);
         floats += (size_t)(ks[i] - 1) * align_up((size_t)jobs[i].M * jobs[i].N, 64);
     }
     return floats;
@@ -505,10 +535,11 @@ hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work, si
 namespace {
 hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
 {
+    const bool wide = split_gemm_wide(jobs, n);
     std::vector<int> cfg(n);
     std::vector<int> wave, split;
     for (int i = 0; i < n; ++i) {
-        if (jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0 && split_gemm_eligible(jobs[i])) {
+        if (jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0 && split_gemm_eligible(jobs[i], wide)) {
             cfg[i] = -1;
             split.push_back(i);
         } else if (jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0 && wave_gemm_eligible(jobs[i])) {

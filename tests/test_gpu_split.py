@@ -54,6 +54,12 @@ def operands(M, N, K, kind, seed):
     (1281, 1281, 1, 2, 1280, 1281, "normal"),
     (2305, 2305, 250, 2, 0, 512, "columns"),
     (769, 769, 256, 2, 768, 769, "opposite"),
+    (128, 1090, 128, 0, 0, 0, "normal"),            # the smallest stores: rows, depth, share of the tiles filled
+    (1100, 129, 129, 0, 0, 0, "columns"),
+    (257, 513, 135, 0, 0, 0, "zeros_first"),
+    (511, 321, 200, 0, 0, 0, "opposite"),
+    (1090, 127, 128, 0, 0, 0, "relu"),              # ... and just outside: the other kernels
+    (640, 512, 127, 0, 0, 0, "normal"),
 ])
 def test_split_product(M, N, K, mode, p0, p1, kind):
     A, B = operands(M, N, K, kind, 11)
@@ -71,4 +77,25 @@ def test_split_product(M, N, K, mode, p0, p1, kind):
         ref, mag = np.where(live, 3.0 - ref, 3.0), np.where(live, mag + 3.0, 3.0)
     bound = (2.0 ** -21 + (K + 2) * 2.0 ** -24) * mag
     worst = np.max(np.abs(got - ref) / bound)
+    assert worst <= 1.0, f"error {worst:.3f} of the bound"
+
+
+@pytest.mark.parametrize("d_in,d_out", [(1023, 400), (1024, 300), (2300, 200), (5000, 130)])
+def test_k_slices_of_one_layer(d_in, d_out):
+    """A call of one layer: its deep products are cut into slices of 40 stages and more, up to eight of them.  The same
+    bound as above, twice: the first product's error passes through the second."""
+    d = kf.LayerDesc.linear(d_in, d_out, True, kf.KFAC_F32)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+    n = d_in + 1
+    A, G, W = (torch.randn(*s, generator=g, device=DEV) for s in ((n, n), (d_out, d_out), (d_out, n)))
+    A, G = (A + A.T) / 2, (G + G.T) / 2
+    work = torch.empty(kf.kfac_workspace_bytes(d, 8, 1, 1), dtype=torch.uint8, device=DEV)
+    out = torch.empty(d_out, n, device=DEV)
+    kf.kfac_precondition(d, A, G, W, out, work)
+    torch.cuda.synchronize()
+    a, b, w = A.double().cpu(), G.double().cpu(), W.double().cpu()
+    mag = b.abs() @ w.abs() @ a.abs()
+    bound = (2.0 ** -20 + (n + d_out + 4) * 2.0 ** -24) * mag
+    worst = ((out.double().cpu() - b @ w @ a).abs() / bound).max().item()
     assert worst <= 1.0, f"error {worst:.3f} of the bound"
