@@ -319,8 +319,8 @@ def run_config(name, args, kf, torch, steps, warmup, cpu_budget):
     if traffic_note:
         roofline["traffic_note"] = traffic_note
     if dom == "gemm_split_kernel":
-        roofline["note"] = ("fp32 products as three fp16 MFMA products of the operands' fp16 pieces: 'achieved' counts the "
-                            "fp16 flops executed (3 x 2 M N K) against the fp16 peak (that of bf16); "
+        roofline["note"] = ("fp32 products as six bf16 MFMA products of the operands' bf16 pieces: 'achieved' counts the "
+                            "bf16 flops executed (6 x 2 M N K) against the bf16 peak; "
                             "definition_equiv_tflops counts 2 M N K, for comparison with the fp32 MFMA peak of 157.3")
 
     out = dict(ms_per_step=round(ms_per_step, 4), cold_ms_per_step=round(cold_ms, 4),

@@ -67,8 +67,7 @@ struct GemmJob {
     float gate_cond = 0.f;
     const float *D = nullptr;    // kSubFrom
     long ldd = 0;
-    int krow = 0;                // this product is a K slice that starts at this row of the operands
-    bool wide_tiles = false;     // kStore: take the split-fp16 kernel whatever the depth and tile fill
+    bool wide_tiles = false;     // kStore: take the split-bf16 kernel whatever the depth and tile fill
 };
 
 enum GemmMode : int {
@@ -139,7 +138,7 @@ struct Tuning {
     long eigen_max_sweeps = 20;      // sweep budget of the block Jacobi eigen-decomposition (12-13 used at order 577)
     long eigen_inner_sweeps = 1;     // Jacobi sweeps over the 32 x 32 Gram matrix of a pair of blocks per round
     long bf16_rows_copy = 1;         // bf16 NCHW operands with an odd number of positions: row-major copy first
-    long invert_panel_split = 1;     // blocked sweep: panel products on the split-fp16 kernel
+    long invert_panel_split = 1;     // blocked sweep: panel products on the split-bf16 kernel
     long invert_refine = 1;          // blocked sweep: refinement step of the panel products (see invert.hip) ...
     long invert_fused_refine_cond = 300;  // the same test for the 64 x 64 pivot blocks of the one-launch-per-step path
     long invert_refine_cond = 3000;  // ... of pivot blocks whose condition number (maximum norm) exceeds this
@@ -155,12 +154,12 @@ struct Tuning {
     long use_bf16_mfma = 1;          // row-major bf16 operands: bf16 MFMA kernel instead of widening to fp32
     long gemm_xcd_remap_min = 8;     // wave GEMM launches with at least this many problems renumber their tiles per XCD
     long use_wave_gemm = 1;          // wide A^T B products on the wave-unit GEMM
-    long use_split_syrk = 1;         // wide fp32 factors as three fp16 MFMA products of the inputs' fp16 pieces
-    long split_syrk_min_d = 192;     // narrowest factor the split-fp16 KF-GEMM takes
+    long use_split_syrk = 1;         // wide fp32 factors as six bf16 MFMA products of the inputs' bf16 pieces
+    long split_syrk_min_d = 192;     // narrowest factor the split-bf16 KF-GEMM takes
     long split_syrk_fill_rows = 60;  // ... row-major inputs: when the factor fills this percentage of its 256 x 128 tiles
     long split_syrk_fill_nchw = 40;  // ... NCHW inputs (tile fill x share of real positions in the K stages)
     long split_syrk_max_stages = 32; // ... K stages (of 16 rows) per slice at most: bounds the accumulation chain
-    long use_split_gemm = 1;         // large A^T B products as three fp16 MFMA products of the operands' fp16 pieces
+    long use_split_gemm = 1;         // large A^T B products as six bf16 MFMA products of the operands' bf16 pieces
     long split_gemm_min_m = 128;     // ... stores: from this many output rows on
     long split_gemm_min_k = 128;     // ... and this depth
     long split_gemm_min_fill = 40;   // ... when the product fills at least this percentage of its 256 x 128 tiles
@@ -168,7 +167,7 @@ struct Tuning {
     long gemm_kslice_groups = 400;   // ... and as many more as leave about this many workgroups
     long use_small_kernel = 1;       // direct MFMA kernel for narrow NCHW operands (d <= 64)
     long fuse_conv3 = 1;             // 3x3/s1/p1 fp32 convs: build A straight from the NCHW input
-    long fuse_conv3_max_c = 64;      // ... up to this many input channels (wider ones: patch matrix + split-fp16 kernel)
+    long fuse_conv3_max_c = 64;      // ... up to this many input channels (wider ones: patch matrix + split-bf16 kernel)
     long update_bm = 64;             // block tile of the inverse's rank-64 update GEMM (0 = choose; 64 measured best)
     long gemm_bm = 0;                // block tile of the preconditioning GEMMs (0 = choose)
     long wave_debug = 0;             // measurement only: 1 = skip MFMAs, 2 = skip data loads (results are wrong)

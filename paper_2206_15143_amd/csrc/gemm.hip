@@ -287,7 +287,7 @@ hipError_t wave_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hi
 }  // namespace
 
 namespace {
-// Products that fill 256 x 128 tiles reasonably go to the split-fp16 kernel (gemm_split.hpp).
+// Products that fill 256 x 128 tiles reasonably go to the split-bf16 kernel (gemm_split.hpp).
 bool split_gemm_eligible(const GemmJob &j, bool wide)
 {
     if (!tuning().use_split_gemm || (j.mode != kStore && j.mode != kSubLowerSkip && j.mode != kSubRect && j.mode != kAddRect))
@@ -357,8 +357,8 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         }
         for (; x < 8; ++x) tab.xcd[x] = (int)blocks;
         for (int k = 0; k < 8; ++k) most = std::max(most, tab.xcd[k + 1] - tab.xcd[k]);
-        KFAC_LAUNCH(KFAC_K_GEMM_SPLIT, s, gemm_split_kernel<4>, dim3((unsigned)(8 * most)), dim3(256), 0, tab);
-        timing_work(flops, 3.0 * flops);
+        KFAC_LAUNCH(KFAC_K_GEMM_SPLIT, s, gemm_split_kernel, dim3((unsigned)(8 * most)), dim3(256), 0, tab);
+        timing_work(flops, 6.0 * flops);
         tab.count = 0;
         blocks = 0;
         flops = 0.0;
@@ -375,10 +375,9 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         p.mode = j.mode; p.p0 = j.p0; p.p1 = j.p1;
         p.doff = (int)std::min<long>(j.doff, 1l << 30);
         if (j.mode == kSubLowerSkip) p.doff = 0;
-        p.krow = j.krow;
         p.gate = j.gate; p.gate_cond = j.gate_cond;
         p.blk_start = (int)blocks;
-        for (int I = 0; I < p.tI; ++I) blocks += split_row_len(p.mode, p.tJ, p.doff, I, S_BM);
+        for (int I = 0; I < p.tI; ++I) blocks += split_row_len(p.mode, p.tJ, p.doff, I);
         if (!j.gate) flops += gemm_job_flops(j);       // a gated product may be skipped on the device: not counted
         if (tab.count == kMaxProblems) {
             hipError_t e = flush();
@@ -499,8 +498,7 @@ hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work, si
             t.A = j.A + k0 * j.lda;
             t.B = j.B + k0 * j.ldb;
             t.K = (int)std::min<long>(per, j.K - k0);
-            t.krow = (int)k0;
-            t.wide_tiles = true;            // a slice stays on the split-fp16 kernel whatever its depth
+            t.wide_tiles = true;            // a slice stays on the split-bf16 kernel whatever its depth
             if (made > 0) {
                 t.C = part + (size_t)(made - 1) * stride;
                 t.ldc = j.N;

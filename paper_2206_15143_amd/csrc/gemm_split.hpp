@@ -1,9 +1,9 @@
-// C = A^T B for fp32 operands (both K-major) on the fp16 MFMA units, at fp32 accuracy: the split-fp16 core of
+// C = A^T B for fp32 operands (both K-major) on the bf16 MFMA units, at fp32 accuracy: the split-bf16 core of
 // split_common.hpp with the epilogues of the preconditioning (Eq. 5 of the DP-KFAC paper) and of the blocked
 // inversion's rank-k updates and panel products (section 5.2).
 //
-// Bound: fp16 MFMA, three products per fp32 product (2.5 PFLOP/s / 3 = 830 TFLOP/s in flops of the definition;
-// v_mfma_f32_32x32x16_f16 reaches 2.1 of the 2.5 when fed from registers).  Two workgroups share a CU, so the
+// Bound: bf16 MFMA, six products per fp32 product (2.5 PFLOP/s / 6 = 417 TFLOP/s in flops of the definition;
+// v_mfma_f32_32x32x16_bf16 reaches 2.1 of the 2.5 when fed from registers).  Two workgroups share a CU, so the
 // prologue and the read-modify-write epilogue of one run beside the MFMAs of the other.
 #pragma once
 
@@ -22,7 +22,6 @@ struct GemmSProb {
     int mode;        // kStore, kSubLowerSkip, kSubRect or kAddRect
     int p0, p1;
     int doff;        // the subtracting modes touch n <= m + doff (0 for kSubLowerSkip)
-    int krow;        // first row of the operands inside the matrices they are slices of
     const int *gate; // null, or two float bit patterns: leave C alone unless their product exceeds gate_cond
     float gate_cond;
 };
@@ -33,19 +32,17 @@ struct GemmSTable {
     GemmSProb p[kMaxProblems];
 };
 
-// column tiles of tile row i (of bm rows): all of them, or those that reach the line n = m + doff
-__host__ __device__ inline int split_row_len(int mode, int tJ, int doff, int i, int bm)
+// column tiles of tile row i: all of them, or those that reach the line n = m + doff
+__host__ __device__ inline int split_row_len(int mode, int tJ, int doff, int i)
 {
     if (mode == kStore) return tJ;
-    const long last = ((long)i * bm + bm - 1 + doff) / S_BN + 1;
+    const long last = ((long)i * S_BM + S_BM - 1 + doff) / S_BN + 1;
     return (int)(last < tJ ? last : tJ);
 }
 
-template <int NTI>
 __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab)
 {
-    constexpr int BM = 64 * NTI;
-    __shared__ __attribute__((aligned(16))) SplitLds<NTI> L;
+    __shared__ __attribute__((aligned(16))) SplitLds L;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -71,7 +68,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const bool rows_skip = pr.mode == kSubLowerSkip;
     const bool add = pr.mode == kAddRect;
     {
-        auto row_len = [&](int i) { return i >= pr.tI ? 0 : split_row_len(pr.mode, pr.tJ, pr.doff, i, BM); };
+        auto row_len = [&](int i) { return i >= pr.tI ? 0 : split_row_len(pr.mode, pr.tJ, pr.doff, i); };
         int g = 0;
         for (;;) {
             const int c = row_len(4 * g) + row_len(4 * g + 1) + row_len(4 * g + 2) + row_len(4 * g + 3);
@@ -99,15 +96,15 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
         }
         I = 4 * g + i;
     }
-    const int m0 = I * BM, n0 = J * S_BN;
+    const int m0 = I * S_BM, n0 = J * S_BN;
     if (lower) {
         // tiles wholly inside the pivot rows or columns are left untouched
-        const int m1 = min(m0 + BM, pr.M), n1 = min(n0 + S_BN, pr.N);
+        const int m1 = min(m0 + S_BM, pr.M), n1 = min(n0 + S_BN, pr.N);
         if ((rows_skip && m0 >= pr.p0 && m1 <= pr.p1) || (n0 >= pr.p0 && n1 <= pr.p1)) return;
     }
 
     const long lda = pr.lda, ldb = pr.ldb;
-    SplitSrc<NTI, kRows> src;
+    SplitSrc<kRows> src;
     {
         const long na = (long)pr.K * lda * 4, nb = (long)pr.K * ldb * 4;      // the host checked: below 2 GiB
         src.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A), 0, (int)na, 0x00020000);
@@ -118,28 +115,22 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
         src.init_thread(tid);
         src.lim_a = pr.M - m0;
         src.lim_b = pr.N - n0;
-        src.rows = pr.K;
-        src.diag_a = m0 - pr.krow;
-        src.diag_b = n0 - pr.krow;
-        src.off_a = 4u * (unsigned)m0;
-        src.off_b = 4u * (unsigned)n0;
         const int ca = m0 + src.col_a(0), cb = n0 + src.col_b(0);
         src.va[0] = ca < pr.M ? (unsigned)ca * 4u + 4u * (unsigned)src.kq * src.lda4 : W_OOB;
         src.vb[0] = cb < pr.N ? (unsigned)cb * 4u + 4u * (unsigned)src.kq * src.ldb4 : W_OOB;
     }
     const int lr = lane & 31, lg = lane >> 5;
     // row tiles this wavefront has to compute: none above the line n = m + doff or past the edges
-    const int mleft = pr.M - (m0 + wm * (BM / 2));
-    const bool idle = (lower && (n0 + wn * 64 > m0 + wm * (BM / 2) + BM / 2 - 1 + pr.doff)) || mleft <= 0 ||
+    const int mleft = pr.M - (m0 + wm * (S_BM / 2));
+    const bool idle = (lower && (n0 + wn * 64 > m0 + wm * (S_BM / 2) + S_BM / 2 - 1 + pr.doff)) || mleft <= 0 ||
                       n0 + wn * 64 >= pr.N;
     const int rows = idle ? 0 : (mleft + 31) / 32;
-    floatx16 acc[2 * NTI];
-    float none[NTI];
-    split_tile<NTI, kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid);
-    __syncthreads();
+    floatx16 acc[8];
+    float none[4];
+    split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid);
     if (idle) return;
 
-    // ---- epilogue: acc[ti*2 + tj][v] = C[m0 + wm*BM/2 + ti*32 + 8*(v>>2) + 4*lg + (v&3)][n0 + wn*64 + tj*32 + lr]
+    // ---- epilogue: acc[ti*2 + tj][v] = C[m0 + wm*S_BM/2 + ti*32 + 8*(v>>2) + 4*lg + (v&3)][n0 + wn*64 + tj*32 + lr]
     // A lane of the MFMA result holds single elements of many rows: written or updated from there, every memory
     // instruction moves 4 bytes per lane.  Instead each wavefront passes its part through LDS (the ring is free
     // now), 32 rows x 64 columns at a time, and reads it back with 16 lanes along a row, four columns each: the
@@ -154,7 +145,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     // epilogue take 40 us whatever K, more than half of a rank-256 update.  Such a chunk is now read like any other, and
     // stored with a 16-byte access by the lanes whose four columns are all wanted and up to three 4-byte accesses by
     // the others; what must not be written gets an offset outside the buffer.
-    const int mw = m0 + wm * (BM / 2), nw = n0 + wn * 64;
+    const int mw = m0 + wm * (S_BM / 2), nw = n0 + wn * 64;
     const int ldc = pr.ldc;
     constexpr int EP = 68;                                   // LDS row pitch of a chunk (floats)
     float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
@@ -164,9 +155,9 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const unsigned vo = (unsigned)(rr * ldc + c4) * 4u;
     const float sign = (lower && !add) ? -1.f : 1.f;
     auto row_off = [&](int ti, int q) { return (unsigned)((mw + ti * 32 + 4 * q) * ldc + nw) * 4u; };
-    floatx4 out[NTI][8];
+    floatx4 out[4][8];
 #pragma unroll
-    for (int t0 = 0; t0 < NTI; t0 += 2) {
+    for (int t0 = 0; t0 < 4; t0 += 2) {
 #pragma unroll
         for (int ti = t0; ti < t0 + 2; ++ti)
 #pragma unroll
@@ -182,7 +173,6 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
         for (int ti = t0; ti < t0 + 2; ++ti) {
 #pragma unroll
             for (int tj = 0; tj < 2; ++tj) {
-                split_unscale<NTI>(acc[2 * ti + tj], L, wm * (BM / 2) + ti * 32, wn * 64 + tj * 32 + lr, lg);
 #pragma unroll
                 for (int v = 0; v < 16; ++v)
                     wl[(8 * (v >> 2) + 4 * lg + (v & 3)) * EP + tj * 32 + lr] = acc[ti * 2 + tj][v];
@@ -210,7 +200,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
         return skip ? 0 : limit - n;
     };
 #pragma unroll
-    for (int ti = 0; ti < NTI; ++ti)
+    for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int have = wanted(mw + ti * 32 + 4 * q + rr);

@@ -20,7 +20,7 @@
 //     the next pivot block fused;
 //   - above: two-level blocking with 256-row outer blocks (BlockedRun below): the
 //     pivot block is inverted by the first form, the panel product W = P V, its
-//     gated refinement and the rank-256 update run on the split-fp16 GEMM
+//     gated refinement and the rank-256 update run on the split-bf16 GEMM
 //     (gemm_split.hpp), small kernels gather the old panel K-major and scatter
 //     the new one; with the library's streams the short dependent launches of
 //     step K+1 run beside the update of step K (look-ahead).
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void sweep_init_kernel(const InvTable tab)
 // Outer pivot blocks of PB rows (invert_outer_block, 256; a multiple of the 32-wide gather / scatter tiles, at
 // most 512).  Per outer step: the pivot block is inverted by the one-launch-per-step sweep above (a PB x PB
 // problem), the old panel is gathered K-major into V, W = V P (refined once where the pivot block is
-// ill-conditioned) and the rank-PB update of the rest of the triangle run on the split-fp16 GEMM, and the new panel
+// ill-conditioned) and the rank-PB update of the rest of the triangle run on the split-bf16 GEMM, and the new panel
 // and -P are scattered back in place.  512 is 12 % faster on the workloads with many large factors, but the error
 // of the inverse grows with the order of the explicitly inverted pivot block (measured at order 2305:
 // 2.8e-5 / 6.2e-5 for 256 / 512), so 256 stays.

@@ -16,7 +16,7 @@
 //   syrk_conv3_kernel      : 3x3 convolution inputs, patch matrix never built (syrk_conv3.hpp)
 //   syrk_small_nchw_kernel : narrow NCHW fp32, no LDS staging (syrk_small.hpp)
 //   syrk_bf16_kernel       : bf16 inputs on the bf16 MFMA units (syrk_bf16.hpp)
-//   syrk_split_kernel      : wide fp32 inputs as two fp16 pieces on the fp16 MFMA units (syrk_split.hpp)
+//   syrk_split_kernel      : wide fp32 inputs as three bf16 pieces on the bf16 MFMA units (syrk_split.hpp)
 //   syrk_reduce_kernel     : sums the slices in a fixed order (deterministic), applies scale and
 //                            the running average, writes both triangles.
 // The planner below picks the kernel and the split of K per factor and groups
@@ -684,10 +684,10 @@ void plan_group(const FactorJob *jobs, const std::vector<int> &idx, std::vector<
                 tpb_j = std::max<long>(1, std::min<long>(tpb_j, 0x7fffffffl / (64 * jobs[j].ld) - 1));
             if (p.cfg == kBf16Cfg && jobs[j].layout == kRows)
                 tpb_j = std::max<long>(1, std::min<long>(tpb_j, 0x7fffffffl / (2 * H_KT * jobs[j].ld) - 1));
-            // The MFMA adds its sixteen products to the accumulator with the low bits of the aligned addends cut off: on
-            // non-negative inputs (post-ReLU activations) every instruction biases the sum down a little (measured
-            // -9e-8 of the result over 256 stages of three products).  Slices are kept short; the reduction adds them
-            // in fp32 with round-to-nearest.
+            // The MFMA adds its sixteen products to the accumulator with the low bits of the aligned addends cut off, and
+            // every instruction rounds: an error of the result of 2.4e-7 after 32 stages of six products on post-ReLU
+            // data (6e-7 after 256; fp32 MFMA 1.7e-7 and 4.9e-7).  Slices are kept short; the reduction adds them in
+            // fp32 with round-to-nearest.
             if (p.cfg == kSplitCfg) tpb_j = std::max<long>(1, std::min<long>(tpb_j, tu.split_syrk_max_stages));
             p.splits = (int)((ktiles + tpb_j - 1) / tpb_j);
             // every element of the block-tile kernels' partials is summed serially over the splits by one
@@ -1038,7 +1038,7 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
                     KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, (syrk_split_kernel<kNCHW, true>), dim3(blocks), dim3(256), 0, tab);
                 else
                     KFAC_LAUNCH(KFAC_K_SYRK_SPLIT, s, (syrk_split_kernel<kNCHW, false>), dim3(blocks), dim3(256), 0, tab);
-                timing_work(flops, 3.0 * flops);
+                timing_work(flops, 6.0 * flops);
                 e = hipGetLastError();
                 break;
             }

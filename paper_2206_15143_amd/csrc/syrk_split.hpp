@@ -1,5 +1,5 @@
 // X^T X partial products for fp32 X (row-major patch matrices and linear-layer inputs, NCHW inputs of 1x1
-// convolutions and output gradients) on the fp16 MFMA units at fp32 accuracy: the split-fp16 core of
+// convolutions and output gradients) on the bf16 MFMA units at fp32 accuracy: the split-bf16 core of
 // split_common.hpp applied to the Kronecker factors of Eq. 4 of the DP-KFAC paper.
 //
 // A workgroup of four wavefronts owns a 256 x 128 tile of the lower triangle (256 columns of X as rows of the
@@ -29,8 +29,8 @@ __host__ __device__ inline int syrk_split_tiles(int d)
 template <int LAYOUT, bool MASK>
 __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
 {
-    __shared__ __attribute__((aligned(16))) SplitLds<4> L;
-    typedef SplitSrc<4, LAYOUT> Src;
+    __shared__ __attribute__((aligned(16))) SplitLds L;
+    typedef SplitSrc<LAYOUT> Src;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -70,9 +70,6 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
     src.init_thread(tid);
     src.lim_a = d - m0;
     src.lim_b = d - n0;
-    src.rows = 0;                                     // no diagonal elements to look at
-    src.diag_a = src.diag_b = 0;
-    src.off_a = src.off_b = 0u;
     if (LAYOUT == kRows) {
         const long ktiles = (pr.K + S_KT - 1) / S_KT;
         const long t1 = (t0 + pr.tiles_per_split < ktiles) ? t0 + pr.tiles_per_split : ktiles;
@@ -120,8 +117,8 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
     const int mleft = d - (m0 + wm * 128);
     const bool idle = n0 + wn * 64 > m0 + wm * 128 + 127 || mleft <= 0 || n0 + wn * 64 >= d;
     const int rows = idle ? 0 : (mleft + 31) / 32;
-    if (J >= 2 * I) split_tile<4, LAYOUT, true, MASK>(src, L, acc, csum, n0 - m0, rows, wm, wn, tid);
-    else split_tile<4, LAYOUT, false, MASK>(src, L, acc, csum, 0, rows, wm, wn, tid);
+    if (J >= 2 * I) split_tile<LAYOUT, true, MASK>(src, L, acc, csum, n0 - m0, rows, wm, wn, tid);
+    else split_tile<LAYOUT, false, MASK>(src, L, acc, csum, 0, rows, wm, wn, tid);
 
     // ---- partial tile -> block (bi, bj) = (I, J / 2) of the slice, columns 128 (J & 1) .. of the block ----
     const int nblk = pr.nb * (pr.nb + 1) / 2;
@@ -147,7 +144,6 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
     for (int ti = 0; ti < 4; ++ti) {
 #pragma unroll
         for (int tj = 0; tj < 2; ++tj) {
-            split_unscale<4>(acc[ti * 2 + tj], L, wm * 128 + ti * 32, wn * 64 + tj * 32 + lr, lg);
 #pragma unroll
             for (int v = 0; v < 16; ++v)
                 wl[(8 * (v >> 2) + 4 * lg + (v & 3)) * EP + tj * 32 + lr] = acc[ti * 2 + tj][v];
