@@ -272,7 +272,8 @@ def test_preconditioning_of_unevenly_scaled_features(sigma):
 @pytest.mark.parametrize("d_in,d_out", [(1023, 400), (1024, 300), (2300, 200), (5000, 130)])
 def test_k_slices_of_one_layer(d_in, d_out):
     """A call of one layer: its deep products are cut into slices of 40 stages and more, up to eight of them.  The same
-    bound as above, twice: the first product's error passes through the second."""
+    bound as above, twice: the first product's error passes through the second.  A workspace without room for the slices
+    leaves the products in one piece: other bits, or the slices were not used."""
     d = kf.LayerDesc.linear(d_in, d_out, True, kf.KFAC_F32)
     g = torch.Generator(device=DEV)
     g.manual_seed(5)
@@ -282,7 +283,12 @@ def test_k_slices_of_one_layer(d_in, d_out):
     work = torch.empty(kf.kfac_workspace_bytes(d, 8, 1, 1), dtype=torch.uint8, device=DEV)
     out = torch.empty(d_out, n, device=DEV)
     kf.kfac_precondition(d, A, G, W, out, work)
+    whole = torch.empty_like(out)
+    least = (d_out * n * 4 + 255) // 256 * 256
+    assert work.numel() > least
+    kf.kfac_precondition(d, A, G, W, whole, work[:least])
     torch.cuda.synchronize()
+    assert not torch.equal(out, whole), "the slices were not used"
     a, b, w = A.double().cpu(), G.double().cpu(), W.double().cpu()
     mag = b.abs() @ w.abs() @ a.abs()
     bound = (2 + n + d_out + 4) * 2.0 ** -24 * mag
