@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const int rows = idle ? 0 : (mleft + 31) / 32;
     floatx16 acc[8];
     float none[4];
-    split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid);
+    const float unscale = split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid);
     if (idle) return;
 
     // ---- epilogue: acc[ti*2 + tj][v] = C[m0 + wm*S_BM/2 + ti*32 + 8*(v>>2) + 4*lg + (v&3)][n0 + wn*64 + tj*32 + lr]
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     // the host checked that M rows of C are below 2 GiB
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.C, 0, (int)((long)pr.M * ldc * 4), 0x00020000);
     const unsigned vo = (unsigned)(rr * ldc + c4) * 4u;
-    const float sign = (lower && !add) ? -1.f : 1.f;
+    const float sign = (lower && !add) ? -unscale : unscale;
     auto row_off = [&](int ti, int q) { return (unsigned)((mw + ti * 32 + 4 * q) * ldc + nw) * 4u; };
     floatx4 out[4][8];
 #pragma unroll

@@ -1,10 +1,12 @@
 // The split-bf16 product core shared by gemm_split.hpp and syrk_split.hpp: tiles of C = A^T B for fp32 operands on
 // the bf16 MFMA units, at fp32 accuracy for every finite input.
 //
-// Arithmetic.  Every operand value is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1)
-// and x3 the rest, x1 and x2 rounded to nearest.  The cut is exact: x - x1 has 16 bits left, x - x1 - x2 seven, and bf16
-// has the exponents of fp32, so that nothing depends on how an operand's values compare with each other.  The product
-// keeps the six largest of the nine piece products,
+// Arithmetic.  Every operand value, times 2^16, is cut into three bf16 pieces, x = x1 + x2 + x3 with x1 = bf16(x),
+// x2 = bf16(x - x1) and x3 the rest, x1 and x2 rounded to nearest.  The cut is exact: x - x1 has 16 bits left,
+// x - x1 - x2 seven, and bf16 has the exponents of fp32, so that nothing depends on how an operand's values compare with
+// each other.  (The last bit of a bf16 number is at least 2^-133, of an fp32 number 2^-149: without the 2^16, values
+// below 2^-110 lost bits of their last piece, those of 2^-120 kept 14 of 24.  The results are divided by 2^32.)
+// The product keeps the six largest of the nine piece products,
 //     a b  ~  a1 b1 + a1 b2 + a2 b1 + a1 b3 + a3 b1 + a2 b2,
 // each exact in the fp32 accumulator of v_mfma_f32_32x32x16_bf16.  |x2| <= 2^-8 |x| and |x3| <= 2^-17 |x|, so the terms
 // left out (a2 b3, a3 b2, a3 b3) are below 2^-24 |a b| and as often positive as negative.  The rounding matters: the
@@ -15,7 +17,7 @@
 // largest one of its column only: a feature of scale 2^24 whose inverse column is as much smaller came out with an error of
 // 1e-3, and no test on the results finds every such case.)
 //
-// Infinities, NaN and values that round up to infinity give accumulators that are not finite (inf - inf in the
+// Infinities, NaN, values from 2^112 and sums from 2^96 on give accumulators that are not finite (inf - inf in the
 // cut).  A tile with such a result is computed once more on the fp32 MFMA, which leaves what fp32 arithmetic gives.
 //
 // Pipeline.  A workgroup of four wavefronts owns a tile of 256 x 128, a wavefront 128 x 64 of it.  K goes in stages of
@@ -23,13 +25,14 @@
 // instruction costs a wavefront about 16 cycles of the address unit whatever its width), two stages ahead.  The values
 // are converted ONCE per workgroup and written to LDS as halves of ready fragments (a fragment = the eight k of one
 // column and piece = 16 bytes) in two buffers (74 KB: two workgroups per CU), one barrier per stage.  The conversion
-// (7.5 VALU operations per value) runs between the MFMAs, about four operations beside each of the 48 of a wavefront.
+// (8.5 VALU operations per value) runs between the MFMAs, about four operations beside each of the 48 of a wavefront.
 // Fragments of consecutive columns are spread over LDS by split_slot so that the MFMA reads (32 consecutive columns) and
 // the writes (every fourth column) both touch every bank group equally.
-// Bound: MFMA.  4096^3 (705 us, 1170 TFLOP/s of bf16 products): the units are busy 80 % of the cycles, no bank conflicts,
-// and the chip, short of power, runs at about 1.5 GHz.  (The barrier ahead of the last MFMAs of a stage, with the first
-// fragments of the next one read behind it: 735 us.  Six products of truncated pieces cut by every wavefront for itself:
-// 779 us.)
+// Bound: MFMA.  4096^3: the units are busy 80 % of the cycles, no bank conflicts, and the chip, short of power, runs at
+// about 1.5 GHz.  624 us (1320 TFLOP/s of bf16 products) where the form without the 2^16 takes 614; 1024^3, one tile per
+// CU at most, 77 against 73 us.  (On a card where that form takes 705 us: the barrier ahead of the last MFMAs of a stage,
+// with the first fragments of the next one read behind it, 735 us; six products of truncated pieces cut by every wavefront
+// for itself, 779 us.)
 #pragma once
 
 #include <type_traits>
@@ -48,12 +51,20 @@ typedef unsigned suint2 __attribute__((ext_vector_type(2)));
 typedef int sint4 __attribute__((ext_vector_type(4)));
 typedef int sint2 __attribute__((ext_vector_type(2)));
 
+constexpr int kSplitShift = 16;                          // every operand value times 2^16 ...
+constexpr float kSplitUnscale = 1.f / 4294967296.f;      // ... and every sum of products times 2^-32
+
 // The cut of four values (the k of one column), in eight steps of about four operations that the K loop spreads over
 // its MFMAs.  Rounded to bf16 (ties away from zero): half a unit added to the bit pattern, which may carry into the exponent.
 // (v_cvt_pk_bf16_f32 issues at a quarter of the rate of these.)
 struct SplitCut {
     unsigned t[4];
     float h[4];
+    __device__ __forceinline__ void scale(float (&x)[4]) const
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = __builtin_amdgcn_ldexpf(x[e], kSplitShift);
+    }
     __device__ __forceinline__ void half(const float (&x)[4], int from, int to)
     {
 #pragma unroll
@@ -210,7 +221,8 @@ struct SplitSrc {
     }
 };
 
-// The K loop of a tile.  acc: eight accumulator tiles, [ti][tj], of the wavefront's 128 x 64 part.  SHARED: B's columns
+// The K loop of a tile.  acc: eight accumulator tiles, [ti][tj], of the wavefront's 128 x 64 part, times the inverse of
+// what is returned (the same for the whole workgroup).  SHARED: B's columns
 // are columns boff .. boff + 127 of A (tiles on the diagonal of X^T X; boff is 0 or 128): B is neither loaded nor
 // converted, and the sums of this thread's columns of A over its k go to csum.  MASK: some NCHW problem of the launch has a
 // number of positions that is no multiple of 4 (positions past the end of an image hold the next channel's data).
@@ -218,8 +230,8 @@ struct SplitSrc {
 // multiplies that one (the bias column makes orders of 2^n + 1 the rule here: a tile for a single row would otherwise
 // cost as much power, which is what the full chip is short of, as a whole one); more: all of them.
 template <int LAYOUT, bool SHARED, bool MASK>
-__device__ __forceinline__ void split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, floatx16 (&acc)[8], float (&csum)[4], int boff,
-                                           int rows, int wm, int wn, int tid)
+__device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, floatx16 (&acc)[8], float (&csum)[4], int boff,
+                                            int rows, int wm, int wn, int tid)
 {
     typedef SplitSrc<LAYOUT> Src;
     typedef SplitLds Lds;
@@ -269,24 +281,25 @@ __device__ __forceinline__ void split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, f
                 for (int e = 0; e < 4; ++e) x[e] = 4 * src.kq + e < valid ? x[e] : 0.f;
             }
             if (SHARED) csum[i] += (x[0] + x[1]) + (x[2] + x[3]);
-            cut.half(x, 0, 4);
+            cut.scale(x);
         } else if (step == 1) {
-            cut.top(0, 4);
+            cut.half(x, 0, 4);
         } else if (step == 2) {
+            cut.top(0, 4);
+        } else if (step == 3) {
             d[0] = cut.pack();
             cut.rest(x, 0, 2);
-        } else if (step == 3) {
+        } else if (step == 4) {
             cut.rest(x, 2, 4);
             cut.half(x, 0, 2);
-        } else if (step == 4) {
+        } else if (step == 5) {
             cut.half(x, 2, 4);
             cut.top(0, 2);
-        } else if (step == 5) {
+        } else if (step == 6) {
             cut.top(2, 4);
             d[next] = cut.pack();
-        } else if (step == 6) {
-            cut.rest(x, 0, 4);
         } else {
+            cut.rest(x, 0, 4);
             d[2 * next] = cut.pack_last(x);
         }
     };
@@ -399,7 +412,7 @@ __device__ __forceinline__ void split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, f
         if (!finite) L.redo = 1;
     }
     __syncthreads();
-    if (L.redo == 0) return;
+    if (L.redo == 0) return kSplitUnscale;
     // ---- the fp32 MFMA: rare, written for size ----
 #pragma unroll
     for (int i = 0; i < 8; ++i)
@@ -436,6 +449,7 @@ __device__ __forceinline__ void split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, f
         }
         __syncthreads();
     }
+    return 1.f;
 }
 
 }  // namespace kfac

@@ -117,8 +117,8 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
     const int mleft = d - (m0 + wm * 128);
     const bool idle = n0 + wn * 64 > m0 + wm * 128 + 127 || mleft <= 0 || n0 + wn * 64 >= d;
     const int rows = idle ? 0 : (mleft + 31) / 32;
-    if (J >= 2 * I) split_tile<LAYOUT, true, MASK>(src, L, acc, csum, n0 - m0, rows, wm, wn, tid);
-    else split_tile<LAYOUT, false, MASK>(src, L, acc, csum, 0, rows, wm, wn, tid);
+    const float unscale = J >= 2 * I ? split_tile<LAYOUT, true, MASK>(src, L, acc, csum, n0 - m0, rows, wm, wn, tid)
+                                     : split_tile<LAYOUT, false, MASK>(src, L, acc, csum, 0, rows, wm, wn, tid);
 
     // ---- partial tile -> block (bi, bj) = (I, J / 2) of the slice, columns 128 (J & 1) .. of the block ----
     const int nblk = pr.nb * (pr.nb + 1) / 2;
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void syrk_split_kernel(const SyrkTable tab)
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             const int row = 4 * q + rr;
-            const floatx4 val = *reinterpret_cast<const floatx4 *>(wl + row * EP + c4);
+            const floatx4 val = *reinterpret_cast<const floatx4 *>(wl + row * EP + c4) * unscale;
             *reinterpret_cast<floatx4 *>(dst + (long)(wm * 128 + ti * 32 + row) * S_BM + c4) = val;
         }
     }

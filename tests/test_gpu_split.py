@@ -1,7 +1,7 @@
 """The split-bf16 kernels against float64: edges of their 256 x 128 tiles and 16-row stages, lower triangle updates with
 an untouched band, operands whose columns or rows differ wildly in size, large values of one operand that only meet
-zeros or tiny values of the other (in all of a tile, in a few of its rows, in a quarter of its columns), infinities, NaN
-and values next to the largest one, and what lies between the columns of an operand and its pitch.
+zeros or tiny values of the other (in all of a tile, in a few of its rows, in a quarter of its columns), the smallest
+fp32 numbers, sums of the largest, infinities, NaN and values next to the largest one, and what lies between the columns of an operand and its pitch.
 
 Bound per element: the cut into pieces leaves 2^-24 |a||b| per product, and a sum of K products that is accumulated in
 fp32 loses at most K 2^-24 of sum |a||b|.
@@ -57,6 +57,16 @@ def operands(M, N, K, kind, seed):
         A[1] *= 2.0 ** 24
         B[1] *= 2.0 ** -24
         A[1, :4] = 0
+    elif kind == "tiny":                             # next to the smallest fp32 numbers, down to subnormal ones
+        A *= 2.0 ** -119 * torch.exp2(torch.linspace(0, -20, K, device=DEV))[:, None]
+        B *= 2.0 ** 100 * torch.exp2(torch.linspace(0, 20, K, device=DEV))[:, None]
+    elif kind == "tiny_rest":                        # tiny values of B beside ordinary ones that meet zeros
+        A[::2] = 0
+        A[1::2] *= 2.0 ** 90
+        B[1::2] *= 2.0 ** -121
+    elif kind == "huge":                             # sums that leave the range of the scaled accumulators
+        A *= 2.0 ** 60
+        B *= 2.0 ** 50
     return A, B
 
 
@@ -85,6 +95,11 @@ def operands(M, N, K, kind, seed):
     (256, 769, 769, 0, 0, 0, "one_feature"),
     (1153, 1153, 256, 2, 512, 768, "two_levels"),
     (1153, 1153, 256, 2, 512, 768, "features"),
+    (512, 769, 256, 0, 0, 0, "tiny"),
+    (769, 512, 1030, 0, 0, 0, "tiny_rest"),
+    (1153, 1153, 256, 2, 512, 768, "tiny"),
+    (257, 513, 135, 0, 0, 0, "huge"),
+    (1025, 1025, 256, 2, 256, 512, "huge"),
     (1090, 127, 128, 0, 0, 0, "relu"),              # ... and just outside: the other kernels
     (640, 512, 127, 0, 0, 0, "normal"),
 ])
@@ -164,12 +179,13 @@ def test_columns_between_the_operand_and_its_pitch_have_no_say(fill):
 
 
 def factor_bound(x, scale):
-    """sum over rows of |x_i x_j|, times what the cut and the sums in fp32 may cost per term"""
+    """sum over rows of |x_i x_j|, times what the cut and the sums in fp32 may cost per term, and the last bit of the
+    smallest fp32 numbers for each of them"""
     mag = np.abs(x).T @ np.abs(x) * scale
-    return (4 + x.shape[0]) * 2.0 ** -24 * mag
+    return (4 + x.shape[0]) * (2.0 ** -24 * mag + 2.0 ** -149)
 
 
-@pytest.mark.parametrize("kind", ["normal", "late", "features", "samples", "two_levels"])
+@pytest.mark.parametrize("kind", ["normal", "late", "features", "samples", "two_levels", "tiny"])
 @pytest.mark.parametrize("shape", ["rows", "nchw_even", "nchw_odd"])
 def test_split_factors(kind, shape):
     """Factors of uneven inputs through the public call, element by element: row-major operands, NCHW operands on maps
@@ -199,6 +215,9 @@ def test_split_factors(kind, shape):
             half = len(v) // 2
             v[:half, col % 2 == 0] *= 1e-12
             v[half:, col % 2 == 1] *= 1e-12
+        elif kind == "tiny":             # one column in two next to the smallest fp32 numbers, the others large
+            v[:, col % 2 == 0] *= 2.0 ** -119
+            v[:, col % 2 == 1] *= 2.0 ** 40
     x, y = x.astype(np.float32), y.astype(np.float32)
     if shape != "rows":
         x, y = x.reshape(B, d_in, h, w), y.reshape(B, d_out, h, w)
