@@ -237,20 +237,28 @@ def test_split_factors(kind, shape):
         assert np.all(err <= bound), f"error {np.max(err / np.maximum(bound, 1e-300)):.3f} of the bound"
 
 
-def test_infinite_input_of_a_split_factor():
+@pytest.mark.parametrize("shape", ["rows", "nchw_even", "nchw_odd"])
+def test_infinite_input_of_a_split_factor(shape):
     """One infinite activation: its row and column of the factor are infinite (NaN where it meets a zero), the rest is
-    what it was."""
-    B, n = 400, 512
+    what it was.  Row-major operands and NCHW ones, whose positions past the end of an image are cut off in the second
+    computation of a tile too; tiles on the diagonal and off it."""
+    n = 512
     g = torch.Generator(device=DEV)
     g.manual_seed(9)
-    x = torch.randn(B, n, generator=g, device=DEV)
-    y = torch.randn(B, 256, generator=g, device=DEV)
-    x[17] = x[17].abs() + 0.1
-    x[17, 300], x[17, 31] = float("inf"), 0.0
-    d = kf.LayerDesc.linear(n, 256, False, kf.KFAC_F32)
-    work = torch.empty(kf.kfac_workspace_bytes(d, B, 1, 1), dtype=torch.uint8, device=DEV)
+    if shape == "rows":
+        B, h, w = 400, 1, 1
+        d = kf.LayerDesc.linear(n, 256, False, kf.KFAC_F32)
+    else:
+        B, (h, w) = 9, (8, 6) if shape == "nchw_even" else (7, 5)
+        d = kf.LayerDesc.conv2d(n, 256, 1, 1, 0, False, kf.KFAC_F32)
+    X = torch.randn(B * h * w, n, generator=g, device=DEV)            # one row per example and position
+    X[17] = X[17].abs() + 0.1
+    X[17, 300], X[17, 31] = float("inf"), 0.0
+    x = X if shape == "rows" else X.view(B, h, w, n).permute(0, 3, 1, 2).contiguous()
+    y = torch.randn((B, 256) if shape == "rows" else (B, 256, h, w), generator=g, device=DEV)
+    work = torch.empty(kf.kfac_workspace_bytes(d, B, h, w), dtype=torch.uint8, device=DEV)
     A, G = torch.zeros(n, n, device=DEV), torch.zeros(256, 256, device=DEV)
-    kf.kfac_update_factors(d, x, y, B, 1, 1, 1.0, 1.0, 0.0, A, G, work)
+    kf.kfac_update_factors(d, x, y, B, h, w, 1.0, 1.0, 0.0, A, G, work)
     torch.cuda.synchronize()
     got = A.cpu()
     want = torch.full((n,), float("inf"))
@@ -258,7 +266,7 @@ def test_infinite_input_of_a_split_factor():
     assert torch.equal(got[300].isnan(), want.isnan()) and torch.equal(got[300].nan_to_num(0.0), want.nan_to_num(0.0))
     assert torch.equal(got[300].isnan(), got[:, 300].isnan())
     keep = torch.arange(n) != 300
-    ref = x.double().cpu()[:, keep]
+    ref = X.double().cpu()[:, keep]
     err = (got[keep][:, keep].double() - ref.T @ ref).abs().numpy()
     assert np.all(err <= factor_bound(ref.numpy(), 1.0))
 
