@@ -55,3 +55,26 @@ def test_batched_inverses_equal_single_ones(orders):
             cond = float(torch.linalg.matrix_norm(damped, 2) * torch.linalg.matrix_norm(ref, 2))
             err = float((x.double().cpu() - ref).norm() / ref.norm())
             assert err <= 8 * cond * 2.0 ** -24, (m.shape[0], err, cond)
+
+
+@pytest.mark.parametrize("a,g", [(1, 63), (64, 65), (127, 128), (129, 192), (193, 300), (640, 641), (1280, 1279)])
+def test_only_the_lower_triangle_has_a_say(a, g):
+    """Bit for bit the same inverse whatever lies above the diagonal of the factor: tiles on the diagonal are read whole,
+    and those that the edge of the matrix cuts off from clamped addresses."""
+    d = kf.LayerDesc.linear(a, g, False, kf.KFAC_F32)
+    work = torch.empty(kf.kfac_workspace_bytes(d, 1, 1, 1), dtype=torch.uint8, device=DEV)
+    info = torch.full((2,), -1, dtype=torch.int32, device=DEV)
+    got = []
+    for fill in (False, True):
+        A, G = factor(a, 3), factor(g, 4)
+        if fill:
+            for m in (A, G):
+                m.masked_fill_(torch.ones_like(m, dtype=torch.bool).triu(1), float("nan"))
+        Ai, Gi = torch.full_like(A, float("nan")), torch.full_like(G, float("nan"))
+        kf.kfac_invert(d, A, G, LAM, LAM, Ai, Gi, info, work)
+        torch.cuda.synchronize()
+        assert int(info.abs().max()) == 0
+        got.append((Ai, Gi))
+    for x, y in zip(*got):
+        assert torch.equal(x, y) and bool(torch.isfinite(x).all())
+        assert torch.equal(x, x.T)
