@@ -6,10 +6,11 @@ factor construction (im2col + SYRK + running average), damped inversion of
 every A and G, and two-sided preconditioning of every layer gradient, through
 the batched C-ABI entry points.  Inputs are synthetic, resident in HBM before
 the timed region.  Prints ONE JSON line: the headline workload (ResNet-50-shaped,
-fp32, the paper's precision) at the top level, the other configurations as
-sub-objects of `other_configs`.
+fp32, the paper's precision) at the top level, the main figures of the other
+configurations as sub-objects of `other_configs`.  --details writes everything that
+was measured (every kernel class of every configuration, what the figures mean).
 
-    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config NAME] [--only-headline]
+    python bench.py [--gpus 1] [--steps K] [--warmup W] [--config NAME] [--only-headline] [--details FILE]
 """
 from __future__ import annotations
 
@@ -56,6 +57,7 @@ def parse():
     ap.add_argument("--only-headline", action="store_true", help="skip the other configurations")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--tune", action="append", default=[], help="development knob key=value")
+    ap.add_argument("--details", default=None, help="write all figures to this file, as JSON")
     ap.add_argument("--seed", type=int, default=2000)
     ap.add_argument("--variant", choices=["inverse", "eigen"], default="inverse",
                     help="inverse: damped inverses + G_inv grad A_inv (the headline path); "
@@ -385,6 +387,45 @@ def run_config(name, args, kf, torch, steps, warmup, cpu_budget):
     return out
 
 
+def printed(out):
+    """What the printed line holds of `out`.  It stays below 6000 characters, whatever kernels ran: logs that keep the
+    last few thousand characters of a run then keep it whole (with every figure of every configuration it had 20 000)."""
+    def pick(d, *keys):
+        return {k: d[k] for k in keys if k in d}
+
+    def short(d):
+        r = {}
+        if "roofline" in d:
+            r["roofline"] = pick(d["roofline"], "bound", "kernel", "achieved", "peak", "unit", "frac", "traffic", "mfma_dtype",
+                                 "launches_per_step", "avg_launch_ms", "executed_flops_per_launch", "definition_equiv_tflops",
+                                 "share_of_step", "note", "traffic_note")
+        for k in ("running_average", "im2col"):
+            if k in d:
+                r[k] = pick(d[k], "kernel", "achieved", "unit", "frac", "ms_per_step", "moved_gbps")
+        if "kf_gemm" in d:
+            r["kf_gemm"] = pick(d["kf_gemm"], "mfma_util_pct", "ms_per_step", "definition_equiv_tflops")
+        if "cpu_baseline" in d:
+            r["cpu_baseline"] = pick(d["cpu_baseline"], "value", "unit", "cores", "kind", "sample")
+        if "stale_schedule" in d:
+            r["stale_schedule"] = d["stale_schedule"]
+        return r
+
+    line = {k: v for k, v in out.items() if k not in ("cold_note", "kernels", "algorithmic_work", "other_configs", "paper_context")}
+    line.update(short(out))
+    line["kernels"] = {k: pick(v, "ms_per_step", "launches_per_step", "achieved", "frac")
+                       for k, v in out.get("kernels", {}).items()}
+    if "other_configs" in out:
+        line["other_configs"] = {}
+        for name, d in out["other_configs"].items():
+            o = pick(d, "ms_per_step", "cold_ms_per_step", "dtype", "steps")
+            s = short(d)
+            o["roofline"] = pick(s.get("roofline", {}), "kernel", "achieved", "peak", "frac")
+            o["kf_gemm_mfma_util_pct"] = s.get("kf_gemm", {}).get("mfma_util_pct")
+            o["cpu_baseline_ms"] = s.get("cpu_baseline", {}).get("value")
+            line["other_configs"][name] = o
+    return line
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -432,7 +473,10 @@ def main():
     cdst = torch.empty_like(csrc)
     kf.kfac_profile_copy(cdst, csrc, csrc.numel())
     torch.cuda.synchronize()
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(printed(out)))
 
 
 if __name__ == "__main__":
