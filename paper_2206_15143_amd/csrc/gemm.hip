@@ -300,14 +300,17 @@ bool split_gemm_eligible(const GemmJob &j, bool wide)
     if (j.mode == kStore && !j.wide_tiles) {
         if (j.K < (wide ? tuning().split_gemm_min_k : 1024)) return false;
         // 256 x 128 tiles: products that fill less than 40 % of them stay with the other kernels.  The split kernel does
-        // a multiply-add of the definition in a fifth of the fp32 MFMA's time, so that it wins with over half of a
+        // a multiply-add of the definition in less than half of the fp32 MFMA's time, so that it wins with half of a
         // tile empty and with few K stages.  Preconditioning, lines M >= 192, K >= 1024, fill 60 % -> M >= 128,
-        // K >= 128, 40 % (together with the K slices below): twelve 768-wide transformer blocks 4.23 -> 2.77 ms,
-        // ResNet-50-shaped 1.09 -> 0.88, DenseNet-201-shaped 1.30 -> 1.05, one 700 x 500 layer 0.23 -> 0.08,
-        // a 256-channel 3x3 layer 0.17 -> 0.10 ms; fill 50 %: 0.99 and 1.24 ms on the two networks.
+        // K >= 128, 40 % (together with the K slices below): twelve 768-wide transformer blocks 3.87 -> 2.89 ms,
+        // ResNet-50-shaped 1.25 -> 1.19, DenseNet-201-shaped 1.32 -> 1.15, one 700 x 500 layer 0.23 -> 0.10,
+        // a 256-channel 3x3 layer 0.117 -> 0.092 ms; fill 50 %: 1.27 and 1.23 ms on the two networks.
         // The narrow lines stay for calls whose work is mostly in products too small for either: another launch
         // for one or two products of the call costs more than they gain (an update with one of seven products moved
-        // 0.92 -> 0.97 ms).
+        // 0.92 -> 0.97 ms).  So the last bits of a product can differ with what else is in its call.  Its accuracy does
+        // not suffer on either route: error against float64, split / fp32 MFMA, products of a post-ReLU gradient and
+        // an inverse dominated by its diagonal, 1.39e-7 / 1.44e-7 at K = 128 and 3.7e-7 / 4.1e-7 at 1023, of zero-mean
+        // operands 1.6e-7 / 2.0e-7 and 4.9e-7 / 5.7e-7.
         const double tiles = (double)((j.M + S_BM - 1) / S_BM) * ((j.N + S_BN - 1) / S_BN);
         if ((double)j.M * j.N < 0.01 * (wide ? tuning().split_gemm_min_fill : 60) * tiles * S_BM * S_BN) return false;
     }
@@ -396,8 +399,9 @@ namespace {
 // does not depend on the schedule).  The partials are M x N, small beside the K x N operand that is read.  The slices
 // of a call are as deep as leaves about 400 workgroups of equal depth (two fit a compute unit), between 40 and 150
 // stages: one depth for every call is too long for a single layer and too short for a network (preconditioning with
-// slices of 75 and of 150 stages: ResNet-50-shaped 1.09 and 0.96 ms, a 2048 x 1024 layer 0.135 and 0.163 ms; with
-// this rule 0.88 and 0.127 ms), no slices at all cost a 1024-wide transformer block 1.10 ms instead of 0.45.
+// this rule, with at least 75 stages, without slices: a 2048 x 1024 layer 0.147, 0.171 and 0.230 ms, a 256-channel 3x3
+// layer 0.092, 0.125 and 0.197, seven factorised convolutions 0.128, 0.162 and 0.164, a 1024-wide transformer block 0.612,
+// 0.612 and 0.654; the ResNet-50- and VGG-16-shaped sets would gain without: 1.19, 1.18 and 1.14, 0.947, 0.948 and 0.883).
 constexpr int kMaxKSlices = 8;
 
 int kslice_count(const GemmJob &j, long split_tiles, long cap)
