@@ -363,7 +363,8 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
 // has its operands swapped, so that a lane's four accumulators are neighbours of a row of the matrix.  24 memory
 // instructions per wavefront and tile instead of 72; the pitch of 68 keeps both LDS operand reads (rows 4 apart)
 // free of conflicts and makes room for four workgroups per CU.
-// All steps of the matrices up to order 1280 of a DenseNet-201-shaped network 9.2 -> 7.1 ms of kernel time, of 24
+// All steps of the matrices up to order 1280 of a DenseNet-201-shaped network 9.2 -> 7.1 ms of kernel time (6.0 with
+// the loads of the diagonal and edge tiles as they are below), of 24
 // transformer blocks of width 1024 (144 matrices of order 1024 and pivot blocks beside other kernels) 20.8 -> 11.9 ms.
 __device__ __forceinline__ int fold_k(int s4, int lk) { return 16 * (s4 >> 2) + 4 * lk + (s4 & 3); }
 
