@@ -321,3 +321,33 @@ def test_k_slices_of_one_layer(d_in, d_out):
     bound = (2 + n + d_out + 4) * 2.0 ** -24 * mag
     worst = ((out.double().cpu() - b @ w @ a).abs() / bound).max().item()
     assert worst <= 1.0, f"error {worst:.3f} of the bound"
+
+
+def test_accuracy_of_a_layer_does_not_depend_on_its_call():
+    """Alone in its call a 700 x 500 layer is multiplied by the split kernel, beside many small ones by the fp32 kernels
+    (other bits, or the routes were the same): the bound of preconditioning holds for both, and both are equally close."""
+    descs = [kf.LayerDesc.linear(699, 500, True, kf.KFAC_F32)] + [kf.LayerDesc.linear(99, 100, True, kf.KFAC_F32)] * 400
+    g = torch.Generator(device=DEV)
+    g.manual_seed(8)
+
+    def inverse(n):
+        r = torch.randn(n, n, generator=g, device=DEV)
+        return (r + r.T) * (0.05 / n ** 0.5) + torch.diag(torch.rand(n, generator=g, device=DEV) + 0.5)
+    A, G = [inverse(700)] + [inverse(100)] * 400, [inverse(500)] + [inverse(100)] * 400
+    W = [torch.randn(500, 700, generator=g, device=DEV)] + [torch.randn(100, 100, generator=g, device=DEV)] * 400
+    got = []
+    for n in (1, 401):
+        one = [1] * n
+        work = torch.empty(kf.kfac_workspace_bytes_batched(descs[:n], one, one, one), dtype=torch.uint8, device=DEV)
+        out = [torch.empty_like(w) for w in W[:n]]
+        kf.kfac_precondition_batched(descs[:n], A[:n], G[:n], W[:n], out, work)
+        torch.cuda.synchronize()
+        got.append(out[0].double().cpu())
+    assert not torch.equal(*got)
+    a, b, w = A[0].double().cpu(), G[0].double().cpu(), W[0].double().cpu()
+    ref = b @ w @ a
+    bound = (2 + 700 + 500 + 4) * 2.0 ** -24 * (b.abs() @ w.abs() @ a.abs())
+    for x in got:
+        assert ((x - ref).abs() / bound).max().item() <= 1.0
+    alone, batched = ((x - ref).norm().item() for x in got)
+    assert alone <= 1.1 * batched
