@@ -4,6 +4,7 @@
 
 #include "common.hpp"
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -358,13 +359,42 @@ void precond_jobs(const kfac_layer_desc &d, const float *A_inv, const float *G_i
     b.M = dG; b.N = dA; b.K = dA; b.lda = dG; b.ldb = dA; b.ldc = dA; b.mode = kStore; b.p0 = b.p1 = 0;
 }
 
-// ... plus room for the K-slice partials of the deeper of the two groups of products
+// ... plus room for the K-slice partials of the deeper of the two groups of products, whether the narrow layers go
+// through the one-launch form or (an output overlaps a gradient) through the two products like the others
 size_t precond_ws(int n, const kfac_layer_desc *descs)
 {
-    std::vector<GemmJob> g1(n), g2(n);
-    for (int i = 0; i < n; ++i) precond_jobs(descs[i], nullptr, nullptr, nullptr, nullptr, nullptr, g1[i], g2[i]);
-    return precond_ws_min(n, descs) + align_up(std::max(gemm_workspace_bytes(g1.data(), n),
-                                                        gemm_workspace_bytes(g2.data(), n)), 256);
+    std::vector<GemmJob> g1(n), g2(n), w1, w2;
+    for (int i = 0; i < n; ++i) {
+        precond_jobs(descs[i], nullptr, nullptr, nullptr, nullptr, nullptr, g1[i], g2[i]);
+        if (precond_fused_takes(g1[i].M, g1[i].N)) continue;
+        w1.push_back(g1[i]);
+        w2.push_back(g2[i]);
+    }
+    const int nw = (int)w1.size();
+    const size_t all = std::max(gemm_workspace_bytes(g1.data(), n), gemm_workspace_bytes(g2.data(), n));
+    const size_t wide = std::max(gemm_workspace_bytes(w1.data(), nw), gemm_workspace_bytes(w2.data(), nw));
+    return precond_ws_min(n, descs) + align_up(std::max(all, wide), 256);
+}
+
+// Whether an output of the call overlaps a layer gradient of the call (its own, in place, is allowed).
+bool precond_overlap(int n, const kfac_layer_desc *descs, const float *const *grad, float *const *out)
+{
+    typedef std::pair<uintptr_t, uintptr_t> Range;
+    std::vector<Range> g(n);
+    std::vector<uintptr_t> reach(n);              // furthest end among the gradients that start no later
+    auto range = [&](const void *p, int i) {
+        const size_t dA = core_dim(&descs[i]) + descs[i].has_bias, dG = descs[i].d_out;
+        return Range((uintptr_t)p, (uintptr_t)p + dA * dG * sizeof(float));
+    };
+    for (int i = 0; i < n; ++i) g[i] = range(grad[i], i);
+    std::sort(g.begin(), g.end());
+    for (int i = 0; i < n; ++i) reach[i] = std::max(g[i].second, i ? reach[i - 1] : (uintptr_t)0);
+    for (int i = 0; i < n; ++i) {
+        const Range o = range(out[i], i);
+        const size_t k = std::lower_bound(g.begin(), g.end(), Range(o.second, 0)) - g.begin();   // gradients that start before its end
+        if (k > 0 && reach[k - 1] > o.first) return true;
+    }
+    return false;
 }
 
 std::vector<EigenJob> eigen_jobs(int n, const kfac_layer_desc *descs, const float *const *A, const float *const *G,
@@ -627,19 +657,32 @@ kfac_status kfac_precondition_batched(int n, const kfac_layer_desc *descs, const
     if (!aligned(d_work, 256)) return KFAC_ERR_ALIGN;
     // the intermediates are required; the K-slice partials behind them are used when there is room for them
     if (precond_ws_min(n, descs) > work_bytes) return KFAC_ERR_WORKSPACE;
-    std::vector<GemmJob> g1(n), g2(n);
+    // Narrow layers in one launch, which reads a layer's gradient in workgroups that do not wait for one another: an output
+    // that overlaps a gradient goes through the intermediate like the wide layers.
+    const bool in_place = precond_overlap(n, descs, d_grad, d_out);
+    std::vector<GemmJob> g1, g2;
+    std::vector<PrecJob> narrow;
     size_t off = 0;
     for (int i = 0; i < n; ++i) {
-        const size_t dA = (size_t)core_dim(&descs[i]) + descs[i].has_bias, dG = descs[i].d_out;
+        const int dA = core_dim(&descs[i]) + descs[i].has_bias, dG = descs[i].d_out;
         float *Ut = reinterpret_cast<float *>(static_cast<char *>(d_work) + off);
-        off += align_up(dA * dG * sizeof(float), 256);
-        precond_jobs(descs[i], d_A_inv[i], d_G_inv[i], d_grad[i], d_out[i], Ut, g1[i], g2[i]);
+        off += align_up((size_t)dA * dG * sizeof(float), 256);
+        if (!in_place && precond_fused_takes(dA, dG)) {
+            narrow.push_back(PrecJob{d_grad[i], d_A_inv[i], d_G_inv[i], d_out[i], nullptr, nullptr, dA, dG});
+            continue;
+        }
+        GemmJob a, b;
+        precond_jobs(descs[i], d_A_inv[i], d_G_inv[i], d_grad[i], d_out[i], Ut, a, b);
+        g1.push_back(a);
+        g2.push_back(b);
     }
     void *slices = static_cast<char *>(d_work) + off;
     const size_t slice_bytes = work_bytes - off;
     hipStream_t s = (hipStream_t)hip_stream;
-    if (gemm_launch(g1.data(), n, s, slices, slice_bytes) != hipSuccess) return KFAC_ERR_HIP;
-    if (gemm_launch(g2.data(), n, s, slices, slice_bytes) != hipSuccess) return KFAC_ERR_HIP;
+    const int nw = (int)g1.size();
+    if (gemm_launch(g1.data(), nw, s, slices, slice_bytes) != hipSuccess) return KFAC_ERR_HIP;
+    if (gemm_launch(g2.data(), nw, s, slices, slice_bytes) != hipSuccess) return KFAC_ERR_HIP;
+    if (precond_fused_launch(narrow.data(), (int)narrow.size(), 0.f, s) != hipSuccess) return KFAC_ERR_HIP;
     return KFAC_OK;
 }
 
@@ -709,7 +752,9 @@ kfac_status kfac_precondition_eigen_batched(int n, const kfac_layer_desc *descs,
     //   T1  [dG, dA] = U^T Q_A  ./ (v_G v_A^T + gamma)   (division in the epilogue)
     //   T2t [dA, dG] = T1^T Q_G^T                      (= (Q_G T1)^T)
     //   P   [dG, dA] = T2t^T Q_A^T
-    std::vector<GemmJob> g1(n), g2(n), g3(n), g4(n);
+    // (narrow layers: T1 and P in one launch each, P from the transposes)
+    std::vector<GemmJob> g1, g2, g3, g4;
+    std::vector<PrecJob> n1, n2;
     std::vector<const float *> tsrc;
     std::vector<float *> tdst;
     std::vector<int> tn;
@@ -725,26 +770,35 @@ kfac_status kfac_precondition_eigen_batched(int n, const kfac_layer_desc *descs,
         float *QAt = take((size_t)dA * dA), *QGt = take((size_t)dG * dG);
         tsrc.push_back(d_Q_A[i]); tdst.push_back(QAt); tn.push_back(dA);
         tsrc.push_back(d_Q_G[i]); tdst.push_back(QGt); tn.push_back(dG);
-        GemmJob &a = g1[i];
+        if (precond_fused_takes(dA, dG)) {
+            n1.push_back(PrecJob{d_grad[i], d_Q_A[i], d_Q_G[i], T1, d_v_G[i], d_v_A[i], dA, dG});
+            n2.push_back(PrecJob{T1, QAt, QGt, d_out[i], nullptr, nullptr, dA, dG});
+            continue;
+        }
+        GemmJob a{}, b{}, c{}, e{};
         a.A = d_grad[i]; a.B = d_Q_G[i]; a.C = U;
         a.M = dA; a.N = dG; a.K = dG; a.lda = dA; a.ldb = dG; a.ldc = dG; a.mode = kStore; a.p0 = a.p1 = 0;
-        GemmJob &b = g2[i];
         b.A = U; b.B = d_Q_A[i]; b.C = T1;
         b.M = dG; b.N = dA; b.K = dA; b.lda = dG; b.ldb = dA; b.ldc = dA; b.mode = kStoreDiv; b.p0 = b.p1 = 0;
         b.rv = d_v_G[i]; b.cv = d_v_A[i]; b.gamma = gamma;
-        GemmJob &c = g3[i];
         c.A = T1; c.B = QGt; c.C = U;
         c.M = dA; c.N = dG; c.K = dG; c.lda = dA; c.ldb = dG; c.ldc = dG; c.mode = kStore; c.p0 = c.p1 = 0;
-        GemmJob &e = g4[i];
         e.A = U; e.B = QAt; e.C = d_out[i];
         e.M = dG; e.N = dA; e.K = dA; e.lda = dG; e.ldb = dA; e.ldc = dA; e.mode = kStore; e.p0 = e.p1 = 0;
+        g1.push_back(a);
+        g2.push_back(b);
+        g3.push_back(c);
+        g4.push_back(e);
     }
     hipStream_t s = (hipStream_t)hip_stream;
     if (transpose_launch(tsrc.data(), tdst.data(), tn.data(), (int)tn.size(), s) != hipSuccess) return KFAC_ERR_HIP;
-    if (gemm_launch(g1.data(), n, s) != hipSuccess) return KFAC_ERR_HIP;
-    if (gemm_launch(g2.data(), n, s) != hipSuccess) return KFAC_ERR_HIP;
-    if (gemm_launch(g3.data(), n, s) != hipSuccess) return KFAC_ERR_HIP;
-    if (gemm_launch(g4.data(), n, s) != hipSuccess) return KFAC_ERR_HIP;
+    const int nw = (int)g1.size(), nn = (int)n1.size();
+    if (gemm_launch(g1.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
+    if (gemm_launch(g2.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
+    if (gemm_launch(g3.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
+    if (gemm_launch(g4.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
+    if (precond_fused_launch(n1.data(), nn, gamma, s) != hipSuccess) return KFAC_ERR_HIP;
+    if (precond_fused_launch(n2.data(), nn, 0.f, s) != hipSuccess) return KFAC_ERR_HIP;
     return KFAC_OK;
 }
 
@@ -932,6 +986,8 @@ int kfac_tune(const char *key, long value)
     else if (k == "split_gemm_min_fill") t.split_gemm_min_fill = value;
     else if (k == "gemm_xcd_remap_min") t.gemm_xcd_remap_min = value;
     else if (k == "gemm_bm") t.gemm_bm = value;
+    else if (k == "use_precond_fused") t.use_precond_fused = value;
+    else if (k == "precond_wide_tiles") t.precond_wide_tiles = value;
     else return 1;
     return 0;
 }

@@ -89,6 +89,14 @@ struct EigenJob {
     int n;
 };
 
+// out = G^T W A (divided by rv[m] cv[n] + gamma where rv is set): W and out [dG, dA], A [dA, dA], G [dG, dG]
+struct PrecJob {
+    const float *W, *A, *G;
+    float *out;
+    const float *rv, *cv;
+    int dA, dG;
+};
+
 struct Im2colJob {
     const void *x;   // NCHW
     void *out;       // [B*Ho*Wo, ld]
@@ -111,6 +119,10 @@ hipError_t pi_damping_launch(const float *const *A, const float *const *G, const
 // it (or with less) every product is computed in one piece
 hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work = nullptr, size_t work_bytes = 0);
 size_t gemm_workspace_bytes(const GemmJob *jobs, int n);
+
+// whether a layer of these orders takes the one-launch form of the two-sided product; out must not overlap any W of the call
+bool precond_fused_takes(int dA, int dG);
+hipError_t precond_fused_launch(const PrecJob *jobs, int n, float gamma, hipStream_t s);
 
 hipError_t im2col_launch(const Im2colJob *jobs, int n, hipStream_t s);
 // whether the patch kernel can stage one output row (Wo outputs) of its narrowest channel chunk in LDS
@@ -170,6 +182,8 @@ struct Tuning {
     long fuse_conv3_max_c = 64;      // ... up to this many input channels (wider ones: patch matrix + split-bf16 kernel)
     long update_bm = 64;             // block tile of the inverse's rank-64 update GEMM (0 = choose; 64 measured best)
     long gemm_bm = 0;                // block tile of the preconditioning GEMMs (0 = choose)
+    long precond_wide_tiles = 256;   // ... with 64-wide tiles from this many of them on, else 32-wide ones
+    long use_precond_fused = 1;      // two-sided products of layers with a dimension of at most 64 in one launch
     long wave_debug = 0;             // measurement only: 1 = skip MFMAs, 2 = skip data loads (results are wrong)
 };
 Tuning &tuning();
