@@ -975,6 +975,7 @@ int kfac_tune(const char *key, long value)
     else if (k == "im2col_lds_bytes") t.im2col_lds_bytes = value;
     else if (k == "im2col_min_blocks") t.im2col_min_blocks = value;
     else if (k == "use_bf16_mfma") t.use_bf16_mfma = value;
+    else if (k == "wave_gemm_min_blocks") t.wave_gemm_min_blocks = value;
     else if (k == "use_wave_gemm") t.use_wave_gemm = value;
     else if (k == "use_split_gemm") t.use_split_gemm = value;
     else if (k == "use_split_syrk") t.use_split_syrk = value;

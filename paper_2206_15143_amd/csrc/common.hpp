@@ -165,6 +165,7 @@ struct Tuning {
     long use_wave_kernel = 1;        // wave-unit SYRK for aligned row-major fp32 operands
     long use_bf16_mfma = 1;          // row-major bf16 operands: bf16 MFMA kernel instead of widening to fp32
     long gemm_xcd_remap_min = 8;     // wave GEMM launches with at least this many problems renumber their tiles per XCD
+    long wave_gemm_min_blocks = 64;  // ... when the call has at least this many workgroups of them
     long use_wave_gemm = 1;          // wide A^T B products on the wave-unit GEMM
     long use_split_syrk = 1;         // wide fp32 factors as six bf16 MFMA products of the inputs' bf16 pieces
     long split_syrk_min_d = 192;     // narrowest factor the split-bf16 KF-GEMM takes
@@ -176,7 +177,7 @@ struct Tuning {
     long split_gemm_min_k = 128;     // ... and this depth
     long split_gemm_min_fill = 40;   // ... when the product fills at least this percentage of its 256 x 128 tiles
     long gemm_kslice_stages = 40;    // ... deep stores of a call with few tiles: K slices of at least this many stages (0 = never)
-    long gemm_kslice_groups = 400;   // ... and as many more as leave about this many workgroups
+    long gemm_kslice_groups = 512;   // ... and as many more as leave about this many workgroups
     long use_small_kernel = 1;       // direct MFMA kernel for narrow NCHW operands (d <= 64)
     long fuse_conv3 = 1;             // 3x3/s1/p1 fp32 convs: build A straight from the NCHW input
     long fuse_conv3_max_c = 64;      // ... up to this many input channels (wider ones: patch matrix + split-bf16 kernel)

@@ -397,11 +397,12 @@ namespace {
 // of 289 stages on 256 units).  Such a product is cut into K slices: slice 0 stores into C, the others into
 // partial matrices in the workspace, and a reduction adds them to C in slice order (a fixed order: the result
 // does not depend on the schedule).  The partials are M x N, small beside the K x N operand that is read.  The slices
-// of a call are as deep as leaves about 400 workgroups of equal depth (two fit a compute unit), between 40 and 150
-// stages: one depth for every call is too long for a single layer and too short for a network (preconditioning with
-// this rule, with at least 75 stages, without slices: a 2048 x 1024 layer 0.147, 0.171 and 0.230 ms, a 256-channel 3x3
-// layer 0.092, 0.125 and 0.197, seven factorised convolutions 0.128, 0.162 and 0.164, a 1024-wide transformer block 0.612,
-// 0.612 and 0.654; the ResNet-50- and VGG-16-shaped sets would gain without: 1.19, 1.18 and 1.14, 0.947, 0.948 and 0.883).
+// of a call are as deep as leaves about 512 workgroups of equal depth (two fit a compute unit), at least 40 stages, and
+// a product is cut only when it is more than 1.3 times as deep: what a slice costs is its partial matrix, what it gains
+// is the part of its depth by which a workgroup outlasts an even share of the call.  Preconditioning of ResNet-50-, VGG-16-
+// (64 and 48 wide), small ResNet-50- (40 wide) shaped sets and two 1024-wide transformer blocks in ms: 0.996, 0.794, 0.492,
+// 0.310, 1.190; slices of at most 150 stages of anything 1.5 times as deep as an even share of 400: 1.038, 0.863, 0.533, 0.319,
+// 1.224; without slices: 0.990, 0.806, 0.534, 0.399, 1.192, and a 2048 x 1024 layer 0.230 instead of 0.147.
 constexpr int kMaxKSlices = 8;
 
 int kslice_count(const GemmJob &j, long split_tiles, long cap)
@@ -409,7 +410,7 @@ int kslice_count(const GemmJob &j, long split_tiles, long cap)
     if (cap <= 0 || split_tiles >= 1024) return 1;     // enough tiles to keep every unit busy as it is
     if (j.mode != kStore || j.gate || j.wide_tiles) return 1;
     const long stages = (j.K + S_KT - 1) / S_KT;
-    if (2 * stages <= 3 * cap) return 1;
+    if (10 * stages <= 13 * cap) return 1;
     return (int)std::min<long>(kMaxKSlices, (stages + cap - 1) / cap);
 }
 
@@ -427,7 +428,7 @@ size_t plan_kslices(const GemmJob *jobs, int n, std::vector<int> &ks)
             stages += (double)t * ((jobs[i].K + S_KT - 1) / S_KT);
         }
     const long least = tuning().gemm_kslice_stages;
-    const long cap = least <= 0 ? 0 : std::max(least, (long)std::min(stages / tuning().gemm_kslice_groups, 150.0));
+    const long cap = least <= 0 ? 0 : std::max(least, (long)(stages / tuning().gemm_kslice_groups));
     size_t floats = 0;
     for (int i = 0; i < n; ++i) {
         if (!(jobs[i].M > 0 && jobs[i].N > 0 && jobs[i].K > 0) || !split_gemm_eligible(jobs[i], wide)) continue;
@@ -550,6 +551,19 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
         } else {
             cfg[i] = choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
         }
+    }
+    // A wave-unit workgroup owns 144 x 288 of a product and walks its whole depth at 110 us per 512 rows whatever else
+    // the launch holds: a launch of few of them is nothing but that chain, which the 64-wide tiles spread over the chip
+    // (eight products of the ResNet-50 shape, 129 x 512 at depth 512 the largest: 22 workgroups, 110 us; as 64-wide tiles 12
+    // us more in a launch that is there anyway).
+    long wave_blocks = 0;
+    for (int i : wave) {
+        const int mI = (jobs[i].M + W_MT - 1) / W_MT, nJ = (jobs[i].N + W_MT - 1) / W_MT;
+        wave_blocks += jobs[i].mode == kSubLowerSkip ? (long)mI * (mI + 3) / 4 : (long)mI * ((nJ + 1) / 2);
+    }
+    if (!wave.empty() && wave_blocks < tuning().wave_gemm_min_blocks) {
+        for (int i : wave) cfg[i] = choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
+        wave.clear();
     }
     {   // a small call is bound by its launches, not by its flops: one tile shape for all its products then
         double flops = 0.0, cost[4] = {0.0, 0.0, 0.0, 0.0};
