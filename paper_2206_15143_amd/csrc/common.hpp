@@ -47,6 +47,7 @@ struct InvertJob {
     const float *damping_dev = nullptr;   // when set, the damping is read from this device float instead
     int ldm = 0;     // row pitch of M (0 = n)
     int ldo = 0;     // row pitch of Minv (0 = n)
+    int border = 0;  // order 64 with one more row and column to be bordered on the spot (see InvProbF)
 };
 
 // C[M, N] = A^T B with A stored [K, lda] (element (k, m)), B stored [K, ldb].

@@ -30,6 +30,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 namespace kfac {
@@ -334,25 +335,30 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
                         void *work, InvProbF *dtab, hipStream_t s)
 {
     const int total = (int)idx.size();
-    // descriptors -> device table
-    for (int g0 = 0; g0 < total; g0 += kInvUploadMax) {
+    auto describe = [&](InvProbF &p, int i) {
+        const InvertJob &j = jobs[i];
+        float *ws = reinterpret_cast<float *>(static_cast<char *>(work) + offs[i]);
+        p.M = j.M; p.W = j.Minv; p.info = j.info; p.n = j.n; p.damping = j.damping; p.dptr = j.damping_dev;
+        p.ldv = (j.n + 3) / 4 * 4;
+        p.nblk = (j.n + FNB - 1) / FNB;
+        p.ldm = j.ldm > 0 ? j.ldm : j.n;
+        p.ldw = j.ldo > 0 ? j.ldo : j.n;
+        p.P = ws;
+        p.Vt = ws + 2 * FNB * FNB;
+        p.S = p.Vt + 2 * (size_t)FNB * p.ldv;
+        p.gate = fused_gate_ptr(ws, j.n);
+        p.border = j.border;
+    };
+    // descriptors: with the first kernel, or, of many matrices, -> device table
+    int classes = 0;
+    for (int k = 0; k < total; ++k)
+        classes += k == 0 || (jobs[idx[k]].n + FNB - 1) / FNB != (jobs[idx[k - 1]].n + FNB - 1) / FNB;
+    const bool with_launch = total <= kInvUploadMax && classes <= kMaxInvClasses;
+    for (int g0 = 0; g0 < total && !with_launch; g0 += kInvUploadMax) {
         InvUpload u;
         u.dst = dtab + g0;
         u.count = std::min(kInvUploadMax, total - g0);
-        for (int k = 0; k < u.count; ++k) {
-            const InvertJob &j = jobs[idx[g0 + k]];
-            InvProbF &p = u.p[k];
-            float *ws = reinterpret_cast<float *>(static_cast<char *>(work) + offs[idx[g0 + k]]);
-            p.M = j.M; p.W = j.Minv; p.info = j.info; p.n = j.n; p.damping = j.damping; p.dptr = j.damping_dev;
-            p.ldv = (j.n + 3) / 4 * 4;
-            p.nblk = (j.n + FNB - 1) / FNB;
-            p.ldm = j.ldm > 0 ? j.ldm : j.n;
-            p.ldw = j.ldo > 0 ? j.ldo : j.n;
-            p.P = ws;
-            p.Vt = ws + 2 * FNB * FNB;
-            p.S = p.Vt + 2 * (size_t)FNB * p.ldv;
-            p.gate = fused_gate_ptr(ws, j.n);
-        }
+        for (int k = 0; k < u.count; ++k) describe(u.p[k], idx[g0 + k]);
         KFAC_LAUNCH(KFAC_K_INV_INIT, s, inv_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -393,7 +399,18 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
         long blocks = 0;
         hipError_t e = hipSuccess;
         blocks = lay_out(q, nclass, [](const InvClass &k) { return k.nblk; });
-        KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, fsweep_pivot0_kernel, dim3((unsigned)blocks), dim3(256), 0, q);
+        auto first = [&](auto few) {          // the smallest argument that holds the descriptors
+            InvInline<decltype(few)::value> own;
+            for (int k = 0; k < total; ++k) describe(own.p[k], idx[k]);
+            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, (fsweep_pivot0_kernel<decltype(few)::value>), dim3((unsigned)blocks), dim3(256), 0, q, own);
+        };
+        if (!with_launch) {
+            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, (fsweep_pivot0_kernel<0>), dim3((unsigned)blocks), dim3(256), 0, q, InvInline<0>{});
+        } else if (total <= 16) {
+            first(std::integral_constant<int, 16>{});
+        } else {
+            first(std::integral_constant<int, kInvUploadMax>{});
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         const int steps = q.c[0].nblk;   // classes are sorted: the first is the largest
@@ -842,7 +859,6 @@ struct BorderProb {
     float damping;
     int n, ldm, ldw;
     int blk_start;
-    int rblk_start;    // first block of the residual kernel (one per 64 rows)
 };
 
 struct BorderTable {
@@ -906,44 +922,70 @@ __global__ __launch_bounds__(256) void border_matvec_kernel(const BorderTable ta
 }
 
 // r = b - (M_11 + damping I) y from the lower triangle of M (the part the inversion may read), where the sticky flag
-// is set.  One workgroup per 64 rows (the order of M_11 is a multiple of 64); the 64 x 64 tiles left of the diagonal
-// are read as they are, those right of it from their mirror images, transposed through LDS.
+// is set.  A workgroup per 16 rows, all loads independent of one another.  Left of the diagonal and on it a wavefront
+// takes four rows, lanes along a row; right of it row i is column i of the rows below, 16 neighbouring columns = 64 bytes
+// of a row per 16 threads, sixteen rows at a time.  (64 rows per workgroup, their 64 x 64 tiles one after the other through LDS,
+// took 60 us at order 577 and 98 at 1153, a round trip to memory per tile.)
 __global__ __launch_bounds__(256) void border_resid_kernel(const BorderTable tab)
 {
-    __shared__ float L[64][65];
     __shared__ float ysh[1280 + 64];
-    __shared__ float part[4][64];
-    int pi = 0;
-    while (pi + 1 < tab.count && (int)blockIdx.x >= tab.p[pi + 1].rblk_start) ++pi;
-    const BorderProb &pr = tab.p[pi];
+    __shared__ float part[4][16];
+    __shared__ float left[16];
+    int chunk;
+    const BorderProb &pr = border_locate(tab, chunk);
     if (!pr.sticky || (!pr.always && *pr.sticky == 0)) return;
-    const int i0 = ((int)blockIdx.x - pr.rblk_start) * 64;
-    const int m = pr.n - 1, t = threadIdx.x;
+    const int m = pr.n - 1, t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const int i0 = chunk * kBorderRows;
     for (int j = t; j < m; j += 256) ysh[j] = pr.y[j];
-    const int r = t & 63, q = t >> 6;
-    float acc = 0.f;
-    for (int j0 = 0; j0 < m; j0 += 64) {
-        const int R0 = j0 > i0 ? j0 : i0, C0 = j0 > i0 ? i0 : j0;
-        __syncthreads();                       // the last tile has been consumed (and, first trip, ysh is complete)
-        for (int e = t; e < 64 * 64; e += 256) {
-            const int a = e >> 6, b = e & 63;
-            L[a][b] = pr.M[(long)(R0 + a) * pr.ldm + C0 + b];
+    __syncthreads();
+    {   // column c of the rows below: rows j0 + 16 u, eight loads in flight
+        const int c = t & 15, j0 = t >> 4;
+        const float *col = pr.M + i0 + c;
+        float acc = 0.f;
+        for (int b = i0 + j0; b < m; b += 128) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = col[(long)min(b + 16 * u, m - 1) * pr.ldm];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = b + 16 * u;
+                acc = __builtin_fmaf(j > i0 + c && j < m ? v[u] : 0.f, ysh[min(j, m - 1)], acc);
+            }
         }
-        __syncthreads();
-#pragma unroll 4
-        for (int c = 16 * q; c < 16 * q + 16; ++c) {
-            float v;
-            if (j0 < i0) v = L[r][c];
-            else if (j0 > i0) v = L[c][r];
-            else v = c <= r ? L[r][c] : L[c][r];
-            acc = __builtin_fmaf(v, ysh[j0 + c], acc);
+        acc += __shfl_xor(acc, 16);
+        acc += __shfl_xor(acc, 32);
+        if (lane < 16) part[w][lane] = acc;
+    }
+    {   // rows i0 + 4 w .. + 3 up to the diagonal
+        float acc[4] = {0.f, 0.f, 0.f, 0.f};
+        const float *row[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) row[q] = pr.M + (long)(i0 + 4 * w + q) * pr.ldm;
+        const int last = i0 + 4 * w + 3;
+        for (int j = lane; j <= last; j += 128) {
+            float v0[4], v1[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { v0[q] = row[q][j]; v1[q] = row[q][min(j + 64, last)]; }
+            const float y0 = ysh[j], y1 = j + 64 < m ? ysh[j + 64] : 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 4 * w + q;
+                acc[q] = __builtin_fmaf(j <= i ? v0[q] : 0.f, y0, acc[q]);
+                acc[q] = __builtin_fmaf(j + 64 <= i ? v1[q] : 0.f, y1, acc[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float a = acc[q];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
+            if (lane == 0) left[4 * w + q] = a;
         }
     }
-    part[q][r] = acc;
     __syncthreads();
-    if (t < 64) {
+    if (t < 16) {
         const float damping = pr.dptr ? *pr.dptr : pr.damping;
-        const float My = part[0][t] + part[1][t] + part[2][t] + part[3][t] + damping * ysh[i0 + t];
+        const float My = left[t] + ((part[0][t] + part[1][t]) + (part[2][t] + part[3][t])) + damping * ysh[i0 + t];
         pr.y[border_vec_len(pr.n) + i0 + t] = pr.M[(long)m * pr.ldm + i0 + t] - My;
     }
 }
@@ -1025,7 +1067,7 @@ hipError_t border_launch(const InvertJob *jobs, const std::vector<int> &idx, con
     for (size_t g0 = 0; g0 < idx.size(); g0 += kMaxProblems) {
         BorderTable tab;
         tab.count = (int)std::min<size_t>(kMaxProblems, idx.size() - g0);
-        int blocks = 0, rblocks = 0;
+        int blocks = 0;
         for (int k = 0; k < tab.count; ++k) {
             const InvertJob &j = jobs[idx[g0 + k]];
             BorderProb &p = tab.p[k];
@@ -1037,14 +1079,12 @@ hipError_t border_launch(const InvertJob *jobs, const std::vector<int> &idx, con
             p.ldw = j.ldo > 0 ? j.ldo : j.n;
             p.blk_start = blocks;
             blocks += (j.n - 1 + kBorderRows - 1) / kBorderRows;
-            p.rblk_start = rblocks;
-            rblocks += (j.n - 1) / 64;
         }
         KFAC_LAUNCH(KFAC_K_INV_FINISH, s, border_matvec_kernel<0>, dim3(blocks), dim3(256), 0, tab);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (tuning().invert_refine) {
-            KFAC_LAUNCH(KFAC_K_INV_FINISH, s, border_resid_kernel, dim3(rblocks), dim3(256), 0, tab);
+            KFAC_LAUNCH(KFAC_K_INV_FINISH, s, border_resid_kernel, dim3(blocks), dim3(256), 0, tab);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
             KFAC_LAUNCH(KFAC_K_INV_FINISH, s, border_matvec_kernel<1>, dim3(blocks), dim3(256), 0, tab);
@@ -1092,6 +1132,11 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
             inner[i].n = n - 1;
             inner[i].ldm = jobs_in[i].ldm > 0 ? jobs_in[i].ldm : n;
             inner[i].ldo = jobs_in[i].ldo > 0 ? jobs_in[i].ldo : n;
+            if (n == FNB + 1) {          // by the workgroup that inverts the leading block
+                inner[i].border = tuning().invert_border_refine >= 2 ? 2 : 1;
+                off += align_up((job_ws_floats(n) + border_ws_floats(n)) * sizeof(float), 256);
+                continue;
+            }
             bordered.push_back(i);
             ybuf.push_back(reinterpret_cast<float *>(static_cast<char *>(work) + off) + job_ws_floats(n));
             sticky.push_back(fused_gate_ptr(reinterpret_cast<float *>(static_cast<char *>(work) + off), n - 1) + 2);

@@ -48,6 +48,8 @@ struct InvProbF {
     int nblk;
     int ldm, ldw;     // row pitches of M and W
     const float *dptr; // device-side damping (overrides `damping` when not null)
+    int border;        // one more row and column behind the order n = 64, bordered by the workgroup that inverts the block:
+                       // 2 with the refinement step, 1 with it where the block is ill-conditioned (see invert.hip); 0: none
 };
 
 // The same with pointers that are known to point to device memory.  Of a pointer read from memory the compiler cannot
@@ -64,15 +66,15 @@ struct InvProbG {
     const gfloat *dptr;
     int n, ldv, nblk, ldm, ldw;
     float damping;
+    int border;
 };
-__device__ __forceinline__ InvProbG load_prob(const InvProbF *tab, int i)
+__device__ __forceinline__ InvProbG load_prob(const InvProbF &p)
 {
-    const InvProbF p = tab[i];
     return InvProbG{(const gfloat *)p.M, (gfloat *)p.W, (gfloat *)p.P, (gfloat *)p.Vt, (gfloat *)p.S, (gint *)p.gate,
-                    (gint *)p.info, (const gfloat *)p.dptr, p.n, p.ldv, p.nblk, p.ldm, p.ldw, p.damping};
+                    (gint *)p.info, (const gfloat *)p.dptr, p.n, p.ldv, p.nblk, p.ldm, p.ldw, p.damping, p.border};
 }
 
-constexpr int kInvUploadMax = 224;   // descriptors per upload launch (a 20 KB kernel argument)
+constexpr int kInvUploadMax = 224;   // descriptors per upload launch (a 22 KB kernel argument)
 
 struct InvUpload {
     InvProbF *dst;
@@ -96,6 +98,13 @@ struct InvSeq {
     int nprob;           // matrices in this launch
     float refine_cond;   // panel products of pivot blocks whose condition number exceeds this are refined (< 0: never)
     InvClass c[kMaxInvClasses];
+};
+
+// The descriptors of a call of few matrices, as an argument of its first kernel, which leaves them in the device table for
+// the later ones: no launch ahead of it (6 us of every outer step of the blocked sweep, whose pivot blocks come this way).
+template <int N>
+struct InvInline {
+    InvProbF p[N];
 };
 
 __global__ __launch_bounds__(64) void inv_upload_kernel(const InvUpload u)
@@ -282,7 +291,9 @@ __device__ __forceinline__ void norm_fold(float *nrm, int slot, int lane)
 // Workgroup 0 of a matrix inverts the first pivot block; workgroup r >= 1 copies block r of the first
 // column panel K-major into V[0] (transposed through LDS), so that step 0 stages its panels like any
 // other step.
-__global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
+// N > 0: the descriptors come with the launch.
+template <int N>
+__global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, const InvInline<N> own)
 {
     __shared__ __attribute__((aligned(16))) float sbuf[64 * SW_PITCH];
     __shared__ __attribute__((aligned(16))) float pw[16 * 17 + 64 * 17];
@@ -290,8 +301,10 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
     float (*tile)[65] = reinterpret_cast<float (*)[65]>(sbuf);
     int prob, local;
     if (!seq_locate(q, blockIdx.x, prob, local)) return;
-    const InvProbG pr = load_prob(q.tab, prob);
     const int tid = threadIdx.x;
+    if (N > 0 && local == 0 && tid < (int)(sizeof(InvProbF) / 4))
+        reinterpret_cast<unsigned *>(const_cast<InvProbF *>(q.tab) + prob)[tid] = reinterpret_cast<const unsigned *>(&own.p[prob])[tid];
+    const InvProbG pr = N > 0 ? load_prob(own.p[prob]) : load_prob(q.tab[prob]);
     if (local > 0) {
         const int g0 = local * FNB;
         for (int e = tid; e < FNB * FNB; e += 256) {
@@ -327,20 +340,85 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q)
     if (test && (tid >> 6) == 1) norm_fold(nrm, 0, tid & 63);       // beside the first in-register sweep of wavefront 0
     const int fail = sweep64_blocked(sbuf, pw, pw + 16 * 17, tid);   // valid in wavefront 0
     const bool whole = pr.nblk == 1;   // the block is the matrix: store the result itself, both triangles
+    const bool border = whole && pr.border;
     colsum = 0.f;
     for (int e = tid; e < FNB * FNB; e += 256) {
         const int i = e >> 6, j = e & 63;
         const bool in = (i < bs && j < bs);
         const float v = sbuf[i * SW_PITCH + j];
         if (in) colsum += fabsf(v);
-        pr.P[i * FNB + j] = in ? -v : 0.f;
-        if (in && j <= i) {
-            pr.W[i * ldw + j] = whole ? -v : v;
-            if (whole) pr.W[j * ldw + i] = -v;
+        if (whole) {
+            if (in && j <= i && !border) {
+                pr.W[i * ldw + j] = -v;
+                pr.W[j * ldw + i] = -v;
+            }
+            continue;
         }
+        pr.P[i * FNB + j] = in ? -v : 0.f;
+        if (in && j <= i) pr.W[i * ldw + j] = v;
+    }
+    if (border) {
+        // The last row and column by bordering, as the kernels of larger orders do it (invert.hip has the formulas):
+        // thread (i, part) sums a quarter of row i.  y, r, z, b in pw.
+        float *yv = pw, *rv = pw + 64, *zv = pw + 128, *bv = pw + 192, *red = pw + 256;
+        const int i = tid & 63, part = tid >> 6;
+        const long lastrow = 64 * ldm;
+        __syncthreads();                                     // the sweep has been read, pw is free
+        if (tid < 64) bv[i] = pr.M[lastrow + i];
+        nrm[tid] = colsum;
+        __syncthreads();
+        if (part == 1 && test) norm_fold(nrm, 1, i);
+        __syncthreads();
+        const bool fix = test && (pr.border == 2 || nrm[256] * nrm[257] > q.refine_cond);
+        auto matvec = [&](float *out, const float *in, auto row) {      // out = row(i, .) in
+            float a = 0.f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) a = __builtin_fmaf(row(16 * part + k), in[16 * part + k], a);
+            red[tid] = a;
+            __syncthreads();
+            if (tid < 64) out[i] = (red[i] + red[64 + i]) + (red[128 + i] + red[192 + i]);
+            __syncthreads();
+        };
+        auto x_row = [&](int j) { return -sbuf[i * SW_PITCH + j]; };
+        matvec(yv, bv, x_row);
+        if (fix) {
+            matvec(rv, yv, [&](int j) { return (float)pr.M[max(i, j) * ldm + min(i, j)]; });
+            if (tid < 64) rv[i] = bv[i] - (rv[i] + damping * yv[i]);
+            __syncthreads();
+            matvec(zv, rv, x_row);
+        }
+        if (tid < 64) {
+            float term = bv[i];
+            if (fix) term += rv[i];
+            red[i] = term * yv[i];
+        }
+        __syncthreads();
+        for (int h = 32; h > 0; h >>= 1) {
+            if (tid < h) red[tid] += red[tid + h];
+            __syncthreads();
+        }
+        const float sp = pr.M[lastrow + 64] + damping - red[0];
+        const float is = 1.0f / sp;
+        if (tid < 64) {
+            if (fix) yv[i] += zv[i];
+            const float e = -yv[i] * is;
+            pr.W[64 * ldw + i] = e;
+            pr.W[i * ldw + 64] = e;
+        }
+        __syncthreads();
+        for (int e = tid; e < FNB * FNB; e += 256) {
+            const int a = e >> 6, b = e & 63;
+            const int hi = max(a, b), lo = min(a, b);
+            pr.W[a * ldw + b] = -sbuf[hi * SW_PITCH + lo] + (yv[hi] * yv[lo]) * is;
+        }
+        if (tid == 0) {
+            pr.W[64 * ldw + 64] = is;
+            *pr.info = fail != 0 ? fail : (sp > 0.f ? 0 : 65);
+        }
+        return;
     }
     if (tid == 0) *pr.info = (fail <= bs) ? fail : 0;
-    if (!test) return;
+    if (!test || whole) return;
     nrm[tid] = colsum;
     __syncthreads();
     if ((tid >> 6) == 0) {
@@ -380,7 +458,7 @@ __global__ __launch_bounds__(256, 4) void fsweep_step_kernel(const InvSeq q)
 
     int prob, t;
     if (!seq_locate(q, blockIdx.x, prob, t)) return;
-    const InvProbG pr = load_prob(q.tab, prob);
+    const InvProbG pr = load_prob(q.tab[prob]);
     const int K = q.step, K1 = K + 1;
     const int nblk = pr.nblk;
     if (K >= nblk) return;

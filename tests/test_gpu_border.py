@@ -1,0 +1,71 @@
+"""The last row and column of orders 64 k + 1: one workgroup at order 65 (in the kernel that inverts the block), four
+kernels above.  Only the lower triangle of the factor may be read: the upper one holds NaN.
+
+Tolerance: rounding the factor's entries alone to fp32 moves its inverse by up to cond 2^-24 relative to its norm, and a
+backward stable elimination behaves like a few such roundings: 1.5 cond 2^-24 (spectra in geometric progression come
+within a factor of 1.2 of the first at order 129; most orders stay below a quarter)."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+import paper_2206_15143_amd as kf
+
+pytestmark = pytest.mark.gpu
+
+
+def _spd(n, cond, seed):
+    rng = np.random.default_rng(seed)
+    q, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    m = (q * np.geomspace(1.0, 1.0 / cond, n)) @ q.T
+    return ((m + m.T) / 2).astype(np.float32)
+
+
+def _invert(mats, damping):
+    """mats: (A, G) of one layer each."""
+    n = len(mats)
+    descs = [kf.LayerDesc.linear(a.shape[0] - 1, g.shape[0], True, kf.KFAC_F32) for a, g in mats]
+    low = lambda m: gu.to_dev(np.where(np.tril(np.ones_like(m)) > 0, m, np.nan).astype(np.float32))  # noqa: E731
+    A, G = [low(a) for a, _ in mats], [low(g) for _, g in mats]
+    Ai, Gi = [torch.full_like(a, float("nan")) for a in A], [torch.full_like(g, float("nan")) for g in G]
+    info = torch.full((2 * n,), -1, dtype=torch.int32, device=gu.DEV)
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_invert_batched(descs, A, G, damping, damping, Ai, Gi, info, ws)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in Ai], [x.cpu().numpy() for x in Gi], info.cpu().numpy()
+
+
+@pytest.mark.parametrize("cond", [1e3, 1e5])
+@pytest.mark.parametrize("n", [65, 129, 577, 1153, 1281])
+def test_bordered_inverse(n, cond):
+    a, g = _spd(n, cond, n), _spd(65, cond, n + 1)
+    Ai, Gi, info = _invert([(a, g)], 0.0)
+    assert list(info) == [0, 0]
+    for m, x in ((a, Ai[0]), (g, Gi[0])):
+        err = gu.rel_fro(x, np.linalg.inv(m.astype(np.float64)))
+        print(n, m.shape[0], f"cond {cond:.0e}: {err:.2e}")
+        assert err < 1.5 * cond * 2.0 ** -24
+        assert np.array_equal(x, x.T)
+
+
+@pytest.mark.parametrize("count", [1, 9, 130])
+def test_many_small_matrices(count):
+    """Descriptors with the launch (16 or 224 of them at most) and through the table (260 matrices)."""
+    mats = [(_spd(65 if i % 3 else 40 + i % 30, 100.0, i), _spd(10 + (7 * i) % 130, 100.0, 1000 + i)) for i in range(count)]
+    Ai, Gi, info = _invert(mats, 0.01)
+    assert not info.any()
+    for (a, g), x, y in zip(mats, Ai, Gi):
+        for m, r in ((a, x), (g, y)):
+            ref = np.linalg.inv(m.astype(np.float64) + 0.01 * np.eye(len(m)))
+            assert gu.rel_fro(r, ref) < 1e-5
+
+
+def test_status_of_order_65():
+    """A failing pivot inside the block and a failing last one are reported by their place; the others are not affected."""
+    good = _spd(65, 100.0, 1)
+    last, mid = good.copy(), good.copy()
+    last[64, 64] = -1.0
+    mid[30, 30] = -1.0
+    Ai, _, info = _invert([(good, good), (last, mid)], 0.0)
+    assert list(info) == [0, 0, 65, 31]
+    assert gu.rel_fro(Ai[0], np.linalg.inv(good.astype(np.float64))) < 1e-5
