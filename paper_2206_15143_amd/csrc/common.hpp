@@ -148,6 +148,7 @@ struct Tuning {
     long im2col_block_bytes = 80 * 1024;  // output bytes per workgroup aimed for
     long im2col_lds_bytes = 20 * 1024;    // slab budget of a workgroup
     long im2col_min_blocks = 1024;   // shorter strips until a layer has this many workgroups
+    long use_eigen_dc = 1;           // orders up to 1280 by tridiagonalisation and divide and conquer
     long eigen_max_sweeps = 20;      // sweep budget of the block Jacobi eigen-decomposition (12-13 used at order 577)
     long eigen_inner_sweeps = 1;     // Jacobi sweeps over the 32 x 32 Gram matrix of a pair of blocks per round
     long bf16_rows_copy = 1;         // bf16 NCHW operands with an odd number of positions: row-major copy first

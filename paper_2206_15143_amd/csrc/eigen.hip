@@ -2,6 +2,8 @@
 // Q_G, v_G that the eigen-decomposition variant of the preconditioner uses (Eq. 13 of the DP-KFAC
 // paper, section 5.2).
 //
+// Orders up to 1280 go through eigen_dc.hpp (tridiagonalisation, divide and conquer).  Above:
+//
 // Method: one-sided block Jacobi on rows.  The working pair (W, V) starts as (M, I) and every step
 // applies the same orthogonal transform to both from the left, so W = V M holds throughout; when the
 // rows of W are mutually orthogonal, row i of V is an eigenvector and <v_i, w_i> its eigenvalue.
@@ -22,7 +24,10 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 #include <vector>
+
+#include "eigen_dc.hpp"
 
 namespace kfac {
 
@@ -366,17 +371,22 @@ struct TrProb {
     int blk_start;
 };
 
+constexpr int kMaxTr = 256;       // matrices per launch (a 6 KB kernel argument)
 struct TrTable {
     int count;
-    TrProb p[kMaxProblems];
+    TrProb p[kMaxTr];
 };
 
 // dst = src^T for square matrices, 32 x 32 tiles through LDS.
 __global__ __launch_bounds__(256) void transpose_kernel(const TrTable tab)
 {
     __shared__ float t[32][33];
-    int pi = 0;
-    while (pi + 1 < tab.count && (int)blockIdx.x >= tab.p[pi + 1].blk_start) ++pi;
+    int pi = 0, hi = tab.count - 1;
+    while (pi < hi) {
+        const int mid = (pi + hi + 1) >> 1;
+        if ((int)blockIdx.x >= tab.p[mid].blk_start) pi = mid;
+        else hi = mid - 1;
+    }
     const TrProb &pr = tab.p[pi];
     const int local = blockIdx.x - pr.blk_start;
     const int nt = (pr.n + 31) / 32;
@@ -397,9 +407,9 @@ __global__ __launch_bounds__(256) void transpose_kernel(const TrTable tab)
 
 hipError_t transpose_launch(const float *const *src, float *const *dst, const int *n, int count, hipStream_t s)
 {
-    for (int g0 = 0; g0 < count; g0 += kMaxProblems) {
+    for (int g0 = 0; g0 < count; g0 += kMaxTr) {
         TrTable tab;
-        tab.count = std::min(kMaxProblems, count - g0);
+        tab.count = std::min(kMaxTr, count - g0);
         int blocks = 0;
         for (int k = 0; k < tab.count; ++k) {
             TrProb &p = tab.p[k];
@@ -437,17 +447,105 @@ EigLayout eig_layout(int n)
 
 }  // namespace
 
-size_t eigen_workspace_bytes(const EigenJob *jobs, int n)
+namespace {
+
+bool takes_dc(int n) { return tuning().use_eigen_dc && n <= kDcMaxN; }
+
+size_t jacobi_workspace_bytes(const EigenJob *jobs, int n)
 {
     size_t total = 0;
     for (int i = 0; i < n; ++i) total += align_up(eig_layout(jobs[i].n).total * sizeof(float), 256);
     return total + align_up((size_t)n * sizeof(int), 256);
 }
 
+// Divide and conquer for up to kDcTab matrices, largest first.
+hipError_t dc_launch(const DcProb *probs, int count, hipStream_t s)
+{
+    DcTable tab;
+    tab.count = count;
+    tab.sweeps = (int)std::max(1l, tuning().eigen_max_sweeps);
+    tab.step = 0;
+    for (int k = 0; k < count; ++k) tab.p[k] = probs[k];
+    auto lay_out = [&](auto blocks_of) {
+        int blocks = 0;
+        for (int k = 0; k < count; ++k) {
+            tab.p[k].first = blocks;
+            blocks += blocks_of(tab.p[k].n);
+        }
+        return blocks;
+    };
+#define KFAC_DC(cls, kernel, threads, blocks_of)                                                  \
+    do {                                                                                          \
+        const int blocks = lay_out(blocks_of);                                                    \
+        if (blocks > 0) {                                                                         \
+            KFAC_LAUNCH(cls, s, kernel, dim3(blocks), dim3(threads), 0, tab);                     \
+            const hipError_t e = hipGetLastError();                                               \
+            if (e != hipSuccess) return e;                                                        \
+        }                                                                                         \
+    } while (0)
+    KFAC_DC(KFAC_K_EIG_INIT, dc_init_kernel, 256, [](int n) { const int t = (n + 31) / 32; return t * (t + 1) / 2; });
+    const int levels = dc_levels(probs[0].n);
+    if (levels > 0) KFAC_DC(KFAC_K_EIG_ROUND, dc_tridiag_kernel, 64 * kTriWaves, [](int) { return 1; });
+    KFAC_DC(KFAC_K_EIG_ROUND, dc_leaf_kernel, 64, [](int n) { return 1 << dc_levels(n); });
+    for (int st = 0; st < levels; ++st) {
+        tab.step = st;
+        auto nodes = [st](int n) { const int l = dc_levels(n) - 1 - st; return l < 0 ? 0 : 1 << l; };
+        auto most = [st](int n) { const int l = std::max(0, dc_levels(n) - 1 - st); return (n + (1 << l) - 1) >> l; };
+        KFAC_DC(KFAC_K_EIG_ROUND, dc_deflate_kernel, 256, nodes);
+        KFAC_DC(KFAC_K_EIG_ROUND, dc_secular_kernel, 256, [&](int n) { return nodes(n) * ((most(n) + 15) / 16); });
+        KFAC_DC(KFAC_K_EIG_ROUND, dc_vectors_kernel, 256, [&](int n) { return nodes(n) * ((most(n) + 63) / 64); });
+        KFAC_DC(KFAC_K_EIG_ROUND, dc_product_kernel, 256,
+                [&](int n) { const int side = (most(n) + 63) / 64; return nodes(n) * side * side; });
+    }
+    if (levels == 0) return hipSuccess;
+    KFAC_DC(KFAC_K_EIG_FINAL, dc_tfactor_kernel, 256, [](int n) { return n <= kDcLeaf ? 0 : (n + 63) / 64; });
+    // one launch per tier of orders: the matrices of another tier get no blocks
+    KFAC_DC(KFAC_K_EIG_FINAL, (dc_back_kernel<1, 1280>), 256, [](int n) { return n > 640 ? (n + 15) / 16 : 0; });
+    KFAC_DC(KFAC_K_EIG_FINAL, (dc_back_kernel<1, 640>), 256, [](int n) { return n > 320 && n <= 640 ? (n + 15) / 16 : 0; });
+    KFAC_DC(KFAC_K_EIG_FINAL, (dc_back_kernel<2, 320>), 256, [](int n) { return n > kDcLeaf && n <= 320 ? (n + 31) / 32 : 0; });
+#undef KFAC_DC
+    return hipSuccess;
+}
+
+hipError_t jacobi_launch(const EigenJob *jobs, int n, void *work, hipStream_t s);
+
+}  // namespace
+
+size_t eigen_workspace_bytes(const EigenJob *jobs, int n)
+{
+    std::vector<EigenJob> rest;
+    size_t total = 0;
+    for (int i = 0; i < n; ++i) {
+        if (takes_dc(jobs[i].n)) total += DcWs(nullptr, jobs[i].n).bytes;
+        else rest.push_back(jobs[i]);
+    }
+    return total + (rest.empty() ? 0 : jacobi_workspace_bytes(rest.data(), (int)rest.size()));
+}
+
 hipError_t eigen_launch(const EigenJob *jobs, int n, void *work, size_t work_bytes, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
     if (eigen_workspace_bytes(jobs, n) > work_bytes) return hipErrorInvalidValue;
+    std::vector<EigenJob> rest;
+    std::vector<DcProb> dc;
+    char *at = static_cast<char *>(work);
+    for (int i = 0; i < n; ++i) {
+        const EigenJob &j = jobs[i];
+        if (!takes_dc(j.n)) { rest.push_back(j); continue; }
+        dc.push_back(DcProb{j.M, j.Q, j.v, j.info, at, j.n, 0});
+        at += DcWs(nullptr, j.n).bytes;
+    }
+    std::stable_sort(dc.begin(), dc.end(), [](const DcProb &a, const DcProb &b) { return a.n > b.n; });
+    for (size_t g0 = 0; g0 < dc.size(); g0 += kDcTab) {
+        const hipError_t e = dc_launch(dc.data() + g0, (int)std::min<size_t>(kDcTab, dc.size() - g0), s);
+        if (e != hipSuccess) return e;
+    }
+    return rest.empty() ? hipSuccess : jacobi_launch(rest.data(), (int)rest.size(), at, s);
+}
+
+namespace {
+hipError_t jacobi_launch(const EigenJob *jobs, int n, void *work, hipStream_t s)
+{
     // matrices of one order back to back (largest first), W and V of a matrix adjacent
     std::vector<int> order(n);
     for (int i = 0; i < n; ++i) order[i] = i;
@@ -542,5 +640,7 @@ hipError_t eigen_launch(const EigenJob *jobs, int n, void *work, size_t work_byt
     }
     return hipSuccess;
 }
+
+}  // namespace
 
 }  // namespace kfac
