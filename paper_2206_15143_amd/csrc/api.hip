@@ -83,6 +83,7 @@ struct Geo {
     int esz;
     bool g_rows;        // bf16 output gradients on a map with an odd number of positions: through a row-major copy
     int ldg;            // its leading dimension (elements)
+    size_t corr_bytes = 0;   // autocorrelations of a padded copy: what they keep in the workspace (counts towards a chunk's bytes)
 };
 
 bool desc_ok(const kfac_layer_desc *d)
@@ -137,6 +138,12 @@ kfac_status geometry(const kfac_layer_desc *d, int batch, int h, int w, Geo &g)
         g.fused3 = tuning().fuse_conv3 && d->in_dtype == KFAC_F32 && d->kh == 3 && d->kw == 3 && d->stride == 1 &&
                    ph == 1 && pw == 1 && d->d_in % 16 == 0 && d->d_in <= tuning().fuse_conv3_max_c && conv3_rows(h, w) > 0 &&
                    (long)batch * d->d_in * h * w * 4 < 0x7fff0000l;
+        const bool corrw = d->in_dtype == KFAC_F32 && d->kh == 3 && d->kw == 3 && d->stride == 1 && ph == 1 && pw == 1 &&
+                           corrw_takes(d->d_in, h, w, batch);
+        g.fused3 = g.fused3 || corrw;
+        // an eighth of the bytes counts: a chunk of few layers leaves every one of its launches half empty (VGG-16-,
+        // DenseNet-201- and ResNet-50-shaped, an eighth / all: 2.02 / 2.33, 15.76 / 16.79, 13.26 / 14.12 ms)
+        g.corr_bytes = corrw ? corrw_bytes(d->d_in, h, w, batch) / 8 : 0;
         if (g.fused3) g.patches = false;
         // The bf16 MFMA kernel reads NCHW operands in 4-byte pieces along a channel row, which an odd number of
         // positions per channel (7 x 7 maps) misaligns; the fp32-widening kernel that would take such operands
@@ -253,7 +260,7 @@ std::vector<Chunk> make_chunks(const std::vector<Geo> &geo, const kfac_layer_des
         acc = 0;
     };
     auto add = [&](int i) {
-        const size_t pb = patch_bytes(geo[i]);
+        const size_t pb = patch_bytes(geo[i]) + geo[i].corr_bytes;
         if (!cur.idx.empty() && (acc + pb > budget || (int)cur.idx.size() >= cap)) flush();
         cur.idx.push_back(i);
         acc += pb;
@@ -266,7 +273,7 @@ std::vector<Chunk> make_chunks(const std::vector<Geo> &geo, const kfac_layer_des
         if (cnt >= 8) {
             // a long run of equal layers gets chunks of its own, cut into equal parts
             flush();
-            const size_t pb = patch_bytes(geo[order[r0]]);
+            const size_t pb = patch_bytes(geo[order[r0]]) + geo[order[r0]].corr_bytes;
             int per = cap;
             if (pb > 0) per = (int)std::max<size_t>(1, std::min<size_t>(cap, budget / pb));
             const int parts = (cnt + per - 1) / per;
@@ -959,6 +966,8 @@ int kfac_tune(const char *key, long value)
     else if (k == "use_small_kernel") t.use_small_kernel = value;
     else if (k == "invert_fused_max_n") t.invert_fused_max_n = value;
     else if (k == "use_corr3") t.use_corr3 = value;
+    else if (k == "corrw_min_c") t.corrw_min_c = value;
+    else if (k == "corrw_max_pad") t.corrw_max_pad = value;
     else if (k == "corr3_lds_kb") t.corr3_lds_kb = value;
     else if (k == "invert_border") t.invert_border = value;
     else if (k == "invert_two_streams") t.invert_two_streams = value;

@@ -69,6 +69,10 @@ struct GemmJob {
     const float *D = nullptr;    // kSubFrom
     long ldd = 0;
     bool wide_tiles = false;     // kStore: take the split-bf16 kernel whatever the depth and tile fill
+    // gemm_split_products only: K in kslices slices of kper rows (a multiple of 16), slice i into C + i cstride; abytes:
+    // from A to the end of its buffer (rows of A may overlap: M > lda), what lies past it counts as zero
+    int kslices = 1, kper = 0;
+    long cstride = 0, abytes = 0;
 };
 
 enum GemmMode : int {
@@ -120,6 +124,9 @@ hipError_t pi_damping_launch(const float *const *A, const float *const *G, const
 // it (or with less) every product is computed in one piece
 hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work = nullptr, size_t work_bytes = 0);
 size_t gemm_workspace_bytes(const GemmJob *jobs, int n);
+// kStore products on the split-bf16 kernel, whatever their sizes, launches timed as class `cls`; `definition`: flops of what
+// they serve
+hipError_t gemm_split_products(const GemmJob *jobs, int n, int cls, double definition, hipStream_t s);
 
 // whether a layer of these orders takes the one-launch form of the two-sided product; out must not overlap any W of the call
 bool precond_fused_takes(int dA, int dG);
@@ -131,6 +138,11 @@ bool im2col_fits(int kh, int kw, int stride, int Wo, int esz);
 size_t eigen_workspace_bytes(const EigenJob *jobs, int n);
 hipError_t eigen_launch(const EigenJob *jobs, int n, void *work, size_t work_bytes, hipStream_t s);
 hipError_t transpose_launch(const float *const *src, float *const *dst, const int *n, int count, hipStream_t s);
+
+// whether the factor of a 3x3 / stride 1 / pad 1 fp32 convolution comes from channel autocorrelations of a padded copy of
+// its input (syrk_corrw.hpp); bytes of that copy and of the partial sums
+bool corrw_takes(int c, int h, int w, int batch);
+size_t corrw_bytes(int c, int h, int w, int batch);
 
 // output rows per stage of the fused 3x3 convolution factor kernel; 0 = image shape not supported
 int conv3_rows(int h, int w);
@@ -161,6 +173,8 @@ struct Tuning {
     long invert_border = 1;          // orders 64 k + 1: last row and column by bordering instead of a one-row pivot block
     long invert_two_streams = 1;     // blocked sweep and smaller factors on the library's streams (look-ahead); 0: everything on the caller's stream
     long corr3_lds_kb = 72;          // LDS budget (both slabs) of the autocorrelation kernel
+    long corrw_min_c = 20;           // ... of at least this many channels from products of a padded, transposed copy (0 = never)
+    long corrw_max_pad = 170;        // ... on maps whose copy has at most this percentage of their positions
     long use_corr3 = 1;              // 3x3 convolution factors of 16 / 32 / 64 channels from input autocorrelations
     long invert_fused_max_n = 1280;  // orders up to this take the one-launch-per-step sweep
     long syrk_force_bm = 0;          // 0 = choose

@@ -335,7 +335,8 @@ bool split_gemm_wide(const GemmJob *jobs, int n)
     return split >= rest;
 }
 
-hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hipStream_t s)
+hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, hipStream_t s, int cls = KFAC_K_GEMM_SPLIT,
+                             double definition = -1.0)
 {
     GemmSTable tab;
     tab.count = 0;
@@ -345,7 +346,7 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         if (tab.count == 0) return hipSuccess;
         // tile ranges of the XCDs, of equal cost: the K stages of a tile and about twelve more for its start and end
         double total = 0.0;
-        auto cost = [&](const GemmSProb &p) { return (p.K + S_KT - 1) / S_KT + 12.0; };
+        auto cost = [&](const GemmSProb &p) { return (std::min(p.K, p.kper) + S_KT - 1) / S_KT + 12.0; };
         for (int k = 0; k < tab.count; ++k)
             total += cost(tab.p[k]) * ((k + 1 < tab.count ? tab.p[k + 1].blk_start : (int)blocks) - tab.p[k].blk_start);
         int most = 1, x = 1;
@@ -360,8 +361,9 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         }
         for (; x < 8; ++x) tab.xcd[x] = (int)blocks;
         for (int k = 0; k < 8; ++k) most = std::max(most, tab.xcd[k + 1] - tab.xcd[k]);
-        KFAC_LAUNCH(KFAC_K_GEMM_SPLIT, s, gemm_split_kernel, dim3((unsigned)(8 * most)), dim3(256), 0, tab);
-        timing_work(flops, 6.0 * flops);
+        KFAC_LAUNCH(cls, s, gemm_split_kernel, dim3((unsigned)(8 * most)), dim3(256), 0, tab);
+        timing_work(definition < 0.0 ? flops : definition, 6.0 * flops);
+        if (definition > 0.0) definition = 0.0;          // with the first launch
         tab.count = 0;
         blocks = 0;
         flops = 0.0;
@@ -380,9 +382,15 @@ hipError_t split_gemm_launch(const GemmJob *jobs, const std::vector<int> &idx, h
         if (j.mode == kSubLowerSkip) p.doff = 0;
         p.gate = j.gate; p.gate_cond = j.gate_cond;
         p.blk_start = (int)blocks;
-        for (int I = 0; I < p.tI; ++I) blocks += split_row_len(p.mode, p.tJ, p.doff, I);
+        tab.starts[tab.count - 1] = (int)blocks;
+        p.tiles = 0;
+        for (int I = 0; I < p.tI; ++I) p.tiles += split_row_len(p.mode, p.tJ, p.doff, I);
+        p.kper = j.kslices > 1 ? j.kper : j.K;
+        p.cstride = j.cstride;
+        p.abytes = (int)(j.abytes > 0 ? j.abytes : (long)j.K * j.lda * 4);
+        blocks += (long)p.tiles * std::max(1, j.kslices);
         if (!j.gate) flops += gemm_job_flops(j);       // a gated product may be skipped on the device: not counted
-        if (tab.count == kMaxProblems) {
+        if (tab.count == kMaxGemmS) {
             hipError_t e = flush();
             if (e != hipSuccess) return e;
         }
@@ -473,6 +481,13 @@ __global__ __launch_bounds__(256) void gemm_kreduce_kernel(const KRedTable tab)
 
 hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s);
 }  // namespace
+
+hipError_t gemm_split_products(const GemmJob *jobs, int n, int cls, double definition, hipStream_t s)
+{
+    std::vector<int> idx(n);
+    for (int i = 0; i < n; ++i) idx[i] = i;
+    return split_gemm_launch(jobs, idx, s, cls, definition);
+}
 
 size_t gemm_workspace_bytes(const GemmJob *jobs, int n)
 {

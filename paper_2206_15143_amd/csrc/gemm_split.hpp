@@ -24,12 +24,19 @@ struct GemmSProb {
     int doff;        // the subtracting modes touch n <= m + doff (0 for kSubLowerSkip)
     const int *gate; // null, or two float bit patterns: leave C alone unless their product exceeds gate_cond
     float gate_cond;
+    int tiles;       // of one K slice
+    int kper;        // rows of K per slice (a multiple of 16, or K); slice i stores into C + i cstride
+    long cstride;
+    int abytes;      // bytes from A to the end of its buffer: what lies past it reads as zero
 };
+
+constexpr int kMaxGemmS = 96;        // products per launch (a 10 KB kernel argument)
 
 struct GemmSTable {
     int count;
     int xcd[9];      // XCD x takes the tiles xcd[x] .. xcd[x + 1] - 1
-    GemmSProb p[kMaxProblems];
+    int starts[kMaxGemmS];
+    GemmSProb p[kMaxGemmS];
 };
 
 // column tiles of tile row i: all of them, or those that reach the line n = m + doff
@@ -57,12 +64,18 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const int x = blockIdx.x & 7;
     const int bid = tab.xcd[x] + (int)(blockIdx.x >> 3);
     if (bid >= tab.xcd[x + 1]) return;
-    int pi = 0;
-    while (pi + 1 < tab.count && bid >= tab.p[pi + 1].blk_start) ++pi;
+    int pi = 0, hi = tab.count - 1;
+    while (pi < hi) {
+        const int mid = (pi + hi + 1) >> 1;
+        if (bid >= tab.starts[mid]) pi = mid;
+        else hi = mid - 1;
+    }
     const GemmSProb &pr = tab.p[pi];
     // uniform over the workgroup, before any barrier or load
     if (pr.gate && !(__int_as_float(pr.gate[0]) * __int_as_float(pr.gate[1]) > pr.gate_cond)) return;
     int local = bid - pr.blk_start;
+    const int slice = local / pr.tiles, k0 = slice * pr.kper, K = min(pr.kper, pr.K - k0);
+    local -= slice * pr.tiles;
     int I, J;
     const bool lower = pr.mode != kStore;         // read-modify-write below the line n = m + doff
     const bool rows_skip = pr.mode == kSubLowerSkip;
@@ -106,12 +119,14 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     const long lda = pr.lda, ldb = pr.ldb;
     SplitSrc<kRows> src;
     {
-        const long na = (long)pr.K * lda * 4, nb = (long)pr.K * ldb * 4;      // the host checked: below 2 GiB
-        src.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A), 0, (int)na, 0x00020000);
-        src.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.B), 0, (int)nb, 0x00020000);
+        // the host checked: below 2 GiB.  (A slice past the last row has no stages.)
+        const long sa = (long)min(k0, pr.K) * lda, sb = (long)min(k0, pr.K) * ldb;
+        const long na = max(0l, pr.abytes - sa * 4), nb = (long)pr.K * ldb * 4 - sb * 4;
+        src.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A + sa), 0, (int)na, 0x00020000);
+        src.rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.B + sb), 0, (int)nb, 0x00020000);
         src.lda4 = (unsigned)lda * 4u;
         src.ldb4 = (unsigned)ldb * 4u;
-        src.nstages = (pr.K + S_KT - 1) / S_KT;
+        src.nstages = (max(K, 0) + S_KT - 1) / S_KT;
         src.init_thread(tid);
         src.lim_a = pr.M - m0;
         src.lim_b = pr.N - n0;
@@ -151,7 +166,7 @@ __global__ __launch_bounds__(256, 2) void gemm_split_kernel(const GemmSTable tab
     float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
     const int rr = lane >> 4, c4 = (lane & 15) * 4;
     // the host checked that M rows of C are below 2 GiB
-    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.C, 0, (int)((long)pr.M * ldc * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.C + slice * pr.cstride, 0, (int)((long)pr.M * ldc * 4), 0x00020000);
     const unsigned vo = (unsigned)(rr * ldc + c4) * 4u;
     const float sign = (lower && !add) ? -unscale : unscale;
     auto row_off = [&](int ti, int q) { return (unsigned)((mw + ti * 32 + 4 * q) * ldc + nw) * 4u; };

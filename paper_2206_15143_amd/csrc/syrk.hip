@@ -30,6 +30,7 @@
 #include "syrk_wave.hpp"
 #include "syrk_conv3.hpp"
 #include "syrk_corr3.hpp"
+#include "syrk_corrw.hpp"
 #include "syrk_small.hpp"
 #include "syrk_bf16.hpp"
 #include "syrk_split.hpp"
@@ -474,7 +475,7 @@ namespace {
 struct Cfg { int wt, nw, bm; };
 // the last entry is the wave-unit kernel (syrk_wave.hpp): 144-wide macro tiles, same partial layout as Tile<3,3>
 const Cfg kCfgs[] = {{4, 2, 128}, {3, 3, 144}, {2, 2, 64}, {1, 2, 32}, {0, 0, 144}, {0, 0, 144}, {0, 0, 32}, {0, 0, 64},
-                     {0, 0, 256}, {0, 0, 144}, {0, 0, 16}, {0, 0, 16}, {0, 0, 16}, {0, 0, 256}};
+                     {0, 0, 256}, {0, 0, 144}, {0, 0, 16}, {0, 0, 16}, {0, 0, 16}, {0, 0, 256}, {0, 0, 16}};
 constexpr int kWaveCfg = 4;
 constexpr int kCorr3Cfg = 10;  // 3x3 convolution factors from autocorrelations (syrk_corr3.hpp): 10 / 11 / 12 = 16 / 32 / 64 channels
 constexpr int kConv3Cfg = 5;   // fused 3x3 convolution kernel (syrk_conv3.hpp), same partial layout
@@ -483,6 +484,7 @@ constexpr int kSmall64Cfg = 7; // same, 64 x 64 (d <= 64)
 constexpr int kWaveNchwCfg = 9; // wave-unit kernel for NCHW fp32 operands (same partial layout as kWaveCfg)
 constexpr int kBf16Cfg = 8;    // row-major bf16 operands on the bf16 MFMA units (syrk_bf16.hpp), 256 x 256 tiles
 inline bool is_corr3_cfg(int cfg) { return cfg >= kCorr3Cfg && cfg < kCorr3Cfg + 3; }
+constexpr int kCorrWCfg = 14;  // wide 3x3 convolution factors from autocorrelations (syrk_corrw.hpp)
 constexpr int kSplitCfg = 13;  // wide fp32 operands on the bf16 MFMA units (syrk_split.hpp), same partial layout as kBf16Cfg
 
 bool small_eligible(const FactorJob &j)
@@ -615,6 +617,13 @@ struct Planned {
 void plan_group(const FactorJob *jobs, const std::vector<int> &idx, std::vector<Planned> &pl)
 {
     const Tuning &tu = tuning();
+    if (pl[idx[0]].cfg == kCorrWCfg) {
+        for (int j : idx) {
+            pl[j].nb = pl[j].nblk = pl[j].bps = pl[j].splits = pl[j].tps = 1;
+            pl[j].partial_floats = CorrW(jobs[j].ctot, jobs[j].h, jobs[j].w, (int)(jobs[j].K / jobs[j].hw)).total;
+        }
+        return;
+    }
     if (is_corr3_cfg(pl[idx[0]].cfg)) {
         // autocorrelation kernel: (image, strip) units dealt evenly to about target_blocks workgroups
         const long halves = pl[idx[0]].cfg == kCorr3Cfg + 2 ? 2 : 1;
@@ -714,6 +723,8 @@ void plan_all(const FactorJob *jobs, int n, std::vector<Planned> &pl, std::vecto
     std::vector<int> keys(n);
     for (int i = 0; i < n; ++i) {
         if (corr3_eligible(jobs[i])) pl[i].cfg = kCorr3Cfg + (jobs[i].ctot == 16 ? 0 : (jobs[i].ctot == 32 ? 1 : 2));
+        else if (jobs[i].layout == kConv3 && corrw_takes(jobs[i].ctot, jobs[i].h, jobs[i].w, (int)(jobs[i].K / jobs[i].hw)))
+            pl[i].cfg = kCorrWCfg;
         else if (jobs[i].layout == kConv3) pl[i].cfg = kConv3Cfg;
         else if (small_eligible(jobs[i])) pl[i].cfg = jobs[i].d_core <= 32 ? kSmall32Cfg : kSmall64Cfg;
         else if (bf16_eligible(jobs[i])) pl[i].cfg = kBf16Cfg;
@@ -723,7 +734,7 @@ void plan_all(const FactorJob *jobs, int n, std::vector<Planned> &pl, std::vecto
         keys[i] = group_key(jobs[i], pl[i].cfg);
     }
     groups.clear();
-    for (int key = 0; key < 8 * (kSplitCfg + 1); ++key) {
+    for (int key = 0; key < 8 * (kCorrWCfg + 1); ++key) {
         std::vector<int> cur;
         for (int i = 0; i < n; ++i) {
             if (keys[i] != key) continue;
@@ -848,6 +859,20 @@ hipError_t corr3_launch_nt(CorrTable &tab, const std::vector<size_t> &lds, doubl
     return e;
 }
 
+// assembly, scale, running average: one wavefront per channel, kernel row and 64 partner channels (+ the bias row)
+hipError_t corr3_assemble(CorrTable &tab, hipStream_t s)
+{
+    int blocks = 0;
+    for (int k = 0; k < tab.count; ++k) {
+        const CorrProb &p = tab.p[k];
+        tab.p[k].blk_start = blocks;
+        tab.starts[k] = blocks;
+        blocks += ((3 * p.C + p.has_bias) * ((p.C + 63) / 64) + C3_ARW - 1) / C3_ARW;
+    }
+    KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corr3_assemble_kernel, dim3(blocks), dim3(256), 0, tab);
+    return hipGetLastError();
+}
+
 hipError_t corr3_launch(const FactorJob *jobs, const std::vector<int> &g, const std::vector<Planned> &pl,
                         const std::vector<size_t> &offs, void *work, double flops, double exflops, hipStream_t s)
 {
@@ -898,19 +923,89 @@ hipError_t corr3_launch(const FactorJob *jobs, const std::vector<int> &g, const 
     KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corr3_sum_kernel, dim3(blocks), dim3(256), 0, tab);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // assembly, scale, running average
-    blocks = 0;
+    return corr3_assemble(tab, s);
+}
+
+// The copies, their products (one launch for as many factors as a table holds), the sums, the assembly.
+hipError_t corrw_launch(const FactorJob *jobs, const std::vector<int> &g, const std::vector<size_t> &offs, void *work,
+                        double flops, hipStream_t s)
+{
+    CorrWTable tab;
+    CorrTable asm_tab;
+    tab.count = asm_tab.count = (int)g.size();
+    std::vector<GemmJob> gj;
+    int copy_blocks = 0, sum_blocks = 0;
+    std::vector<int> sum_start(g.size());
     for (int k = 0; k < tab.count; ++k) {
-        const CorrProb &p = tab.p[k];
-        tab.p[k].blk_start = blocks;
-        tab.starts[k] = blocks;
-        blocks += (3 * p.C + p.has_bias + C3_ARW - 1) / C3_ARW;       // one wavefront per channel and kernel row (+ the bias row)
+        const FactorJob &job = jobs[g[k]];
+        const CorrW L(job.ctot, job.h, job.w, (int)(job.K / job.hw));
+        float *base = reinterpret_cast<float *>(static_cast<char *>(work) + offs[g[k]]);
+        const size_t cc = (size_t)L.C * L.C;
+        CorrWProb &p = tab.p[k];
+        p.x = static_cast<const float *>(job.x);
+        p.Xp = base + L.Xp; p.R = base + L.R; p.Cc = base + L.Cc; p.Q = base + L.Q; p.V = base + L.V;
+        p.Fp = base + L.Fp; p.Bp = base + L.Bp; p.Fs = base + L.Fs; p.FsT = base + L.FsT; p.Bs = base + L.Bs; p.BsT = base + L.BsT;
+        p.C = L.C; p.H = L.H; p.W = L.W; p.B = L.B;
+        p.parts = L.parts; p.slices = L.slices; p.bslices = L.bslices;
+        p.blk_start = copy_blocks;
+        copy_blocks += L.B * L.parts * ((L.C + 63) / 64);
+        const int side = (L.C + 31) / 32;
+        sum_start[k] = sum_blocks;
+        sum_blocks += (C3_LAGS + C3_BQ) * side * side + (9 * L.C + 255) / 256;
+        auto product = [&](const float *X, long K, long off, int lags, float *out, int mats, int slices, int kper) {
+            GemmJob j{};
+            j.A = X + off * L.C; j.B = X; j.C = out;
+            j.M = lags * L.C; j.N = L.C; j.K = (int)K;
+            j.lda = j.ldb = j.ldc = L.C;
+            j.mode = kStore;
+            j.kslices = slices; j.kper = kper; j.cstride = (long)(mats * cc);
+            j.abytes = (K - off) * L.C * 4;
+            gj.push_back(j);
+        };
+        const long wp = L.W + 2;
+        product(p.Xp, L.Kp, 0, 3, p.Fp, C3_LAGS, L.slices, L.kper);
+        product(p.Xp, L.Kp, wp - 2, 5, p.Fp + 3 * cc, C3_LAGS, L.slices, L.kper);
+        product(p.Xp, L.Kp, 2 * wp - 2, 5, p.Fp + 8 * cc, C3_LAGS, L.slices, L.kper);
+        for (int sd = 0; sd < 2; ++sd) {
+            product(p.R + sd * L.Kr * L.C, L.Kr, 0, 3, p.Bp + 3 * sd * cc, C3_BQ, L.bslices, L.kper_r);
+            product(p.Cc + sd * L.Kc * L.C, L.Kc, 0, 3, p.Bp + (6 + 3 * sd) * cc, C3_BQ, L.bslices, L.kper_c);
+        }
+        for (int q = 0; q < 4; ++q)
+            product(p.Q + (size_t)q * L.B * L.C, L.B, 0, 1, p.Bp + (12 + q) * cc, C3_BQ, L.bslices, L.kper_q);
+        CorrProb &a = asm_tab.p[k];
+        a = CorrProb{};
+        a.Fs = p.Fs; a.FsT = p.FsT; a.Bs = p.Bs; a.BsT = p.BsT;
+        a.F = job.F; a.C = L.C; a.H = L.H; a.W = L.W; a.B = L.B;
+        a.has_bias = job.has_bias; a.scale = job.scale; a.decay = job.decay;
     }
-    KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corr3_assemble_kernel, dim3(blocks), dim3(256), 0, tab);
-    return hipGetLastError();
+    KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corrw_copy_kernel, dim3(copy_blocks), dim3(256), 0, tab);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    // deepest slices first
+    std::stable_sort(gj.begin(), gj.end(), [](const GemmJob &a, const GemmJob &b) { return std::min(a.K, a.kper) > std::min(b.K, b.kper); });
+    e = gemm_split_products(gj.data(), (int)gj.size(), KFAC_K_SYRK_SPLIT, flops, s);
+    if (e != hipSuccess) return e;
+    for (int k = 0; k < tab.count; ++k) tab.p[k].blk_start = sum_start[k];
+    KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corrw_sum_kernel, dim3(sum_blocks), dim3(256), 0, tab);
+    e = hipGetLastError();
+    return e == hipSuccess ? corr3_assemble(asm_tab, s) : e;
 }
 
 }  // namespace
+
+// From 20 channels on (16 lose: 1.84 -> 2.13 ms on a network of 8, 16 and 32), on maps whose copy is at most 1.7 times their
+// size (7 x 7: 1.65; at 4 x 4, 2.25, a 512-channel layer takes 365 us this way and 305 over the patch matrix).  Rows of the copy
+// are read 16 bytes at a time: whole groups of four channels.  The copy below 2 GiB: 32-bit buffer offsets.
+bool corrw_takes(int c, int h, int w, int batch)
+{
+    return tuning().fuse_conv3 && tuning().use_corr3 && tuning().corrw_min_c > 0 && c >= tuning().corrw_min_c && c % 4 == 0 && c <= 2048 && h >= 2 && w >= 2 &&
+           (h + 2l) * (w + 2l) * 100 <= tuning().corrw_max_pad * h * w && (double)batch * (h + 2) * (w + 2) * c * 4 < 2.0e9;
+}
+size_t corrw_bytes(int c, int h, int w, int batch)
+{
+    const CorrW l(c, h, w, batch);
+    return l.total * sizeof(float);
+}
 
 int conv3_rows(int h, int w) { return conv3_choose_rows(h, w); }
 
@@ -986,6 +1081,11 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
         const int cfg = pl[g[0]].cfg;
         const int layout = jobs[g[0]].layout, dt = jobs[g[0]].dtype;
         hipError_t e = hipSuccess;
+        if (cfg == kCorrWCfg) {
+            e = corrw_launch(jobs, g, offs, work, flops, s);
+            if (e != hipSuccess) return e;
+            continue;
+        }
         if (is_corr3_cfg(cfg)) {
             e = corr3_launch(jobs, g, pl, offs, work, flops, corr_flops, s);
             if (e != hipSuccess) return e;

@@ -661,7 +661,7 @@ __global__ __launch_bounds__(256) void corr3_sum_kernel(const CorrTable tab)
 }
 
 // Assembly of A from the lag matrices and the border terms, with scale and running average.  A wavefront
-// takes three rows of A (input channel c, kernel row i), lane c2 their entries for the channel pair (c, c2):
+// takes three rows of A (input channel c, kernel row i) and 64 partner channels, lane c2 the entries of the pair (c, c2):
 // every lag matrix and border matrix is read once at [c][c2] and once at [c2][c] (F(-d)[c][c'] = F(d)[c'][c]; the
 // summation kernel leaves a transposed copy, so both reads run along rows),
 // and which of them enters element ((i,j), (i',j')) is known at compile time.  The nine values of a lane per
@@ -671,13 +671,14 @@ __global__ __launch_bounds__(256) void corr3_sum_kernel(const CorrTable tab)
 constexpr int C3_ARW = 4;          // row triples (wavefronts) per workgroup
 
 template <int I>
-__device__ __forceinline__ void corr3_assemble_rows(const CorrProb &pr, int c, int lane, float *st)
+__device__ __forceinline__ void corr3_assemble_rows(const CorrProb &pr, int c, int cb, int lane, float *st)
 {
     const int C = pr.C, d = 9 * C, dF = d + pr.has_bias;
+    const int x0 = 9 * 64 * cb, xn = min(9 * 64, d - x0);             // columns of this block of partner channels
     const float *Fs = pr.Fs, *Ts = pr.Fs + (long)C3_LAGS * C * C;
     const float *Bs = pr.Bs, *Bv = pr.Bs + (long)C3_BQ * C * C;
     const float wnew = (1.0f - pr.decay) * pr.scale, decay = pr.decay;
-    const int c2 = lane < C ? lane : 0;                              // idle lanes repeat a valid address
+    const int c2 = 64 * cb + lane < C ? 64 * cb + lane : 0;          // idle lanes repeat a valid address
     // the old rows (clamped addresses: no branch, all loads in flight at once) and the bias column entries:
     // column sum of patch column (c, I, j) = all pixels minus the removed row / column plus the corner
     float old[3][9], oldb[3];
@@ -685,7 +686,7 @@ __device__ __forceinline__ void corr3_assemble_rows(const CorrProb &pr, int c, i
     for (int j = 0; j < 3; ++j) {
         const float *row = pr.F + (long)(9 * c + 3 * I + j) * dF;
 #pragma unroll
-        for (int k = 0; k < 9; ++k) old[j][k] = row[min(lane + 64 * k, dF - 1)];
+        for (int k = 0; k < 9; ++k) old[j][k] = row[min(x0 + lane + 64 * k, dF - 1)];
         float t = Ts[c];
         if (I != 1) t -= Bv[(I == 0 ? 1 : 0) * C + c];
         if (j != 1) t -= Bv[(j == 0 ? 3 : 2) * C + c];
@@ -726,14 +727,14 @@ __device__ __forceinline__ void corr3_assemble_rows(const CorrProb &pr, int c, i
                 val -= di >= 0 ? Rp[sd][di >= 0 ? di : 0] : Rn[sd][di < 0 ? -di : 0];
             }
             if (i2 == I && I != 1 && j2 == j && j != 1) val += Cq[(I == 0 ? 2 : 0) + (j == 0 ? 1 : 0)];
-            if (lane < C) st[9 * lane + ij2] = val;
+            st[9 * lane + ij2] = val;
         }
         __builtin_amdgcn_wave_barrier();       // LDS serves a wavefront's accesses in order: the reads below see the row
         float *row = pr.F + (long)(9 * c + 3 * I + j) * dF;
 #pragma unroll
         for (int k = 0; k < 9; ++k)
-            if (lane + 64 * k < d) row[lane + 64 * k] = decay * old[j][k] + wnew * st[lane + 64 * k];
-        if (pr.has_bias && lane == 0) row[d] = oldb[j];
+            if (lane + 64 * k < xn) row[x0 + lane + 64 * k] = decay * old[j][k] + wnew * st[lane + 64 * k];
+        if (pr.has_bias && lane == 0 && cb == 0) row[d] = oldb[j];
         __builtin_amdgcn_wave_barrier();
     }
 }
@@ -744,9 +745,10 @@ __global__ __launch_bounds__(256) void corr3_assemble_kernel(const CorrTable tab
     const CorrProb &pr = tab.p[corr_locate(tab, blockIdx.x)];
     const int C = pr.C, d = 9 * C, dF = d + pr.has_bias;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int rt = C3_ARW * (blockIdx.x - pr.blk_start) + w;         // row triple: the same for the whole wavefront
+    // row triple and block of 64 partner channels: the same for the whole wavefront
+    const int cbs = (C + 63) / 64, unit = C3_ARW * (blockIdx.x - pr.blk_start) + w, rt = unit / cbs, cb = unit - rt * cbs;
     const int c = rt / 3, i = rt - 3 * c;
-    if (c > C || (c == C && (i > 0 || !pr.has_bias))) return;
+    if (c > C || (c == C && (i > 0 || cb > 0 || !pr.has_bias))) return;
     if (c == C) {
         const float *Ts = pr.Fs + (long)C3_LAGS * C * C, *Bv = pr.Bs + (long)C3_BQ * C * C;
         const float wnew = (1.0f - pr.decay) * pr.scale;
@@ -766,9 +768,9 @@ __global__ __launch_bounds__(256) void corr3_assemble_kernel(const CorrTable tab
         }
         return;
     }
-    if (i == 0) corr3_assemble_rows<0>(pr, c, lane, strip[w]);
-    else if (i == 1) corr3_assemble_rows<1>(pr, c, lane, strip[w]);
-    else corr3_assemble_rows<2>(pr, c, lane, strip[w]);
+    if (i == 0) corr3_assemble_rows<0>(pr, c, cb, lane, strip[w]);
+    else if (i == 1) corr3_assemble_rows<1>(pr, c, cb, lane, strip[w]);
+    else corr3_assemble_rows<2>(pr, c, cb, lane, strip[w]);
 }
 
 }  // namespace kfac
