@@ -69,6 +69,7 @@ struct GemmJob {
     const float *D = nullptr;    // kSubFrom
     long ldd = 0;
     bool wide_tiles = false;     // kStore: take the split-bf16 kernel whatever the depth and tile fill
+    bool direct = false;         // take the 64-wide tiles of the latency-bound products
     // gemm_split_products only: K in kslices slices of kper rows (a multiple of 16), slice i into C + i cstride; abytes:
     // from A to the end of its buffer (rows of A may overlap: M > lda), what lies past it counts as zero
     int kslices = 1, kper = 0;
@@ -77,12 +78,11 @@ struct GemmJob {
 
 enum GemmMode : int {
     kStore = 0,          // C[m][n] = acc
-    kStoreT = 1,         // C[n][m] = acc   (ldc is the pitch of the transposed matrix)
     kSubLowerSkip = 2,   // C[m][n] -= acc for n <= m, m and n outside [p0, p1)
     kStoreDiv = 3,       // C[m][n] = acc / (rv[m] * cv[n] + gamma)   (the division of Eq. 13)
     kSubRect = 4,        // C[m][n] -= acc for n <= m + doff, n outside [p0, p1)   (a rectangle of a lower triangle)
     kAddRect = 5,        // the same entries, C[m][n] += acc
-    kSubFrom = 6         // C[m][n] = D[m][n] - acc   (D a second matrix, row pitch ldd; block-tile kernel only)
+    kSubFrom = 6         // C[m][n] = D[m][n] - acc   (D a second matrix, row pitch ldd; block-tile kernels only)
 };
 
 // Symmetric eigen-decomposition M = Q diag(v) Q^T (eigenvectors in the columns of Q, order not sorted).

@@ -3,7 +3,7 @@
 // Eq. 12 of the DP-KFAC paper): U^T = grad^T G_inv, then P = (U^T)^T A_inv, both
 // with row-major outputs, no operand is ever read with a strided K; and for the
 // panel products and rank-k updates of the blocked inversion.  Wide products
-// go to the wave-unit kernel (gemm_wave.hpp), the rest to the block-tile kernel
+// go to the wave-unit kernel (gemm_wave.hpp), the rest to the two block-tile kernels
 // below.
 #include <type_traits>
 #include "gemm_wave.hpp"
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(T::NT) void gemm_tn_kernel(const GemmTable tab)
     // issued D stages earlier: the short, latency-bound products (a few workgroups per matrix, each walking
     // the whole depth) live on that.  Set r holds stage t with t mod D = r; it is free again once that stage
     // has been written to LDS.  The large tiles keep one set (registers).
-    constexpr int D = T::BM <= 64 ? 3 : 1;
+    constexpr int D = T::BM <= 32 ? 3 : 1;
     const long ktiles = (pr.K + T::KT - 1) / T::KT;
     auto k_loop = [&](auto vec_a, auto vec_b) {
         constexpr bool VA = decltype(vec_a)::value, VB = decltype(vec_b)::value;
@@ -141,8 +141,6 @@ __global__ __launch_bounds__(T::NT) void gemm_tn_kernel(const GemmTable tab)
                 const float val = acc[ti][tj][v];
                 if (pr.mode == kStore) {
                     pr.C[(long)m * pr.ldc + n] = val;
-                } else if (pr.mode == kStoreT) {
-                    pr.C[(long)n * pr.ldc + m] = val;
                 } else if (pr.mode == kStoreDiv) {
                     pr.C[(long)m * pr.ldc + n] = val / (pr.rv[m] * pr.cv[n] + pr.gamma);
                 } else if (pr.mode == kSubFrom) {
@@ -156,6 +154,158 @@ __global__ __launch_bounds__(T::NT) void gemm_tn_kernel(const GemmTable tab)
                 }
             }
         }
+}
+
+// 64 x 64 tiles of the same products for the launches that are bound by the latency of one tile: a few workgroups per
+// matrix, each walking the whole depth (the short products of the blocked inversion's chain, small preconditioning
+// products).  The four wavefronts split K (chunks of 16 in turn), every one computes the whole tile: a lane loads 16 bytes
+// of a row of either operand, which are one column each of four interleaved MFMA tiles, straight into the registers the
+// MFMA reads, two chunks ahead; no LDS and no barrier until the four parts are added in wavefront order.  At K = 256 a
+// tile takes 9 us where the staged form with all wavefronts on one K stage (16 stages, an LDS round trip and a barrier
+// each) took 21; the pieces of an operand past its edge feed outputs that are not stored.
+typedef float gmfloat4 __attribute__((ext_vector_type(4), aligned(4)));
+__global__ __launch_bounds__(256, 2) void gemm_direct_kernel(const GemmTable tab)
+{
+    __shared__ floatx4 lds[4 * 3 * 4 * 64];
+    int pi = 0, hi = tab.count - 1;
+    while (pi < hi) {
+        const int mid = (pi + hi + 1) >> 1;
+        if ((int)blockIdx.x >= tab.starts[mid]) pi = mid;
+        else hi = mid - 1;
+    }
+    const GemmProb &pr = tab.p[pi];
+    if (pr.gate && !(__int_as_float(pr.gate[0]) * __int_as_float(pr.gate[1]) > pr.gate_cond)) return;   // uniform
+    const int local = blockIdx.x - pr.blk_start;
+    int bi, bj;
+    if (pr.mode == kSubLowerSkip) {
+        tri_decode(local, bi, bj);
+    } else {
+        bi = local / pr.tn;
+        bj = local - bi * pr.tn;
+    }
+    const int m0 = bi * 64, n0 = bj * 64, M = pr.M, N = pr.N, K = pr.K;
+    const bool lower = pr.mode == kSubLowerSkip || pr.mode == kSubRect || pr.mode == kAddRect;
+    if (lower && (long)n0 > (long)min(m0 + 63, M - 1) + pr.doff) return;      // wholly above the line n = m + doff
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
+    typedef int gint4 __attribute__((ext_vector_type(4)));
+    // the host checked: below 2 GiB; rows past K are past the end and read as zero
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A), 0, (int)((long)K * pr.lda * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.B), 0, (int)((long)K * pr.ldb * 4), 0x00020000);
+    const unsigned pa = (unsigned)pr.lda * 4u, pb = (unsigned)pr.ldb * 4u;
+    // a lane whose four columns all lie past the edge reads the tile's first ones
+    const unsigned ao = (unsigned)(m0 + (m0 + 4 * lr < M ? 4 * lr : 0)) * 4u, bo = (unsigned)(n0 + (n0 + 4 * lr < N ? 4 * lr : 0)) * 4u;
+    floatx4 acc[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[i][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto load = [&](gint4 (&a)[4], gint4 (&b)[4], int k) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int kk = k + 4 * e + lk;
+            const unsigned ro = kk < K ? (unsigned)kk * pa + ao : 0x80000000u, so = kk < K ? (unsigned)kk * pb + bo : 0x80000000u;
+            a[e] = __builtin_bit_cast(gint4, __builtin_amdgcn_raw_buffer_load_b128(ra, ro, 0, 0));
+            b[e] = __builtin_bit_cast(gint4, __builtin_amdgcn_raw_buffer_load_b128(rb, so, 0, 0));
+        }
+    };
+    auto multiply = [&](const gint4 (&a)[4], const gint4 (&b)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__int_as_float(a[e][i]), __int_as_float(b[e][t]), acc[i][t], 0, 0, 0);
+    };
+    gint4 a0[4], b0[4], a1[4], b1[4];
+    load(a0, b0, 16 * w);
+    __builtin_amdgcn_sched_barrier(0);
+    load(a1, b1, 16 * w + 64);
+    __builtin_amdgcn_sched_barrier(0);
+    for (int k = 16 * w; k < K; k += 128) {
+        multiply(a0, b0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(a0, b0, k + 128);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(a1, b1);
+        __builtin_amdgcn_sched_barrier(0);
+        load(a1, b1, k + 192);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // the parts: wavefront t sums MFMA column tile t
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t != w) {
+            floatx4 *d = lds + ((t * 3 + (w < t ? w : w - 1)) * 4) * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i * 64] = acc[i][t];
+        }
+    __syncthreads();
+    floatx4 sum[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        floatx4 own = acc[i][0];
+#pragma unroll
+        for (int t = 1; t < 4; ++t)
+            if (t == w) own = acc[i][t];
+        sum[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) sum[i] += ww == w ? own : lds[((w * 3 + (ww < w ? ww : ww - 1)) * 4 + i) * 64 + lane];
+    }
+    __syncthreads();
+    constexpr int PO = 68;
+    float *o = reinterpret_cast<float *>(lds);          // the tile: row 4 (4 lk + v) + i, column 4 lr + w
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[(4 * (4 * lk + v) + i) * PO + 4 * lr + w] = sum[i][v];
+    __syncthreads();
+    // 16 lanes along a row, four columns each: all old values before the first store
+    const int mr = tid >> 4, c = 4 * (tid & 15), n = n0 + c;
+    floatx4 old[4];
+    const bool reads = lower || pr.mode == kSubFrom;
+    const float *from = pr.mode == kSubFrom ? pr.D : pr.C;
+    const long ldf = pr.mode == kSubFrom ? pr.ldd : pr.ldc;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + mr + 16 * r;
+        old[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (reads && m < M && n < N) {
+            const float *src = from + (long)m * ldf + n;
+            if (n + 3 < N) old[r] = *reinterpret_cast<const gmfloat4 *>(src);
+            else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (n + e < N) old[r][e] = src[e];
+            }
+        }
+    }
+    const bool rows_skip = pr.mode == kSubLowerSkip;
+    const float sign = pr.mode == kStore || pr.mode == kStoreDiv || pr.mode == kAddRect ? 1.f : -1.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + mr + 16 * r;
+        if (m >= M || (rows_skip && m >= pr.p0 && m < pr.p1)) continue;
+        floatx4 val = *reinterpret_cast<const floatx4 *>(o + (mr + 16 * r) * PO + c);
+        if (pr.mode == kStoreDiv) {
+            const float rv = pr.rv[m];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) val[e] = val[e] / (rv * pr.cv[min(n + e, N - 1)] + pr.gamma);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[e] = __builtin_fmaf(sign, val[e], old[r][e]);
+        const long last = lower ? min((long)N - 1, (long)m + pr.doff) : N - 1;
+        float *dst = pr.C + (long)m * pr.ldc + n;
+        const bool band = lower && n + 3 >= pr.p0 && n < pr.p1;       // columns of the pivot band are left alone
+        if (n + 3 <= last && !band) *reinterpret_cast<gmfloat4 *>(dst) = val;
+        else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e <= last && !(lower && n + e >= pr.p0 && n + e < pr.p1)) dst[e] = val[e];
+        }
+    }
 }
 
 namespace {
@@ -181,10 +331,8 @@ int choose_bm(int M, int N, bool square_lower)
     return best;
 }
 
-template <class T>
-hipError_t launch_one(const GemmTable &tab, int blocks, hipStream_t s)
+hipError_t launch_done(const GemmTable &tab)
 {
-    KFAC_LAUNCH(KFAC_K_GEMM, s, (gemm_tn_kernel<T>), dim3(blocks), dim3(T::NT), 0, tab);
     double flops = 0.0;
     for (int k = 0; k < tab.count; ++k) {
         const GemmProb &p = tab.p[k];
@@ -195,6 +343,19 @@ hipError_t launch_one(const GemmTable &tab, int blocks, hipStream_t s)
     }
     timing_work(flops, flops);
     return hipGetLastError();
+}
+
+template <class T>
+hipError_t launch_one(const GemmTable &tab, int blocks, hipStream_t s)
+{
+    KFAC_LAUNCH(KFAC_K_GEMM, s, (gemm_tn_kernel<T>), dim3(blocks), dim3(T::NT), 0, tab);
+    return launch_done(tab);
+}
+
+hipError_t launch_direct(const GemmTable &tab, int blocks, hipStream_t s)
+{
+    KFAC_LAUNCH(KFAC_K_GEMM, s, gemm_direct_kernel, dim3(blocks), dim3(256), 0, tab);
+    return launch_done(tab);
 }
 
 }  // namespace
@@ -225,10 +386,10 @@ double gemm_job_flops(const GemmJob &j)
 // update qualifies only when its untouched band starts and ends on macro-tile boundaries.
 bool wave_gemm_eligible(const GemmJob &j)
 {
-    if (!tuning().use_wave_gemm || j.mode == kStoreT || j.mode == kStoreDiv || j.mode == kSubRect || j.mode == kAddRect ||
+    if (!tuning().use_wave_gemm || j.mode == kStoreDiv || j.mode == kSubRect || j.mode == kAddRect ||
         j.mode == kSubFrom || j.gate)
         return false;
-    if (j.M < 100 || j.N < 100 || j.K < 16) return false;
+    if (j.direct || j.M < 100 || j.N < 100 || j.K < 16) return false;
     if ((long)j.K * j.lda * 4 > 0x7fffffffl || (long)j.K * j.ldb * 4 > 0x7fffffffl) return false;
     if (((uintptr_t)j.A) % 4 || ((uintptr_t)j.B) % 4) return false;
     if (j.mode == kSubLowerSkip)
@@ -293,7 +454,7 @@ bool split_gemm_eligible(const GemmJob &j, bool wide)
     if (!tuning().use_split_gemm || (j.mode != kStore && j.mode != kSubLowerSkip && j.mode != kSubRect && j.mode != kAddRect))
         return false;
     const long min_m = wide && j.mode == kStore ? tuning().split_gemm_min_m : 192;
-    if (j.M < min_m || j.N < 64 || j.K < 16) return false;
+    if (j.direct || j.M < min_m || j.N < 64 || j.K < 16) return false;
     // a product of a tile or two is bound by the latency of one tile's K loop and read-modify-write (55 us at
     // K = 256): the 64-wide tiles of the block-tile kernel spread it over many CUs and finish in 10-15 us
     if ((long)j.M * j.N < 4l * S_BM * S_BN) return false;
@@ -564,7 +725,7 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             cfg[i] = -1;
             wave.push_back(i);
         } else {
-            cfg[i] = choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
+            cfg[i] = jobs[i].direct ? 2 : choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
         }
     }
     // A wave-unit workgroup owns 144 x 288 of a product and walks its whole depth at 110 us per 512 rows whatever else
@@ -600,7 +761,7 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             for (int c = 1; c < 4; ++c)
                 if (cost[c] < cost[best]) best = c;
             for (int i = 0; i < n; ++i)
-                if (cfg[i] >= 0 && jobs[i].mode != kSubLowerSkip) cfg[i] = best;
+                if (cfg[i] >= 0 && jobs[i].mode != kSubLowerSkip && !jobs[i].direct) cfg[i] = best;
         }
     }
     if (!tuning().gemm_bm) {
@@ -617,6 +778,9 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             for (int i = 0; i < n; ++i)
                 if (cfg[i] >= 0 && jobs[i].mode != kSubLowerSkip && kBms[cfg[i]] > 64) cfg[i] = 2;
     }
+    // 32-bit offsets in the 64-wide kernel: operands of 2 GiB and more take the 128-wide tiles
+    for (int i = 0; i < n; ++i)
+        if (cfg[i] == 2 && ((long)jobs[i].K * jobs[i].lda * 4 > 0x7fffffffl || (long)jobs[i].K * jobs[i].ldb * 4 > 0x7fffffffl)) cfg[i] = 0;
     if (!split.empty()) {
         std::stable_sort(split.begin(), split.end(), [&](int a, int b) { return jobs[a].K > jobs[b].K; });
         hipError_t e = split_gemm_launch(jobs, split, s);
@@ -638,7 +802,7 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             switch (c) {
                 case 0: e = launch_one<Tile<4, 2>>(tab, blocks, s); break;
                 case 1: e = launch_one<Tile<3, 3>>(tab, blocks, s); break;
-                case 2: e = launch_one<Tile<2, 2>>(tab, blocks, s); break;
+                case 2: e = launch_direct(tab, blocks, s); break;
                 default: e = launch_one<Tile<1, 2>>(tab, blocks, s); break;
             }
             tab.count = 0;

@@ -51,7 +51,8 @@ struct InvProb {
     float damping;
     int blk_start;
     const float *dptr;   // device-side damping (overrides `damping` when not null)
-    int *gate;           // null, or the two gate words of the blocked sweep, cleared with info
+    int fold = 0;        // rows of the last pivot block whose update the finishing pass applies (panels Vt, Wt)
+    int *gate;           // null, or the two pairs of gate words of the blocked sweep, cleared with info
 };
 
 struct InvTable {
@@ -60,22 +61,59 @@ struct InvTable {
     InvProb p[kMaxProblems];
 };
 
-// W(lower) = M(lower) + damping I
+constexpr int kFoldRows = 4;   // a last pivot block of up to this many rows is applied by the finishing pass
+
+// rows of a matrix of any order, four elements at a time
+__device__ __forceinline__ floatx4 load_row4(const float *p, int have)
+{
+    floatx4 v = {0.f, 0.f, 0.f, 0.f};
+    if (have >= 4) v = *reinterpret_cast<const ufloatx4 *>(p);
+    else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < have) v[e] = p[e];
+    }
+    return v;
+}
+__device__ __forceinline__ void store_row4(float *p, int have, const floatx4 &v)
+{
+    if (have >= 4) *reinterpret_cast<ufloatx4 *>(p) = v;
+    else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < have) p[e] = v[e];
+    }
+}
+
+// W = M + damping I on and below the diagonal.  A workgroup per 64 x 64 tile, 16 bytes per lane (one element per lane and a
+// division for its place: 155 us on the large factors of the ResNet-50 shape).
 __global__ __launch_bounds__(256) void sweep_init_kernel(const InvTable tab)
 {
     int pi = 0;
     while (pi + 1 < tab.count && (int)blockIdx.x >= tab.p[pi + 1].blk_start) ++pi;
     const InvProb &pr = tab.p[pi];
     const int local = blockIdx.x - pr.blk_start;
-    const long total = (long)pr.n * pr.n;
     const float damping = pr.dptr ? *pr.dptr : pr.damping;
     if (local == 0 && threadIdx.x == 0) {
         *pr.info = 0;
-        if (pr.gate) { pr.gate[0] = 0; pr.gate[1] = 0; }
+        if (pr.gate) { pr.gate[0] = 0; pr.gate[1] = 0; pr.gate[2] = 0; pr.gate[3] = 0; }
     }
-    for (long e = (long)local * 4096 + threadIdx.x; e < lmin(total, (long)(local + 1) * 4096); e += 256) {
-        const int i = (int)(e / pr.n), j = (int)(e - (long)i * pr.n);
-        if (j <= i) pr.W[e] = pr.M[e] + (i == j ? damping : 0.f);
+    int bi, bj;
+    tri_decode(local, bi, bj);
+    const long n = pr.n;
+    const int j = 64 * bj + 4 * (threadIdx.x & 15), i0 = 64 * bi + (threadIdx.x >> 4);
+    floatx4 v[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = min(i0 + 16 * r, pr.n - 1);
+        v[r] = load_row4(pr.M + i * n + j, i - j + 1);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + 16 * r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[r][e] += i == j + e ? damping : 0.f;
+        if (i < pr.n) store_row4(pr.W + i * n + j, i - j + 1, v[r]);
     }
 }
 
@@ -281,47 +319,79 @@ __global__ __launch_bounds__(256) void blk_scatter_kernel(const BlkTable tab)
     }
 }
 
-// out = -W mirrored to both triangles (in place).  One workgroup per 32 x 32 tile of the lower
-// triangle; the mirror image goes through LDS so that both stores are along rows.
+// out = -W mirrored to both triangles (in place).  One workgroup per 64 x 64 tile of the lower triangle; the mirror image
+// goes through LDS so that both stores are along rows, 16 bytes per lane.  Where the last pivot block has at most four
+// rows (orders 256 k + 1: a bias column behind 256 k features), its update of the rows before it is applied here: a pass
+// over the matrix of its own cost as much as this one.
 __global__ __launch_bounds__(256) void sweep_finish_kernel(const InvTable tab)
 {
-    __shared__ float t[32][33];
+    __shared__ float t[64][65];
     int pi = 0;
     while (pi + 1 < tab.count && (int)blockIdx.x >= tab.p[pi + 1].blk_start) ++pi;
     const InvProb &pr = tab.p[pi];
     int bi, bj;
     tri_decode(blockIdx.x - pr.blk_start, bi, bj);
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     const long n = pr.n;
-    const int i0 = bi * 32, j0 = bj * 32;
+    const int tx = 4 * (threadIdx.x & 15), ty = threadIdx.x >> 4;
+    const int i0 = 64 * bi, j0 = 64 * bj, j = j0 + tx;
+    floatx4 v[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int i = i0 + ty + 8 * r, j = j0 + tx;
-        float v = 0.f;
-        if (i < pr.n && j <= i) {
-            v = -pr.W[i * n + j];
-            pr.W[i * n + j] = v;
+        const int i = min(i0 + ty + 16 * r, pr.n - 1);
+        v[r] = load_row4(pr.W + i * n + j, i - j + 1);
+    }
+    const int p0 = pr.n - pr.fold;
+    for (int k = 0; k < pr.fold; ++k) {
+        const floatx4 vj = load_row4(pr.Vt + (long)k * pr.ldv + j, p0 - j);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + ty + 16 * r;
+            const float wi = i < p0 ? pr.Wt[(long)k * pr.ldv + i] : 0.f;
+            if (i < p0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[r][e] = __builtin_fmaf(-wi, vj[e], v[r][e]);
+            }
         }
-        t[ty + 8 * r][tx] = v;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = i0 + ty + 16 * r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            v[r][e] = -v[r][e];
+            t[ty + 16 * r][tx + e] = v[r][e];
+        }
+        if (i < pr.n) store_row4(pr.W + i * n + j, i - j + 1, v[r]);
     }
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        // element (j, i) of the upper triangle, j from this tile's columns, i from its rows
-        const int j = j0 + ty + 8 * r, i = i0 + tx;
-        if (i < pr.n && j < i) pr.W[j * n + i] = t[tx][ty + 8 * r];
+        // elements (a, b .. b + 3) of the upper triangle, a from this tile's columns, b from its rows
+        const int la = ty + 16 * r, a = j0 + la, b = i0 + tx;
+        if (a >= pr.n || b >= pr.n) continue;
+        floatx4 m;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) m[e] = t[tx + e][la];
+        float *dst = pr.W + a * n + b;
+        if (b > a && b + 3 < pr.n) *reinterpret_cast<ufloatx4 *>(dst) = m;
+        else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (b + e > a && b + e < pr.n) dst[e] = m[e];
+        }
     }
 }
 
 namespace {
 bool takes_fused(int n) { return n <= tuning().invert_fused_max_n; }
 size_t fused_ws_floats(int n) { return 4 * (size_t)NB * NB + 2 * (size_t)NB * ((n + 3) / 4 * 4) + 16; }
-// large matrices: two sets of V, W panels, P, the workspace of the nested pivot-block inversion, its status word
+// large matrices: two sets of V, W panels, of the pivot block and of its inverse, W and the residual of the next pivot
+// block's columns, the workspace of the nested pivot-block inversion, its status and gate words
 size_t job_ws_floats(int n)
 {
     if (takes_fused(n)) return fused_ws_floats(n);
     const size_t PB = (size_t)outer_block();
-    return 5 * PB * ((n + 3) / 4 * 4) + 2 * PB * PB + fused_ws_floats((int)PB) + 64;
+    return 5 * PB * ((n + 3) / 4 * 4) + 6 * PB * PB + fused_ws_floats((int)PB) + 64;
 }
 // the three flags at the end of a matrix's one-launch-per-step workspace: gate of either step parity, sticky flag
 int *fused_gate_ptr(float *ws, int n)
@@ -434,14 +504,16 @@ hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, cons
     return hipSuccess;
 }
 // Two-level blocked sweep of the matrices listed in `idx` (sorted by order, largest first).  An outer step K is
-// cut into a *chain* (inverse of pivot block K, gather of the old panel, panel product, scatter: short dependent
-// launches) and a *bulk* rank-PB update of everything outside the pivot rows and columns.  With look-ahead the
-// chain of step K+1 runs on a second stream beside the bulk update of step K: the bulk update then leaves out
-// the rows and columns of pivot block K+1 as well, and the chain of step K+1 first applies update K to just
-// that band (two rectangular products), so that its pivot block and panel are ready without waiting for the
-// bulk.  Panels are double buffered (the bulk of step K reads panels K while the chain writes panels K+1).
+// cut into a *chain* of short dependent launches (inverse of pivot block K; its products with the columns of the next
+// pivot block, and update K of that block, after which its inversion can start), the *panel* (gather of the old panel,
+// product with the inverse, scatter) and a *bulk* rank-PB update of everything outside the pivot rows and columns.  With
+// look-ahead the chain runs on a stream of its own beside panel and bulk: the bulk update leaves out the rows and columns
+// of pivot block K+1, to which update K is applied first (two rectangular products), so that the old panel of
+// step K+1 is ready without waiting for the bulk.  Panels, pivot blocks and their inverses are double buffered (the bulk of
+// step K reads panels K while the gather writes panels K+1, the panel of step K reads inverse K while the chain writes the
+// next one).
 struct BlockedRun {
-    struct Big { float *Vt[2], *Wt[2], *Rt, *S, *P, *nws; int *ninfo; int ldv; };
+    struct Big { float *Vt[2], *Wt[2], *Rt, *S[2], *P[2], *Wn, *Rn, *nws; int *ninfo; int ldv; };
     bool refine = false;
     const InvertJob *jobs = nullptr;
     std::vector<int> idx;
@@ -461,10 +533,16 @@ struct BlockedRun {
         while (a < total && jobs[idx[a]].n > st * PB) ++a;
         return a;
     }
+    // whether step st is the last of matrix k and its pivot block small enough to be applied by the finishing pass
+    bool folds(int k, int st) const { return jobs[idx[k]].n - st * PB <= kFoldRows && st > 0; }
+    // of step st: status of the nested inversion, gate words
+    int *ninfo(int k, int st) const { return big[k].ninfo + (st & 1); }
+    int *gate(int k, int st) const { return big[k].ninfo + 2 + 2 * (st & 1); }
     hipError_t start(hipStream_t s);
-    hipError_t look(int st, int part, hipStream_t s);   // update st applied to the band of pivot block st + 1
-    hipError_t chain(int st, hipStream_t sn, hipStream_t sc, hipEvent_t before_gather, hipEvent_t ev_nest,
-                     hipEvent_t ev_cond);
+    hipError_t nest(int st, hipStream_t s);        // inverse of pivot block st
+    hipError_t next(int st, hipStream_t s);        // update st applied to pivot block st + 1
+    hipError_t panel(int st, hipStream_t s, hipEvent_t cond_done);   // product, refinement, scatter
+    hipError_t band(int st, hipStream_t s);        // update st applied to the rest of the band of pivot block st + 1
     hipError_t bulk(int st, bool skip_next, hipStream_t s);
     hipError_t finish(hipStream_t s);
     hipError_t copy_kernel(int what, int st, int act, hipStream_t s);    // 0 gather, 1 scatter, 2 condition test
@@ -487,9 +565,10 @@ hipError_t BlockedRun::start(hipStream_t s)
         b.Vt[1] = ws + 2 * panel;
         b.Wt[1] = ws + 3 * panel;
         b.Rt = ws + 4 * panel;
-        b.S = ws + 5 * panel;
-        b.P = b.S + (size_t)PB * PB;
-        b.nws = b.P + (size_t)PB * PB;
+        const size_t blk = (size_t)PB * PB;
+        float *at = ws + 5 * panel;
+        for (float **p : {&b.S[0], &b.S[1], &b.P[0], &b.P[1], &b.Wn, &b.Rn}) { *p = at; at += blk; }
+        b.nws = at;
         b.ninfo = reinterpret_cast<int *>(b.nws + fused_ws_floats(PB));
     }
     // W = M + damping I (lower), info = 0
@@ -503,9 +582,10 @@ hipError_t BlockedRun::start(hipStream_t s)
             InvProb &p = tab.p[k];
             p.M = j.M; p.W = j.Minv; p.info = j.info; p.n = j.n; p.damping = j.damping; p.dptr = j.damping_dev;
             p.ldv = big[g0 + k].ldv; p.P = nullptr; p.Vt = nullptr; p.Wt = nullptr;
-            p.gate = big[g0 + k].ninfo + 1;
+            p.gate = gate(g0 + k, 0);
             p.blk_start = blocks;
-            blocks += (int)(((long)j.n * j.n + 4095) / 4096);
+            const int nb64 = (j.n + 63) / 64;
+            blocks += nb64 * (nb64 + 1) / 2;
         }
         KFAC_LAUNCH(KFAC_K_INV_INIT, s, sweep_init_kernel, dim3(blocks), dim3(256), 0, tab);
         hipError_t e = hipGetLastError();
@@ -526,11 +606,12 @@ hipError_t BlockedRun::copy_kernel(int what, int st, int act, hipStream_t s)
         for (int k = 0; k < tab.count; ++k) {
             const InvertJob &j = jobs[idx[g0 + k]];
             BlkProb &p = tab.p[k];
-            p.W = j.Minv; p.Vt = big[g0 + k].Vt[st & 1]; p.Wt = big[g0 + k].Wt[st & 1]; p.P = big[g0 + k].P;
-            p.S = (refine && !scatter) ? big[g0 + k].S : nullptr;   // the condition test reads the matrix itself
-            p.gate = refine ? big[g0 + k].ninfo + 1 : nullptr;
+            p.W = j.Minv; p.Vt = big[g0 + k].Vt[st & 1]; p.Wt = big[g0 + k].Wt[st & 1];
+            p.P = big[g0 + k].P[st & 1];
+            p.S = (refine && !scatter) ? big[g0 + k].S[st & 1] : nullptr;   // the condition test reads the matrix itself
+            p.gate = refine ? gate(g0 + k, st) : nullptr;
             p.gate_cond = (float)tuning().invert_refine_cond;
-            p.info = j.info; p.ninfo = big[g0 + k].ninfo;
+            p.info = j.info; p.ninfo = ninfo(g0 + k, st);
             p.n = j.n; p.ldv = big[g0 + k].ldv; p.p0 = p0; p.bs = std::min(PB, j.n - p0); p.pb = PB;
             p.blk_start = blocks;
             blocks += ((j.n + 31) / 32) * ((p.bs + 31) / 32);
@@ -553,11 +634,10 @@ hipError_t BlockedRun::copy_kernel(int what, int st, int act, hipStream_t s)
     return hipSuccess;
 }
 
-// Update st restricted to the band of pivot block st + 1, leaving out the columns of pivot block st, which the
-// scatter of step st owns.  part 0: the diagonal block of the band alone (all the nested inversion of step st + 1
-// needs); part 1: the rest, i.e. the rows q0..q1 left of pivot block st and the columns q0..q1 below the diagonal
-// block (what the gather of step st + 1 needs as well).
-hipError_t BlockedRun::look(int st, int part, hipStream_t s)
+// Update st restricted to the band of pivot block st + 1 without its diagonal block (next), leaving out the columns of
+// pivot block st, which the scatter of step st owns: the rows q0..q1 left of pivot block st and the columns q0..q1 below the
+// diagonal block, what the gather of step st + 1 needs.
+hipError_t BlockedRun::band(int st, hipStream_t s)
 {
     const int p0 = st * PB, q0 = p0 + PB;
     const int act = active(st + 1);
@@ -567,14 +647,6 @@ hipError_t BlockedRun::look(int st, int part, hipStream_t s)
         const int q1 = std::min(q0 + PB, j.n);
         const Big &b = big[k];
         const float *Wt = b.Wt[st & 1], *Vt = b.Vt[st & 1];
-        if (part == 0) {
-            GemmJob d{};   // rows and columns q0..q1, on and below the diagonal
-            d.A = Wt + q0; d.B = Vt + q0; d.C = j.Minv + (size_t)q0 * j.n + q0;
-            d.M = q1 - q0; d.N = q1 - q0; d.K = PB; d.lda = b.ldv; d.ldb = b.ldv; d.ldc = j.n;
-            d.mode = kSubRect; d.p0 = d.p1 = 0; d.doff = 0;
-            gj.push_back(d);
-            continue;
-        }
         if (p0 > 0) {
             GemmJob r{};   // rows q0..q1, columns left of pivot block st
             r.A = Wt + q0; r.B = Vt; r.C = j.Minv + (size_t)q0 * j.n;
@@ -593,18 +665,10 @@ hipError_t BlockedRun::look(int st, int part, hipStream_t s)
     return gj.empty() ? hipSuccess : gemm_launch(gj.data(), (int)gj.size(), s);
 }
 
-// The chain of step st.  The nested inversion of the pivot block and the test of its condition number go to
-// stream sn, the gather, the panel product, its refinement and the scatter to stream sc: the gather needs the band
-// of the pivot block (before_gather: null, or the event after which it is up to date) but not the inverse, so
-// with two streams it runs beside the nested inversion, the longest link of the chain; ev_nest and ev_cond (used
-// when the streams differ) order the panel product after the inversion and the refinement after the test.
-hipError_t BlockedRun::chain(int st, hipStream_t sn, hipStream_t sc, hipEvent_t before_gather, hipEvent_t ev_nest,
-                             hipEvent_t ev_cond)
+// Inverse of the pivot blocks of step st (in their current, updated state) -> P.
+hipError_t BlockedRun::nest(int st, hipStream_t s)
 {
-    const bool two = sn != sc;
-    const int p0 = st * PB;
-    const int act = active(st);
-    // 1. inverse of the pivot blocks (in their current, updated state) -> P
+    const int p0 = st * PB, act = active(st);
     nested.assign(act, InvertJob());
     nidx.resize(act);
     noffs.resize(act);
@@ -612,10 +676,10 @@ hipError_t BlockedRun::chain(int st, hipStream_t sn, hipStream_t sc, hipEvent_t 
         const InvertJob &j = jobs[idx[k]];
         InvertJob &q = nested[k];
         q.M = j.Minv + (size_t)p0 * j.n + p0;
-        q.Minv = big[k].P;
+        q.Minv = big[k].P[st & 1];
         q.n = std::min(PB, j.n - p0);
         q.damping = 0.f;
-        q.info = big[k].ninfo;
+        q.info = ninfo(k, st);
         q.ldm = j.n;
         q.ldo = PB;
         nidx[k] = k;
@@ -623,52 +687,83 @@ hipError_t BlockedRun::chain(int st, hipStream_t sn, hipStream_t sc, hipEvent_t 
     }
     // nested problems are grouped by order (all PB except possibly the last block of a matrix)
     std::stable_sort(nidx.begin(), nidx.end(), [&](int a, int b) { return nested[a].n > nested[b].n; });
-    hipError_t e = fused_launch(nested.data(), nidx, noffs, work, dtab, sn);
-    if (e != hipSuccess) return e;
-    if (two && hipEventRecord(ev_nest, sn) != hipSuccess) return hipErrorUnknown;
-    if (refine) {
-        e = copy_kernel(2, st, act, sn);
-        if (e != hipSuccess) return e;
-        if (two && hipEventRecord(ev_cond, sn) != hipSuccess) return hipErrorUnknown;
+    return fused_launch(nested.data(), nidx, noffs, work, dtab, s);
+}
+
+// Update st applied to the diagonal block of the next pivot block, all that its inversion needs: W for its columns alone
+// (256 of up to thousands), refined under the same gate as the panel, and the product with V.  Four launches of
+// 64-wide tiles, 40 us with the gates shut, in place of waiting for the whole panel (product, refinement, scatter: 100 to
+// 150 us beside the bulk update).
+hipError_t BlockedRun::next(int st, hipStream_t s)
+{
+    const int q0 = (st + 1) * PB, act = active(st + 1);
+    hipError_t e = hipSuccess;
+    for (int what = refine ? 0 : 2; what < 4 && e == hipSuccess; ++what) {
+        // 0 W = P V (1, 2 behind it: R = V - S W, W += P R), 3 block -= W^T V; without the refinement 2 is W = P V
+        const int step = !refine && what == 2 ? 0 : what;
+        gj.assign(act, GemmJob());
+        for (int k = 0; k < act; ++k) {
+            const InvertJob &j = jobs[idx[k]];
+            const Big &b = big[k];
+            const int bn = std::min(PB, j.n - q0);
+            const float *V = b.Vt[st & 1] + q0;
+            GemmJob &g = gj[k];
+            g.N = bn; g.M = step == 3 ? bn : PB; g.K = PB;
+            g.lda = PB; g.ldb = step == 0 || step == 3 ? b.ldv : PB; g.ldc = step == 3 ? j.n : PB;
+            g.A = step == 1 ? b.S[st & 1] : step == 3 ? b.Wn : b.P[st & 1];
+            g.B = step == 1 ? b.Wn : step == 2 ? b.Rn : V;
+            g.C = step == 1 ? b.Rn : step == 3 ? j.Minv + (size_t)q0 * j.n + q0 : b.Wn;
+            g.mode = step == 0 ? kStore : step == 1 ? kSubFrom : step == 2 ? kAddRect : kSubRect;
+            g.doff = step == 3 ? 0 : 1l << 30;
+            if (step == 1) { g.D = V; g.ldd = b.ldv; }
+            if (step == 1 || step == 2) {
+                g.gate = gate(k, st);
+                g.gate_cond = (float)tuning().invert_refine_cond;
+            }
+            g.direct = true;
+        }
+        e = gemm_launch(gj.data(), act, s);
     }
-    hipStream_t s = sc;
-    if (before_gather && hipStreamWaitEvent(s, before_gather, 0) != hipSuccess) return hipErrorUnknown;
-    // 2. gather V, 3. W^T = P V^T, 4. scatter
-    e = copy_kernel(0, st, act, s);
-    if (e != hipSuccess) return e;
-    if (two && hipStreamWaitEvent(s, ev_nest, 0) != hipSuccess) return hipErrorUnknown;
+    return e;
+}
+
+// W^T = P V^T, its refinement, the new panel back in place.  cond_done: null, or the event behind the condition test.
+hipError_t BlockedRun::panel(int st, hipStream_t s, hipEvent_t cond_done)
+{
+    const int p0 = st * PB;
+    const int act = active(st);
     gj.assign(act, GemmJob());
     for (int k = 0; k < act; ++k) {
         const InvertJob &j = jobs[idx[k]];
         const int bs = std::min(PB, j.n - p0);
         GemmJob &a = gj[k];
-        a.A = big[k].P; a.B = big[k].Vt[st & 1]; a.C = big[k].Wt[st & 1];
+        a.A = big[k].P[st & 1]; a.B = big[k].Vt[st & 1]; a.C = big[k].Wt[st & 1];
         a.M = bs; a.N = j.n; a.K = bs; a.lda = PB; a.ldb = big[k].ldv; a.ldc = big[k].ldv;
         a.mode = kStore; a.p0 = a.p1 = 0;
         a.wide_tiles = tuning().invert_panel_split != 0;
     }
-    e = gemm_launch(gj.data(), act, s);
+    hipError_t e = gemm_launch(gj.data(), act, s);
     if (e != hipSuccess) return e;
+    if (cond_done && hipStreamWaitEvent(s, cond_done, 0) != hipSuccess) return hipErrorUnknown;
     if (refine) {
         // One step of iterative refinement of the panel product.  W = V P with an explicitly inverted pivot block
         // S carries an error of eps |V| |P|, which for an ill-conditioned S is far above eps |W|; the residual
         // V - W S is made of small terms and comes out accurately, and W += (V - W S) P removes most of that error
         // (the inverse of a factor with condition number 1e5 goes from useless to the accuracy of an fp32
         // Cholesky inverse).  K-major: R^T = V^T - S W^T, W^T += P R^T.
-        if (two && hipStreamWaitEvent(s, ev_cond, 0) != hipSuccess) return hipErrorUnknown;
         for (int pass = 0; pass < 2; ++pass) {
             for (int k = 0; k < act; ++k) {
                 const InvertJob &j = jobs[idx[k]];
                 const int bs = std::min(PB, j.n - p0);
                 GemmJob &a = gj[k];
                 a = GemmJob();
-                a.A = pass == 0 ? big[k].S : big[k].P;
+                a.A = pass == 0 ? big[k].S[st & 1] : big[k].P[st & 1];
                 a.B = pass == 0 ? big[k].Wt[st & 1] : big[k].Rt;
                 a.C = pass == 0 ? big[k].Rt : big[k].Wt[st & 1];
                 a.M = bs; a.N = j.n; a.K = bs; a.lda = PB; a.ldb = big[k].ldv; a.ldc = big[k].ldv;
                 a.mode = pass == 0 ? kSubFrom : kAddRect; a.p0 = a.p1 = 0; a.doff = 1l << 30;
                 if (pass == 0) { a.D = big[k].Vt[st & 1]; a.ldd = big[k].ldv; }
-                a.gate = big[k].ninfo + 1;
+                a.gate = gate(k, st);
                 a.gate_cond = (float)tuning().invert_refine_cond;
             }
             e = gemm_launch(gj.data(), act, s);
@@ -688,6 +783,7 @@ hipError_t BlockedRun::bulk(int st, bool skip_next, hipStream_t s)
         const int bs = std::min(PB, j.n - p0);
         const int p1 = std::min(j.n, p0 + bs + (skip_next ? PB : 0));
         if (p1 - p0 >= j.n) continue;      // nothing outside the bands
+        if (folds(k, st)) continue;        // applied by the finishing pass
         GemmJob u{};
         u.A = big[k].Wt[st & 1]; u.B = big[k].Vt[st & 1]; u.C = j.Minv;
         u.M = j.n; u.N = j.n; u.K = bs; u.lda = big[k].ldv; u.ldb = big[k].ldv; u.ldc = j.n;
@@ -709,11 +805,14 @@ hipError_t BlockedRun::finish(hipStream_t s)
             const InvertJob &j = jobs[idx[g0 + k]];
             InvProb &p = tab.p[k];
             p.M = j.M; p.W = j.Minv; p.info = j.info; p.n = j.n; p.damping = j.damping; p.dptr = j.damping_dev;
-            p.ldv = big[g0 + k].ldv; p.P = nullptr; p.Vt = nullptr; p.Wt = nullptr;
+            p.ldv = big[g0 + k].ldv; p.P = nullptr;
+            const int last = (j.n - 1) / PB;
+            p.fold = folds(g0 + k, last) ? j.n - last * PB : 0;
+            p.Vt = big[g0 + k].Vt[last & 1]; p.Wt = big[g0 + k].Wt[last & 1];
             p.gate = nullptr;
             p.blk_start = blocks;
-            const int nb32 = (j.n + 31) / 32;
-            blocks += nb32 * (nb32 + 1) / 2;
+            const int nb64 = (j.n + 63) / 64;
+            blocks += nb64 * (nb64 + 1) / 2;
         }
         KFAC_LAUNCH(KFAC_K_INV_FINISH, s, sweep_finish_kernel, dim3(blocks), dim3(256), 0, tab);
         hipError_t e = hipGetLastError();
@@ -727,8 +826,8 @@ struct AuxStreams {
     static constexpr int kEvents = 64;
     hipStream_t chain = nullptr, nest = nullptr, side = nullptr;
     hipEvent_t fork = nullptr, side_done = nullptr;
-    hipEvent_t ev_chain[kEvents] = {}, ev_bulk[kEvents] = {}, ev_look[kEvents] = {}, ev_nest[kEvents] = {},
-               ev_cond[kEvents] = {};
+    hipEvent_t ev_panel[kEvents] = {}, ev_band[kEvents] = {}, ev_next[kEvents] = {}, ev_nest[kEvents] = {},
+               ev_cond[kEvents] = {}, ev_gather[kEvents] = {}, ev_bulk[kEvents] = {};
     bool ok = false;
 };
 
@@ -753,11 +852,8 @@ AuxStreams *aux_streams()
                 hipEventCreateWithFlags(&a.fork, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&a.side_done, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; good && i < AuxStreams::kEvents; ++i)
-        good = hipEventCreateWithFlags(&a.ev_chain[i], hipEventDisableTiming) == hipSuccess &&
-               hipEventCreateWithFlags(&a.ev_bulk[i], hipEventDisableTiming) == hipSuccess &&
-               hipEventCreateWithFlags(&a.ev_look[i], hipEventDisableTiming) == hipSuccess &&
-               hipEventCreateWithFlags(&a.ev_nest[i], hipEventDisableTiming) == hipSuccess &&
-               hipEventCreateWithFlags(&a.ev_cond[i], hipEventDisableTiming) == hipSuccess;
+        for (hipEvent_t *e : {a.ev_panel, a.ev_band, a.ev_next, a.ev_nest, a.ev_cond, a.ev_gather, a.ev_bulk})
+            good = good && hipEventCreateWithFlags(&e[i], hipEventDisableTiming) == hipSuccess;
     if (!good) {
         if (!a.chain) a.chain = reinterpret_cast<hipStream_t>(1);   // marks the failed attempt
         return nullptr;
@@ -766,57 +862,81 @@ AuxStreams *aux_streams()
     return &a;
 }
 
-// One stream: chain and bulk of every step in a row.
+// One stream: every step in a row.
 hipError_t blocked_serial(BlockedRun &run, hipStream_t s)
 {
     hipError_t e = run.start(s);
     for (int st = 0; st < run.steps && e == hipSuccess; ++st) {
-        e = run.chain(st, s, s, nullptr, nullptr, nullptr);
+        e = run.nest(st, s);
+        if (e == hipSuccess && run.refine) e = run.copy_kernel(2, st, run.active(st), s);
+        if (e == hipSuccess) e = run.copy_kernel(0, st, run.active(st), s);
+        if (e == hipSuccess) e = run.panel(st, s, nullptr);
         if (e == hipSuccess) e = run.bulk(st, false, s);
     }
     return e == hipSuccess ? run.finish(s) : e;
 }
 
-// Look-ahead on three streams: updates on the caller's stream `s`, nested inversions on `aux->nest`, the rest of
-// the chains on `aux->chain`.
-//   update stream: wait chain(st); look(st, 0) [update st on the diagonal block of band st + 1]; record A;
-//                  look(st, 1) [the rest of the band]; record B; bulk(st) without that band
-//   nest stream:   wait A(st - 1); nested inversion of pivot block st; record N; condition test; record C
-//   chain stream:  wait B(st - 1); gather; wait N; panel product; wait C; refinement; scatter; record
-// The nested inversion, the longest link of the chain, only needs the diagonal block, a product of two tiles per
-// matrix; it runs beside the rest of the band product, the gather and the bulk update.  Panels st (buffer st mod 2)
-// are not overwritten before bulk(st) is done: the gather of step st + 2 waits for B(st + 1), which follows
-// bulk(st) on its stream.  The inverse of pivot block st - 1 is not overwritten before scatter(st - 1) is done:
-// A(st - 1) follows chain(st - 1).
+// Look-ahead on three streams: updates on the caller's stream `s`, the chain on `aux->nest`, panels on `aux->chain`.
+//   chain:    inverse of pivot block st [nest]; condition test [cond]; wait gather(st), bulk(st - 1); update st of the
+//             next pivot block [next]
+//   panels:   wait band(st - 1), next(st - 1); gather [gather]; wait nest(st); product; wait cond(st); refinement;
+//             scatter [panel]
+//   updates:  wait panel(st); update st of the rest of the next band [band]; bulk update without that band [bulk]
+// The chain needs nothing of the panel but its gather.  What keeps the buffers apart: panels st (buffer st mod 2) are
+// overwritten by gather(st + 2), which waits for band(st + 1), behind bulk(st) on its stream, and for next(st + 1); inverse
+// st by nest(st + 2), behind next(st + 1), which waits for bulk(st), behind panel(st); the next pivot block, which next(st)
+// updates, last by bulk(st - 1); pivot block st, which cond(st) reads and gather(st) copies, is overwritten by the
+// scatter of panel(st), behind both.
 hipError_t blocked_lookahead(BlockedRun &run, AuxStreams *aux, hipStream_t s)
 {
     hipError_t e = run.start(s);
     if (e != hipSuccess) return e;
     hipStream_t c = aux->chain, nn = aux->nest;
-    if (hipEventRecord(aux->fork, s) != hipSuccess || hipStreamWaitEvent(c, aux->fork, 0) != hipSuccess ||
-        hipStreamWaitEvent(nn, aux->fork, 0) != hipSuccess)
-        return hipErrorUnknown;
+    auto rec = [&](hipEvent_t ev, hipStream_t on) {
+        if (e == hipSuccess && hipEventRecord(ev, on) != hipSuccess) e = hipErrorUnknown;
+    };
+    auto wait = [&](hipStream_t on, hipEvent_t ev) {
+        if (e == hipSuccess && hipStreamWaitEvent(on, ev, 0) != hipSuccess) e = hipErrorUnknown;
+    };
+    rec(aux->fork, s);
+    wait(c, aux->fork);
+    wait(nn, aux->fork);
     bool joined = false;
     for (int st = 0; st < run.steps && e == hipSuccess; ++st) {
         joined = false;
-        e = run.chain(st, nn, c, st > 0 ? aux->ev_bulk[st - 1] : nullptr, aux->ev_nest[st], aux->ev_cond[st]);
-        if (e == hipSuccess && hipEventRecord(aux->ev_chain[st], c) != hipSuccess) e = hipErrorUnknown;
-        if (e == hipSuccess && hipStreamWaitEvent(s, aux->ev_chain[st], 0) != hipSuccess) e = hipErrorUnknown;
-        if (e != hipSuccess) break;
-        joined = true;            // everything the other two streams hold so far is ordered before what follows on `s`
         const bool more = st + 1 < run.steps;
+        e = run.nest(st, nn);
+        rec(aux->ev_nest[st], nn);
+        if (e == hipSuccess && run.refine) e = run.copy_kernel(2, st, run.active(st), nn);
+        rec(aux->ev_cond[st], nn);
+        if (st > 0) {
+            wait(c, aux->ev_band[st - 1]);
+            wait(c, aux->ev_next[st - 1]);
+        }
+        if (e == hipSuccess) e = run.copy_kernel(0, st, run.active(st), c);
+        rec(aux->ev_gather[st], c);
         if (more) {
-            e = run.look(st, 0, s);
-            if (e == hipSuccess && hipEventRecord(aux->ev_look[st], s) != hipSuccess) e = hipErrorUnknown;
-            if (e == hipSuccess && hipStreamWaitEvent(nn, aux->ev_look[st], 0) != hipSuccess) e = hipErrorUnknown;
-            if (e == hipSuccess) e = run.look(st, 1, s);
-            if (e == hipSuccess && hipEventRecord(aux->ev_bulk[st], s) != hipSuccess) e = hipErrorUnknown;
+            wait(nn, aux->ev_gather[st]);
+            if (st > 0) wait(nn, aux->ev_bulk[st - 1]);
+            if (e == hipSuccess) e = run.next(st, nn);
+            rec(aux->ev_next[st], nn);
+        }
+        wait(c, aux->ev_nest[st]);
+        if (e == hipSuccess) e = run.panel(st, c, aux->ev_cond[st]);
+        rec(aux->ev_panel[st], c);
+        wait(s, aux->ev_panel[st]);
+        if (e != hipSuccess) break;
+        if (more) {
+            e = run.band(st, s);
+            rec(aux->ev_band[st], s);
         }
         if (e == hipSuccess) e = run.bulk(st, more, s);
+        if (more) rec(aux->ev_bulk[st], s);
+        joined = !more;           // the last panel is behind everything the other two streams hold
     }
     if (!joined) {
         // after an error the caller's stream must still not run ahead of what the other two streams hold
-        if (hipEventRecord(aux->ev_chain[0], c) == hipSuccess) (void)hipStreamWaitEvent(s, aux->ev_chain[0], 0);
+        if (hipEventRecord(aux->ev_panel[0], c) == hipSuccess) (void)hipStreamWaitEvent(s, aux->ev_panel[0], 0);
         if (hipEventRecord(aux->ev_nest[0], nn) == hipSuccess) (void)hipStreamWaitEvent(s, aux->ev_nest[0], 0);
     }
     return e == hipSuccess ? run.finish(s) : e;

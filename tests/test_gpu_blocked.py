@@ -1,0 +1,77 @@
+"""The blocked inversion (orders above 1280) where its pieces meet: last pivot blocks of one to five rows (up to four are
+applied by the finishing pass), whole ones and one row short of it, several orders in a call, on the library's streams and on
+one; pivot blocks ill-conditioned enough to open the gate of the refinement.  The upper triangle of the factor holds NaN.
+
+Tolerance as in test_gpu_border.py: 1.5 cond 2^-24."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+import paper_2206_15143_amd as kf
+
+pytestmark = pytest.mark.gpu
+
+
+def _spd(n, cond, seed):
+    """Spectrum in geometric progression, vectors from two reflections (cheap at these orders)."""
+    rng = np.random.default_rng(seed)
+    lam = rng.permutation(np.geomspace(1.0, 1.0 / cond, n))
+    m = np.diag(lam)
+    inv = np.diag(1.0 / lam)
+    for _ in range(3):
+        u = rng.standard_normal(n)
+        u /= np.linalg.norm(u)
+        for x in (m, inv):
+            x -= 2.0 * np.outer(u, u @ x)
+            x -= 2.0 * np.outer(x @ u, u)
+    return ((m + m.T) / 2).astype(np.float32), inv
+
+
+def _invert(mats):
+    n = len(mats)
+    descs = [kf.LayerDesc.linear(m.shape[0], 8, False, kf.KFAC_F32) for m in mats]
+    A = [gu.to_dev(np.where(np.tril(np.ones_like(m)) > 0, m, np.nan).astype(np.float32)) for m in mats]
+    G = [torch.eye(8, device=gu.DEV) for _ in mats]
+    Ai, Gi = [torch.full_like(a, float("nan")) for a in A], [torch.empty_like(g) for g in G]
+    info = torch.full((2 * n,), -1, dtype=torch.int32, device=gu.DEV)
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_invert_batched(descs, A, G, 0.0, 0.0, Ai, Gi, info, ws)
+    torch.cuda.synchronize()
+    return [x.cpu().numpy() for x in Ai], info.cpu().numpy()
+
+
+@pytest.mark.parametrize("streams", [1, 0])
+@pytest.mark.parametrize("cond", [1e2, 1e5])
+@pytest.mark.parametrize("orders", [(1282,), (1284, 1285), (1536, 1537, 1535, 1300), (1540, 1541, 1792, 1793, 2049)])
+def test_orders(orders, cond, streams):
+    pairs = [_spd(n, cond, n) for n in orders]
+    kf.kfac_tune("invert_two_streams", streams)
+    try:
+        got, info = _invert([m for m, _ in pairs])
+    finally:
+        kf.kfac_tune("invert_two_streams", 1)
+    assert not info.any()
+    for n, x, (m, inv) in zip(orders, got, pairs):
+        # the fp32 entries of the factor are what is inverted: one step of Newton's iteration from the exact inverse of the
+        # unrounded factor gives their inverse to second order
+        ref = inv @ (2.0 * np.eye(n) - m.astype(np.float64) @ inv)
+        err = gu.rel_fro(x, ref)
+        print(n, f"cond {cond:.0e} streams {streams}: {err:.2e}", flush=True)
+        assert err < 1.5 * cond * 2.0 ** -24
+        assert np.array_equal(x, x.T)
+
+
+def test_status_in_every_block():
+    """A negative diagonal entry is reported by its place, whichever pivot block (or the last, folded row) holds it."""
+    n = 1537
+    base, _ = _spd(n, 10.0, 3)
+    places = [0, 255, 256, 700, 1535, 1536]
+    mats = []
+    for p in places:
+        m = base.copy()
+        m[p, p] = -5.0
+        mats.append(m)
+    got, info = _invert(mats + [base])
+    assert list(info[0::2]) == [p + 1 for p in places] + [0]
+    assert np.isfinite(got[-1]).all()
