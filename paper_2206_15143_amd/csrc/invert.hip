@@ -827,7 +827,7 @@ struct AuxStreams {
     hipStream_t chain = nullptr, nest = nullptr, side = nullptr;
     hipEvent_t fork = nullptr, side_done = nullptr;
     hipEvent_t ev_panel[kEvents] = {}, ev_band[kEvents] = {}, ev_next[kEvents] = {}, ev_nest[kEvents] = {},
-               ev_cond[kEvents] = {}, ev_gather[kEvents] = {}, ev_bulk[kEvents] = {};
+               ev_cond[kEvents] = {}, ev_gather[kEvents] = {}, ev_ready[kEvents] = {};
     bool ok = false;
 };
 
@@ -852,7 +852,7 @@ AuxStreams *aux_streams()
                 hipEventCreateWithFlags(&a.fork, hipEventDisableTiming) == hipSuccess &&
                 hipEventCreateWithFlags(&a.side_done, hipEventDisableTiming) == hipSuccess;
     for (int i = 0; good && i < AuxStreams::kEvents; ++i)
-        for (hipEvent_t *e : {a.ev_panel, a.ev_band, a.ev_next, a.ev_nest, a.ev_cond, a.ev_gather, a.ev_bulk})
+        for (hipEvent_t *e : {a.ev_panel, a.ev_band, a.ev_next, a.ev_nest, a.ev_cond, a.ev_gather, a.ev_ready})
             good = good && hipEventCreateWithFlags(&e[i], hipEventDisableTiming) == hipSuccess;
     if (!good) {
         if (!a.chain) a.chain = reinterpret_cast<hipStream_t>(1);   // marks the failed attempt
@@ -877,13 +877,15 @@ hipError_t blocked_serial(BlockedRun &run, hipStream_t s)
 }
 
 // Look-ahead on three streams: updates on the caller's stream `s`, the chain on `aux->nest`, panels on `aux->chain`.
-//   chain:    inverse of pivot block st [nest]; condition test [cond]; wait gather(st), bulk(st - 1); update st of the
-//             next pivot block [next]
+//   chain:    inverse of pivot block st [nest]; condition test [cond]; wait ready(st); update st of the next pivot
+//             block [next]
 //   panels:   wait band(st - 1), next(st - 1); gather [gather]; wait nest(st); product; wait cond(st); refinement;
 //             scatter [panel]
-//   updates:  wait panel(st); update st of the rest of the next band [band]; bulk update without that band [bulk]
-// The chain needs nothing of the panel but its gather.  What keeps the buffers apart: panels st (buffer st mod 2) are
-// overwritten by gather(st + 2), which waits for band(st + 1), behind bulk(st) on its stream, and for next(st + 1); inverse
+//   updates:  behind bulk(st - 1), wait gather(st) [ready]; wait panel(st); update st of the rest of the next band [band];
+//             bulk update without that band [bulk]
+// The chain needs nothing of the panel but its gather, for which it waits through the caller's stream: two streams that wait
+// for each other's events and are both forked from a captured one end the process when the capture ends.
+// What keeps the buffers apart: panels st (buffer st mod 2) are overwritten by gather(st + 2), which waits for band(st + 1), behind bulk(st) on its stream, and for next(st + 1); inverse
 // st by nest(st + 2), behind next(st + 1), which waits for bulk(st), behind panel(st); the next pivot block, which next(st)
 // updates, last by bulk(st - 1); pivot block st, which cond(st) reads and gather(st) copies, is overwritten by the
 // scatter of panel(st), behind both.
@@ -916,8 +918,9 @@ hipError_t blocked_lookahead(BlockedRun &run, AuxStreams *aux, hipStream_t s)
         if (e == hipSuccess) e = run.copy_kernel(0, st, run.active(st), c);
         rec(aux->ev_gather[st], c);
         if (more) {
-            wait(nn, aux->ev_gather[st]);
-            if (st > 0) wait(nn, aux->ev_bulk[st - 1]);
+            wait(s, aux->ev_gather[st]);            // behind bulk(st - 1); `s` goes on with panel(st) only
+            rec(aux->ev_ready[st], s);
+            wait(nn, aux->ev_ready[st]);
             if (e == hipSuccess) e = run.next(st, nn);
             rec(aux->ev_next[st], nn);
         }
@@ -931,7 +934,6 @@ hipError_t blocked_lookahead(BlockedRun &run, AuxStreams *aux, hipStream_t s)
             rec(aux->ev_band[st], s);
         }
         if (e == hipSuccess) e = run.bulk(st, more, s);
-        if (more) rec(aux->ev_bulk[st], s);
         joined = !more;           // the last panel is behind everything the other two streams hold
     }
     if (!joined) {
