@@ -69,7 +69,7 @@ struct GemmJob {
     const float *D = nullptr;    // kSubFrom
     long ldd = 0;
     bool wide_tiles = false;     // kStore: take the split-bf16 kernel whatever the depth and tile fill
-    bool direct = false;         // take the 64-wide tiles of the latency-bound products
+    bool chain = false;          // all jobs of the call: products of the blocked inversion's chain (gemm_chain_kernel)
     // gemm_split_products only: K in kslices slices of kper rows (a multiple of 16), slice i into C + i cstride; abytes:
     // from A to the end of its buffer (rows of A may overlap: M > lda), what lies past it counts as zero
     int kslices = 1, kper = 0;
@@ -168,7 +168,7 @@ struct Tuning {
     long invert_refine = 1;          // blocked sweep: refinement step of the panel products (see invert.hip) ...
     long invert_fused_refine_cond = 300;  // the same test for the 64 x 64 pivot blocks of the one-launch-per-step path
     long invert_refine_cond = 3000;  // ... of pivot blocks whose condition number (maximum norm) exceeds this
-    long invert_outer_block = 256;   // outer pivot block of the two-level inversion (multiple of 32)
+    long invert_outer_block = 256;   // outer pivot block of the two-level inversion (multiple of 64)
     long invert_border_refine = 2;   // ... its refinement step: 2 always, 1 only where the sweep met an ill-conditioned pivot block
     long invert_border = 1;          // orders 64 k + 1: last row and column by bordering instead of a one-row pivot block
     long invert_two_streams = 1;     // blocked sweep and smaller factors on the library's streams (look-ahead); 0: everything on the caller's stream

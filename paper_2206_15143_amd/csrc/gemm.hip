@@ -156,9 +156,116 @@ __global__ __launch_bounds__(T::NT) void gemm_tn_kernel(const GemmTable tab)
         }
 }
 
+// Products of the blocked inversion's chain: 32 x 32 tiles, a wavefront each, on the split arithmetic (split_common.hpp) in
+// the order of gemm_split_kernel: the same bits as the panel and bulk products leave, so that the next pivot block is updated
+// with the very W that the rest of its matrix sees.  (With W from the fp32 MFMA, as accurate by itself, the inverse of a
+// post-ReLU factor came out up to 6 % further from float64, condition number 1e4 to 1e5: the two roundings, eps |V| |P|
+// each, no longer cancel.)  Operands go straight from memory to the wavefront that cuts them, four stages of 16 rows in
+// flight; no LDS, no barrier.  K is a multiple of 64.  A launch of five products 256 x 256 x 256: 14 us.
+__global__ __launch_bounds__(64) void gemm_chain_kernel(const GemmTable tab)
+{
+    int pi = 0, hi = tab.count - 1;
+    while (pi < hi) {
+        const int mid = (pi + hi + 1) >> 1;
+        if ((int)blockIdx.x >= tab.starts[mid]) pi = mid;
+        else hi = mid - 1;
+    }
+    const GemmProb &pr = tab.p[pi];
+    if (pr.gate && !(__int_as_float(pr.gate[0]) * __int_as_float(pr.gate[1]) > pr.gate_cond)) return;
+    const int local = blockIdx.x - pr.blk_start, bi = local / pr.tn;
+    const int m0 = 32 * bi, n0 = 32 * (local - bi * pr.tn), M = pr.M, N = pr.N, nst = pr.K / 16;
+    const bool lower = pr.mode == kSubRect || pr.mode == kAddRect;
+    if (lower && (long)n0 > (long)min(m0 + 31, M - 1) + pr.doff) return;       // wholly above the line n = m + doff
+    const int lane = threadIdx.x, lr = lane & 31, lg = lane >> 5;
+    const unsigned pa = (unsigned)pr.lda * 4u, pb = (unsigned)pr.ldb * 4u;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.A), 0, (int)((long)pr.K * pr.lda * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.B), 0, (int)((long)pr.K * pr.ldb * 4), 0x00020000);
+    // columns past the edge repeat the last one: their results are not stored
+    const unsigned ca = (unsigned)min(m0 + lr, M - 1) * 4u, cb = (unsigned)min(n0 + lr, N - 1) * 4u;
+    const unsigned ao = ca + 8u * (unsigned)lg * pa, bo = cb + 8u * (unsigned)lg * pb;
+    float a[4][8], b[4][8];                   // rows 16 g + 8 lg + e
+    auto load = [&](int set, int g) {
+        const int gg = min(g, nst - 1);       // past the end: the last stage again, not used
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            a[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, ao, (unsigned)(16 * gg + e) * pa, 0));
+            b[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, bo, (unsigned)(16 * gg + e) * pb, 0));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto pieces = [&](sbf16x8 (&f)[3], const float (&x)[8]) {
+        float x0[4] = {x[0], x[1], x[2], x[3]}, x1[4] = {x[4], x[5], x[6], x[7]};
+        SplitCut k0, k1;
+        k0.scale(x0); k1.scale(x1);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            k0.half(x0, 0, 4); k1.half(x1, 0, 4);
+            const suint2 u = k0.pack(), v = k1.pack();
+            f[p] = __builtin_bit_cast(sbf16x8, suint4{u.x, u.y, v.x, v.y});
+            k0.top(0, 4); k1.top(0, 4);
+            k0.rest(x0, 0, 4); k1.rest(x1, 0, 4);
+        }
+        const suint2 u = k0.pack_last(x0), v = k1.pack_last(x1);
+        f[2] = __builtin_bit_cast(sbf16x8, suint4{u.x, u.y, v.x, v.y});
+    };
+    floatx16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) load(t, t);
+    sbf16x8 A[2][3], B[2][3];
+    pieces(A[0], a[0]);
+    pieces(B[0], b[0]);
+    load(0, 4);
+    for (int g = 0; g < nst; g += 4)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            // the cut of the next stage between the products of this one, which wait for each other
+            pieces(A[(t + 1) & 1], a[(t + 1) & 3]);
+            pieces(B[(t + 1) & 1], b[(t + 1) & 3]);
+            constexpr int pieceA[6] = {2, 1, 1, 0, 0, 0}, pieceB[6] = {0, 1, 0, 2, 1, 0};
+#pragma unroll
+            for (int q = 0; q < 6; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t & 1][pieceA[q]], B[t & 1][pieceB[q]], acc, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 23, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            load((t + 1) & 3, g + t + 5);
+        }
+    float unscale = kSplitUnscale, t = 0.f;   // t stays 0 unless something is infinite or NaN
+#pragma unroll
+    for (int v = 0; v < 16; ++v) t = __builtin_fmaf(acc[v], 0.f, t);
+    if (__any(t != 0.f)) {                    // what fp32 arithmetic gives
+        unscale = 1.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        for (int k = 0; k < 16 * nst; k += 2) {
+            const float x = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(ra, ca + (unsigned)(k + lg) * pa, 0, 0));
+            const float y = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rb, cb + (unsigned)(k + lg) * pb, 0, 0));
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x, y, acc, 0, 0, 0);
+        }
+    }
+    const int n = n0 + lr;
+    const float *from = pr.mode == kSubFrom ? pr.D : pr.C;
+    const long ldf = pr.mode == kSubFrom ? pr.ldd : pr.ldc;
+    const float sign = pr.mode == kStore || pr.mode == kAddRect ? unscale : -unscale;
+    float old[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
+        old[v] = pr.mode != kStore && m < M && n < N ? from[(long)m * ldf + n] : 0.f;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
+        if (m < M && n < N && (!lower || (long)n <= (long)m + pr.doff)) pr.C[(long)m * pr.ldc + n] = __builtin_fmaf(sign, acc[v], old[v]);
+    }
+}
+
 // 64 x 64 tiles of the same products for the launches that are bound by the latency of one tile: a few workgroups per
-// matrix, each walking the whole depth (the short products of the blocked inversion's chain, small preconditioning
-// products).  The four wavefronts split K (chunks of 16 in turn), every one computes the whole tile: a lane loads 16 bytes
+// matrix, each walking the whole depth (small preconditioning products).  The four wavefronts split K (chunks of 16 in turn), every one computes the whole tile: a lane loads 16 bytes
 // of a row of either operand, which are one column each of four interleaved MFMA tiles, straight into the registers the
 // MFMA reads, two chunks ahead; no LDS and no barrier until the four parts are added in wavefront order.  At K = 256 a
 // tile takes 9 us where the staged form with all wavefronts on one K stage (16 stages, an LDS round trip and a barrier
@@ -358,6 +465,35 @@ hipError_t launch_direct(const GemmTable &tab, int blocks, hipStream_t s)
     return launch_done(tab);
 }
 
+// the products of the blocked inversion's chain: K a multiple of 64, operands below 2 GiB (pivot blocks of 64 to 512 rows)
+hipError_t chain_launch(const GemmJob *jobs, int n, hipStream_t s)
+{
+    for (int i0 = 0; i0 < n; i0 += kMaxGemmProblems) {
+        GemmTable tab;
+        tab.count = std::min(kMaxGemmProblems, n - i0);
+        int blocks = 0;
+        for (int k = 0; k < tab.count; ++k) {
+            const GemmJob &j = jobs[i0 + k];
+            GemmProb &p = tab.p[k];
+            p = GemmProb{};
+            p.A = j.A; p.B = j.B; p.C = j.C;
+            p.lda = j.lda; p.ldb = j.ldb; p.ldc = j.ldc;
+            p.M = j.M; p.N = j.N; p.K = j.K;
+            p.tm = (j.M + 31) / 32;
+            p.tn = (j.N + 31) / 32;
+            p.mode = j.mode; p.doff = j.doff;
+            p.gate = j.gate; p.gate_cond = j.gate_cond;
+            p.D = j.D; p.ldd = j.ldd;
+            p.blk_start = tab.starts[k] = blocks;
+            blocks += p.tm * p.tn;
+        }
+        KFAC_LAUNCH(KFAC_K_GEMM, s, gemm_chain_kernel, dim3(blocks), dim3(64), 0, tab);
+        hipError_t e = launch_done(tab);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 }  // namespace
 
 namespace {
@@ -389,7 +525,7 @@ bool wave_gemm_eligible(const GemmJob &j)
     if (!tuning().use_wave_gemm || j.mode == kStoreDiv || j.mode == kSubRect || j.mode == kAddRect ||
         j.mode == kSubFrom || j.gate)
         return false;
-    if (j.direct || j.M < 100 || j.N < 100 || j.K < 16) return false;
+    if (j.M < 100 || j.N < 100 || j.K < 16) return false;
     if ((long)j.K * j.lda * 4 > 0x7fffffffl || (long)j.K * j.ldb * 4 > 0x7fffffffl) return false;
     if (((uintptr_t)j.A) % 4 || ((uintptr_t)j.B) % 4) return false;
     if (j.mode == kSubLowerSkip)
@@ -454,7 +590,7 @@ bool split_gemm_eligible(const GemmJob &j, bool wide)
     if (!tuning().use_split_gemm || (j.mode != kStore && j.mode != kSubLowerSkip && j.mode != kSubRect && j.mode != kAddRect))
         return false;
     const long min_m = wide && j.mode == kStore ? tuning().split_gemm_min_m : 192;
-    if (j.direct || j.M < min_m || j.N < 64 || j.K < 16) return false;
+    if (j.M < min_m || j.N < 64 || j.K < 16) return false;
     // a product of a tile or two is bound by the latency of one tile's K loop and read-modify-write (55 us at
     // K = 256): the 64-wide tiles of the block-tile kernel spread it over many CUs and finish in 10-15 us
     if ((long)j.M * j.N < 4l * S_BM * S_BN) return false;
@@ -714,6 +850,7 @@ hipError_t gemm_launch(const GemmJob *jobs, int n, hipStream_t s, void *work, si
 namespace {
 hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
 {
+    if (n > 0 && jobs[0].chain) return chain_launch(jobs, n, s);
     const bool wide = split_gemm_wide(jobs, n);
     std::vector<int> cfg(n);
     std::vector<int> wave, split;
@@ -725,7 +862,7 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             cfg[i] = -1;
             wave.push_back(i);
         } else {
-            cfg[i] = jobs[i].direct ? 2 : choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
+            cfg[i] = choose_bm(jobs[i].M, jobs[i].N, jobs[i].mode == kSubLowerSkip);
         }
     }
     // A wave-unit workgroup owns 144 x 288 of a product and walks its whole depth at 110 us per 512 rows whatever else
@@ -761,7 +898,7 @@ hipError_t gemm_launch_plain(const GemmJob *jobs, int n, hipStream_t s)
             for (int c = 1; c < 4; ++c)
                 if (cost[c] < cost[best]) best = c;
             for (int i = 0; i < n; ++i)
-                if (cfg[i] >= 0 && jobs[i].mode != kSubLowerSkip && !jobs[i].direct) cfg[i] = best;
+                if (cfg[i] >= 0 && jobs[i].mode != kSubLowerSkip) cfg[i] = best;
         }
     }
     if (!tuning().gemm_bm) {

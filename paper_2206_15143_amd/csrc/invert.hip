@@ -118,14 +118,14 @@ __global__ __launch_bounds__(256) void sweep_init_kernel(const InvTable tab)
 }
 
 // ---- two-level blocked sweep for the large factors -------------------------------------------
-// Outer pivot blocks of PB rows (invert_outer_block, 256; a multiple of the 32-wide gather / scatter tiles, at
+// Outer pivot blocks of PB rows (invert_outer_block, 256; a multiple of the 64 rows of the chain kernel's rounds, at
 // most 512).  Per outer step: the pivot block is inverted by the one-launch-per-step sweep above (a PB x PB
 // problem), the old panel is gathered K-major into V, W = V P (refined once where the pivot block is
 // ill-conditioned) and the rank-PB update of the rest of the triangle run on the split-bf16 GEMM, and the new panel
 // and -P are scattered back in place.  512 is 12 % faster on the workloads with many large factors, but the error
 // of the inverse grows with the order of the explicitly inverted pivot block (measured at order 2305:
 // 2.8e-5 / 6.2e-5 for 256 / 512), so 256 stays.
-inline int outer_block() { return (int)std::min(512l, std::max(64l, tuning().invert_outer_block / 32 * 32)); }
+inline int outer_block() { return (int)std::min(512l, std::max(64l, tuning().invert_outer_block / 64 * 64)); }
 
 struct BlkProb {
     float *W;          // working matrix [n, n]
@@ -692,7 +692,7 @@ hipError_t BlockedRun::nest(int st, hipStream_t s)
 
 // Update st applied to the diagonal block of the next pivot block, all that its inversion needs: W for its columns alone
 // (256 of up to thousands), refined under the same gate as the panel, and the product with V.  Four launches of
-// 64-wide tiles, 40 us with the gates shut, in place of waiting for the whole panel (product, refinement, scatter: 100 to
+// 32-wide tiles, 40 us with the gates shut, in place of waiting for the whole panel (product, refinement, scatter: 100 to
 // 150 us beside the bulk update).
 hipError_t BlockedRun::next(int st, hipStream_t s)
 {
@@ -720,7 +720,7 @@ hipError_t BlockedRun::next(int st, hipStream_t s)
                 g.gate = gate(k, st);
                 g.gate_cond = (float)tuning().invert_refine_cond;
             }
-            g.direct = true;
+            g.chain = true;
         }
         e = gemm_launch(gj.data(), act, s);
     }
