@@ -172,7 +172,7 @@ struct Tuning {
     long invert_border_refine = 2;   // ... its refinement step: 2 always, 1 only where the sweep met an ill-conditioned pivot block
     long invert_border = 1;          // orders 64 k + 1: last row and column by bordering instead of a one-row pivot block
     long invert_two_streams = 1;     // blocked sweep and smaller factors on the library's streams (look-ahead); 0: everything on the caller's stream
-    long corr3_lds_kb = 72;          // LDS budget (both slabs) of the autocorrelation kernel
+    long corr3_lds_kb = 160;          // LDS budget (both slabs) of the autocorrelation kernel
     long corrw_min_c = 20;           // ... of at least this many channels from products of a padded, transposed copy (0 = never)
     long corrw_max_pad = 170;        // ... on maps whose copy has at most this percentage of their positions
     long use_corr3 = 1;              // 3x3 convolution factors of 16 / 32 / 64 channels from input autocorrelations

@@ -573,22 +573,26 @@ int choose_cfg(int d)
     return best;
 }
 
-// Strip height of the autocorrelation kernel: the largest divisor of H whose two slabs fit 72 KB of LDS and
-// whose slab is at most 12 float4 items per thread (0 = not eligible).  plane = floats per channel, padded
-// so that consecutive channels start 4 banks apart.
+// Strip height of the autocorrelation kernel (0 = not eligible): two slabs within the LDS of a CU, at most C3_ITEMS
+// octets per staging thread, and among these heights the one with the least work, products (k-steps, whole rounds of the
+// product wavefronts) plus a tenth for the octets to stage.  plane = octets per channel; odd, so that the
+// operand reads of 16 channels fall on different banks.
 int corr3_rows(int C, int H, int W, int *plane_out)
 {
+    const int opr = (W + 7) / 8, ks = corr3_ks(C);
     int best = 0;
+    long best_cost = 0;
     for (int SR = 1; SR <= H; ++SR) {
-        if (H % SR) continue;
-        if ((SR * W) % 16) continue;                           // whole groups of 16 pixels
-        int plane = (SR + 2) * (W + 8);
-        plane += (4 - plane % 32 + 32) % 32;
-        const long bytes = 2l * C * plane * 4;
-        const long copies = ((long)C * plane / 4 + 63) / 64;       // 1 KB global -> LDS copies per slab, nine per staging wavefront at most
-        if (bytes > std::min<long>(tuning().corr3_lds_kb, 80) * 1024 || copies > 36) continue;   // 80 KB: what the launch asks the runtime for
-        best = SR;
-        if (plane_out) *plane_out = plane;
+        const int plane = (SR + 2) * opr | 1;
+        const long bytes = C3_ZERO + 2l * C * plane * C3_OCT, items = (long)C * (SR + 2) * opr;
+        if (bytes > std::min<long>(tuning().corr3_lds_kb, 160) * 1024 || items > 64 * C3_SW * C3_ITEMS) break;   // 160 KB: what the launch asks the runtime for
+        const long steps = ((SR * opr + 3) / 4 + ks - 1) / ks * ks;
+        const long cost = (long)((H + SR - 1) / SR) * (40 * steps + (SR + 2) * opr + 10 * ks);
+        if (best == 0 || cost <= best_cost) {
+            best = SR;
+            best_cost = cost;
+            if (plane_out) *plane_out = plane;
+        }
     }
     return best;
 }
@@ -626,8 +630,7 @@ void plan_group(const FactorJob *jobs, const std::vector<int> &idx, std::vector<
     }
     if (is_corr3_cfg(pl[idx[0]].cfg)) {
         // autocorrelation kernel: (image, strip) units dealt evenly to about target_blocks workgroups
-        const long halves = pl[idx[0]].cfg == kCorr3Cfg + 2 ? 2 : 1;
-        const long per = std::max<long>(1, tu.target_blocks / ((long)idx.size() * halves));
+        const long per = std::max<long>(1, tu.target_blocks / 2 / ((long)idx.size() * corr3_sharers(jobs[idx[0]].ctot)));
         for (int j : idx) {
             Planned &p = pl[j];
             const FactorJob &job = jobs[j];
@@ -635,11 +638,11 @@ void plan_group(const FactorJob *jobs, const std::vector<int> &idx, std::vector<
             int plane = 0;
             p.rows_per_stage = corr3_rows(C, job.h, job.w, &plane);
             p.unit_rows = plane;                                   // carried to the launch
-            const long units = (job.K / job.hw) * (job.h / p.rows_per_stage);
+            const long units = (job.K / job.hw) * ((job.h + p.rows_per_stage - 1) / p.rows_per_stage);
             p.tps = (int)std::max<long>(1, (units + per - 1) / per);       // units per block
             p.splits = (int)((units + p.tps - 1) / p.tps);
             p.nb = 1; p.nblk = 1; p.bps = 1;
-            const size_t parts = (size_t)p.splits * (C == 16 ? 4 : 1);
+            const size_t parts = (size_t)p.splits;
             const size_t nF = (size_t)C3_LAGS * C * C, nB = (size_t)C3_BQ * C * C + (size_t)C3_BV * C;
             p.partial_floats = parts * (nF + C) + (nF + C) + (size_t)C3_CHUNKS * nB + nB + 64 +
                                nF + (size_t)C3_BQ * C * C +                        // transposed copies
@@ -819,15 +822,15 @@ hipError_t corr3_launch_nt(CorrTable &tab, const std::vector<size_t> &lds, doubl
     for (int k = 0; k < tab.count; ++k) {
         tab.p[k].blk_start = blocks;
         tab.starts[k] = blocks;
-        blocks += tab.p[k].splits * (NT == 4 ? 2 : 1);   // 64 channels: two workgroups per range of units
+        blocks += tab.p[k].parts * corr3_sharers(16 * NT);
         lds_bytes = std::max(lds_bytes, lds[k]);
     }
     {   // per device and cheap: set on every launch rather than remembered in a process-wide flag
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&corr3_main_kernel<NT>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
     }
-    KFAC_LAUNCH(KFAC_K_SYRK_CORR3, s, (corr3_main_kernel<NT>), dim3(blocks), dim3(512), lds_bytes, tab);
+    KFAC_LAUNCH(KFAC_K_SYRK_CORR3, s, (corr3_main_kernel<NT>), dim3(blocks), dim3(C3_THREADS), lds_bytes, tab);
     timing_work(flops, exflops);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -888,10 +891,10 @@ hipError_t corr3_launch(const FactorJob *jobs, const std::vector<int> &g, const 
         const size_t nF = (size_t)C3_LAGS * C * C, nB = (size_t)C3_BQ * C * C + (size_t)C3_BV * C;
         p.x = static_cast<const float *>(job.x);
         p.C = C; p.H = job.h; p.W = job.w; p.B = (int)(job.K / job.hw);
-        p.SR = P.rows_per_stage; p.strips = job.h / P.rows_per_stage;
+        p.SR = P.rows_per_stage; p.strips = (job.h + P.rows_per_stage - 1) / P.rows_per_stage;
         p.units = p.B * p.strips;
-        p.splits = P.splits; p.upb = P.tps;
-        p.parts = P.splits * (C == 16 ? 4 : 1);
+        p.upb = P.tps;
+        p.parts = P.splits;
         p.plane = P.unit_rows;
         p.has_bias = job.has_bias; p.scale = job.scale; p.decay = job.decay;
         p.F = job.F;
@@ -904,7 +907,7 @@ hipError_t corr3_launch(const FactorJob *jobs, const std::vector<int> &g, const 
         p.BsT = p.FsT + nF;
         p.cols = p.BsT + (size_t)C3_BQ * C * C;
         p.blk_start = 0;
-        lds[k] = (size_t)2 * C * p.plane * sizeof(float);
+        lds[k] = std::max((size_t)corr3_tail_lds(C), C3_ZERO + (size_t)2 * C * p.plane * C3_OCT);
     }
     const int cfg = pl[g[0]].cfg;
     hipError_t e = cfg == kCorr3Cfg ? corr3_launch_nt<1>(tab, lds, flops, exflops, s)
@@ -917,8 +920,7 @@ hipError_t corr3_launch(const FactorJob *jobs, const std::vector<int> &g, const 
         const CorrProb &p = tab.p[k];
         tab.p[k].blk_start = blocks;
         tab.starts[k] = blocks;
-        const long total = (long)(C3_LAGS + C3_BQ) * p.C * p.C / 4 + (long)(1 + C3_BV) * p.C;   // four matrix elements per thread
-        blocks += (int)((total + 255) / 256);
+        blocks += corr3_sum_blocks(p.C, p.parts, tab.p[k].fblocks);
     }
     KFAC_LAUNCH(KFAC_K_CORR3_ASM, s, corr3_sum_kernel, dim3(blocks), dim3(256), 0, tab);
     e = hipGetLastError();
@@ -1039,14 +1041,14 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
         tab.count = (int)g.size();
         tab.debug = (int)tuning().wave_debug;
         int blocks = 0;
-        double flops = 0.0, corr_flops = 0.0;   // corr_flops: 13 lag tiles per channel-tile pair and pixel, 26 C^2 per pixel
+        double flops = 0.0, corr_flops = 0.0;   // corr_flops: six piece products of 13 lag tiles per channel-tile pair and pixel, 6 x 26 C^2 per pixel
         std::vector<int> red_n(g.size());
         std::vector<double> red_b(g.size());
         for (int k = 0; k < tab.count; ++k) {
             const int j = g[k];
             const FactorJob &job = jobs[j];
             flops += (double)job.K * (job.d_core + job.has_bias) * (job.d_core + job.has_bias + 1);
-            corr_flops += 26.0 * job.ctot * job.ctot * (double)job.K;
+            corr_flops += 6.0 * 26.0 * job.ctot * job.ctot * (double)job.K;
             {   // reduce + running average: the split slices and the old factor read (one triangle), the factor written (both)
                 const double dF = job.d_core + job.has_bias, tri = dF * (dF + 1) / 2;
                 red_b[k] = 4.0 * ((pl[j].splits + 1) * tri + dF * dF);

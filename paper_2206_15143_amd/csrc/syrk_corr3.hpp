@@ -20,6 +20,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "split_common.hpp"
 #include "tn_engine.hpp"
 #include "wave_common.hpp"
 
@@ -42,9 +43,10 @@ struct CorrProb {
     int C, H, W, B;
     int SR, strips;    // rows per strip, strips per image
     int units;         // B * strips
-    int splits, upb;   // blocks of the main kernel, units per block
-    int parts;         // splits * (wavefronts that split the k-steps)
-    int plane;         // floats per channel plane of a slab
+    int upb;           // units per block of the main kernel
+    int parts;         // blocks (ranges of units) of the main kernel
+    int fblocks;       // blocks of the sum kernel for the lag matrices
+    int plane;         // octets per channel plane of a slab
     int blk_start;     // first block of this problem in the kernel at hand
     int has_bias;
     float scale, decay;
@@ -68,245 +70,284 @@ __device__ __forceinline__ int corr_locate(const CorrTable &tab, int blk)
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Lag matrices.  A workgroup (four product and four staging wavefronts) walks (image, strip) units: the strip of
-// all C channels with two halo rows below is staged in LDS (double buffered, the next unit's global loads in
-// flight under the products) with four zero columns left and right; the A operand of a k-step is channel tile
-// ct at four pixels, the B operand channel tile ct' at the pixels shifted by the lag.
-//   NT = 1 (C = 16): one tile pair; the four product wavefronts take every fourth group (four parts per block).
-//   NT = 2 (C = 32): four tile pairs, one per product wavefront.
-//   NT = 4 (C = 64): product wavefront w = A tile w and two of the four B tiles; two workgroups share a range of
-//   units (all 52 lag tiles per wavefront would leave one wavefront per SIMD).
-template <int NT>
-__global__ __launch_bounds__(512) void corr3_main_kernel(const CorrTable tab)
-{
-    extern __shared__ __align__(16) float corr_lds[];
-    constexpr int C = 16 * NT;
-    constexpr int KS = NT == 1 ? 4 : 1;        // wavefronts that split the pixel groups
-    constexpr int PW = NT == 4 ? 2 : 1;        // B tiles per wavefront
-    constexpr int HALVES = NT == 4 ? 2 : 1;    // workgroups that share a range of units (each takes half the B tiles)
-    constexpr int SCI = 2;                     // border-column cells per staging thread with a precomputed address
+// Lag matrices, on the bf16 units at fp32 accuracy (split_common.hpp: every value cut into three pieces, six products).
+// A workgroup (eight product and four staging wavefronts, one per CU) walks (image, strip) units: the strip of all C channels with two
+// halo rows below lies in LDS as octets, eight pixels of a row and channel in three pieces of 16 bytes (double buffered; the
+// loads of the next unit are in flight under the products, and the staging wavefronts cut and store it beside them).
+// A k-step is four octets, one per 16 lanes.  The sum over a row of x[c][a] x'[c'][a + dj] is taken as that of x[c][y - dj]
+// x'[c'][y]: the shift is applied to the A operand alone, in registers, from the octet and the pixel pairs beside it, so that
+// five shifts of A serve the three row lags of B, and all operands are aligned 16-byte reads.
+//   NT = 1 (C = 16): one tile pair; the product wavefronts take every eighth k-step.
+//   NT = 2 (C = 32): four tile pairs, each by two wavefronts with every second k-step.
+//   NT = 4 (C = 64): 16 tile pairs, half of them (two B tiles) in either of two workgroups that share a range of units.
+// Bound: MFMA, 78 of 16 cycles per k-step and wavefront, with 115 VALU operations and 16 operand reads beside them.  36 layers
+// of 16 x 32 x 32, batch 128: 159 us, 1185 TFLOP/s of bf16 products (the library's large split product runs at 1320, short of
+// power); 32 x 16 x 16: 147, 64 x 8 x 8: 154.  On the fp32 MFMA, at 120 of its 157 TFLOP/s: 261, 260 and 277 us.  The six products
+// interleaved by hand with the shifts and sums of their neighbours: no gain.  Six wavefronts a workgroup, two of them on a
+// CU, do not run together (their wavefronts 0 and 1 want the same SIMDs): 219, 175, 203 us.
+// A wavefront with a result that is not finite (inf or NaN in the input, values from 2^112 on) computes its tiles once
+// more on the fp32 MFMA from the input in memory, which leaves what fp32 arithmetic gives.
+constexpr int C3_PW = 8, C3_SW = 4;              // product and staging wavefronts: three a SIMD, of 168 registers
+constexpr int C3_THREADS = 64 * (C3_PW + C3_SW);
+constexpr int C3_ITEMS = 6;                      // octets per staging thread and slab at most (checked by the planner)
+constexpr int C3_OCT = 48;                       // bytes of an octet
+constexpr int C3_ZERO = 64;                      // bytes ahead of the slabs: an octet of zeros
+constexpr int corr3_ks(int C) { return C == 16 ? 8 : C == 32 ? 2 : 1; }       // product wavefronts that split the k-steps
+constexpr int corr3_rounds(int C) { return C == 16 ? 3 : C == 32 ? 1 : 0; }     // of the sum over them (log2)
+constexpr int C3_RED = 8192;                     // bytes of LDS for the channel sums, ahead of four wavefronts' lag tiles
+constexpr int corr3_tail_lds(int C) { return C3_RED + (corr3_ks(C) > 1 ? 4 * C3_LAGS * 64 * 16 : 0); }
+constexpr int corr3_sharers(int C) { return C == 64 ? 2 : 1; }  // workgroups that share a range of units
+constexpr __host__ __device__ int corr3_lag(int di, int dj) { return 5 * di + dj; }      // di = 0: dj = 0, 1, 2; else -2 .. 2
 
+template <int NT>
+__global__ __launch_bounds__(C3_THREADS, 3) void corr3_main_kernel(const CorrTable tab)
+{
+    extern __shared__ __align__(16) unsigned char corr_lds[];
+    constexpr int C = 16 * NT, KS = corr3_ks(C), SHARERS = corr3_sharers(C);
     const CorrProb &pr = tab.p[corr_locate(tab, blockIdx.x)];
     const int blk_raw = blockIdx.x - pr.blk_start;
-    const int blk = blk_raw / HALVES, half = blk_raw - blk * HALVES;
+    const int blk = blk_raw / SHARERS, share = blk_raw - blk * SHARERS;
     const int u0 = blk * pr.upb, u1 = min(pr.units, u0 + pr.upb);
-    const int lane = threadIdx.x & 63, w8 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int H = pr.H, W = pr.W, Wp = W + 8, SR = pr.SR, plane = pr.plane, w4 = W >> 2;
-    float *buf0 = corr_lds, *buf1 = corr_lds + C * plane;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int H = pr.H, W = pr.W, SR = pr.SR, plane = pr.plane;
+    const int opr = (W + 7) >> 3;                          // octets per image row
+    const unsigned slab = (unsigned)(C * plane * C3_OCT);
+    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.x), 0,
+                                                                        (int)((long)pr.B * C * H * W * 4), 0x00020000);   // below 2^31 (planner)
 
-    // Wavefronts 4 .. 7 stage the slabs, wavefronts 0 .. 3 only read operands and issue products.  Workgroups
-    // that share a CU advance at the same pace (the MFMA unit alternates between their wavefronts), so staging
-    // done by the product wavefronts themselves would fall into the same moments in all of them and leave the
-    // MFMA unit idle; as wavefronts of their own the loads, LDS stores and address arithmetic run beside it.
-    // One barrier per unit: past barrier `it` the slab of unit `it` is complete and every product wavefront is
-    // done with unit it - 1, whose buffer the staging wavefronts then fill with unit it + 1.
-    if (w8 >= 4) {
-        const int tid = threadIdx.x - 256;
-        // The slab is filled by global -> LDS copies of 1 KB (64 lanes x 16 bytes, consecutive in LDS): instruction
-        // i of a slab covers its 16-byte cells 64 i .. 64 i + 63; a lane whose cell is a pixel piece reads it from
-        // the input, a lane whose cell is padding (the four columns either side of a row, the tail of a plane)
-        // reads out of range, which stores zeros, and so does a halo row below the image.  Per unit that is at
-        // most MAXD copies per wavefront with precomputed lane offsets and one scalar base: every instruction of
-        // these wavefronts takes an issue slot from the product wavefronts of its SIMD.
-        constexpr int MAXD = 9;                    // copies per wavefront and slab at most (checked by the planner)
-        const int rows = SR + 2;
-        const int cells = C * plane / 4, ninstr = (cells + 63) / 64;
-        const int lw = w8 - 4;
-        unsigned vo[MAXD];
-        int vr[MAXD];                              // slab row of the cell (rows below the image are masked per unit)
-        bool vlive[MAXD];
+    // Wavefronts 8 .. 11 stage the slabs.  One barrier per unit: past barrier `it` the slab of unit `it` is complete and every
+    // product wavefront is done with unit it - 1, whose buffer is then filled with unit it + 1.
+    if (w >= C3_PW) {
+        const int tid = threadIdx.x - 64 * C3_PW, rows = SR + 2, per_c = rows * opr, nitems = C * per_c;
+        unsigned vo[C3_ITEMS];                             // byte offset of the octet in the image, from row a0 on
+        int vr[C3_ITEMS];                                  // its row of the slab
+        unsigned at[C3_ITEMS], co[C3_ITEMS];               // its place in a slab, and that of its row among the border columns
+        unsigned first = 0, last = 0;                      // bit per octet: it is the first, the last of its image row
+        float sums[C3_ITEMS];
+        floatx4 raw[2][C3_ITEMS][2];                       // the loads of two units in flight
 #pragma unroll
-        for (int j = 0; j < MAXD; ++j) {
-            const int q = (lw + 4 * j) * 64 + lane;
-            vo[j] = W_OOB;
-            vr[j] = 0;
-            vlive[j] = lw + 4 * j < ninstr && q < cells;
-            if (vlive[j]) {
-                const int f = 4 * q, c = f / plane, rem = f - c * plane;
-                const int r = rem / Wp, x = rem - r * Wp;
-                vr[j] = r;
-                if (r < rows && x >= 4 && x < 4 + W) vo[j] = (unsigned)(((c * H + r) * W + x - 4) * 4);
-            }
+        for (int j = 0; j < C3_ITEMS; ++j) {
+            const int q = tid + 64 * C3_SW * j, c = q / per_c, rem = q - c * per_c, r = rem / opr;
+            vr[j] = q < nitems ? r : 1 << 20;
+            vo[j] = (unsigned)(((c * H + r) * W + 8 * (rem - r * opr)) * 4);
+            at[j] = C3_ZERO + (unsigned)((c * plane + rem) * C3_OCT);
+            co[j] = (unsigned)(c * H + r);
+            first |= (rem == r * opr ? 1u : 0u) << j;
+            last |= (rem == r * opr + opr - 1 ? 1u : 0u) << j;
+            sums[j] = 0.f;
         }
-        int4v rsrc;
-        {
-            const unsigned long ba = (unsigned long)pr.x;
-            rsrc.x = (int)(unsigned)ba;
-            rsrc.y = (int)(unsigned)(ba >> 32);
-            rsrc.z = (int)((long)pr.B * C * H * W * 4);          // below 2^31 (checked by the planner)
-            rsrc.w = 0x00020000;
-        }
-        const unsigned lds0 = (unsigned)(unsigned long)(__attribute__((address_space(3))) float *)corr_lds;
-        const unsigned slab_bytes = (unsigned)(C * plane * 4);
-        auto issue = [&](unsigned dst, int u) {
+        if (tid < C3_ZERO / 4) reinterpret_cast<float *>(corr_lds)[tid] = 0.f;
+        auto load = [&](int u, floatx4 (&x)[C3_ITEMS][2]) {        // past the last unit: nothing is read
             const int n = u / pr.strips, a0 = (u - n * pr.strips) * SR;
             const unsigned so = (unsigned)((n * C * H + a0) * W) * 4u;
-            const bool tail = a0 + rows > H;       // uniform: this slab reaches below the image
 #pragma unroll
-            for (int j = 0; j < MAXD; ++j) {
-                if (lw + 4 * j < ninstr) {         // uniform
-                    const unsigned v = (tail && a0 + vr[j] >= H) ? W_OOB : vo[j];
-                    const unsigned to = (unsigned)__builtin_amdgcn_readfirstlane((int)(dst + (unsigned)(lw + 4 * j) * 1024u));
-                    if (vlive[j]) dma16(to, v, rsrc, (unsigned)__builtin_amdgcn_readfirstlane((int)so));
-                }
+            for (int j = 0; j < C3_ITEMS; ++j) {
+                const bool in = u < u1 && a0 + vr[j] < H;
+                const bool half = (W & 4) && (last >> j & 1);      // four of its pixels lie past the row
+                x[j][0] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rx, in ? vo[j] : W_OOB, so, 0));
+                x[j][1] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rx, in && !half ? vo[j] + 16u : W_OOB, so, 0));
             }
         };
-        // the first and the last pixel of every image row also go to a compact buffer (the border kernel would
-        // otherwise pull a whole cache line per pixel of those two columns): read back from the slab,
-        // consecutive threads = consecutive rows of a channel
-        int sc_l[SCI], sc_g[SCI];
-#pragma unroll
-        for (int j = 0; j < SCI; ++j) {
-            const int t = tid + 256 * j;
-            sc_l[j] = -1;
-            sc_g[j] = 0;
-            if (NT != 4 && t < 2 * C * SR) {
-                const int side = t / (C * SR), rem = t - side * (C * SR);
-                const int c = rem / SR, r = rem - c * SR;
-                sc_l[j] = c * plane + r * Wp + 4 + (side ? W - 1 : 0);
-                sc_g[j] = (side * C + c) * H + r;
-            }
-        }
-        auto save_cols = [&](const float *b, int u) {
-            if (NT == 4) return;             // 64 channels: short columns, the border kernel reads them from the input
+        auto store = [&](int u, const floatx4 (&x)[C3_ITEMS][2], int buf) {
             const int n = u / pr.strips, a0 = (u - n * pr.strips) * SR;
-            float *cbase = pr.cols + (long)n * 2 * C * H + a0;
 #pragma unroll
-            for (int j = 0; j < SCI; ++j)
-                if (sc_l[j] >= 0) cbase[sc_g[j]] = b[sc_l[j]];
-            for (int t = tid + 256 * SCI; t < 2 * C * SR; t += 256) {
-                const int side = t / (C * SR), rem = t - side * (C * SR);
-                const int c = rem / SR, r = rem - c * SR;
-                cbase[(side * C + c) * H + r] = b[c * plane + r * Wp + 4 + (side ? W - 1 : 0)];
+            for (int j = 0; j < C3_ITEMS; ++j) {
+                if (64 * C3_SW * j >= nitems) continue;    // uniform
+                if (vr[j] >= rows) continue;
+                float x0[4], x1[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { x0[e] = x[j][0][e]; x1[e] = x[j][1][e]; }
+                if (vr[j] < SR) {
+                    sums[j] += ((x0[0] + x0[1]) + (x0[2] + x0[3])) + ((x1[0] + x1[1]) + (x1[2] + x1[3]));
+                    // the first and the last pixel of every image row also go to a compact buffer (the border kernel would
+                    // otherwise pull a whole cache line per pixel; 64 channels have short columns, read from the input)
+                    if (NT != 4 && a0 + vr[j] < H) {
+                        float *cols = pr.cols + (long)n * 2 * C * H + a0;
+                        if (first >> j & 1) cols[co[j]] = x0[0];
+                        if (last >> j & 1) cols[co[j] + (unsigned)(C * H)] = (W & 4) ? x0[3] : x1[3];
+                    }
+                }
+                SplitCut k0, k1;
+                suint4 *to = reinterpret_cast<suint4 *>(corr_lds + at[j] + (unsigned)buf * slab);
+                k0.scale(x0); k1.scale(x1);
+#pragma unroll
+                for (int piece = 0; piece < 2; ++piece) {
+                    k0.half(x0, 0, 4); k1.half(x1, 0, 4);
+                    const suint2 p = k0.pack(), r = k1.pack();
+                    to[piece] = suint4{p.x, p.y, r.x, r.y};
+                    k0.top(0, 4); k1.top(0, 4);
+                    k0.rest(x0, 0, 4); k1.rest(x1, 0, 4);
+                }
+                const suint2 p = k0.pack_last(x0), r = k1.pack_last(x1);
+                to[2] = suint4{p.x, p.y, r.x, r.y};
             }
         };
-        if (u0 < u1) issue(lds0, u0);
-        for (int u = u0, it = 0; u < u1; ++u, ++it) {
-            float *b = (it & 1) ? buf1 : buf0;
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // the copies of this unit have landed
+        load(u0, raw[0]);
+        __builtin_amdgcn_sched_barrier(0);
+        load(u0 + 1, raw[1]);
+        for (int u = u0; u < u1; u += 2) {                 // (no condition on the loads: their number is what the waits count)
+            store(u, raw[0], 0);
+            __builtin_amdgcn_sched_barrier(0);
+            load(u + 2, raw[0]);
             __syncthreads();
-            // the other buffer is free now: every product wavefront is past unit it - 1
-            if (u + 1 < u1) issue(lds0 + ((it & 1) ? 0u : slab_bytes), u + 1);
-            save_cols(b, u);                    // the slab stays as it is until the barrier after next
+            if (u + 1 >= u1) break;
+            store(u + 1, raw[1], 1);
+            __builtin_amdgcn_sched_barrier(0);
+            load(u + 3, raw[1]);
+            __syncthreads();
         }
+        // channel sums: the octets of a channel in order
+        __syncthreads();
+        float *red = reinterpret_cast<float *>(corr_lds);
+#pragma unroll
+        for (int j = 0; j < C3_ITEMS; ++j)
+            if (tid + 64 * C3_SW * j < nitems) red[tid + 64 * C3_SW * j] = sums[j];
+        static_assert(C3_ITEMS * 64 * C3_SW * 4 <= C3_RED, "the channel sums fit");
+        __syncthreads();
+        if (share == 0 && tid < C) {
+            float t = 0.f;
+            for (int o = 0; o < SR * opr; ++o) t += red[tid * per_c + o];
+            pr.Fp[(long)pr.parts * (C3_LAGS * C * C) + (long)blk * C + tid] = t;
+        }
+        for (int r = 1; r < corr3_rounds(C); ++r) __syncthreads();
         return;
     }
 
-    const int w = w8;
     const int lr = lane & 15, kk = lane >> 4;
-    int ct, ctp0;
-    if (NT == 1) { ct = 0; ctp0 = 0; }
-    else if (NT == 2) { ct = w >> 1; ctp0 = w & 1; }
-    else { ct = w; ctp0 = 2 * half; }
-
-    floatx4 acc[PW][C3_LAGS];
+    const int ct = NT == 1 ? 0 : NT == 2 ? (w >> 1) & 1 : w & 3;
+    const int ctp = NT == 1 ? 0 : NT == 2 ? w & 1 : 2 * share + (w >> 2);
+    floatx4 acc[C3_LAGS];
 #pragma unroll
-    for (int p = 0; p < PW; ++p)
-#pragma unroll
-        for (int l = 0; l < C3_LAGS; ++l) acc[p][l] = floatx4{0.f, 0.f, 0.f, 0.f};
-    float tsum = 0.f;
+    for (int l = 0; l < C3_LAGS; ++l) acc[l] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // A group is 16 consecutive pixels of the strip (row-major); lane kk holds pixels 4 kk .. 4 kk + 3 of it and
-    // k-step e of the group takes pixel 4 kk + e from every lane.  For the shifted operand a lane reads, per
-    // row lag, the window around its four pixels: every lag (di, dj) of k-step e is element e + dj of the window
-    // of row di, a register chosen at compile time.
-    // A stage is one group and one B tile: 52 products on 9 operand reads.  Two register sets alternate, the
-    // reads of the next stage are issued before the products of the current one (all wavefronts of a SIMD
-    // advance at the same pace, so none of them would cover the read latency of another).
-    const int ngroups = SR * W / 16;
-    const int gfirst = (KS == 4) ? w : 0;
-    const int nstages = ((ngroups - gfirst + KS - 1) / KS) * PW;
-    const int q0 = 16 * gfirst + 4 * kk;                       // first pixel of this lane in its first group
-    const int row0 = q0 / W, col0 = q0 - row0 * W;
-    const int drow = (16 * KS) / W, dcol = 16 * KS - drow * W;  // from a group to the next of this wavefront
+    const int noct = SR * opr;                                 // octets of a strip
+    const int gfirst = NT == 1 ? w : NT == 2 ? w >> 2 : 0;
+    const int nsteps = ((noct + 3) / 4 - gfirst + KS - 1) / KS;
+    const int dcol = (4 * KS) % opr;
     for (int u = u0, it = 0; u < u1; ++u, ++it) {
-        float *b = (it & 1) ? buf1 : buf0;
         __syncthreads();
-        const float *pa = b + (16 * ct + lr) * plane + 4;
-        const float *pb[PW];
+        const unsigned b0 = C3_ZERO + (unsigned)(it & 1) * slab;
+        const unsigned pa = b0 + (unsigned)((16 * ct + lr) * plane * C3_OCT);
+        const unsigned pb = b0 + (unsigned)((16 * ctp + lr) * plane * C3_OCT);
+        int o = 4 * gfirst + kk, col = o % opr;
+        for (int s = 0; s < nsteps; ++s) {
+            const bool live = o < noct;
+            const unsigned oa = live ? pa + (unsigned)(o * C3_OCT) : 0u;
+            const unsigned op = live && col > 0 ? oa - C3_OCT + 12u : 0u;          // the pixel pairs beside the octet
+            const unsigned on = live && col + 1 < opr ? oa + C3_OCT : 0u;
+            const unsigned ob = pb + (unsigned)((live ? o : 0) * C3_OCT);
+            suint4 m[3], b[3][3];
+            unsigned p[3], n[3];
 #pragma unroll
-        for (int p = 0; p < PW; ++p) pb[p] = b + (16 * (ctp0 + p) + lr) * plane + 4;
-        // operand registers of a set: the four pixels of the A tile, and per row lag the window elements that
-        // some lag uses (pixels -2 .. 5 around the lane's first pixel; 0 .. 5 for row lag 0), read as 8 + 16 + 8 bytes
-        typedef float floatx2 __attribute__((ext_vector_type(2)));
-        floatx4 a4[2], wmid[2][3];
-        floatx2 wlo[2][3], whi[2][3];
-        auto load = [&](int set, int base, int p) {
-            a4[set] = *reinterpret_cast<const floatx4 *>(pa + base);
-#pragma unroll
-            for (int di = 0; di < 3; ++di) {
-                const float *q = pb[p] + base + di * Wp;
-                if (di > 0) wlo[set][di] = *reinterpret_cast<const floatx2 *>(q - 2);
-                wmid[set][di] = *reinterpret_cast<const floatx4 *>(q);
-                whi[set][di] = *reinterpret_cast<const floatx2 *>(q + 4);
+            for (int e = 0; e < 3; ++e) {
+                m[e] = *reinterpret_cast<const suint4 *>(corr_lds + oa + 16 * e);
+                p[e] = *reinterpret_cast<const unsigned *>(corr_lds + op + 16 * e);
+                n[e] = *reinterpret_cast<const unsigned *>(corr_lds + on + 16 * e);
             }
-        };
-        auto products = [&](int set, int p) {
-            if (p == 0) tsum += (a4[set].x + a4[set].y) + (a4[set].z + a4[set].w);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
+            for (int di = 0; di < 3; ++di)
 #pragma unroll
-                for (int l = 0; l < C3_LAGS; ++l) {
-                    const int di = l < 3 ? 0 : (l < 8 ? 1 : 2);
-                    const int dj = l < 3 ? l : (l < 8 ? l - 5 : l - 10);
-                    const int idx = e + dj;                           // -2 .. 5 relative to the lane's first pixel
-                    const float bv = idx < 0 ? wlo[set][di][idx + 2] : (idx < 4 ? wmid[set][di][idx] : whi[set][di][idx - 4]);
-                    acc[p][l] = __builtin_amdgcn_mfma_f32_16x16x4f32(a4[set][e], bv, acc[p][l], 0, 0, 0);
+                for (int e = 0; e < 3; ++e)
+                    b[di][e] = *reinterpret_cast<const suint4 *>(corr_lds + ob + (unsigned)(di * opr * C3_OCT) + 16 * e);
+#pragma unroll
+            for (int k = 0; k < 5; ++k) {
+                constexpr int order[5] = {0, 1, 2, -1, -2};
+                const int dj = order[k];
+                suint4 f[3];
+#pragma unroll
+                for (int e = 0; e < 3; ++e) {
+                    const suint4 q = m[e];
+                    if (dj == 0) f[e] = q;
+                    else if (dj == 2) f[e] = suint4{p[e], q.x, q.y, q.z};
+                    else if (dj == -2) f[e] = suint4{q.y, q.z, q.w, n[e]};
+                    else if (dj == 1)
+                        f[e] = suint4{__builtin_amdgcn_alignbit(q.x, p[e], 16), __builtin_amdgcn_alignbit(q.y, q.x, 16),
+                                      __builtin_amdgcn_alignbit(q.z, q.y, 16), __builtin_amdgcn_alignbit(q.w, q.z, 16)};
+                    else
+                        f[e] = suint4{__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
+                                      __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(n[e], q.w, 16)};
                 }
-        };
-        // Positions run one stage ahead of the reads, which run one stage ahead of the products: no address
-        // arithmetic and no branch between the reads of a stage and the products before them.
-        int row = row0, col = col0;
-        auto advance = [&](bool take, int base) {               // next group of this wavefront, if there is one
-            int c = col + dcol, r = row + drow;
-            const bool wrap = c >= W;
-            c -= wrap ? W : 0;
-            r += wrap ? 1 : 0;
-            col = take ? c : col;
-            row = take ? r : row;
-            return take ? r * Wp + c : base;
-        };
-        const int b0 = row0 * Wp + col0;
-        if (nstages > 0) load(0, b0, 0);        // a wavefront without a group has no valid address to read
-        int b1 = PW == 1 ? advance(1 < nstages, b0) : b0;
-        for (int s = 0; s < nstages; s += 2) {
-            // stage s sits in set 0; with two B tiles per wavefront stage s + 1 is the same group, second tile.
-            // The reads are unconditional (past the last stage they repeat a valid address and are dropped):
-            // reads under a branch of their own would be moved down to the products that use them.
-            const bool more1 = s + 1 < nstages;
-            load(1, b1, PW - 1);
-            const int b2 = advance(s + 2 < nstages, b1);
-            products(0, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 9, 0);      // the reads first,
-            __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);      // the address arithmetic under the products
-            __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 48, 0);
-            if (more1) {
-                load(0, b2, 0);
-                b1 = PW == 1 ? advance(s + 3 < nstages, b2) : b2;
-                products(1, PW - 1);
-                __builtin_amdgcn_sched_group_barrier(0x100, 9, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 16, 0);
-                __builtin_amdgcn_sched_group_barrier(0x008, 48, 0);
+                // The MFMA cuts off the low bits of what it adds to an accumulator: the six products of a k-step are summed from
+                // zero, smallest first, and added to the running sum with round-to-nearest.  (One chain over 64 k-steps: error
+                // of the factor 1.3e-6 on zero-mean data; this way 5e-8, and 1.1e-7 on the fp32 MFMA.)
+                constexpr int fa[6] = {1, 0, 2, 0, 1, 0}, fb[6] = {1, 2, 0, 1, 0, 0};
+                floatx4 sum[3] = {};
+#pragma unroll
+                for (int t = 0; t < 6; ++t)
+#pragma unroll
+                    for (int di = dj < 0 ? 1 : 0; di < 3; ++di)
+                        sum[di] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(sbf16x8, f[fa[t]]), __builtin_bit_cast(sbf16x8, b[di][fb[t]]), sum[di], 0, 0, 0);
+#pragma unroll
+                for (int di = dj < 0 ? 1 : 0; di < 3; ++di) acc[corr3_lag(di, dj)] += sum[di];
             }
+            o += 4 * KS;
+            col += dcol;
+            col -= col >= opr ? opr : 0;
         }
     }
-
-    // channel sums: the four k-lanes of a channel
-    tsum += __shfl_xor(tsum, 16);
-    tsum += __shfl_xor(tsum, 32);
-    const int part = blk * KS + (KS == 4 ? w : 0);
-    float *Fo = pr.Fp + (long)part * (C3_LAGS * C * C);
+    bool bad = false;
 #pragma unroll
-    for (int p = 0; p < PW; ++p)
+    for (int l = 0; l < C3_LAGS; ++l)
 #pragma unroll
-        for (int l = 0; l < C3_LAGS; ++l)
+        for (int v = 0; v < 4; ++v) {
+            bad |= !(fabsf(acc[l][v]) < __builtin_inff());
+            acc[l][v] *= kSplitUnscale;
+        }
+    if (__any(bad)) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                Fo[(l * C + 16 * ct + 4 * kk + v) * C + 16 * (ctp0 + p) + lr] = acc[p][l][v];
-    if (ctp0 == 0 && kk == 0)
-        pr.Fp[(long)pr.parts * (C3_LAGS * C * C) + (long)part * C + 16 * ct + lr] = tsum;
+        for (int l = 0; l < C3_LAGS; ++l) acc[l] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const int ca = 16 * ct + lr, cb = 16 * ctp + lr;
+        for (int u = u0; u < u1; ++u) {
+            const int img = u / pr.strips, a0 = (u - img * pr.strips) * SR;
+            const unsigned so = (unsigned)(img * C * H * W) * 4u;
+            auto pixel = [&](int c, int row, int x) {
+                return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    rx, row < H && x >= 0 && x < W ? (unsigned)(((c * H + row) * W + x) * 4) : W_OOB, so, 0));
+            };
+            for (int s = 0; s < nsteps; ++s)
+                for (int o = 4 * (gfirst + s * KS); o < min(noct, 4 * (gfirst + s * KS) + 4); ++o) {
+                    const int row = a0 + o / opr, y0 = 8 * (o % opr) + kk;
+                    for (int y = y0; y < y0 + 8; y += 4) {
+                        float a[5], b[3];
+#pragma unroll
+                        for (int k = 0; k < 5; ++k) a[k] = pixel(ca, row, y - (k - 2));
+#pragma unroll
+                        for (int di = 0; di < 3; ++di) b[di] = pixel(cb, row + di, y);
+#pragma unroll
+                        for (int di = 0; di < 3; ++di)
+#pragma unroll
+                            for (int dj = di ? -2 : 0; dj < 3; ++dj)
+                                acc[corr3_lag(di, dj)] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[dj + 2], b[di], acc[corr3_lag(di, dj)], 0, 0, 0);
+                    }
+                }
+        }
+    }
+    // sum over the wavefronts that split the k-steps, halving their number: the upper half leaves its tiles in LDS, the lower
+    // half adds them to its own (every place is read by the wavefront that writes it in the next round)
+    __syncthreads();       // the slabs are free, here and for the channel sums
+    int half = 4;
+    auto place = [&](int slot, int l) -> floatx4 & {
+        return *reinterpret_cast<floatx4 *>(corr_lds + C3_RED + (unsigned)(((slot * C3_LAGS + l) * 64 + lane) * 16));
+    };
+#pragma unroll
+    for (int r = 0; r < (KS > 1 ? corr3_rounds(C) : 1); ++r) {
+        if (KS > 1 && w >= half && w < 2 * half)
+#pragma unroll
+            for (int l = 0; l < C3_LAGS; ++l) place(w & 3, l) = acc[l];
+        __syncthreads();
+        if (KS > 1 && w < half)
+#pragma unroll
+            for (int l = 0; l < C3_LAGS; ++l) acc[l] += place((w + half) & 3, l);
+        half >>= 1;
+    }
+    if (KS > 1 && gfirst != 0) return;
+    float *Fo = pr.Fp + (long)blk * (C3_LAGS * C * C);
+#pragma unroll
+    for (int l = 0; l < C3_LAGS; ++l)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            Fo[(l * C + 16 * ct + 4 * kk + v) * C + 16 * ctp + lr] = acc[l][v];
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -615,14 +656,27 @@ __global__ __launch_bounds__(256) void corr3_border_plane_kernel(const CorrTable
     }
 }
 
-// Sums over the parts (lag matrices, channel sums) and over the image chunks (border terms), fixed order.
+// Sums over the parts (lag matrices, channel sums) and over the image chunks (border terms), fixed order.  A thread takes four
+// consecutive elements of a matrix.  A network of few layers has many parts a layer (256 of one layer of 16 channels, whose 13
+// matrices are 832 threads' work): from 32 parts on, 16 threads share an element (346 -> 72 us for
+// the factor of one layer of 16 x 32 x 32, batch 128, together with the sum over the wavefronts of a block; the 108 layers of
+// a network of three widths, 3 to 7 parts each, take 21 us without).
+constexpr int C3_SLICES = 16;
+constexpr int corr3_slices(int parts) { return parts >= 32 ? C3_SLICES : 1; }
+inline int corr3_sum_blocks(int C, int parts, int &fblocks)
+{
+    fblocks = (C3_LAGS * C * C / 4 * corr3_slices(parts) + 255) / 256;
+    return fblocks + (C3_BQ * C * C / 4 + (1 + C3_BV) * C + 255) / 256;
+}
+
 __global__ __launch_bounds__(256) void corr3_sum_kernel(const CorrTable tab)
 {
+    __shared__ floatx4 slice_sum[C3_SLICES][256 / C3_SLICES];
     const CorrProb &pr = tab.p[corr_locate(tab, blockIdx.x)];
     const int C = pr.C, cc = C * C;
     const long nF = (long)C3_LAGS * cc, nB = (long)C3_BQ * cc;
     const long qF = nF / 4, qB = nB / 4;            // matrices: four consecutive elements (one row) per thread
-    const long q = (long)(blockIdx.x - pr.blk_start) * 256 + threadIdx.x;
+    const int local = blockIdx.x - pr.blk_start;
     auto store_both = [&](float *dst, float *dstT, long e, const floatx4 &v) {
         *reinterpret_cast<floatx4 *>(dst + e) = v;
         const int l = (int)(e / cc), rem = (int)(e - (long)l * cc), c = rem / C, c2 = rem - c * C;
@@ -630,30 +684,55 @@ __global__ __launch_bounds__(256) void corr3_sum_kernel(const CorrTable tab)
 #pragma unroll
         for (int i = 0; i < 4; ++i) t[(long)i * C] = v[i];
     };
-    if (q < qF) {
+    if (local < pr.fblocks) {
+        const int sl = corr3_slices(pr.parts);
+        const int first = sl == 1 ? 0 : threadIdx.x / (256 / C3_SLICES);
+        const long q = sl == 1 ? (long)local * 256 + threadIdx.x : (long)local * (256 / C3_SLICES) + threadIdx.x % (256 / C3_SLICES);
+        const long e = 4 * min(q, qF - 1);
+        // the matrix of lag 0 is symmetric up to the order of its piece products: both halves from the lower one
+        const int row = (int)(e / C), col = (int)(e - (long)row * C);
+        const bool mirrored = e < cc && col + 3 > row;
+        auto part = [&](int p) -> floatx4 {
+            const float *src = pr.Fp + (long)p * nF;
+            if (!mirrored) return *reinterpret_cast<const floatx4 *>(src + e);
+            floatx4 v;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = src[(long)max(row, col + i) * C + min(row, col + i)];
+            return v;
+        };
         // four interleaved running sums (fixed order) keep loads in flight
-        const long e = 4 * q;
         floatx4 a[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) a[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-        int p = 0;
-        for (; p + 4 <= pr.parts; p += 4)
+        int p = first;
+        for (; p + 3 * sl < pr.parts; p += 4 * sl)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) a[j] += *reinterpret_cast<const floatx4 *>(pr.Fp + (long)(p + j) * nF + e);
-        for (; p < pr.parts; ++p) a[0] += *reinterpret_cast<const floatx4 *>(pr.Fp + (long)p * nF + e);
-        store_both(pr.Fs, pr.FsT, e, (a[0] + a[1]) + (a[2] + a[3]));
-    } else if (q < qF + qB) {
-        const long i = 4 * (q - qF);
+            for (int j = 0; j < 4; ++j) a[j] += part(p + j * sl);
+        for (; p < pr.parts; p += sl) a[0] += part(p);
+        floatx4 sum = (a[0] + a[1]) + (a[2] + a[3]);
+        if (sl > 1) {
+            slice_sum[first][threadIdx.x % (256 / C3_SLICES)] = sum;
+            __syncthreads();
+            if (first > 0) return;
+            for (int k = 1; k < C3_SLICES; ++k) sum += slice_sum[k][threadIdx.x];
+        }
+        if (q < qF) store_both(pr.Fs, pr.FsT, e, sum);
+        return;
+    }
+    const long q = (long)(local - pr.fblocks) * 256 + threadIdx.x;
+    if (q < qB) {
+        const long i = 4 * q;
         floatx4 sum = {0.f, 0.f, 0.f, 0.f};
         for (int k = 0; k < C3_CHUNKS; ++k) sum += *reinterpret_cast<const floatx4 *>(pr.Bp + (long)k * nB + i);
         store_both(pr.Bs, pr.BsT, i, sum);
-    } else if (q < qF + qB + C) {
-        const long c = q - qF - qB;
+    } else if (q < qB + C) {
+        const long c = q - qB;
         float sum = 0.f;
+#pragma unroll 8
         for (int p = 0; p < pr.parts; ++p) sum += pr.Fp[(long)pr.parts * nF + (long)p * C + c];
         pr.Fs[nF + c] = sum;
-    } else if (q < qF + qB + C + C3_BV * C) {
-        const long i = q - qF - qB - C;
+    } else if (q < qB + C + C3_BV * C) {
+        const long i = q - qB - C;
         float sum = 0.f;
         for (int k = 0; k < C3_CHUNKS; ++k) sum += pr.Bp[(long)C3_CHUNKS * nB + (long)k * (C3_BV * C) + i];
         pr.Bs[nB + i] = sum;
