@@ -9,7 +9,7 @@
 // parts), 1.2 the six levels of merges, 0.5 dc_back.  Error of Eq. 13's result against float64 at order 577: 1.1e-5 with
 // Jacobi, 2.1e-6 here.
 //   dc_init       the lower triangle mirrored into the working matrix, vectors cleared
-//   dc_tridiag    a workgroup of 16 wavefronts per matrix (all matrices at once, each on a CU of its own)
+//   dc_tridiag    a workgroup of 8 wavefronts per matrix (all matrices at once, each on a CU of its own)
 //   dc_leaf       the tree of halved tridiagonal matrices ends at orders up to 16: two-sided Jacobi in LDS, fp64
 //   per level     dc_deflate (a workgroup per merge), dc_secular (16 lanes per root), dc_vectors (the orthogonal matrix of
 //                 the rank-one problem), dc_product (its product with the vectors so far, fp32 MFMA)
