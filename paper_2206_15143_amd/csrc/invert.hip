@@ -132,8 +132,8 @@ struct BlkProb {
     float *Vt;         // [PB, ldv]
     float *Wt;         // [PB, ldv]
     float *S;          // [PB, pb] the pivot block before its inversion, both triangles, or null
-    int *gate;         // two words: bit patterns of the maximum norms of S and of P (see blk_cond_kernel)
-    float gate_cond;   // the refinement runs when their product exceeds this
+    int *gate;         // two words: bit patterns of the maximum norms of S and of P (blk_cond_kernel), those of the next
+                       // step, to be cleared (blk_gather_kernel), or null
     const float *P;    // [PB, PB] inverse of the pivot block
     int *info;
     const int *ninfo;  // status of the pivot block inversion (0 or 1-based pivot index inside the block)
@@ -151,15 +151,11 @@ struct BlkTable {
 // maximum norm, ||S|| ||P|| with the largest absolute row sums (S from the lower triangle of the working matrix,
 // P from the nested inversion).  A workgroup per 32 rows forms the sums of its rows and folds their largest into
 // gate[0] (S) and gate[1] (P) with an integer atomic maximum on the bit patterns (the values are not negative:
-// the order is the same and the result does not depend on the order of arrival).  The gather kernel and the two
-// refinement products compare the product of the two with the threshold; the scatter kernel at the end of the
-// step clears both words for the next one.  (A comparison with a NaN is false: a block whose inversion failed
-// is left alone, its matrix is already flagged.)
-__device__ __forceinline__ bool blk_gate_open(const int *gate, float cond)
-{
-    return __int_as_float(gate[0]) * __int_as_float(gate[1]) > cond;
-}
-
+// the order is the same and the result does not depend on the order of arrival).  The refinement products of the panel
+// and of the chain compare the product of the two with the threshold.  Steps take the two pairs of words in turn; the
+// gather kernel of a step clears the pair of the step before for the step after it: it is behind all that reads the one
+// (panel and chain of the step before) and ahead of what writes the other.  (A comparison with a NaN is false: a block whose
+// inversion failed is left alone, its matrix is already flagged.)
 __global__ __launch_bounds__(256) void blk_cond_kernel(const BlkTable tab)
 {
     __shared__ float part[3][8][33];
@@ -232,6 +228,7 @@ __global__ __launch_bounds__(256) void blk_gather_kernel(const BlkTable tab)
     const long n = pr.n;
     const int p0 = pr.p0, p1 = pr.p0 + pr.bs;
     float *S = pr.S;      // null unless the refinement is on
+    if (local == 0 && threadIdx.x == 0 && pr.gate) { pr.gate[0] = 0; pr.gate[1] = 0; }
     // p0 and p1 are multiples of 32 (or p1 = n): a tile lies wholly in one of the three regions
     if (g0 < p0) {
 #pragma unroll
@@ -289,7 +286,6 @@ __global__ __launch_bounds__(256) void blk_scatter_kernel(const BlkTable tab)
     if (local == 0 && threadIdx.x == 0) {
         const int f = *pr.ninfo;
         if (f != 0 && *pr.info == 0) *pr.info = p0 + f;
-        if (pr.gate) { pr.gate[0] = 0; pr.gate[1] = 0; }   // for the next step's blk_cond_kernel
     }
     if (g0 < p0) {
 #pragma unroll
@@ -609,8 +605,7 @@ hipError_t BlockedRun::copy_kernel(int what, int st, int act, hipStream_t s)
             p.W = j.Minv; p.Vt = big[g0 + k].Vt[st & 1]; p.Wt = big[g0 + k].Wt[st & 1];
             p.P = big[g0 + k].P[st & 1];
             p.S = (refine && !scatter) ? big[g0 + k].S[st & 1] : nullptr;   // the condition test reads the matrix itself
-            p.gate = refine ? gate(g0 + k, st) : nullptr;
-            p.gate_cond = (float)tuning().invert_refine_cond;
+            p.gate = !refine || scatter ? nullptr : gate(g0 + k, what == 0 ? st + 1 : st);
             p.info = j.info; p.ninfo = ninfo(g0 + k, st);
             p.n = j.n; p.ldv = big[g0 + k].ldv; p.p0 = p0; p.bs = std::min(PB, j.n - p0); p.pb = PB;
             p.blk_start = blocks;
@@ -885,10 +880,12 @@ hipError_t blocked_serial(BlockedRun &run, hipStream_t s)
 //             bulk update without that band [bulk]
 // The chain needs nothing of the panel but its gather, for which it waits through the caller's stream: two streams that wait
 // for each other's events and are both forked from a captured one end the process when the capture ends.
-// What keeps the buffers apart: panels st (buffer st mod 2) are overwritten by gather(st + 2), which waits for band(st + 1), behind bulk(st) on its stream, and for next(st + 1); inverse
-// st by nest(st + 2), behind next(st + 1), which waits for bulk(st), behind panel(st); the next pivot block, which next(st)
-// updates, last by bulk(st - 1); pivot block st, which cond(st) reads and gather(st) copies, is overwritten by the
-// scatter of panel(st), behind both.
+// What keeps the buffers apart: panels st (buffer st mod 2) are overwritten by gather(st + 2), which waits for band(st + 1),
+// behind bulk(st) on its stream, and for next(st + 1); inverse st by nest(st + 2), behind next(st + 1), which waits for bulk(st),
+// behind panel(st); the next pivot block, which next(st) updates, last by bulk(st - 1); pivot block st, which cond(st) reads and
+// gather(st) copies, is overwritten by the scatter of panel(st), behind both; gate words st (pair st mod 2), which panel(st)
+// and next(st) read, are cleared by gather(st + 1), behind the one on its stream and waiting for the other, and written
+// by cond(st + 2), behind next(st + 1), which waits for gather(st + 1).
 hipError_t blocked_lookahead(BlockedRun &run, AuxStreams *aux, hipStream_t s)
 {
     hipError_t e = run.start(s);

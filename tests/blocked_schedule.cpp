@@ -1,0 +1,295 @@
+// What an inversion call enqueues, recorded on the host: every launch with the memory its kernel reads and writes, every
+// event recorded and waited for.  Prints the pairs of launches that touch the same memory, at least one of them writing,
+// and that neither the order of a stream nor an event puts in an order.  Compiled and run by test_blocked_schedule.py; needs no GPU:
+// the calls of the runtime that the host code makes are answered here and only noted down, no kernel runs.
+//
+//   blocked_schedule REFINE ORDER...      two calls in a row on one stream, with the same buffers
+#include "../paper_2206_15143_amd/csrc/common.hpp"
+
+#include <algorithm>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+struct Node {
+    std::string kernel;                        // empty: an event recorded or waited for
+    hipStream_t stream;
+    std::vector<std::vector<char>> args;
+    std::vector<int> before;                   // nodes that come directly before
+};
+static std::vector<Node> nodes;
+static std::map<hipStream_t, int> last_of;     // last node of a stream
+static std::map<hipEvent_t, int> record_of;    // node of an event's last record
+
+static Node &add(hipStream_t s)
+{
+    nodes.push_back(Node{"", s, {}, {}});
+    if (last_of.count(s)) nodes.back().before.push_back(last_of[s]);
+    last_of[s] = (int)nodes.size() - 1;
+    return nodes.back();
+}
+template <class T>
+static std::vector<char> bytes_of(const T &x)
+{
+    const char *p = reinterpret_cast<const char *>(&x);
+    return std::vector<char>(p, p + sizeof(T));
+}
+template <class... T>
+static void note_launch(const char *kernel, hipStream_t s, const T &...args)
+{
+    Node &n = add(s);
+    n.kernel = kernel;
+    n.args = {bytes_of(args)...};
+}
+
+#undef KFAC_LAUNCH
+#define KFAC_LAUNCH(cls, stream, kernel, grid, block, smem, ...) note_launch(#kernel, stream, __VA_ARGS__)
+#include "../paper_2206_15143_amd/csrc/gemm.hip"
+#include "../paper_2206_15143_amd/csrc/invert.hip"
+
+// ---- the runtime -----------------------------------------------------------------------------------------------
+static uintptr_t handles = 0x1000;
+extern "C" {
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { add(s); record_of[e] = (int)nodes.size() - 1; return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
+{
+    Node &n = add(s);
+    if (record_of.count(e)) n.before.push_back(record_of[e]);
+    return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)(handles += 16); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { *e = (hipEvent_t)(handles += 16); return hipSuccess; }
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipLaunchKernel(const void *, dim3, dim3, void **, size_t, hipStream_t) { abort(); }
+hipError_t __hipPopCallConfiguration(dim3 *, dim3 *, size_t *, hipStream_t *) { abort(); }
+void **__hipRegisterFatBinary(const void *) { static void *none; return &none; }
+void __hipRegisterFunction(void **, const void *, char *, const char *, unsigned, void *, void *, void *, void *, int *) {}
+void __hipUnregisterFatBinary(void **) {}
+}
+namespace kfac {
+Tuning &tuning() { static Tuning t; return t; }
+bool timing_active() { return false; }
+void timing_begin(int, hipStream_t) {}
+void timing_end(hipStream_t) {}
+void timing_work(double, double) {}
+}  // namespace kfac
+
+// ---- what the kernels touch ------------------------------------------------------------------------------------
+using namespace kfac;
+typedef std::pair<uintptr_t, uintptr_t> Range;
+struct Set {
+    std::vector<Range> r;
+    void put(const void *p, size_t bytes) { if (p && bytes) r.push_back({(uintptr_t)p, (uintptr_t)p + bytes}); }
+    // `rows` rows of `cols` floats
+    void mat(const float *p, long pitch, long rows, long cols) { for (long i = 0; i < rows; ++i) put(p + i * pitch, 4 * (size_t)std::max(0l, cols)); }
+    void lower(const float *p, long pitch, long n) { for (long i = 0; i < n; ++i) put(p + i * pitch, 4 * (size_t)(i + 1)); }
+    void merge()
+    {
+        std::sort(r.begin(), r.end());
+        std::vector<Range> m;
+        for (const Range &x : r) {
+            if (!m.empty() && x.first <= m.back().second) m.back().second = std::max(m.back().second, x.second);
+            else m.push_back(x);
+        }
+        r.swap(m);
+    }
+};
+static bool meet(const Set &a, const Set &b, uintptr_t &where)
+{
+    for (size_t i = 0, j = 0; i < a.r.size() && j < b.r.size();) {
+        where = std::max(a.r[i].first, b.r[j].first);
+        if (where < std::min(a.r[i].second, b.r[j].second)) return true;
+        (a.r[i].second < b.r[j].second) ? ++i : ++j;
+    }
+    return false;
+}
+struct Access { Set rd, wr; };
+
+static std::map<const InvProbF *, InvProbF> device_table;      // in the order the launches are enqueued in
+
+static void touch_nested(Access &a, const InvSeq &q, const InvProbF *own)
+{
+    for (int k = q.c[0].first; k < q.c[0].first + q.nprob; ++k) {
+        if (own) { device_table[q.tab + k] = own[k]; a.wr.put(q.tab + k, sizeof(InvProbF)); }
+        else a.rd.put(q.tab + k, sizeof(InvProbF));
+        const InvProbF &p = device_table.at(q.tab + k);
+        a.rd.lower(p.M, p.ldm, p.n + (p.border != 0));
+        a.rd.put(p.dptr, p.dptr ? 4 : 0);
+        a.wr.mat(p.W, p.ldw, p.n + (p.border != 0), p.n + (p.border != 0));
+        a.wr.put(p.P, 4 * fused_ws_floats(p.n));
+        a.wr.put(p.info, 4);
+    }
+}
+static void touch_product(Access &a, const float *A, const float *B, float *C, long lda, long ldb, long ldc, int M, int N, int K,
+                          int mode, int p0, int p1, long doff, const int *gate, const float *D, long ldd)
+{
+    a.rd.mat(A, lda, K, M);
+    a.rd.mat(B, ldb, K, N);
+    a.rd.put(gate, gate ? 8 : 0);
+    if (mode == kSubFrom) a.rd.mat(D, ldd, M, N);
+    for (long m = 0; m < M; ++m) {
+        float *row = C + m * ldc;
+        if (mode == kStore || mode == kStoreDiv || mode == kSubFrom) { a.wr.put(row, 4 * (size_t)N); continue; }
+        if (mode == kSubLowerSkip && m >= p0 && m < p1) continue;
+        const long end = std::min<long>(N, m + (mode == kSubLowerSkip ? 0 : doff) + 1);       // read, then written
+        a.wr.put(row, 4 * (size_t)std::max(0l, std::min<long>(end, p0)));
+        a.wr.put(row + p1, 4 * (size_t)std::max(0l, end - p1));
+    }
+}
+template <class T>
+static const T &arg(const Node &n, int i = 0) { if (n.args.at(i).size() != sizeof(T)) abort(); return *reinterpret_cast<const T *>(n.args[i].data()); }
+
+static Access touched(const Node &n)
+{
+    Access a;
+    auto is = [&](const char *s) { return n.kernel.find(s) != std::string::npos; };
+    if (is("sweep_init_kernel")) {
+        const InvTable &t = arg<InvTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const InvProb &p = t.p[k];
+            a.rd.lower(p.M, p.n, p.n);
+            a.wr.lower(p.W, p.n, p.n);
+            a.wr.put(p.info, 4);
+            a.wr.put(p.gate, p.gate ? 16 : 0);
+        }
+    } else if (is("sweep_finish_kernel")) {
+        const InvTable &t = arg<InvTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const InvProb &p = t.p[k];
+            a.wr.mat(p.W, p.n, p.n, p.n);
+            a.rd.mat(p.Vt, p.ldv, p.fold, p.n);
+            a.rd.mat(p.Wt, p.ldv, p.fold, p.n);
+        }
+    } else if (is("inv_upload_kernel")) {
+        const InvUpload &u = arg<InvUpload>(n);
+        for (int k = 0; k < u.count; ++k) device_table[u.dst + k] = u.p[k];
+        a.wr.put(u.dst, u.count * sizeof(InvProbF));
+    } else if (is("fsweep_pivot0_kernel")) {
+        const bool own = n.args.at(1).size() > sizeof(InvProbF);
+        touch_nested(a, arg<InvSeq>(n), own ? reinterpret_cast<const InvProbF *>(n.args[1].data()) : nullptr);
+    } else if (is("fsweep_step_kernel")) {
+        touch_nested(a, arg<InvSeq>(n), nullptr);
+    } else if (is("blk_")) {
+        const BlkTable &t = arg<BlkTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const BlkProb &p = t.p[k];
+            const long p1 = p.p0 + p.bs;
+            Set panel, block;                   // outside the pivot block, the pivot block
+            panel.mat(p.W + p.p0 * (long)p.n, p.n, p.bs, p.p0);
+            panel.mat(p.W + p1 * p.n + p.p0, p.n, p.n - p1, p.bs);
+            block.lower(p.W + p.p0 * (long)p.n + p.p0, p.n, p.bs);
+            auto join = [](Set &x, const Set &y) { x.r.insert(x.r.end(), y.r.begin(), y.r.end()); };
+            if (is("blk_cond_kernel")) {
+                join(a.rd, block);
+                a.rd.mat(p.P, p.pb, p.bs, p.bs);
+            } else if (is("blk_gather_kernel")) {
+                join(a.rd, panel);
+                a.wr.mat(p.Vt, p.ldv, p.bs, p.n);
+                if (p.S) { join(a.rd, block); a.wr.mat(p.S, p.pb, p.bs, p.bs); }
+            } else {
+                a.rd.mat(p.Wt, p.ldv, p.bs, p.n);
+                a.rd.mat(p.P, p.pb, p.bs, p.bs);
+                a.rd.put(p.ninfo, 4);
+                join(a.wr, panel);
+                join(a.wr, block);
+                a.wr.put(p.info, 4);
+            }
+            a.wr.put(p.gate, p.gate ? 8 : 0);   // folded into by the test, cleared by the one of the other two that has it
+        }
+    } else if (is("gemm_split_kernel")) {
+        const GemmSTable &t = arg<GemmSTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const GemmSProb &p = t.p[k];
+            touch_product(a, p.A, p.B, p.C, p.lda, p.ldb, p.ldc, p.M, p.N, p.K, p.mode, p.p0, p.p1, p.doff, p.gate, nullptr, 0);
+        }
+    } else if (is("gemm_wave_kernel")) {
+        const GemmWTable &t = arg<GemmWTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const GemmWProb &p = t.p[k];
+            touch_product(a, p.A, p.B, p.C, p.lda, p.ldb, p.ldc, p.M, p.N, p.K, p.mode, p.p0, p.p1, 0, nullptr, nullptr, 0);
+        }
+    } else if (is("gemm_")) {
+        const GemmTable &t = arg<GemmTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const GemmProb &p = t.p[k];
+            touch_product(a, p.A, p.B, p.C, p.lda, p.ldb, p.ldc, p.M, p.N, p.K, p.mode, p.p0, p.p1, p.doff, p.gate, p.D, p.ldd);
+        }
+    } else if (is("border_")) {
+        const BorderTable &t = arg<BorderTable>(n);
+        for (int k = 0; k < t.count; ++k) {
+            const BorderProb &p = t.p[k];
+            a.rd.lower(p.M, p.ldm, p.n);
+            a.rd.put(p.sticky, p.sticky ? 4 : 0);
+            a.wr.mat(p.W, p.ldw, p.n, p.n);
+            a.wr.put(p.y, 4 * border_ws_floats(p.n));
+            a.wr.put(p.info, 4);
+        }
+    } else {
+        fprintf(stderr, "unknown kernel %s\n", n.kernel.c_str());
+        abort();
+    }
+    a.rd.merge();
+    a.wr.merge();
+    return a;
+}
+
+int main(int argc, char **argv)
+{
+    tuning().invert_refine = atoi(argv[1]);
+    std::vector<InvertJob> jobs;
+    char *at = reinterpret_cast<char *>(uintptr_t(1) << 40);          // addresses only: nothing is read or written
+    auto take = [&](size_t bytes) { char *p = at; at += align_up(bytes, 256); return p; };
+    int *info = reinterpret_cast<int *>(take(4 * (size_t)argc));
+    for (int i = 2; i < argc; ++i) {
+        InvertJob j{};
+        j.n = atoi(argv[i]);
+        j.M = reinterpret_cast<float *>(take(4 * (size_t)j.n * j.n));
+        j.Minv = reinterpret_cast<float *>(take(4 * (size_t)j.n * j.n));
+        j.info = info + i - 2;
+        jobs.push_back(j);
+    }
+    const size_t work_bytes = invert_workspace_bytes(jobs.data(), (int)jobs.size());
+    char *work = take(work_bytes);
+    const hipStream_t s = (hipStream_t)uintptr_t(0x10);
+    for (int call = 0; call < 2; ++call)
+        if (invert_launch(jobs.data(), (int)jobs.size(), work, work_bytes, s) != hipSuccess) return 2;
+    // behind[i]: the nodes that come before node i
+    const size_t n = nodes.size();
+    std::vector<std::vector<bool>> behind(n, std::vector<bool>(n, false));
+    std::vector<Access> acc(n);
+    std::vector<hipStream_t> streams;
+    for (size_t i = 0; i < n; ++i) {
+        for (int b : nodes[i].before) {
+            behind[i][b] = true;
+            for (int k = 0; k < b; ++k)
+                if (behind[b][k]) behind[i][k] = true;
+        }
+        if (nodes[i].kernel.empty()) continue;
+        acc[i] = touched(nodes[i]);
+        if (std::find(streams.begin(), streams.end(), nodes[i].stream) == streams.end()) streams.push_back(nodes[i].stream);
+    }
+    long launches = 0, free_pairs = 0;
+    for (size_t i = 0; i < n; ++i) {
+        if (nodes[i].kernel.empty()) continue;
+        ++launches;
+        for (size_t j = 0; j < i; ++j) {
+            if (nodes[j].kernel.empty() || behind[i][j]) continue;
+            ++free_pairs;
+            uintptr_t where = 0;
+            const char *how = meet(acc[i].wr, acc[j].wr, where) ? "both write" : meet(acc[i].wr, acc[j].rd, where)   ? "read by the first, written by the second"
+                                                                            : meet(acc[i].rd, acc[j].wr, where) ? "written by the first, read by the second"
+                                                                                                                : nullptr;
+            if (how)
+                printf("unordered: %s (launch %zu) and %s (launch %zu): %s at %s + %zu\n", nodes[j].kernel.c_str(), j, nodes[i].kernel.c_str(), i, how,
+                       where >= (uintptr_t)work ? "work" : "matrices", where >= (uintptr_t)work ? where - (uintptr_t)work : where - (uintptr_t)info);
+        }
+    }
+    for (const Node &k : nodes)                // whatever a call enqueued comes before what follows on the caller's stream
+        if (!k.kernel.empty() && !behind[last_of[s]][&k - nodes.data()] && &k != &nodes[last_of[s]]) printf("not joined: %s\n", k.kernel.c_str());
+    printf("launches %ld streams %zu free pairs %ld\n", launches, streams.size(), free_pairs);
+    return 0;
+}

@@ -1,0 +1,39 @@
+"""Order of the launches of an inversion call (the blocked sweep's look-ahead on three streams, the smaller factors beside
+it): every two launches that touch the same memory, one of them writing, must be ordered by a stream or by events.  The host code runs
+as it is, compiled without device code against a runtime that only notes down what is enqueued (blocked_schedule.cpp);
+the kernels' arguments say what they read and write.  No GPU."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="no hipcc")
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("schedule")
+    obj, exe = str(d / "s.o"), str(d / "s")
+    subprocess.run(["hipcc", "-x", "hip", "--offload-arch=gfx950", "--cuda-host-only", "-O1", "-std=c++17", "-w", "-c",
+                    os.path.join(HERE, "blocked_schedule.cpp"), "-o", obj], check=True)
+    # the one open symbol is the device code that was left out
+    subprocess.run(["g++", "-no-pie", obj, "-o", exe, "-Wl,--unresolved-symbols=ignore-all", "-lpthread"], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("refine", [1, 0])
+@pytest.mark.parametrize("orders", [(1282,), (1540, 1541, 1792, 1793, 2049), (1301, 2049, 1536, 700, 577, 1793, 64, 65, 2304),
+                                    (4097, 1025, 1025, 1345)])
+def test_launches_that_share_memory_are_ordered(program, orders, refine):
+    r = subprocess.run([program, str(refine)] + [str(n) for n in orders], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    lines = r.stdout.splitlines()
+    print(lines[-1])
+    counts = lines[-1].split()
+    launches, streams, free = int(counts[1]), int(counts[3]), int(counts[6])
+    # not vacuous: the caller's stream and the library's two or three, with launches that may run side by side
+    assert streams == (4 if min(orders) <= 1280 else 3) and free > launches
+    assert len(lines) == 1, "\n".join(lines[:10])

@@ -75,3 +75,32 @@ def test_status_in_every_block():
     got, info = _invert(mats + [base])
     assert list(info[0::2]) == [p + 1 for p in places] + [0]
     assert np.isfinite(got[-1]).all()
+
+
+def test_refinement_beside_long_updates():
+    """Pivot blocks whose gates open in a call whose updates take longer than the panel products: the refinement of the next
+    pivot block must not depend on which of the streams is ahead.  The copies of a matrix in a call and the repetitions of the
+    call give the same bits, and the error is that of one stream, where nothing runs side by side: both are roundings of the
+    same order, 4.7e-5 and 4.0e-5 at order 2304, where leaving the refinement out of the next pivot blocks alone gives 4.0e-4
+    (1.5 cond 2^-24 is 9e-3 and would not show it)."""
+    orders = (2304, 2049, 1793)
+    pairs = [_spd(n, 1e5, 40 + n) for n in orders]
+    mats = [m for m, _ in pairs] * 6
+    kf.kfac_tune("invert_two_streams", 0)
+    try:
+        serial, info = _invert([m for m, _ in pairs])
+    finally:
+        kf.kfac_tune("invert_two_streams", 1)
+    assert not info.any()
+    first = None
+    for rep in range(3):
+        got, info = _invert(mats)
+        assert not info.any()
+        first = first or got[:3]
+        for i, x in enumerate(got):
+            assert np.array_equal(x, first[i % 3]), f"repetition {rep}, matrix {i}"
+    for n, x, y, (m, inv) in zip(orders, first, serial, pairs):
+        ref = inv @ (2.0 * np.eye(n) - m.astype(np.float64) @ inv)
+        e, e_serial = gu.rel_fro(x, ref), gu.rel_fro(y, ref)
+        print(n, f"{e:.2e}, one stream {e_serial:.2e}", flush=True)
+        assert e < 1.5 * e_serial
