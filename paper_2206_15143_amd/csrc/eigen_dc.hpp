@@ -279,12 +279,14 @@ __device__ __forceinline__ void dc_tridiag(const DcProb &pr, float *lds)
                 tau = 1.0 + fabs(alpha) * ir;
                 scale = alpha > 0.0 ? id : -id;
             }
-            const float tauf = (float)tau, scalef = (float)scale;
+            const float tauf = (float)tau;
             float v[RP];
 #pragma unroll
             for (int q = 0; q < RP; ++q) {
                 const int i = tid + NT * q;
-                v[q] = i <= j || i >= n ? 0.f : (i == j + 1 ? 1.f : a[q] * scalef);
+                // the product in fp64: the reciprocal of a column's norm need not be in the range of fp32 (rows of a feature that
+                // no longer fires decay to a few multiples of 2^-149)
+                v[q] = i <= j || i >= n ? 0.f : (i == j + 1 ? 1.f : (float)((double)a[q] * scale));
                 if (i < NP) V[k * NP + i] = v[q];
             }
             dc_lds_barrier();

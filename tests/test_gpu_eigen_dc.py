@@ -34,6 +34,8 @@ def _eigen(mats):
 
 
 def _check(M, Q, v, tag):
+    """Numbers below 2^-126 are rounded to multiples of q = 2^-149: n columns, each rounding n x n entries by at most q, add
+    n^2 q to what the relative bounds allow."""
     n = len(M)
     Md, Qd, vd = M.astype(np.float64), Q.astype(np.float64), v.astype(np.float64)
     Md = np.tril(Md) + np.tril(Md, -1).T
@@ -43,9 +45,10 @@ def _check(M, Q, v, tag):
     e_orth = np.linalg.norm(Qd.T @ Qd - np.eye(n)) / np.sqrt(n)
     e_res = np.linalg.norm(Md @ Qd - Qd * vd) / max(np.linalg.norm(Md), 1e-300)
     print(f"{tag}: eigenvalues {e_val:.2e} orthogonality {e_orth:.2e} residual {e_res:.2e}", flush=True)
-    assert e_val <= 2e-6, tag
+    q = n * n * 2.0 ** -149
+    assert e_val <= 2e-6 + q / top, tag
     assert e_orth < 1e-4, tag
-    assert e_res < 2e-5, tag
+    assert e_res < 2e-5 + q / max(np.linalg.norm(Md), 1e-300), tag
 
 
 def _factor(n, rows, seed, relu=True):
@@ -91,6 +94,46 @@ def test_spectra(kind, n):
     m = SPECTRA[kind](n)
     (a, _), info = _eigen([(m, np.eye(3, dtype=np.float32))])
     assert list(info) == [0, 0]
+    _check(*a, f"{kind} n={n}")
+
+
+def _dead(n, at, value, count=1):
+    """Rows and columns at .. at + count - 1 of a factor whose features stopped firing: every update multiplied them by the
+    decay, and rounding keeps them at a few multiples of 2^-149; entries that were zero stay zero."""
+    m = _factor(n, 2 * n, n + at)
+    for i in range(at, at + count):
+        m[i, :] = m[:, i] = value
+        m[i, ::3] = m[::3, i] = 0.0
+    for i in range(at, at + count):
+        m[i, i] = 2 * value
+    return m
+
+
+SUBNORMAL = {
+    "first feature dead": lambda n: _dead(n, 0, 1.3e-44),
+    "first feature nearly dead": lambda n: _dead(n, 0, 1e-39),
+    "middle feature dead": lambda n: _dead(n, n // 2, 1.3e-44),
+    "last feature dead": lambda n: _dead(n, n - 1, 1.3e-44),
+    "last third dead": lambda n: _dead(n, n - n // 3, 1.3e-44, n // 3),
+    "first third dead": lambda n: _dead(n, 0, 1.3e-44, n // 3),
+    "one subnormal pair": lambda n: (np.diag(np.arange(1.0, n + 1)) + 1e-40 * (np.eye(n, k=3) + np.eye(n, k=-3)) * (np.arange(n) < 4)
+                                     * (np.arange(n)[:, None] < 4)).astype(np.float32),
+    "all subnormal": lambda n: (1e-40 * _factor(n, 2 * n, 13)).astype(np.float32),
+    "largest": lambda n: (_factor(n, 2 * n, 14) * (1e38 / np.linalg.norm(_factor(n, 2 * n, 14), 2))).astype(np.float32),
+}
+
+
+@pytest.mark.parametrize("kind", sorted(SUBNORMAL))
+@pytest.mark.parametrize("n", [40, 145, 300, 800])
+def test_ends_of_the_range(kind, n):
+    """A column's reflector is scaled by the reciprocal of a norm that may lie outside the range of fp32 although the column does
+    not: below 2.9e-39 the reciprocal is infinite, above 8.5e37 it has few bits left.  (With many dead features the reduction finds
+    their direction in steps whose reflectors have hundreds of equal entries, and sums of equal terms round the same way each
+    time: orthogonality 1.7e-5 at order 800, below n 2^-24.)"""
+    m = SUBNORMAL[kind](n)
+    (a, _), info = _eigen([(m, np.eye(3, dtype=np.float32))])
+    assert list(info) == [0, 0]
+    assert np.isfinite(a[1]).all() and np.isfinite(a[2]).all()
     _check(*a, f"{kind} n={n}")
 
 
