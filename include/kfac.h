@@ -181,8 +181,9 @@ kfac_status kfac_precondition_static(const kfac_layer_desc *desc, const float *d
  * fp32 row-major with the eigenvectors in their COLUMNS; d_v_A [d_A], d_v_G [d_G] the eigenvalues, entry k
  * belonging to column k (no particular order).  The running factors are read (lower triangle) and not
  * modified; outputs must not alias them.  Orders up to 1280: tridiagonalisation and divide and conquer; above: block
- * Jacobi.  d_info: 2 ints (A, G): 0 = converged, 1 = the sweep budget of a Jacobi iteration (of the whole matrix above
- * order 1280, of a leaf of order up to 16 below) ran out: Q is then still orthogonal.
+ * Jacobi.  d_info: 2 ints (A, G): 0 = converged, 1 = a budget ran out: of the sweeps of a Jacobi iteration (of the whole
+ * matrix above order 1280, of a leaf of order up to 16 below; Q is then still orthogonal), or of the steps to an
+ * eigenvalue of a merge (orders 17 to 1280; Q is then as orthogonal as that eigenvalue is accurate).
  *
  * kfac_precondition_eigen:  P = Q_G [ (Q_G^T grad Q_A) ./ (v_G v_A^T + gamma) ] Q_A^T, gamma >= 0.
  * Shapes of grad / out as in kfac_precondition; d_out may alias d_grad. */

@@ -979,6 +979,7 @@ int kfac_tune(const char *key, long value)
     else if (k == "invert_fused_refine_cond") t.invert_fused_refine_cond = value < 0 ? 0 : value;
     else if (k == "use_eigen_dc") t.use_eigen_dc = value;
     else if (k == "eigen_max_sweeps") t.eigen_max_sweeps = value;
+    else if (k == "eigen_secular_steps") t.eigen_secular_steps = value;
     else if (k == "eigen_inner_sweeps") t.eigen_inner_sweeps = value;
     else if (k == "im2col_piece_elems") t.im2col_piece_elems = value;
     else if (k == "im2col_block_bytes") t.im2col_block_bytes = value;

@@ -162,6 +162,7 @@ struct Tuning {
     long im2col_min_blocks = 1024;   // shorter strips until a layer has this many workgroups
     long use_eigen_dc = 1;           // orders up to 1280 by tridiagonalisation and divide and conquer
     long eigen_max_sweeps = 20;      // sweep budget of the block Jacobi eigen-decomposition (12-13 used at order 577)
+    long eigen_secular_steps = 60;   // step budget of the iteration for an eigenvalue of a merge
     long eigen_inner_sweeps = 1;     // Jacobi sweeps over the 32 x 32 Gram matrix of a pair of blocks per round
     long bf16_rows_copy = 1;         // bf16 NCHW operands with an odd number of positions: row-major copy first
     long invert_panel_split = 1;     // blocked sweep: panel products on the split-bf16 kernel

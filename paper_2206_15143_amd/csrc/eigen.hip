@@ -464,6 +464,7 @@ hipError_t dc_launch(const DcProb *probs, int count, hipStream_t s)
     DcTable tab;
     tab.count = count;
     tab.sweeps = (int)std::max(1l, tuning().eigen_max_sweeps);
+    tab.iters = (int)std::max(1l, tuning().eigen_secular_steps);
     tab.step = 0;
     for (int k = 0; k < count; ++k) tab.p[k] = probs[k];
     auto lay_out = [&](auto blocks_of) {

@@ -44,6 +44,7 @@ struct DcProb {
 
 struct DcTable {
     int count, sweeps, step;
+    int iters;                     // steps of the iteration for a root at most
     DcProb p[kDcTab];
 };
 
@@ -735,7 +736,7 @@ __global__ __launch_bounds__(256) void dc_deflate_kernel(const DcTable tab)
 
 // Root i of 1 / rho + sum_j z_j^2 / (d_j - x) between d_i and d_{i+1} (the last one up to d_i + rho), as a distance from
 // the nearer pole.  Sixteen lanes sum; each side of the root is replaced by a constant and its nearest pole with the
-// same value and slope, the zero of that is the next iterate, and a bracket guards it.
+// same value and slope, the zero of that is the next iterate, and a bracket guards it.  info = 1 if the step budget ran out.
 __global__ __launch_bounds__(256) void dc_secular_kernel(const DcTable tab)
 {
     int local, node, sub, lo, mid, hi;
@@ -781,11 +782,15 @@ __global__ __launch_bounds__(256) void dc_secular_kernel(const DcTable tab)
     } else if (!last) {
         xr = 0.5 * gap;
     }
-    for (int it = 0; it < 60; ++it) {
+    for (int it = 0;; ++it) {
         const double f = ri + psi + phi;
         if (f < 0.0) xl = fmax(xl, x);
         else xr = fmin(xr, x);
         if (fabs(f) <= 8e-16 * (ri + fabs(psi) + phi) || !(xr - xl > 2e-16 * fmax(fabs(xl), fabs(xr)))) break;
+        if (it == tab.iters) {
+            if (lane == 0) *pr.info = 1;
+            break;
+        }
         const double da = a - x, db = b - x;
         const double s1 = da * da * dpsi;
         double nx;

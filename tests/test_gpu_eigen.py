@@ -109,6 +109,19 @@ def test_eigen_sweep_budget_is_reported():
     assert np.linalg.norm(Qd.T @ Qd - np.eye(100)) / 10 < 1e-3       # still an orthogonal iterate
 
 
+def test_eigen_step_budget_is_reported():
+    # one step to each eigenvalue of a merge does not reach it; leaves (order 16 at most) have none to reach
+    A = _factor_like(71, 100)
+    G = _factor_like(72, 16)
+    desc = kf.LayerDesc.linear(100, 16, has_bias=False)
+    kf.kfac_tune("eigen_secular_steps", 1)
+    try:
+        info = _gpu_eigen(desc, A, G)[4]
+    finally:
+        kf.kfac_tune("eigen_secular_steps", 60)
+    assert list(info) == [1, 0]
+
+
 @pytest.mark.parametrize("dA,dG,gamma", [(1, 1, 0.5), (20, 7, 0.03), (65, 32, 0.03), (145, 16, 0.001), (300, 150, 0.01)])
 def test_precondition_eigen_given_oracle_decomposition(dA, dG, gamma):
     # the four products and the division alone: Q, v from the oracle (rounded to fp32, and the oracle
