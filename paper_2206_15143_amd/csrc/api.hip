@@ -799,12 +799,14 @@ kfac_status kfac_precondition_eigen_batched(int n, const kfac_layer_desc *descs,
     }
     hipStream_t s = (hipStream_t)hip_stream;
     if (transpose_launch(tsrc.data(), tdst.data(), tn.data(), (int)tn.size(), s) != hipSuccess) return KFAC_ERR_HIP;
+    // An output may lie in the gradient of any layer of the call: the launches that read the gradients come before those that
+    // write the outputs (the last product of the wide layers, the second launch of the narrow ones).
     const int nw = (int)g1.size(), nn = (int)n1.size();
+    if (precond_fused_launch(n1.data(), nn, gamma, s) != hipSuccess) return KFAC_ERR_HIP;
     if (gemm_launch(g1.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
     if (gemm_launch(g2.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
     if (gemm_launch(g3.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
     if (gemm_launch(g4.data(), nw, s) != hipSuccess) return KFAC_ERR_HIP;
-    if (precond_fused_launch(n1.data(), nn, gamma, s) != hipSuccess) return KFAC_ERR_HIP;
     if (precond_fused_launch(n2.data(), nn, 0.f, s) != hipSuccess) return KFAC_ERR_HIP;
     return KFAC_OK;
 }

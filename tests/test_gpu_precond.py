@@ -79,3 +79,32 @@ def test_infinite_column_stays_in_its_columns():
     ref = (G.astype(np.float64) @ W.astype(np.float64) @ A.astype(np.float64)[:, keep])
     assert not np.isfinite(got[:, 70]).any()
     assert gu.rel_fro(got[:, keep], ref) < 1e-5
+
+
+def _eigen_layers(shapes, seed):
+    rng = np.random.default_rng(seed)
+    out = []
+    for dA, dG in shapes:
+        QA, QG = (np.linalg.qr(rng.standard_normal((d, d)))[0].astype(np.float32) for d in (dA, dG))
+        vA, vG = ((rng.random(d) + 0.5).astype(np.float32) for d in (dA, dG))
+        W = rng.standard_normal((dG, dA)).astype(np.float32)
+        a, g = QA.astype(np.float64), QG.astype(np.float64)
+        out.append((QA, vA, QG, vG, W, g @ ((g.T @ W @ a) / (np.outer(vG, vA).astype(np.float64) + 0.1)) @ a.T))
+    return out
+
+
+@pytest.mark.parametrize("turn", [0, 1, 2, 3])
+def test_eigen_form_with_outputs_over_gradients(turn):
+    """Wide and narrow layers in one call, every output in the gradient buffer of the layer `turn` places on (0: its own): all
+    gradients are read before an output is stored."""
+    shapes = [(200, 130), (520, 50), (130, 200), (50, 520)]
+    layers = _eigen_layers(shapes, 21)
+    n = len(shapes)
+    QA, vA, QG, vG, W = ([gu.to_dev(l[k]) for l in layers] for k in range(5))
+    out = [W[(i + turn) % n].view(shapes[i][1], shapes[i][0]) for i in range(n)]
+    descs = [_desc(*s) for s in shapes]
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_precondition_eigen_batched(descs, QA, vA, QG, vG, 0.1, W, out, ws)
+    torch.cuda.synchronize()
+    for s, l, o in zip(shapes, layers, out):
+        assert gu.rel_fro(o.cpu().numpy(), l[5]) < 1e-5, s
