@@ -383,24 +383,25 @@ size_t precond_ws(int n, const kfac_layer_desc *descs)
     return precond_ws_min(n, descs) + align_up(std::max(all, wide), 256);
 }
 
-// Whether an output of the call overlaps a layer gradient of the call (its own, in place, is allowed).
-bool precond_overlap(int n, const kfac_layer_desc *descs, const float *const *grad, float *const *out)
+// Whether an output of the call overlaps the gradient (its own included) or G_inv of a layer that the one-launch form would
+// take: what the first of the two products reads, ahead of all outputs.
+bool precond_overlap(int n, const kfac_layer_desc *descs, const float *const *grad, const float *const *G_inv, float *const *out)
 {
     typedef std::pair<uintptr_t, uintptr_t> Range;
-    std::vector<Range> g(n);
-    std::vector<uintptr_t> reach(n);              // furthest end among the gradients that start no later
-    auto range = [&](const void *p, int i) {
-        const size_t dA = core_dim(&descs[i]) + descs[i].has_bias, dG = descs[i].d_out;
-        return Range((uintptr_t)p, (uintptr_t)p + dA * dG * sizeof(float));
+    std::vector<Range> o(n);
+    std::vector<uintptr_t> reach(n);              // furthest end among the outputs that start no later
+    auto range = [](const void *p, size_t a, size_t b) { return Range((uintptr_t)p, (uintptr_t)p + a * b * sizeof(float)); };
+    auto dA = [&](int i) { return (size_t)core_dim(&descs[i]) + descs[i].has_bias; };
+    auto dG = [&](int i) { return (size_t)descs[i].d_out; };
+    for (int i = 0; i < n; ++i) o[i] = range(out[i], dA(i), dG(i));
+    std::sort(o.begin(), o.end());
+    for (int i = 0; i < n; ++i) reach[i] = std::max(o[i].second, i ? reach[i - 1] : (uintptr_t)0);
+    auto hit = [&](const Range &r) {
+        const size_t k = std::lower_bound(o.begin(), o.end(), Range(r.second, 0)) - o.begin();   // outputs that start before its end
+        return k > 0 && reach[k - 1] > r.first;
     };
-    for (int i = 0; i < n; ++i) g[i] = range(grad[i], i);
-    std::sort(g.begin(), g.end());
-    for (int i = 0; i < n; ++i) reach[i] = std::max(g[i].second, i ? reach[i - 1] : (uintptr_t)0);
-    for (int i = 0; i < n; ++i) {
-        const Range o = range(out[i], i);
-        const size_t k = std::lower_bound(g.begin(), g.end(), Range(o.second, 0)) - g.begin();   // gradients that start before its end
-        if (k > 0 && reach[k - 1] > o.first) return true;
-    }
+    for (int i = 0; i < n; ++i)
+        if (precond_fused_takes((int)dA(i), (int)dG(i)) && (hit(range(grad[i], dA(i), dG(i))) || hit(range(G_inv[i], dG(i), dG(i))))) return true;
     return false;
 }
 
@@ -664,9 +665,9 @@ kfac_status kfac_precondition_batched(int n, const kfac_layer_desc *descs, const
     if (!aligned(d_work, 256)) return KFAC_ERR_ALIGN;
     // the intermediates are required; the K-slice partials behind them are used when there is room for them
     if (precond_ws_min(n, descs) > work_bytes) return KFAC_ERR_WORKSPACE;
-    // Narrow layers in one launch, which reads a layer's gradient in workgroups that do not wait for one another: an output
-    // that overlaps a gradient goes through the intermediate like the wide layers.
-    const bool in_place = precond_overlap(n, descs, d_grad, d_out);
+    // Narrow layers in one launch, which reads a layer's gradient and G_inv in workgroups that do not wait for one another: where
+    // an output overlaps one of these, they go through the intermediates like the wide layers.
+    const bool in_place = precond_overlap(n, descs, d_grad, d_G_inv, d_out);
     std::vector<GemmJob> g1, g2;
     std::vector<PrecJob> narrow;
     size_t off = 0;

@@ -128,7 +128,8 @@ size_t gemm_workspace_bytes(const GemmJob *jobs, int n);
 // they serve
 hipError_t gemm_split_products(const GemmJob *jobs, int n, int cls, double definition, hipStream_t s);
 
-// whether a layer of these orders takes the one-launch form of the two-sided product; out must not overlap any W of the call
+// whether a layer of these orders takes the one-launch form of the two-sided product; out must not overlap any W, A or G of the
+// call
 bool precond_fused_takes(int dA, int dG);
 hipError_t precond_fused_launch(const PrecJob *jobs, int n, float gamma, hipStream_t s);
 

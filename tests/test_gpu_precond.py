@@ -108,3 +108,21 @@ def test_eigen_form_with_outputs_over_gradients(turn):
     torch.cuda.synchronize()
     for s, l, o in zip(shapes, layers, out):
         assert gu.rel_fro(o.cpu().numpy(), l[5]) < 1e-5, s
+
+
+def test_outputs_over_inverses_of_g():
+    """G_inv of a layer may be reused for another layer's output: two products read all of them before an output is stored, and
+    so must a call of more layers than one launch of the fused form holds (128)."""
+    n, d = 160, 64
+    rng = np.random.default_rng(31)
+    A, G = [_sym(d, rng) for _ in range(n)], [_sym(d, rng) for _ in range(n)]
+    W = [rng.standard_normal((d, d)).astype(np.float32) for _ in range(n)]
+    dev = [[gu.to_dev(x) for x in xs] for xs in (A, G, W)]
+    out = [dev[1][128 + i] if i < 32 else torch.full((d, d), float("nan"), device=gu.DEV) for i in range(n)]
+    descs = [_desc(d, d)] * n
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_precondition_batched(descs, *dev, out, ws)
+    torch.cuda.synchronize()
+    for i in range(n):
+        ref = G[i].astype(np.float64) @ W[i].astype(np.float64) @ A[i].astype(np.float64)
+        assert gu.rel_fro(out[i].cpu().numpy(), ref) < 1e-5, i
