@@ -80,6 +80,11 @@ def test_bad_arguments_are_rejected_on_the_host():
     assert lib.kfac_update_factors(ctypes.byref(wide), fake, fake, 1, 8, 600, 1.0, 1.0, 0.5, fake, fake, fake, 1 << 30,
                                    None) == 2
     assert kf.kfac_workspace_bytes(wide, 1, 8, 600) == 0 and kf.kfac_workspace_bytes(wide, 1, 8, 500) > 0
+    # patch extraction by itself refuses them whatever route the factor of the layer takes (3 x 3 fp32 convolutions of 20
+    # channels and more: no patches)
+    wide3 = kf.LayerDesc.conv2d(20, 4, 3, 1, 1)
+    assert lib.kfac_im2col(ctypes.byref(wide3), fake, 1, 8, 1400, fake, None) == 2
+    assert kf.kfac_workspace_bytes(wide3, 1, 8, 1400) > 0
     # padding: negative values are refused; the two directions are separate
     neg = kf.LayerDesc.conv2d(8, 4, 3, 1, 1)
     neg.pad_w = -1
