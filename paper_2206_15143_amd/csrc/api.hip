@@ -493,7 +493,9 @@ kfac_status kfac_im2col(const kfac_layer_desc *d, const void *d_act, int batch, 
     Geo g;
     kfac_status st = geometry(d, batch, h, w, g);
     if (st != KFAC_OK) return st;
-    if (!g.conv || !im2col_fits(d->kh, d->kw, d->stride, g.Wo, g.esz)) return KFAC_ERR_SHAPE;
+    if (!g.conv) return KFAC_ERR_SHAPE;
+    // geometry() has refused what is too wide where the factor needs the patches as well
+    if (g.fused3 && !im2col_fits(d->kh, d->kw, d->stride, g.Wo, g.esz)) return KFAC_ERR_SHAPE;
     if (!d_act || !d_patches) return KFAC_ERR_NULL;
     if (!aligned(d_act, 16) || !aligned(d_patches, 16)) return KFAC_ERR_ALIGN;
     Im2colJob j{};
