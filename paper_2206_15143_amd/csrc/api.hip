@@ -84,6 +84,8 @@ struct Geo {
     bool g_rows;        // bf16 output gradients on a map with an odd number of positions: through a row-major copy
     int ldg;            // its leading dimension (elements)
     size_t corr_bytes = 0;   // autocorrelations of a padded copy: what they keep in the workspace (counts towards a chunk's bytes)
+    bool corr_choice = false;   // ... the patch matrix is the alternative, the call decides (plan_update)
+    double corr_gain = 0.0;     // ... microseconds of work they save
 };
 
 bool desc_ok(const kfac_layer_desc *d)
@@ -140,6 +142,10 @@ kfac_status geometry(const kfac_layer_desc *d, int batch, int h, int w, Geo &g)
                    (long)batch * d->d_in * h * w * 4 < 0x7fff0000l;
         const bool corrw = d->in_dtype == KFAC_F32 && d->kh == 3 && d->kw == 3 && d->stride == 1 && ph == 1 && pw == 1 &&
                            corrw_takes(d->d_in, h, w, batch);
+        if (corrw) {
+            g.corr_gain = corrw_gain(d->d_in, h, w, batch);
+            g.corr_choice = !g.fused3 && g.corr_gain >= 0.0 && im2col_fits(d->kh, d->kw, d->stride, g.Wo, g.esz);
+        }
         g.fused3 = g.fused3 || corrw;
         // an eighth of the bytes counts: a chunk of few layers leaves every one of its launches half empty (VGG-16-,
         // DenseNet-201- and ResNet-50-shaped, an eighth / all: 2.02 / 2.33, 15.76 / 16.79, 13.26 / 14.12 ms)
@@ -298,14 +304,27 @@ struct UpdatePlan {
     size_t patch_region = 0, syrk_region = 0;
 };
 
+// `alone`: with the routes that the layers take in calls of their own
 kfac_status plan_update(int n, const kfac_layer_desc *descs, const int *batch, const int *h, const int *w,
-                        UpdatePlan &pl)
+                        UpdatePlan &pl, bool alone = false)
 {
     pl.geo.resize(n);
+    double gain = 0.0;
+    bool launches = false;                        // some layer takes the autocorrelations of a padded copy whatever the others do
     for (int i = 0; i < n; ++i) {
         kfac_status st = geometry(&descs[i], batch[i], h ? h[i] : 1, w ? w[i] : 1, pl.geo[i]);
         if (st != KFAC_OK) return st;
+        if (pl.geo[i].corr_choice) gain += pl.geo[i].corr_gain;
+        else launches = launches || (pl.geo[i].corr_bytes > 0 && pl.geo[i].corr_gain >= 0.0);
     }
+    const double least = (double)tuning().corrw_min_gain;
+    if (alone || (!launches && gain < least))
+        for (Geo &g : pl.geo)
+            if (g.corr_choice && g.corr_gain < least) {
+                g.fused3 = false;
+                g.patches = true;
+                g.corr_bytes = 0;
+            }
     pl.chunks = make_chunks(pl.geo, descs, batch, h, w);
     for (const Chunk &c : pl.chunks) {
         size_t pb = 0;
@@ -475,6 +494,10 @@ size_t kfac_workspace_bytes_batched(int n, const kfac_layer_desc *descs, const i
     UpdatePlan pl;
     if (plan_update(n, descs, batch, h, w, pl) != KFAC_OK) return 0;
     size_t need = pl.patch_region + pl.syrk_region;
+    // the workspace of a network also serves calls of some of its layers
+    UpdatePlan alone;
+    plan_update(n, descs, batch, h, w, alone, true);
+    need = std::max(need, alone.patch_region + alone.syrk_region);
     need = std::max(need, invert_ws_total(n, descs));
     need = std::max(need, precond_ws(n, descs));
     need = std::max(need, eigen_ws(n, descs));
@@ -972,6 +995,7 @@ int kfac_tune(const char *key, long value)
     else if (k == "invert_fused_max_n") t.invert_fused_max_n = value;
     else if (k == "use_corr3") t.use_corr3 = value;
     else if (k == "corrw_min_c") t.corrw_min_c = value;
+    else if (k == "corrw_min_gain") t.corrw_min_gain = value;
     else if (k == "corrw_max_pad") t.corrw_max_pad = value;
     else if (k == "corr3_lds_kb") t.corr3_lds_kb = value;
     else if (k == "invert_border") t.invert_border = value;

@@ -144,6 +144,9 @@ hipError_t transpose_launch(const float *const *src, float *const *dst, const in
 // its input (syrk_corrw.hpp); bytes of that copy and of the partial sums
 bool corrw_takes(int c, int h, int w, int batch);
 size_t corrw_bytes(int c, int h, int w, int batch);
+// microseconds of work that saves over the patch matrix; negative: another kernel takes the layer, infinite: the patch
+// matrix has no advantage
+double corrw_gain(int c, int h, int w, int batch);
 
 // output rows per stage of the fused 3x3 convolution factor kernel; 0 = image shape not supported
 int conv3_rows(int h, int w);
@@ -176,6 +179,7 @@ struct Tuning {
     long invert_two_streams = 1;     // blocked sweep and smaller factors on the library's streams (look-ahead); 0: everything on the caller's stream
     long corr3_lds_kb = 160;          // LDS budget (both slabs) of the autocorrelation kernel
     long corrw_min_c = 20;           // ... of at least this many channels from products of a padded, transposed copy (0 = never)
+    long corrw_min_gain = 42;        // ... in calls where that saves at least this many microseconds of work
     long corrw_max_pad = 170;        // ... on maps whose copy has at most this percentage of their positions
     long use_corr3 = 1;              // 3x3 convolution factors of 16 / 32 / 64 channels from input autocorrelations
     long invert_fused_max_n = 1280;  // orders up to this take the one-launch-per-step sweep

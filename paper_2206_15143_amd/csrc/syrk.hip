@@ -1003,6 +1003,29 @@ bool corrw_takes(int c, int h, int w, int batch)
     return tuning().fuse_conv3 && tuning().use_corr3 && tuning().corrw_min_c > 0 && c >= tuning().corrw_min_c && c % 4 == 0 && c <= 2048 && h >= 2 && w >= 2 &&
            (h + 2l) * (w + 2l) * 100 <= tuning().corrw_max_pad * h * w && (double)batch * (h + 2) * (w + 2) * c * 4 < 2.0e9;
 }
+// The route costs a call four dependent launches (copy, products, sum, assembly) where the patch matrix takes two or three
+// short ones, and saves work in proportion to K C^2; single layers, the same route off / on, us:
+//   patch matrix to the split kernel   128 x 14 x 14, batch 8: 52 / 83, 32: 87 / 98, 128: 254 / 173
+//   ... to the block-tile kernel        36 x 28 x 28, batch 8: 65 / 76, 32: 95 / 111, 128: 265 / 179
+//   ... of less than 192 columns        20 x 28 x 28, batch 8: 37 / 73, 32: 54 / 103; 58 x 58, batch 128: 438 / 447
+//   ... to the wave-unit kernel         96 x 28 x 28, batch 8: 91 / 90, 32: 239 / 137: one chain of K as long as the launches
+// Twelve layers in a call pay the launches once: 128 x 14 x 14, batch 8: 260 / 169.  So a call takes the route when its layers
+// together save more than the 42 us of the launches; what is left on either side of that line is within a few per cent,
+// up to a quarter on 7 x 7 and 10 x 10 maps, whose copies are 1.4 to 1.65 times their size.
+double corrw_gain(int c, int h, int w, int batch)
+{
+    FactorJob j{};
+    j.layout = kConv3;
+    j.ctot = c; j.h = h; j.w = w; j.hw = h * w;
+    j.K = (long)batch * h * w;
+    if (corr3_eligible(j)) return -1.0;
+    j.layout = kRows;
+    j.d_core = 9 * c;
+    j.ld = 9 * c;                       // c is a multiple of 4
+    if (!split_syrk_eligible(j) && wave_eligible(j)) return HUGE_VAL;
+    const double per_kc2 = split_syrk_eligible(j) ? 0.36e-6 : j.d_core < tuning().split_syrk_min_d ? 0.25e-6 : 1.0e-6;
+    return per_kc2 * c * c * std::max(0.0, (double)j.K - 150.0);
+}
 size_t corrw_bytes(int c, int h, int w, int batch)
 {
     const CorrW l(c, h, w, batch);

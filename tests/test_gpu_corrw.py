@@ -47,7 +47,11 @@ def test_wide_conv_factor(case):
         p = torch.cat([p, torch.ones(len(p), 1, dtype=torch.float64)], 1)
     low = A0.astype(np.float64)
     ref = 0.9 * (low + np.tril(low, -1).T) + 0.1 / b * (p.T @ p).numpy()
-    new = _factor(c, h, w, b, bias, x, A0 + np.triu(A0.T, 1))
+    kf.kfac_tune("corrw_min_gain", 0)                     # most of these layers are too small to take the route by themselves
+    try:
+        new = _factor(c, h, w, b, bias, x, A0 + np.triu(A0.T, 1))
+    finally:
+        kf.kfac_tune("corrw_min_gain", 42)
     kf.kfac_tune("use_corr3", 0)
     try:
         old = _factor(c, h, w, b, bias, x, A0 + np.triu(A0.T, 1))
@@ -58,3 +62,44 @@ def test_wide_conv_factor(case):
     assert e_new < 1e-5
     assert e_new < 1.5 * e_old + 1e-7
     assert np.array_equal(new, new.T)
+
+
+def _extractions(layers):
+    """Patch extractions launched by one call over layers (channels, map, batch)."""
+    descs = [kf.LayerDesc.conv2d(c, 4, 3, 1, 1, True, kf.KFAC_F32) for c, _, _ in layers]
+    b, h = [l[2] for l in layers], [l[1] for l in layers]
+    x = [torch.ones(n, c, s, s, device=gu.DEV) for c, s, n in layers]
+    g = [torch.zeros(n, 4, s, s, device=gu.DEV) for _, s, n in layers]
+    A = [torch.zeros(9 * c + 1, 9 * c + 1, device=gu.DEV) for c, _, _ in layers]
+    G = [torch.zeros(4, 4, device=gu.DEV) for _ in layers]
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, b, h, h))
+    one = [1.0] * len(layers)
+    kf.kfac_timing_enable(True)
+    try:
+        kf.kfac_update_factors_batched(descs, x, g, b, h, h, one, one, 0.0, A, G, ws)
+        launches = kf.kfac_timing_collect().get("im2col", (0.0, 0, 0.0))[1]
+    finally:
+        kf.kfac_timing_enable(False)
+    for a, (c, s, n) in zip(A, layers):                   # all ones: the corner of the bias counts the positions, tap (1, 1) too
+        assert float(a[-1, -1]) == n * s * s and float(a[4, 4]) == n * s * s
+    return launches
+
+
+@pytest.mark.parametrize("layers, patches", [
+    ([(128, 14, 8)], True), ([(128, 14, 128)], False),             # a layer by itself: by its work
+    ([(128, 14, 8)] * 12, False), ([(36, 14, 8)] * 3, True),       # layers of a call together
+    ([(20, 28, 32)], True), ([(96, 28, 8)], False),                # alternatives that cost least and most
+    ([(128, 14, 8), (96, 28, 8)], False),                          # a layer that takes the route anyway brings its launches
+    ([(64, 8, 8), (128, 14, 8)], True),                            # ... but not one that has a kernel of its own (64 channels)
+])
+def test_small_calls_keep_the_patch_matrix(layers, patches):
+    """The route costs four dependent launches: a call too small to earn them keeps the patch matrix."""
+    assert (_extractions(layers) > 0) == patches
+
+
+def test_workspace_of_a_network_serves_its_layers():
+    layers = [(128, 14, 8)] * 12 + [(40, 28, 16)] * 3
+    descs = [kf.LayerDesc.conv2d(c, 4, 3, 1, 1, True, kf.KFAC_F32) for c, _, _ in layers]
+    whole = kf.kfac_workspace_bytes_batched(descs, [l[2] for l in layers], [l[1] for l in layers], [l[1] for l in layers])
+    for d, (_, s, n) in zip(descs, layers):
+        assert kf.kfac_workspace_bytes(d, n, s, s) <= whole
