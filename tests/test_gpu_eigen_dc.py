@@ -84,17 +84,26 @@ SPECTRA = {
     "blocks": lambda n: np.kron(np.eye((n + 9) // 10), _factor(10, 30, 10))[:n, :n].astype(np.float32),
     "tiny": lambda n: (1e-20 * _factor(n, 2 * n, 11)).astype(np.float32),
     "huge": lambda n: (1e25 * _factor(n, 2 * n, 12)).astype(np.float32),
+    "dense among diagonal": lambda n: _among_diagonal(n),
     "zero": lambda n: np.zeros((n, n), dtype=np.float32),
 }
 
 
 @pytest.mark.parametrize("kind", sorted(SPECTRA))
-@pytest.mark.parametrize("n", [50, 145, 300])
+@pytest.mark.parametrize("n", [50, 145, 300, 801])
 def test_spectra(kind, n):
     m = SPECTRA[kind](n)
     (a, _), info = _eigen([(m, np.eye(3, dtype=np.float32))])
     assert list(info) == [0, 0]
     _check(*a, f"{kind} n={n}")
+
+
+def _among_diagonal(n):
+    """Columns with nothing to reduce before and behind those with something, inside a panel of the reduction and across."""
+    m = np.diag(np.linspace(1.0, 2.0, n)).astype(np.float32)
+    for at, size in ((n // 5, n // 4), (n - n // 7 - 3, n // 7)):
+        m[at:at + size, at:at + size] = _factor(size, 2 * size, size)
+    return m
 
 
 def _dead(n, at, value, count=1):
