@@ -103,3 +103,28 @@ def test_workspace_of_a_network_serves_its_layers():
     whole = kf.kfac_workspace_bytes_batched(descs, [l[2] for l in layers], [l[1] for l in layers], [l[1] for l in layers])
     for d, (_, s, n) in zip(descs, layers):
         assert kf.kfac_workspace_bytes(d, n, s, s) <= whole
+
+
+@pytest.mark.parametrize("c, h, b", [(16, 16, 4), (64, 8, 4), (24, 15, 4), (96, 14, 4), (128, 9, 8)])
+def test_border_much_larger_than_the_inside(c, h, b):
+    """Entries of taps that never see a border row or column are the sum over the whole map less the border's, so they carry its
+    rounding: a few 2^-24 of the geometric mean of the two channels' centre-tap entries, which hold every position (Cauchy-
+    Schwarz), whatever the entry itself amounts to.  Norm-wise nothing is lost.  (A direct sum has that bound entry by entry
+    only with the taps' own entries.)"""
+    rng = np.random.default_rng(c + h)
+    x = np.maximum(rng.standard_normal((b, c, h, h)), 0).astype(np.float32)
+    for edge in (np.s_[:, :, 0], np.s_[:, :, -1], np.s_[:, :, :, 0], np.s_[:, :, :, -1]):
+        x[edge] *= 1000.0
+    cols = torch.nn.functional.unfold(torch.from_numpy(x).double(), 3, padding=1).permute(0, 2, 1).reshape(-1, 9 * c)
+    p = torch.cat([cols, torch.ones(len(cols), 1, dtype=torch.float64)], 1)
+    ref = 0.1 / b * (p.T @ p).numpy()
+    kf.kfac_tune("corrw_min_gain", 0)
+    try:
+        got = _factor(c, h, h, b, 1, x, np.zeros_like(ref, dtype=np.float32))
+    finally:
+        kf.kfac_tune("corrw_min_gain", 42)
+    centre = np.sqrt(np.append(np.repeat(np.diag(ref)[4:9 * c:9], 9), ref[-1, -1]))
+    err = np.abs(got - ref) / np.outer(centre, centre)
+    print(c, h, f"norm-wise {gu.rel_fro(got, ref):.2e}, of the centre taps {err.max():.2e}")
+    assert gu.rel_fro(got, ref) < 1e-6
+    assert err.max() < 16 * 2.0 ** -24

@@ -1,4 +1,4 @@
-"""Tridiagonalisation and divide and conquer (orders up to 1280): edges of its tiers (leaves of 32, one CU's panels at 256
+"""Tridiagonalisation and divide and conquer (orders up to 1280): edges of its tiers (leaves of 16, one CU's panels at 256
 and 768 columns, vectors per workgroup at 320 and 640), spectra that deflate or cluster, and what must come out exactly.
 
 Bounds as in test_gpu_eigen.py (a backward stable fp32 method: a small multiple of 6e-8 ||M|| on the eigenvalues, on
@@ -64,7 +64,7 @@ def _with_spectrum(lam, seed):
     return ((m + m.T) / 2).astype(np.float32)
 
 
-@pytest.mark.parametrize("n", [32, 33, 34, 63, 65, 97, 128, 129, 255, 257, 258, 319, 321, 577, 640, 641, 768, 769, 1025, 1280])
+@pytest.mark.parametrize("n", [1, 2, 15, 16, 17, 18, 31, 32, 33, 34, 63, 65, 97, 128, 129, 255, 257, 258, 319, 321, 577, 640, 641, 768, 769, 1025, 1280])
 def test_orders(n):
     (a, g), info = _eigen([(_factor(n, 3 * n, n), _factor(7 + n % 31, 50, n + 1))])
     assert list(info) == [0, 0]
@@ -156,8 +156,10 @@ def test_diagonal_is_exact_and_in_place(n):
 
 
 def test_many_matrices_of_mixed_orders():
-    """More than one launch's table (128), every tier at once, and one matrix beyond the range of the method."""
-    sizes = [(577, 64), (1300, 20), (289, 33), (145, 200)] + [(30 + 5 * (i % 40), 10 + i % 60) for i in range(70)]
+    """More than one launch's table (256), every tier at once, one matrix beyond the range of the method; the second table, the
+    smallest of 279, holds nothing but leaves."""
+    sizes = [(577, 64), (1300, 20), (289, 33), (145, 200)] + [(30 + 5 * (i % 40), 10 + i % 60 if i % 3 else 1 + i % 16) for i in range(136)]
+    assert sorted(n for s in sizes for n in s)[23] <= 16 and len(sizes) == 140
     mats = [(_factor(a, 2 * a, i), _factor(g, 2 * g, 500 + i)) for i, (a, g) in enumerate(sizes)]
     out, info = _eigen(mats)
     assert not info.any()

@@ -126,3 +126,19 @@ def test_outputs_over_inverses_of_g():
     for i in range(n):
         ref = G[i].astype(np.float64) @ W[i].astype(np.float64) @ A[i].astype(np.float64)
         assert gu.rel_fro(out[i].cpu().numpy(), ref) < 1e-5, i
+
+
+def test_eigen_form_of_many_layers():
+    """More transposes than one launch's table holds (256) and more narrow layers (128), wide ones among them."""
+    shapes = [SHAPES[i % len(SHAPES)] if i % 17 else (70 + i, 90) for i in range(150)]
+    shapes = [s if max(s) < 1000 else (100, 30) for s in shapes]
+    layers = _eigen_layers(shapes, 22)
+    n = len(shapes)
+    QA, vA, QG, vG, W = ([gu.to_dev(l[k]) for l in layers] for k in range(5))
+    out = [torch.full_like(w, float("nan")) for w in W]
+    descs = [_desc(*s) for s in shapes]
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_precondition_eigen_batched(descs, QA, vA, QG, vG, 0.1, W, out, ws)
+    torch.cuda.synchronize()
+    for s, l, o in zip(shapes, layers, out):
+        assert gu.rel_fro(o.cpu().numpy(), l[5]) < 1e-5, s
