@@ -982,7 +982,6 @@ int kfac_tune(const char *key, long value)
     else if (k == "use_wave_kernel") t.use_wave_kernel = value;
 #ifdef KFAC_MEASUREMENT_KNOBS
     // skips MFMAs or loads inside the wave kernels (wrong results): only in builds made for measuring
-    else if (k == "wave_debug") t.wave_debug = value;
 #endif
     else if (k == "fuse_conv3") t.fuse_conv3 = value;
     else if (k == "fuse_conv3_max_c") t.fuse_conv3_max_c = value;

@@ -207,7 +207,6 @@ struct Tuning {
     long gemm_bm = 0;                // block tile of the preconditioning GEMMs (0 = choose)
     long precond_wide_tiles = 256;   // ... with 64-wide tiles from this many of them on, else 32-wide ones
     long use_precond_fused = 1;      // two-sided products of layers with a dimension of at most 64 in one launch
-    long wave_debug = 0;             // measurement only: 1 = skip MFMAs, 2 = skip data loads (results are wrong)
 };
 Tuning &tuning();
 

@@ -1062,7 +1062,6 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
     for (auto &g : groups) {
         SyrkTable tab;
         tab.count = (int)g.size();
-        tab.debug = (int)tuning().wave_debug;
         int blocks = 0;
         double flops = 0.0, corr_flops = 0.0;   // corr_flops: six piece products of 13 lag tiles per channel-tile pair and pixel, 6 x 26 C^2 per pixel
         std::vector<int> red_n(g.size());

@@ -84,7 +84,6 @@ struct Conv3Ctx {
     int w, lane, tid;
     int rslot, cslot, ctile0;
     bool single, owns_colsum;
-    bool no_mfma, no_load, no_issue;   // measurement switches
 };
 
 template <int NIW>
@@ -99,14 +98,13 @@ template <int NIW>
 __device__ __forceinline__ void conv3_issue(const Conv3Ctx &c, const Conv3Lanes<NIW> &ln, int g)
 {
     const Conv3Geo &G = c.g;
-    if (c.no_issue) return;
     const unsigned stage_bytes = (unsigned)(W_SLOTS * G.slab * 4);
     const unsigned buf = c.lds_base + (unsigned)(g % C3_NSTAGE) * stage_bytes;
     const unsigned dummy = c.lds_base + (unsigned)C3_NSTAGE * stage_bytes;
 #pragma unroll
     for (int s = 0; s < W_SLOTS; ++s) {
         const int st = c.single ? 3 * g + s : g;       // conv stage (relative to the split) this slot holds
-        const bool live = (s < c.nslots) && (g < c.nstages) && (st < c.nst) && !c.no_load;
+        const bool live = (s < c.nslots) && (g < c.nstages) && (st < c.nst);
         const unsigned sg = (unsigned)(c.sg0 + st);
         const unsigned n = sg / (unsigned)G.spi;
         const int oh0 = (int)(sg - n * (unsigned)G.spi) * G.R;
@@ -230,9 +228,7 @@ __device__ __forceinline__ void conv3_loop(const Conv3Ctx &c, const Conv3Lanes<N
     for (int g = 0; g < c.nstages; ++g) {
         conv3_issue<NIW>(c, ln, g + 2);
         const float *buf = lds + (g % C3_NSTAGE) * (W_SLOTS * G.slab);
-        if (c.no_mfma) {
-            // measurement only
-        } else {
+        {
             // k-steps of this wave: single blocks give wave w the steps w, w+4, ... of each of the three
             // staged conv stages; otherwise the wave walks all steps of its own panels.  The operands of
             // step i+1 are fetched from LDS (two register sets, A and B) while the MFMAs of step i run.
@@ -351,9 +347,6 @@ __global__ __launch_bounds__(256) void syrk_conv3_kernel(const SyrkTable tab)
     c.rslot = r.rslot; c.cslot = r.cslot; c.ctile0 = r.ctile0;
     c.C = pr.ctot;
     c.w = w; c.lane = lane; c.tid = tid;
-    c.no_mfma = (tab.debug & 1) != 0;
-    c.no_load = (tab.debug & 2) != 0;
-    c.no_issue = (tab.debug & 4) != 0;
 
     // conv stages of this split
     const long nimg = pr.K / pr.hw;

@@ -39,7 +39,6 @@ struct WaveCtx {
     int w, lane, tid;
     int rslot, cslot, ctile0;
     bool single, owns_colsum;
-    bool no_mfma, no_load;   // measurement switches
 };
 
 // Issue the loads of stage g into ring buffer g % 4: exactly nine instructions per wave, whatever
@@ -52,7 +51,7 @@ __device__ __forceinline__ void wave_issue(const WaveCtx &c, int g)
 #pragma unroll
     for (int s = 0; s < W_SLOTS; ++s) {
         const int tl = c.single ? 3 * g + s : g;       // K tile (relative to the split) this slot holds
-        const bool live = (s < c.nslots) && (g < c.nstages) && (tl < c.ntl) && !c.no_load;
+        const bool live = (s < c.nslots) && (g < c.nstages) && (tl < c.ntl);
         const unsigned so = live ? (unsigned)tl * c.tile_bytes : 0u;
 #pragma unroll
         for (int qi = 0; qi < 3; ++qi) {
@@ -79,9 +78,7 @@ __device__ __forceinline__ void wave_loop(const WaveCtx &c, const float *lds, fl
     for (int g = 0; g < c.nstages; ++g) {
         wave_issue(c, g + 3);
         const float *buf = lds + (g & (W_NSTAGE - 1)) * W_STAGE;
-        if (c.no_mfma) {
-            // measurement only
-        } else if (KIND == kSingle) {
+        if (KIND == kSingle) {
             // wave w multiplies rows 4w..4w+3 of each of the three staged K tiles
 #pragma unroll
             for (int st = 0; st < 3; ++st) unit_diag(buf + st * W_PANEL, 4 * c.w, c.lane, acc);
@@ -264,8 +261,6 @@ __global__ __launch_bounds__(256) void syrk_wave_kernel(const SyrkTable tab)
     }
     c.lds_base = (unsigned)(unsigned long)(__attribute__((address_space(3))) float *)lds;
     c.w = w; c.lane = lane; c.tid = tid;
-    c.no_mfma = (tab.debug & 1) != 0;
-    c.no_load = (tab.debug & 2) != 0;
     const int ld = (int)pr.ld;
 #pragma unroll
     for (int qi = 0; qi < 3; ++qi) {
