@@ -416,6 +416,7 @@ bool precond_overlap(int n, const kfac_layer_desc *descs, const float *const *gr
     std::sort(o.begin(), o.end());
     for (int i = 0; i < n; ++i) reach[i] = std::max(o[i].second, i ? reach[i - 1] : (uintptr_t)0);
     auto hit = [&](const Range &r) {
+        if (r.second <= o[0].first || r.first >= reach[n - 1]) return false;      // outputs in one buffer of their own: no search
         const size_t k = std::lower_bound(o.begin(), o.end(), Range(r.second, 0)) - o.begin();   // outputs that start before its end
         return k > 0 && reach[k - 1] > r.first;
     };
