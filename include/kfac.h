@@ -115,7 +115,8 @@ size_t kfac_workspace_bytes_batched(int n, const kfac_layer_desc *descs, const i
  * padding, pad columns zero; same element type as the input.
  * The kernel stages one output row of a few channels on chip: a map so wide that
  * (w_out - 1) * stride + kw elements times kh rows times 4 channels (8 for bf16, fewer when kh*kw shares a
- * factor with that) exceed 60 KB is rejected with KFAC_ERR_SHAPE by every call that would extract patches
+ * factor with that) exceed 60 KB is rejected with KFAC_ERR_SHAPE by this call and every call that would extract
+ * patches (the factors of most fp32 3x3 / stride 1 / pad 1 convolutions of 20 channels and more need none)
  * (output rows of more than about 540 columns for a 7x7 kernel, 1270 for 3x3, stride 1, either dtype). */
 kfac_status kfac_im2col(const kfac_layer_desc *desc, const void *d_act, int batch, int h, int w,
                         void *d_patches, void *hip_stream);
@@ -162,13 +163,14 @@ kfac_status kfac_precondition(const kfac_layer_desc *desc, const float *d_A_inv,
                               void *hip_stream);
 
 /* kfac_precondition for callers that cannot allocate device memory or pass a workspace (code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc): the same two products, by the same kernels,
- * with the d_A x d_G intermediate in a buffer of KFAC_STATIC_SCRATCH_BYTES that is part of the library image
- * (one copy per GPU, held until the process ends).  Allocates nothing.  A layer with
+ * capture, tight serving loops, harnesses that forbid hipMalloc): the same kernels, with the d_A x d_G
+ * intermediate of the two products in a buffer of KFAC_STATIC_SCRATCH_BYTES that is part of the library image
+ * (one copy per GPU, held until the process ends; layers with a dimension of at most 64 form both products in
+ * one launch without it, unless d_out overlaps d_grad or d_G_inv).  Allocates nothing.  A layer with
  * d_A * d_G * 4 > KFAC_STATIC_SCRATCH_BYTES is rejected with KFAC_ERR_TOO_LARGE before any launch.  Every
  * call on a GPU shares that GPU's buffer: calls that may overlap on one GPU (different streams, different
  * host threads) race and must be ordered by the caller.  Nothing in the buffer needs clearing between calls
- * (the first product overwrites all of what the second reads).  Every product is computed in one piece (no K
+ * (the first of two products overwrites all of what the second reads).  Every product is computed in one piece (no K
  * slices): the result equals kfac_precondition's bit for bit for a layer that call does not slice, and to
  * rounding otherwise.  Arguments as kfac_precondition. */
 #define KFAC_STATIC_SCRATCH_BYTES (32u << 20)

@@ -21,16 +21,16 @@ enum {
     KFAC_K_INV_PIVOT = 4,
     KFAC_K_INV_PANEL = 5,
     KFAC_K_INV_FINISH = 6,
-    KFAC_K_GEMM = 7,         /* A^T B MFMA GEMM (preconditioning and inverse updates) */
+    KFAC_K_GEMM = 7,         /* A^T B on small tiles (preconditioning, inverse updates), narrow layers' two-sided products */
     KFAC_K_SYRK_WAVE = 8,    /* KF-GEMM, wave-unit kernel for row-major fp32 operands */
     KFAC_K_SYRK_CONV3 = 9,   /* KF-GEMM fused with 3x3 patch extraction (reads the NCHW input) */
     KFAC_K_SYRK_SMALL = 10,  /* KF-GEMM, direct kernel for narrow NCHW operands */
     KFAC_K_INV_STEP = 11,    /* fused sweep step: panel + update + next pivot in one launch */
     KFAC_K_SYRK_BF16 = 12,   /* KF-GEMM on the bf16 MFMA units (row-major bf16 operands) */
     KFAC_K_GEMM_WAVE = 13,   /* A^T B on the wave-unit GEMM (large preconditioning and inverse products) */
-    KFAC_K_EIG_INIT = 14,    /* eigen-decomposition: working copies W = M, V = I */
-    KFAC_K_EIG_ROUND = 15,   /* eigen-decomposition: one round of the block Jacobi sweep */
-    KFAC_K_EIG_FINAL = 16,   /* eigen-decomposition: eigenvalues and Q = V^T; transposes for Eq. 13 */
+    KFAC_K_EIG_INIT = 14,    /* eigen-decomposition: working copies */
+    KFAC_K_EIG_ROUND = 15,   /* eigen-decomposition: reduction, leaves and merges; a round of the block Jacobi sweep */
+    KFAC_K_EIG_FINAL = 16,   /* eigen-decomposition: the reflectors; eigenvalues and Q = V^T; transposes for Eq. 13 */
     KFAC_K_SYRK_CORR3 = 17,  /* KF-GEMM of 3x3 convolutions from input autocorrelations (lag matrices) */
     KFAC_K_CORR3_ASM = 18,   /* border terms, sums and assembly (+ running average) of that path */
     KFAC_K_GEMM_SPLIT = 19,  /* A^T B of fp32 operands as six bf16 MFMA products of their bf16 pieces */

@@ -25,8 +25,10 @@
 
 namespace kfac {
 
-constexpr int kDcMaxN = 1280;      // largest order: LDS of dc_tridiag; one CU streams a matrix of order n in about n^2 / 40 GB/s
-                                   // per column, so that the Jacobi iteration, which spreads over the chip, wins beyond
+// Largest order: the LDS of dc_tridiag.  One matrix alone is where one CU per matrix does worst against the Jacobi iteration,
+// which spreads over the chip: order 257, 513, 769, 1025, 1153, 1280 in ms, here / Jacobi: 1.5 / 5.4, 4.4 / 13.0, 11.2 / 24.0,
+// 22.4 / 37.6, 33 / 48, 46 / 53; 32 matrices at 1280: 63 / 218.  Orders 24 to 32 alone in a call: 0.20 to 0.24 / 0.20.
+constexpr int kDcMaxN = 1280;
 constexpr int kDcLeaf = 16;         // (leaves of 32: a sweep costs eight times as much, a level less gains 0.12 ms)
 constexpr int kDcTab = 256;        // matrices per launch (a 12 KB kernel argument)
 constexpr int kDcNodes = 64;       // merges of a level at most (half of the leaves: 1280 / 16 rounded up to a power of two)

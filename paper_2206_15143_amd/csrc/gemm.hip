@@ -465,7 +465,8 @@ hipError_t launch_direct(const GemmTable &tab, int blocks, hipStream_t s)
     return launch_done(tab);
 }
 
-// the products of the blocked inversion's chain: K a multiple of 64, operands below 2 GiB (pivot blocks of 64 to 512 rows)
+// the products of the blocked inversion's chain: K a multiple of 64, operands below 2 GiB (pivot blocks of 64 to 512 rows).
+// (Never in a timed pass, which keeps everything on one stream: no chain.  Hence the class of the other small products.)
 hipError_t chain_launch(const GemmJob *jobs, int n, hipStream_t s)
 {
     for (int i0 = 0; i0 < n; i0 += kMaxGemmProblems) {
@@ -707,7 +708,8 @@ namespace {
 // is the part of its depth by which a workgroup outlasts an even share of the call.  Preconditioning of ResNet-50-, VGG-16-
 // (64 and 48 wide), small ResNet-50- (40 wide) shaped sets and two 1024-wide transformer blocks in ms: 0.996, 0.794, 0.492,
 // 0.310, 1.190; slices of at most 150 stages of anything 1.5 times as deep as an even share of 400: 1.038, 0.863, 0.533, 0.319,
-// 1.224; without slices: 0.990, 0.806, 0.534, 0.399, 1.192, and a 2048 x 1024 layer 0.230 instead of 0.147.
+// 1.224; without slices: 0.990, 0.806, 0.534, 0.399, 1.192, and a 2048 x 1024 layer 0.230 instead of 0.147.  It loses where a
+// call of 4 to 12 equal products fills one round of the chip as it is: eight 1025 x 1024 layers 0.286 sliced, 0.245 not.
 constexpr int kMaxKSlices = 8;
 
 int kslice_count(const GemmJob &j, long split_tiles, long cap)

@@ -15,7 +15,8 @@
 //   - the parts are added in wavefront order through LDS, wavefront t taking MFMA tile t: the sums land in the very
 //     registers the second product reads as its operand.
 // 110 layers of the ResNet-110 shape: 14 + 48 us as two launches of 64-wide block tiles with all wavefronts on one K stage,
-// now 33 us (one million MFMAs: 13 us of the matrix units), the call 58 -> 31 us.
+// now 33 us (one million MFMAs: 13 us of the matrix units), the call 58 -> 30 us with the operands in the last-level cache
+// and 68 -> 48 with them in memory (two chunks of loads in flight per wavefront).
 #include "common.hpp"
 
 #include <algorithm>

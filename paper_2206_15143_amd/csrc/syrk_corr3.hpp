@@ -12,7 +12,8 @@
 // with a* = H-1 for i = 0 and 0 for i = 2 (b* likewise), Row / Col the 1-D autocorrelations of that border
 // row / column and Corner the outer product of the corner pixel.  The bias border (column sums of the patch
 // matrix) follows the same inclusion-exclusion on plain sums.  The result is the same matrix as the direct
-// sum (up to rounding order) for 13 instead of 45 MFMA tiles per 16 x 16 channel pair and k-step.
+// sum (up to rounding order) for 13 instead of 45 MFMA tiles per 16 x 16 channel pair and k-step.  The subtraction leaves
+// errors relative to the centre-tap entries of the two channels (see syrk_corrw.hpp).
 //
 // Three steps: corr3_main_kernel (the 13 lag matrices, split over images, on the MFMA units),
 // corr3_border_kernel (rows, columns, corners; MFMA as well, K = border pixels), corr3_sum_kernel +
