@@ -84,8 +84,10 @@ struct Geo {
     bool g_rows;        // bf16 output gradients on a map with an odd number of positions: through a row-major copy
     int ldg;            // its leading dimension (elements)
     size_t corr_bytes = 0;   // autocorrelations of a padded copy: what they keep in the workspace (counts towards a chunk's bytes)
-    bool corr_choice = false;   // ... the patch matrix is the alternative, the call decides (plan_update)
+    bool corrw = false;         // ... whether the factor comes from them
+    bool corr_choice = false;   // ... there is another route: the call decides (plan_update)
     double corr_gain = 0.0;     // ... microseconds of work they save
+    bool conv3 = false;         // the other route is the fused 3x3 kernel, not the patch matrix
 };
 
 bool desc_ok(const kfac_layer_desc *d)
@@ -143,8 +145,10 @@ kfac_status geometry(const kfac_layer_desc *d, int batch, int h, int w, Geo &g)
         const bool corrw = d->in_dtype == KFAC_F32 && d->kh == 3 && d->kw == 3 && d->stride == 1 && ph == 1 && pw == 1 &&
                            corrw_takes(d->d_in, h, w, batch);
         if (corrw) {
-            g.corr_gain = corrw_gain(d->d_in, h, w, batch);
-            g.corr_choice = !g.fused3 && g.corr_gain >= 0.0 && im2col_fits(d->kh, d->kw, d->stride, g.Wo, g.esz);
+            g.conv3 = g.fused3;
+            g.corr_gain = corrw_gain(d->d_in, h, w, batch, g.conv3);
+            g.corrw = g.corr_gain >= 0.0;
+            g.corr_choice = g.corrw && (g.conv3 || im2col_fits(d->kh, d->kw, d->stride, g.Wo, g.esz));
         }
         g.fused3 = g.fused3 || corrw;
         // an eighth of the bytes counts: a chunk of few layers leaves every one of its launches half empty (VGG-16-,
@@ -197,6 +201,7 @@ void layer_jobs(const kfac_layer_desc *d, const Geo &g, const void *act, const v
     if (!g.conv) {
         a.x = act; a.layout = kRows; a.ld = d->d_in; a.hw = 1; a.ctot = d->d_in;
     } else if (g.fused3) {
+        a.corrw = g.corrw;
         a.x = act; a.layout = kConv3; a.ld = 0; a.hw = h * w; a.ctot = d->d_in; a.h = h; a.w = w;
     } else if (!g.patches) {
         a.x = act; a.layout = kNCHW; a.ld = 0; a.hw = h * w; a.ctot = d->d_in;
@@ -315,16 +320,18 @@ kfac_status plan_update(int n, const kfac_layer_desc *descs, const int *batch, c
         kfac_status st = geometry(&descs[i], batch[i], h ? h[i] : 1, w ? w[i] : 1, pl.geo[i]);
         if (st != KFAC_OK) return st;
         if (pl.geo[i].corr_choice) gain += pl.geo[i].corr_gain;
-        else launches = launches || (pl.geo[i].corr_bytes > 0 && pl.geo[i].corr_gain >= 0.0);
+        else launches = launches || pl.geo[i].corrw;
     }
     const double least = (double)tuning().corrw_min_gain;
-    if (alone || (!launches && gain < least))
-        for (Geo &g : pl.geo)
-            if (g.corr_choice && g.corr_gain < least) {
-                g.fused3 = false;
-                g.patches = true;
-                g.corr_bytes = 0;
-            }
+    const bool few = alone || (!launches && gain < least);
+    for (Geo &g : pl.geo)
+        if (g.corr_choice && g.corr_gain < least && (few || g.corr_gain <= 0.0)) {
+            g.corrw = false;
+            g.corr_bytes = 0;
+            if (g.conv3) continue;
+            g.fused3 = false;
+            g.patches = true;
+        }
     pl.chunks = make_chunks(pl.geo, descs, batch, h, w);
     for (const Chunk &c : pl.chunks) {
         size_t pb = 0;

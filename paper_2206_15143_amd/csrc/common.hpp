@@ -32,6 +32,7 @@ struct FactorJob {
     int d_core;      // real columns of X
     int hw, ctot;    // kNCHW / kConv3 addressing (ctot = channels)
     int h, w;        // kConv3: image size
+    bool corrw;      // kConv3: from autocorrelations of a padded copy (unless the kernel of 16, 32 and 64 channels takes it)
     int has_bias;    // factor has one more row/column: column sums and the count K
     float scale, decay;
     float *F;        // [d, d], d = d_core + has_bias
@@ -144,9 +145,9 @@ hipError_t transpose_launch(const float *const *src, float *const *dst, const in
 // its input (syrk_corrw.hpp); bytes of that copy and of the partial sums
 bool corrw_takes(int c, int h, int w, int batch);
 size_t corrw_bytes(int c, int h, int w, int batch);
-// microseconds of work that saves over the patch matrix; negative: another kernel takes the layer, infinite: the patch
-// matrix has no advantage
-double corrw_gain(int c, int h, int w, int batch);
+// microseconds of work that saves over the patch matrix, or over the fused kernel where that can take the layer (`conv3`);
+// negative: the kernel of 16, 32 and 64 channels takes it; infinite: the other route has no advantage
+double corrw_gain(int c, int h, int w, int batch, bool conv3);
 
 // output rows per stage of the fused 3x3 convolution factor kernel; 0 = image shape not supported
 int conv3_rows(int h, int w);

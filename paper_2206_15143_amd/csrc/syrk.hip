@@ -726,8 +726,7 @@ void plan_all(const FactorJob *jobs, int n, std::vector<Planned> &pl, std::vecto
     std::vector<int> keys(n);
     for (int i = 0; i < n; ++i) {
         if (corr3_eligible(jobs[i])) pl[i].cfg = kCorr3Cfg + (jobs[i].ctot == 16 ? 0 : (jobs[i].ctot == 32 ? 1 : 2));
-        else if (jobs[i].layout == kConv3 && corrw_takes(jobs[i].ctot, jobs[i].h, jobs[i].w, (int)(jobs[i].K / jobs[i].hw)))
-            pl[i].cfg = kCorrWCfg;
+        else if (jobs[i].layout == kConv3 && jobs[i].corrw) pl[i].cfg = kCorrWCfg;
         else if (jobs[i].layout == kConv3) pl[i].cfg = kConv3Cfg;
         else if (small_eligible(jobs[i])) pl[i].cfg = jobs[i].d_core <= 32 ? kSmall32Cfg : kSmall64Cfg;
         else if (bf16_eligible(jobs[i])) pl[i].cfg = kBf16Cfg;
@@ -1008,12 +1007,15 @@ bool corrw_takes(int c, int h, int w, int batch)
 //   patch matrix to the split kernel   128 x 14 x 14, batch 8: 52 / 83, 32: 87 / 98, 128: 254 / 173
 //   ... to the block-tile kernel        36 x 28 x 28, batch 8: 65 / 76, 32: 95 / 111, 128: 265 / 179
 //   ... of less than 192 columns        20 x 28 x 28, batch 8: 37 / 73, 32: 54 / 103; 58 x 58, batch 128: 438 / 447
-//   ... to the wave-unit kernel         96 x 28 x 28, batch 8: 91 / 90, 32: 239 / 137: one chain of K as long as the launches
+//   ... to the wave-unit kernel         96 x 8 x 8, batch 1: 34 / 49, 8: 77 / 69; 28 x 28, batch 32: 239 / 136
+//   the fused kernel                    48 x 8 x 8, batch 1: 32 / 43, 16: 71 / 64; 32 x 32, batch 128: 377 / 221
 // Twelve layers in a call pay the launches once: 128 x 14 x 14, batch 8: 260 / 169.  So a call takes the route when its layers
-// together save more than the 42 us of the launches; of 1318 calls measured on both routes 402 are 3 % to 2.3 times slower with
-// the route taken throughout, 69 by this rule, by 3 to 27 % (7 x 7 and 10 x 10 maps, whose copies are 1.4 to 1.65 times their
-// size, the most).
-double corrw_gain(int c, int h, int w, int batch)
+// together save more than the 42 us of the launches, and for layers of the last two kinds, whose one chain of K takes as long,
+// anyway.  Nothing is saved on a few hundred positions: the sums over the lag matrices cost as much (twenty layers of
+// 48 x 16 x 16, batch 1, 4, 16: 89 / 112, 99 / 125, 247 / 202).  Of 1318 calls measured on both routes 402 are 3 % to 2.3 times
+// slower with the route taken throughout, 69 by this rule, by 3 to 27 % (7 x 7 and 10 x 10 maps, whose copies are 1.4 to
+// 1.65 times their size, the most).
+double corrw_gain(int c, int h, int w, int batch, bool conv3)
 {
     FactorJob j{};
     j.layout = kConv3;
@@ -1023,8 +1025,10 @@ double corrw_gain(int c, int h, int w, int batch)
     j.layout = kRows;
     j.d_core = 9 * c;
     j.ld = 9 * c;                       // c is a multiple of 4
-    if (!split_syrk_eligible(j) && wave_eligible(j)) return HUGE_VAL;
-    const double per_kc2 = split_syrk_eligible(j) ? 0.36e-6 : j.d_core < tuning().split_syrk_min_d ? 0.25e-6 : 1.0e-6;
+    const bool split = split_syrk_eligible(j);
+    if (conv3) return j.K > 1000 ? HUGE_VAL : 0.0;
+    if (!split && wave_eligible(j)) return j.K > 400 ? HUGE_VAL : 0.0;
+    const double per_kc2 = split ? 0.36e-6 : j.d_core < tuning().split_syrk_min_d ? 0.25e-6 : 1.0e-6;
     return per_kc2 * c * c * std::max(0.0, (double)j.K - 150.0);
 }
 size_t corrw_bytes(int c, int h, int w, int batch)

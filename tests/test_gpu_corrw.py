@@ -64,8 +64,8 @@ def test_wide_conv_factor(case):
     assert np.array_equal(new, new.T)
 
 
-def _extractions(layers):
-    """Patch extractions launched by one call over layers (channels, map, batch)."""
+def _routes(layers):
+    """The kernels that one call over layers (channels, map, batch) launches for their factors."""
     descs = [kf.LayerDesc.conv2d(c, 4, 3, 1, 1, True, kf.KFAC_F32) for c, _, _ in layers]
     b, h = [l[2] for l in layers], [l[1] for l in layers]
     x = [torch.ones(n, c, s, s, device=gu.DEV) for c, s, n in layers]
@@ -77,24 +77,28 @@ def _extractions(layers):
     kf.kfac_timing_enable(True)
     try:
         kf.kfac_update_factors_batched(descs, x, g, b, h, h, one, one, 0.0, A, G, ws)
-        launches = kf.kfac_timing_collect().get("im2col", (0.0, 0, 0.0))[1]
+        launches = kf.kfac_timing_collect()
     finally:
         kf.kfac_timing_enable(False)
     for a, (c, s, n) in zip(A, layers):                   # all ones: the corner of the bias counts the positions, tap (1, 1) too
         assert float(a[-1, -1]) == n * s * s and float(a[4, 4]) == n * s * s
-    return launches
+    names = {"im2col": "patches", "syrk_conv3": "fused", "syrk_split": "copies"}     # (no factor here is split otherwise)
+    return {names[k] for k, v in launches.items() if k in names and v[1]}
 
 
-@pytest.mark.parametrize("layers, patches", [
-    ([(128, 14, 8)], True), ([(128, 14, 128)], False),             # a layer by itself: by its work
-    ([(128, 14, 8)] * 12, False), ([(36, 14, 8)] * 3, True),       # layers of a call together
-    ([(20, 28, 32)], True), ([(96, 28, 8)], False),                # alternatives that cost least and most
-    ([(128, 14, 8), (96, 28, 8)], False),                          # a layer that takes the route anyway brings its launches
-    ([(64, 8, 8), (128, 14, 8)], True),                            # ... but not one that has a kernel of its own (64 channels)
+@pytest.mark.parametrize("layers, routes", [
+    ([(36, 14, 8)], {"patches"}), ([(36, 28, 128)], {"copies"}),      # a layer by itself: by its work
+    ([(36, 14, 8)] * 3, {"patches"}), ([(36, 28, 8)] * 12, {"copies"}),    # layers of a call together
+    ([(20, 28, 32)], {"patches"}), ([(20, 50, 128)] * 2, {"copies"}),       # the alternative that costs least,
+    ([(96, 28, 8)], {"copies"}), ([(96, 8, 1)], {"patches"}),      # those that take as long as the launches
+    ([(48, 28, 8)], {"copies"}), ([(48, 8, 2)], {"fused"}),
+    ([(36, 14, 8), (96, 28, 8)], {"copies"}),                      # a layer that takes the route anyway brings its launches,
+    ([(48, 8, 2), (36, 14, 8), (96, 28, 8)], {"copies", "fused"}),        # but nothing to one without gain
+    ([(64, 8, 8), (36, 14, 8)], {"patches"}),                      # nor one that has a kernel of its own (64 channels)
 ])
-def test_small_calls_keep_the_patch_matrix(layers, patches):
-    """The route costs four dependent launches: a call too small to earn them keeps the patch matrix."""
-    assert (_extractions(layers) > 0) == patches
+def test_small_calls_keep_the_other_routes(layers, routes):
+    """The route costs four dependent launches: a call too small to earn them keeps the patch matrix or the fused kernel."""
+    assert _routes(layers) == routes
 
 
 def test_workspace_of_a_network_serves_its_layers():
