@@ -27,6 +27,7 @@
 // kfac_invert_pi computes the two damping terms of Eq. 12 on the device first
 // (pi_damping_kernel) and the kernels above read them through a device pointer.
 #include "invert_fused.hpp"
+#include "invert_chol.hpp"
 
 #include <algorithm>
 #include <mutex>
@@ -379,12 +380,25 @@ __global__ __launch_bounds__(256) void sweep_finish_kernel(const InvTable tab)
 }
 
 namespace {
-bool takes_fused(int n) { return n <= tuning().invert_fused_max_n; }
+bool takes_chol(int n) { return n > tuning().invert_chol_min_n && n <= kCholMaxOrder; }
+bool takes_fused(int n) { return !takes_chol(n) && n <= tuning().invert_fused_max_n; }
+int chol_thin(int n) { return n > CB && n % CB == 1; }
+// row pitch of T: whole cache lines, and not a multiple of 2 KB (a column of tiles would come from few memory channels)
+int chol_ld(int n)
+{
+    const int ld = (n + 31) / 32 * 32;
+    return ld % 512 == 0 ? ld + 32 : ld;
+}
+size_t chol_ws_floats(int n)
+{
+    return (size_t)n * chol_ld(n) + (n > CB ? (size_t)CB * CB : 0) + align_up(n, 64);
+}
 size_t fused_ws_floats(int n) { return 4 * (size_t)NB * NB + 2 * (size_t)NB * ((n + 3) / 4 * 4) + 16; }
 // large matrices: two sets of V, W panels, of the pivot block and of its inverse, W and the residual of the next pivot
 // block's columns, the workspace of the nested pivot-block inversion, its status and gate words
 size_t job_ws_floats(int n)
 {
+    if (takes_chol(n)) return chol_ws_floats(n);
     if (takes_fused(n)) return fused_ws_floats(n);
     const size_t PB = (size_t)outer_block();
     return 5 * PB * ((n + 3) / 4 * 4) + 6 * PB * PB + fused_ws_floats((int)PB) + 64;
@@ -394,7 +408,126 @@ int *fused_gate_ptr(float *ws, int n)
 {
     return reinterpret_cast<int *>(ws + 4 * (size_t)NB * NB + 2 * (size_t)NB * ((n + 3) / 4 * 4));
 }
-size_t table_bytes(int n) { return align_up((size_t)2 * n * sizeof(InvProbF), 256); }
+size_t table_bytes(int n) { return align_up((size_t)2 * n * sizeof(InvProbF), 256) + align_up((size_t)n * sizeof(CholProb), 256); }
+
+// The matrices listed in `idx` (sorted by order, largest first) by their triangular factors.
+struct CholRun {
+    const InvertJob *jobs;
+    const std::vector<int> &idx;
+    CholProb *tab;
+    hipStream_t s;
+    std::vector<CholClass> classes;      // equal numbers of column tiles, largest first
+
+    int leading(int k) const { const int n = jobs[idx[k]].n; return n - chol_thin(n); }
+    hipError_t upload(const std::vector<size_t> &offs, void *work);
+    // launches of `parts(nt)` workgroups per matrix, classes with none left out
+    template <class Parts, class Launch>
+    hipError_t each(int step, Parts parts, Launch launch)
+    {
+        CholSeq q;
+        q.tab = tab;
+        q.step = step;
+        q.nclass = 0;
+        long blocks = 0;
+        auto flush = [&]() -> hipError_t {
+            if (q.nclass == 0) return hipSuccess;
+            if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
+            launch(q, (unsigned)blocks);
+            q.nclass = 0;
+            blocks = 0;
+            return hipGetLastError();
+        };
+        for (const CholClass &c : classes) {
+            const int per = parts(c.nt);
+            if (per <= 0) continue;
+            CholClass &d = q.c[q.nclass++];
+            d = c;
+            d.per = per;
+            d.blk_start = (int)blocks;
+            blocks += chol_class_blocks(c.count, per);
+            if (q.nclass == kMaxCholClasses) {
+                hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+        }
+        return flush();
+    }
+    hipError_t run();
+};
+
+hipError_t CholRun::upload(const std::vector<size_t> &offs, void *work)
+{
+    const int total = (int)idx.size();
+    for (int g0 = 0; g0 < total; g0 += kCholUploadMax) {
+        CholUpload u;
+        u.dst = tab + g0;
+        u.count = std::min(kCholUploadMax, total - g0);
+        for (int k = 0; k < u.count; ++k) {
+            const InvertJob &j = jobs[idx[g0 + k]];
+            CholProb &p = u.p[k];
+            float *ws = reinterpret_cast<float *>(static_cast<char *>(work) + offs[idx[g0 + k]]);
+            p.M = j.M; p.out = j.Minv; p.info = j.info; p.damping = j.damping; p.dptr = j.damping_dev;
+            p.thin = chol_thin(j.n); p.n = j.n - p.thin;
+            p.ld = chol_ld(j.n);
+            p.ldm = j.ldm > 0 ? j.ldm : j.n;
+            p.ldo = j.ldo > 0 ? j.ldo : j.n;
+            p.T = ws;
+            p.Xt = ws + (size_t)j.n * p.ld;
+            p.z = p.Xt + (j.n > CB ? (size_t)CB * CB : 0);
+        }
+        KFAC_LAUNCH(KFAC_K_INV_INIT, s, chol_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    for (int k = 0; k < total; ++k) {
+        const int nt = (leading(k) + S_BN - 1) / S_BN;
+        if (classes.empty() || classes.back().nt != nt) classes.push_back(CholClass{k, 0, nt, 0, 0});
+        ++classes.back().count;
+    }
+    return hipSuccess;
+}
+
+hipError_t CholRun::run()
+{
+    const int total = (int)idx.size();
+    const int steps = (leading(0) + CB - 1) / CB;
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < steps && e == hipSuccess; ++k) {
+        if (k > 0) {
+            // the panel before into this diagonal block: 32 x 32 tiles of its lower triangle
+            e = each(k - 1, [&](int nt) { const int t = 4 * std::min(2, nt - 2 * k); return t > 0 ? t * (t + 1) / 2 : 0; },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(64), 0, q); });
+            if (e != hipSuccess) return e;
+        }
+        {
+            CholSeq q;
+            q.tab = tab;
+            q.nclass = 1;
+            q.step = k;
+            int active = 0;
+            while (active < total && leading(active) > k * CB) ++active;
+            q.c[0] = CholClass{0, active, 0, 1, 0};
+            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, chol_diag_kernel, dim3(active), dim3(512), 0, q);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        e = each(k, [&](int nt) { return nt > 2 * k ? chol_panel_parts(nt, k) : 0; },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
+    }
+    bool thin = false;
+    for (int k = 0; k < total; ++k) thin = thin || chol_thin(jobs[idx[k]].n);
+    if (e == hipSuccess && thin) {
+        e = each(0, [&](int nt) { return 8 * nt; },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_z_kernel, dim3(blocks), dim3(256), 0, q); });
+        if (e == hipSuccess)
+            e = each(0, [&](int nt) { return 2 * nt; },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_row_kernel, dim3(blocks), dim3(1024), 0, q); });
+    }
+    if (e == hipSuccess)
+        e = each(0, [&](int nt) { return chol_out_parts(nt); },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); });
+    return e;
+}
 
 // One-launch-per-step sweep for the matrices listed in `idx` (sorted by order, largest first).
 hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, const std::vector<size_t> &offs,
@@ -1220,7 +1353,7 @@ hipError_t border_launch(const InvertJob *jobs, const std::vector<int> &idx, con
 // orders the sweep hands to the bordering: 64 k + 1 inside the range of the one-launch-per-step path
 bool takes_border(int n)
 {
-    return tuning().invert_border && n > 64 && n % 64 == 1 && takes_fused(n - 1) && n - 1 <= 1280;   // 1280: the LDS vectors of the two kernels
+    return tuning().invert_border && !takes_chol(n) && n > 64 && n % 64 == 1 && takes_fused(n - 1) && n - 1 <= 1280;   // 1280: the LDS vectors of the two kernels
 }
 size_t border_ws_floats(int n) { return takes_border(n) ? 3 * (size_t)((n - 1 + 63) / 64 * 64) : 0; }
 }  // namespace
@@ -1264,11 +1397,12 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     }
     const InvertJob *jobs = inner.data();
     // largest matrices first so that the matrices still active at a step form a prefix
-    std::vector<int> large, fused;
-    for (int i = 0; i < n_all; ++i) (takes_fused(jobs[i].n) ? fused : large).push_back(i);
+    std::vector<int> large, fused, chol;
+    for (int i = 0; i < n_all; ++i) (takes_chol(jobs_in[i].n) ? chol : takes_fused(jobs[i].n) ? fused : large).push_back(i);
     auto by_size = [&](int a, int b) { return jobs[a].n > jobs[b].n; };
     std::stable_sort(large.begin(), large.end(), by_size);
     std::stable_sort(fused.begin(), fused.end(), by_size);
+    std::stable_sort(chol.begin(), chol.end(), by_size);
     InvProbF *dtab = static_cast<InvProbF *>(work);
     // The library's own streams: the chains of the blocked sweep on one, and, when there are large matrices too,
     // the one-launch-per-step class on the other (independent matrices: the two classes run side by side).
@@ -1304,6 +1438,11 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     if (e == hipSuccess && !bordered.empty()) e = border_launch(jobs_in, bordered, ybuf, sticky, fs);
     if (side_open && hipEventRecord(aux->side_done, fs) != hipSuccess) return hipErrorUnknown;
     if (!side_open && e == hipSuccess) e = run_large();
+    if (e == hipSuccess && !chol.empty()) {
+        CholRun run{jobs_in, chol, reinterpret_cast<CholProb *>(static_cast<char *>(work) + align_up((size_t)2 * n_all * sizeof(InvProbF), 256)), s, {}};
+        e = run.upload(offs, work);
+        if (e == hipSuccess) e = run.run();
+    }
     // always join the side stream, also after an error
     if (side_open && hipStreamWaitEvent(s, aux->side_done, 0) != hipSuccess) return hipErrorUnknown;
     return e;

@@ -122,6 +122,7 @@ struct SplitSrc {
     __amdgpu_buffer_rsrc_t ra, rb;
     unsigned va[LAYOUT == kRows ? 1 : 4], vb[LAYOUT == kRows ? 1 : 2];   // byte offset of the column(s), or W_OOB
     unsigned lda4, ldb4;           // kRows: row pitch in bytes
+    bool down = false;             // kRows: from the last stage to the first
     int lim_a, lim_b;              // columns of the tile that exist
     int nstages;
     int hw, tpi, img0, kt0, ii, ik;   // kNCHW: image walk
@@ -165,8 +166,9 @@ struct SplitSrc {
         At p;
         p.live = g < nstages;
         if constexpr (LAYOUT == kRows) {
-            p.sa = p.live ? (unsigned)(g * S_KT) * lda4 : 0u;
-            p.sb = p.live ? (unsigned)(g * S_KT) * ldb4 : 0u;
+            const int row = (down ? nstages - 1 - g : g) * S_KT;
+            p.sa = p.live ? (unsigned)row * lda4 : 0u;
+            p.sb = p.live ? (unsigned)row * ldb4 : 0u;
             p.valid = S_KT;
         } else {
             p.valid = min(S_KT, hw - ik * S_KT);
@@ -229,9 +231,22 @@ struct SplitSrc {
 // `rows`: row tiles (of 32 rows) of the wavefront's part that are wanted.  0: it only helps with the staging; 1: it
 // multiplies that one (the bias column makes orders of 2^n + 1 the rule here: a tile for a single row would otherwise
 // cost as much power, which is what the full chip is short of, as a whole one); more: all of them.
-template <int LAYOUT, bool SHARED, bool MASK>
+//
+// init(acc, unit) leaves what the products are added to: zero, or values times `unit` (the same function is called again for
+// the recomputation, with another unit).
+struct SplitZero {
+    __device__ __forceinline__ void operator()(floatx16 (&acc)[8], float) const
+    {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    }
+};
+
+template <int LAYOUT, bool SHARED, bool MASK, class Init = SplitZero>
 __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, floatx16 (&acc)[8], float (&csum)[4], int boff,
-                                            int rows, int wm, int wn, int tid)
+                                            int rows, int wm, int wn, int tid, const Init &init = Init())
 {
     typedef SplitSrc<LAYOUT> Src;
     typedef SplitLds Lds;
@@ -369,10 +384,7 @@ __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, 
         __syncthreads();
     };
 
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    init(acc, 1.f / kSplitUnscale);
 #pragma unroll
     for (int i = 0; i < 4; ++i) csum[i] = 0.f;
     src.rewind();
@@ -414,10 +426,7 @@ __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, 
     __syncthreads();
     if (L.redo == 0) return kSplitUnscale;
     // ---- the fp32 MFMA: rare, written for size ----
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    init(acc, 1.f);
     float *xs = reinterpret_cast<float *>(L.ring);           // [16 k][columns of A | of B]
     constexpr int XP = S_BM + S_BN + 8;
     src.rewind();
