@@ -472,8 +472,8 @@ hipError_t CholRun::upload(const std::vector<size_t> &offs, void *work)
             p.ldm = j.ldm > 0 ? j.ldm : j.n;
             p.ldo = j.ldo > 0 ? j.ldo : j.n;
             p.T = ws;
-            p.Xt = ws + (size_t)j.n * p.ld;
-            p.z = p.Xt + (j.n > CB ? (size_t)CB * CB : 0);
+            p.F = ws + (size_t)j.n * p.ld;
+            p.z = p.F + (j.n > CB ? (size_t)CB * CB : 0);
         }
         KFAC_LAUNCH(KFAC_K_INV_INIT, s, chol_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
         hipError_t e = hipGetLastError();
@@ -493,12 +493,6 @@ hipError_t CholRun::run()
     const int steps = (leading(0) + CB - 1) / CB;
     hipError_t e = hipSuccess;
     for (int k = 0; k < steps && e == hipSuccess; ++k) {
-        if (k > 0) {
-            // the panel before into this diagonal block: 32 x 32 tiles of its lower triangle
-            e = each(k - 1, [&](int nt) { const int t = 4 * std::min(2, nt - 2 * k); return t > 0 ? t * (t + 1) / 2 : 0; },
-                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(64), 0, q); });
-            if (e != hipSuccess) return e;
-        }
         {
             CholSeq q;
             q.tab = tab;
@@ -513,6 +507,9 @@ hipError_t CholRun::run()
         }
         e = each(k, [&](int nt) { return nt > 2 * k ? chol_panel_parts(nt, k) : 0; },
                  [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
+        if (e == hipSuccess)
+            e = each(k, [&](int nt) { return chol_next_parts(nt, k); },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(64), 0, q); });
     }
     bool thin = false;
     for (int k = 0; k < total; ++k) thin = thin || chol_thin(jobs[idx[k]].n);

@@ -7,24 +7,25 @@
 // W_m the 256 x n panel of an earlier block m (X's rows left of its diagonal block and in it, L^T's rows to the right),
 //     V   = M[k, c] - sum_{m < k} W_m[:, k]^T W_m[:, c]     right of the diagonal block (c >= p1)
 //     V   =         - sum_{m < k} W_m[:, k]^T W_m[:, c]     left of it (c < p0; W_m[:, c] is X's and begins at c's block)
-//     W_k = X_kk V,   X_kk the inverse of the triangular factor of the diagonal block, after the same sum.
+//     W_k = L_kk^-1 V,   L_kk the triangular factor of the diagonal block after the same sum.
 // A panel is stored as it is needed as an operand, depth first: rows p0 .. p1 - 1 of one n x n matrix T hold W_k.  Nothing is
-// transposed, gathered or scattered, an entry of T is written once (once more by the product with X_kk, by the
-// workgroup that holds it), and the elimination does 2/3 n^3 of the n^3 flops at a depth of up to n; the last third is
+// transposed, gathered or scattered, an entry of T is written once, and the elimination does 2/3 n^3 of the n^3 flops at a depth of up to n; the last third is
 // X^T X, stored straight to both triangles of the result.
 //
-// Three launches per block whatever the number of matrices: the last panel's part of the next diagonal block
-// (chol_next_kernel), its triangular inverse, a workgroup per matrix (chol_diag_kernel), everything else of the row
-// block (chol_panel_kernel).  The diagonal block's sum over the panels before the last one runs with the panel launch
-// of the block before.
+// Three launches per block whatever the number of matrices: the triangular inverse of its diagonal block, a workgroup per
+// matrix (chol_diag_kernel), the rest of its row block (chol_panel_kernel), what that takes away from all diagonal blocks
+// behind it (chol_next_kernel).
 //
 // Orders 256 k + 1 (a bias column behind 256 k features): the last row by itself, two products of a matrix with a
 // vector (chol_thin_kernel) instead of a block.
 //
-// Accuracy: sums right of the diagonal block start from M itself and go down from there: what a first panel takes away (the
-// large eigenvalue of features that are not centred) is gone from the accumulator for the panels behind it.  Sums of
-// the diagonal blocks and of X^T X start from zero, the latter with the last panel first: on matrices that their diagonal
-// dominates, the large terms come last.
+// Accuracy.  Diagonal blocks, their factors and the substitution with them are formed on the fp32 MFMA: their errors are what the inverse
+// of an ill-conditioned matrix shows (the bf16 MFMA cuts off low bits of what it adds: with the split products in
+// their place the error was 1.3 to 2 times as large, with them in all other places it is the same to a few percent).  Sums
+// begin with the small terms, because every addition cuts: X^T X with the last panel, the sums right of a diagonal block too,
+// the entries of M itself ahead of the first panel (which takes away what is large in them where features are not
+// centred: with the entries behind all panels the error is twice as large there, with them ahead of all a third larger on
+// centred features); sums on the diagonal come in chunks of 32 rows.
 #pragma once
 
 #include "split_common.hpp"
@@ -39,7 +40,7 @@ struct CholProb {
     const float *M;      // lower triangle read
     float *T;            // working matrix [n + thin, ld]
     float *out;          // both triangles
-    float *Xt;           // [256, 256] transposed inverse of the triangular factor of the diagonal block
+    float *F;            // [256, 256] factor of the diagonal block: -L, the inverse of its 32 x 32 blocks on the diagonal
     float *z;            // [n] workspace of the last row (thin)
     int *info;
     const float *dptr;   // device-side damping (overrides `damping` when not null)
@@ -143,7 +144,7 @@ __device__ __forceinline__ int chol_leaf(const float *src, float *xs, int lane)
         const bool tiny = d < 0x1p-96f;
         const float ds = tiny ? d * 0x1p64f : d;
         float r = __builtin_amdgcn_rsqf(ds);
-        const float h = ds * r, e = __builtin_fmaf(-h, r, 1.f);
+        const float h = ds * r, e = __builtin_fmaf(-__builtin_fmaf(ds, r, -h), r, __builtin_fmaf(-h, r, 1.f));
         r = __builtin_fmaf(0.5f * r, e, r);
         r = tiny ? r * 0x1p32f : r;
         r = ok && d <= 3.4028235e38f ? r : 0.f;
@@ -164,7 +165,7 @@ __device__ __forceinline__ int chol_leaf(const float *src, float *xs, int lane)
 
 __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
 {
-    __shared__ floatx4 ws4[16 * CD_WP / 4], xs4[16 * CD_XP / 4], leaf4[16 * CD_XP / 4];
+    __shared__ floatx4 ws4[16 * CD_WP / 4], xs4[16 * CD_XP / 4], leaf4[16 * CD_XP / 4], diag4[16][64];
     __shared__ int bad;
     float *ws = reinterpret_cast<float *>(ws4), *xs = reinterpret_cast<float *>(xs4), *leaf = reinterpret_cast<float *>(leaf4);
     const CholProb pr = q.tab[q.c[0].first + blockIdx.x];
@@ -177,19 +178,20 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
 
     floatx4 acc[8][4];
     {   // tile (r, c), c >= r: element (16 r + 4 lq + v, 16 c + ln) of the upper triangle, from the lower one
-        const float *S = q.step == 0 ? pr.M : pr.T + (long)p0 * pr.ld + p0;
-        const long lds = q.step == 0 ? pr.ldm : pr.ld;
-        const float damping = q.step == 0 ? (pr.dptr ? *pr.dptr : pr.damping) : 0.f;
+        const bool first = q.step == 0;
+        const float *S = first ? pr.M : pr.T + (long)p0 * pr.ld + p0;
+        const int pitch = first ? pr.ldm : pr.ld;
+        const float damping = first ? (pr.dptr ? *pr.dptr : pr.damping) : 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int r = 16 * (2 * i + a) + 4 * lq, c = 16 * (4 * j + b) + ln;
+                const int tr = 2 * i + a, tc = 4 * j + b, r = 16 * tr + 4 * lq, c = 16 * tc + ln;
+                typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
                 floatx4 v = {0.f, 0.f, 0.f, 0.f};
                 if (c < bs && r <= c) {
-                    const float *p = S + c * lds + r;
+                    const float *p = S + (long)c * pitch + r;
                     if (r + 3 <= c) {
-                        typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
                         v = *reinterpret_cast<const uf4 *>(p);
                     } else {
 #pragma unroll
@@ -197,9 +199,13 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
                             if (r + e <= c) v[e] = p[e];
                     }
                 }
+                if (tr == tc) {                  // on the diagonal what is taken away is summed by itself
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (r + e == c) v[e] = c < bs ? v[e] + damping : 1.f;      // rows past the edge: the identity
+                    for (int e = 0; e < 4; ++e)
+                        if (r + e == c) v[e] = c < bs ? v[e] + damping : 1.f;          // rows past the edge: the identity
+                    diag4[tr][lane] = v;
+                    v = floatx4{0.f, 0.f, 0.f, 0.f};
+                }
                 acc[i][j] = v;
                 if (j == 3) __builtin_amdgcn_sched_barrier(0);
             }
@@ -231,8 +237,18 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
                     }
 #pragma unroll
                     for (int v = 0; v < 4; ++v) ws[(4 * lq + v) * CD_WP + 16 * c + ln] = t[v];
-                    // X^T, from where the panel product reads X
-                    if (panel) *reinterpret_cast<floatx4 *>(pr.Xt + (16 * c + ln) * CB + 16 * k + 4 * lq) = c <= k ? t : floatx4{0.f, 0.f, 0.f, 0.f};
+                    if (panel) {
+                        // for the substitution: X in the 32 x 32 blocks on the diagonal, -L below them
+                        const bool same = (c >> 1) == (k >> 1);
+                        if (same && c <= k) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) pr.F[(16 * k + 4 * lq + v) * CB + 16 * c + ln] = t[v];
+                        } else if (same) {
+                            *reinterpret_cast<floatx4 *>(pr.F + (16 * k + ln) * CB + 16 * c + 4 * lq) = floatx4{0.f, 0.f, 0.f, 0.f};
+                        } else if (c > k) {
+                            *reinterpret_cast<floatx4 *>(pr.F + (16 * c + ln) * CB + 16 * k + 4 * lq) = -t;
+                        }
+                    }
                 }
             }
             __syncthreads();
@@ -261,6 +277,7 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
                         for (int jj = 0; jj < 4; ++jj) t = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[jj], f[jj], t, 0, 0, 0);
                     }
                 }
+            t += diag4[k + 1][lane];
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 if (4 * lq + v <= ln) {
@@ -288,8 +305,10 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
             for (int j = 0; j < 4; ++j) {
                 const int c = 4 * j + b;
                 if (c > k && c < r) continue;
+                floatx4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], acc[i][j], 0, 0, 0);
+                for (int jj = 0; jj < 4; ++jj) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z, 0, 0, 0);
+                acc[i][j] += z;
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -300,101 +319,80 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
     }
 }
 
-// Diagonal block k + 1 (lower triangle) -= W_k[:, block]^T W_k[:, block]: 32 x 32 tiles, a wavefront each, on the split
-// arithmetic.  Operands go straight from memory to the wavefront that cuts them, four stages of 16 rows in flight; no LDS, no
-// barrier.  A launch of five blocks: 14 us.
-__global__ __launch_bounds__(64) void chol_next_kernel(const CholSeq q)
+// All diagonal blocks behind block k (lower triangles): what W_k takes away from them.  32 x 32 tiles of the fp32 MFMA, a
+// wavefront each; operands go straight from memory into the registers that the MFMA reads, a chunk of 32 rows ahead, no
+// LDS, no barrier.  Tiles on the diagonal form their sum by itself, the others take it from the block as it was (see the
+// head of this file).
+__host__ __device__ __forceinline__ int chol_next_parts(int nt, int k)
+{
+    const int left = nt - 2 * (k + 1);                   // column tiles of 128 behind the block
+    return left <= 0 ? 0 : 36 * (left / 2) + (left % 2 ? 10 : 0);
+}
+
+__global__ __launch_bounds__(64, 4) void chol_next_kernel(const CholSeq q)
 {
     int prob, part, nt;
     if (!chol_locate(q, prob, part, nt)) return;
     const CholProb pr = q.tab[prob];
+    const int blk = part / 36;
     int bi, bj;
-    tri_decode(part, bi, bj);
-    const int p0 = q.step * CB, q0 = p0 + CB, bn = min(CB, pr.n - q0);
-    const int m0 = 32 * bi, n0 = 32 * bj, nst = CB / 16;
+    tri_decode(part - 36 * blk, bi, bj);
+    const int p0 = q.step * CB, q0 = p0 + CB * (blk + 1), bn = min(CB, pr.n - q0);
+    const int m0 = 32 * bi, n0 = 32 * bj;
     if (m0 >= bn) return;
     const int lane = threadIdx.x, lr = lane & 31, lg = lane >> 5;
     const unsigned pitch = (unsigned)pr.ld * 4u;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * pr.ld + q0, 0, (int)(CB * pitch - 4u * (unsigned)q0), 0x00020000);
     // columns past the edge repeat the last one: their results are not stored
-    const unsigned ao = (unsigned)min(m0 + lr, bn - 1) * 4u + 8u * (unsigned)lg * pitch, bo = (unsigned)min(n0 + lr, bn - 1) * 4u + 8u * (unsigned)lg * pitch;
-    float x[4][8], y[4][8];                   // rows 16 g + 8 lg + e
+    const unsigned ao = (unsigned)min(m0 + lr, bn - 1) * 4u + (unsigned)lg * pitch, bo = (unsigned)min(n0 + lr, bn - 1) * 4u + (unsigned)lg * pitch;
+    float x[2][16], y[2][16];                 // rows 32 g + 2 e + lg
     auto load = [&](int set, int g) {
-        const int gg = min(g, nst - 1);       // past the end: the last stage again, not used
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            x[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ao, (unsigned)(16 * gg + e) * pitch, 0));
-            y[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, bo, (unsigned)(16 * gg + e) * pitch, 0));
+        for (int e = 0; e < 16; ++e) {
+            x[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ao, (unsigned)(32 * g + 2 * e) * pitch, 0));
+            y[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, bo, (unsigned)(32 * g + 2 * e) * pitch, 0));
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto pieces = [&](sbf16x8 (&f)[3], const float (&v)[8]) {
-        float x0[4] = {v[0], v[1], v[2], v[3]}, x1[4] = {v[4], v[5], v[6], v[7]};
-        SplitCut k0, k1;
-        k0.scale(x0); k1.scale(x1);
+    load(0, 0);
+    // the block as it was: element (m, n) of lane lr = n, m = 8 (v >> 2) + 4 lg + (v & 3)
+    const bool first = q.step == 0, diag = bi == bj;
+    const float *from = first ? pr.M + (long)q0 * pr.ldm + q0 : pr.T + (long)q0 * pr.ld + q0;
+    const int ldf = first ? pr.ldm : pr.ld;
+    const float damping = !first ? 0.f : pr.dptr ? *pr.dptr : pr.damping;
+    const int n = n0 + lr;
+    floatx16 acc, old;
 #pragma unroll
-        for (int p = 0; p < 2; ++p) {
-            k0.half(x0, 0, 4); k1.half(x1, 0, 4);
-            const suint2 u = k0.pack(), t = k1.pack();
-            f[p] = __builtin_bit_cast(sbf16x8, suint4{u.x, u.y, t.x, t.y});
-            k0.top(0, 4); k1.top(0, 4);
-            k0.rest(x0, 0, 4); k1.rest(x1, 0, 4);
-        }
-        const suint2 u = k0.pack_last(x0), t = k1.pack_last(x1);
-        f[2] = __builtin_bit_cast(sbf16x8, suint4{u.x, u.y, t.x, t.y});
-    };
-    floatx16 acc;
+    for (int v = 0; v < 16; ++v) {
+        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
+        old[v] = m < bn && n <= m ? from[(long)m * ldf + n] : 0.f;
+    }
+    load(1, 1);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    for (int v = 0; v < 16; ++v) acc[v] = diag ? 0.f : -old[v];
+    floatx16 sum;
 #pragma unroll
-    for (int t = 0; t < 4; ++t) load(t, t);
-    sbf16x8 A[2][3], B[2][3];
-    pieces(A[0], x[0]);
-    pieces(B[0], y[0]);
-    load(0, 4);
-    for (int g = 0; g < nst; g += 4)
+    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
+    auto multiply = [&](int set) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            // the cut of the next stage between the products of this one, which wait for each other
-            pieces(A[(t + 1) & 1], x[(t + 1) & 3]);
-            pieces(B[(t + 1) & 1], y[(t + 1) & 3]);
-            constexpr int pieceA[6] = {2, 1, 1, 0, 0, 0}, pieceB[6] = {0, 1, 0, 2, 1, 0};
-#pragma unroll
-            for (int m = 0; m < 6; ++m) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[t & 1][pieceA[m]], B[t & 1][pieceB[m]], acc, 0, 0, 0);
-#pragma unroll
-            for (int m = 0; m < 6; ++m) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 23, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            load((t + 1) & 3, g + t + 5);
-        }
-    float unscale = kSplitUnscale, t = 0.f;   // t stays 0 unless something is infinite or NaN
-#pragma unroll
-    for (int v = 0; v < 16; ++v) t = __builtin_fmaf(acc[v], 0.f, t);
-    if (__any(t != 0.f)) {                    // what fp32 arithmetic gives
-        unscale = 1.f;
+        for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[set][e], y[set][e], acc, 0, 0, 0);
+        sum += acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-        const unsigned ca = ao - 8u * (unsigned)lg * pitch, cb = bo - 8u * (unsigned)lg * pitch;
-        for (int k = 0; k < 16 * nst; k += 2) {
-            const float u = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ca + (unsigned)(k + lg) * pitch, 0, 0));
-            const float v = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, cb + (unsigned)(k + lg) * pitch, 0, 0));
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(u, v, acc, 0, 0, 0);
-        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll 1
+    for (int g = 0; g < 8; g += 2) {
+        multiply(0);
+        load(0, min(g + 2, 7));               // past the end: the last rows again, not used
+        multiply(1);
+        load(1, min(g + 3, 7));
     }
-    const int n = n0 + lr;
     float *C = pr.T + (long)q0 * pr.ld + q0;
-    float old[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-        old[v] = m < bn && n <= m ? C[(long)m * pr.ld + n] : 0.f;
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-        if (m < bn && n <= m) C[(long)m * pr.ld + n] = __builtin_fmaf(-unscale, acc[v], old[v]);
+        if (m < bn && n <= m) C[(long)m * pr.ld + n] = diag ? (old[v] + (m == n ? damping : 0.f)) - sum[v] : -sum[v];
     }
 }
 
@@ -402,11 +400,10 @@ __global__ __launch_bounds__(64) void chol_next_kernel(const CholSeq q)
 __host__ __device__ __forceinline__ int chol_panel_parts(int nt, int k)
 {
     const int right = nt - 2 * (k + 1) > 0 ? nt - 2 * (k + 1) : 0;
-    return right + 2 * k + (right < 2 ? right : 2);
+    return right + 2 * k;
 }
 
-// Operands of a tile: rows of T from row `row` on (K of them), columns ca .. of A, cb .. of B; B from another matrix
-// where `b` is given.
+// Operands of a tile: K rows of A from column ca on, of B from column cb on.
 __device__ __forceinline__ void chol_source(SplitSrc<kRows> &src, const float *A, int lda, int ca, int arows, const float *B, int ldb, int cb, int bcols, int K, int tid)
 {
     src.ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(A), 0, (int)((long)K * lda * 4), 0x00020000);
@@ -421,130 +418,162 @@ __device__ __forceinline__ void chol_source(SplitSrc<kRows> &src, const float *A
     src.vb[0] = src.col_b(0) < bcols ? (unsigned)(cb + src.col_b(0)) * 4u + 4u * (unsigned)src.kq * src.ldb4 : W_OOB;
 }
 
-// Row block k: a tile of 256 rows and 128 columns per workgroup, sum over the panels before it, then, in the same
-// accumulators, X_kk times the tile (which passes through its place in T: written and read back by the same
-// workgroup).  Parts of a matrix, longest first: the tiles right of the diagonal block, those left of it (their depth
-// begins at their columns' block), the diagonal block after this one (sum alone; all panels but W_k).
+// Minus the entries of M for a tile right of the diagonal block; nothing for one left of it.
+struct CholFromM {
+    static constexpr int tail = 2;
+    __amdgpu_buffer_rsrc_t rm;
+    int ldm, ncols, wm, wn, lr, lg;
+    bool right;
+    __device__ __forceinline__ void operator()(floatx16 (&acc)[8], float unit) const
+    {
+        if (!right) return;
+        int first = wn * 64 + lr;
+        asm volatile("" : "+v"(first));          // or the addresses are computed ahead of the K loop, which has no registers for them
+        const unsigned o0 = first < ncols ? (unsigned)(first * ldm + wm * (S_BM / 2) + 4 * lg) * 4u : W_OOB;
+        const unsigned o1 = first + 32 < ncols ? o0 + 128u * (unsigned)ldm : W_OOB;
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti)
+#pragma unroll
+            for (int tj = 0; tj < 2; ++tj) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const sint4 v = __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rm, tj ? o1 : o0, (unsigned)(ti * 32 + 8 * g) * 4u, 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[ti * 2 + tj][4 * g + e] = __builtin_fmaf(-unit, __int_as_float(v[e]), acc[ti * 2 + tj][4 * g + e]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+    }
+};
+
+// Row block k: a tile of 256 rows and 128 columns per workgroup, its sum over the panels before it, then the forward
+// substitution with the diagonal block's factor.  Parts of a matrix, longest first: the tiles right of the diagonal
+// block, those left of it (their depth begins at their columns' block).
+// The substitution stays in registers: the wavefronts exchange halves of their sums so that each holds 32 columns whole, eight
+// tiles of 32 rows.  A tile is the B operand of the fp32 MFMA as it lies (the k of an MFMA may come in any order), the
+// A operand, four k to a load, is a row of the factor.  No LDS, no barrier; 576 MFMAs of 64 cycles.
 __global__ __launch_bounds__(256, 2) void chol_panel_kernel(const CholSeq q)
 {
     __shared__ SplitLds L;
+    static_assert(sizeof(L.ring) >= 4 * 4 * 4 * 64 * 16, "the exchange uses the ring");
     int prob, part, nt;
     if (!chol_locate(q, prob, part, nt)) return;
     const CholProb pr = q.tab[prob];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, wm = w >> 1, wn = w & 1;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
     int lr = lane & 31, lg = lane >> 5;
     const int k = q.step, n = pr.n, ld = pr.ld, p0 = k * CB, bs = min(CB, n - p0), p1 = p0 + bs;
     const int right = max(0, nt - 2 * (k + 1));
-    const bool is_right = part < right, is_diag = part >= right + 2 * k;
-    const int c0 = is_right ? p1 + S_BN * part : is_diag ? p1 + S_BN * (part - right - 2 * k) : S_BN * (part - right);
-    const int kbeg = is_right || is_diag ? 0 : c0 & ~(CB - 1);
-    const int r0 = is_diag ? p1 : p0, nrows = is_diag ? min(CB, n - p1) : bs;
-    const int ncols = min(S_BN, (is_right || is_diag ? n : p0) - c0);
-    const int mleft = nrows - wm * (S_BM / 2);
-    const int rows = mleft <= 0 || wn * 64 >= ncols ? 0 : (mleft + 31) / 32;
-
-    // element (m, n) of the part of M above the diagonal, from below it: m and the three rows after it are neighbours there
-    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.M + (long)c0 * pr.ldm + r0), 0, (int)((long)(ncols - 1) * pr.ldm * 4 + 4 * CB), 0x00020000);
-    auto from_m = [&](int ti, int tj, int g) {
-        const int m = wm * (S_BM / 2) + ti * 32 + 8 * g + 4 * lg, c = wn * 64 + tj * 32 + lr;
-        return __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rm, c < ncols ? (unsigned)(c * pr.ldm + m) * 4u : W_OOB, 0, 0));
-    };
-    bool first = true;
-    auto init = [&](floatx16 (&acc)[8], float unit) {
-        if (first && is_right) {
-#pragma unroll
-            for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-                for (int tj = 0; tj < 2; ++tj)
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const sint4 v = from_m(ti, tj, g);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[ti * 2 + tj][4 * g + e] = -unit * __int_as_float(v[e]);
-                        if (tj == 1 && g == 3) __builtin_amdgcn_sched_barrier(0);
-                    }
-        } else {
-            SplitZero()(acc, unit);
-        }
-    };
-    SplitSrc<kRows> src;
-    const float *rowk = pr.T + (long)p0 * ld;
-    constexpr int EP = 68;                                   // LDS row pitch of a chunk (floats)
-    float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
-    int rr = lane >> 4, c4 = (lane & 15) * 4;
-#pragma unroll 1
-    for (int pass = 0; pass < 2; ++pass) {
-        // (or the addresses of both passes are computed ahead of the loop and kept in scratch memory)
-        asm volatile("" : "+v"(lr), "+v"(lg), "+v"(rr), "+v"(c4));
-        if (pass == 0) chol_source(src, pr.T + (long)kbeg * ld, ld, r0, nrows, pr.T + (long)kbeg * ld, ld, c0, ncols, p0 - kbeg, tid);
-        else chol_source(src, pr.Xt, CB, 0, nrows, rowk, ld, c0, ncols, bs, tid);
-        first = pass == 0;
-        floatx16 acc[8];
+    const bool is_right = part < right;
+    const int c0 = is_right ? p1 + S_BN * part : S_BN * (part - right);
+    const int ncols = min(S_BN, (is_right ? n : p0) - c0);
+    floatx16 acc[8];
+    float unscale;
+    {
+        const int kbeg = is_right ? 0 : c0 & ~(CB - 1);
+        const int mleft = bs - wm * (S_BM / 2);
+        const int rows = mleft <= 0 || wn * 64 >= ncols ? 0 : (mleft + 31) / 32;
+        // element (m, n) of the part of M above the diagonal, from below it: m and the three rows after it are neighbours there
+        const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.M + (long)c0 * pr.ldm + p0), 0, (int)((long)(ncols - 1) * pr.ldm * 4 + 4 * CB), 0x00020000);
+        const CholFromM inject{rm, pr.ldm, ncols, wm, wn, lr, lg, is_right};
+        SplitSrc<kRows> src;
+        chol_source(src, pr.T + (long)kbeg * ld, ld, p0, bs, pr.T + (long)kbeg * ld, ld, c0, ncols, p0 - kbeg, tid);
+        src.ahead = is_right ? CholFromM::tail : CB / S_KT;  // the rows with the large terms last
+        src.back = max(0, src.nstages - src.ahead);
         float none[4];
-        const float unscale = split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid, init);
-        if (is_diag) {
-            // lower triangle, as the kernels of the diagonal blocks read it: M + damping I minus the sum
-            if (rows == 0) return;
-            const float damping = pr.dptr ? *pr.dptr : pr.damping;
-            const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)r0 * ld + r0, 0, (int)((long)nrows * ld * 4 - 4l * r0), 0x00020000);
+        unscale = -split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid, inject);
+    }
+    // V, tile by tile of 32 rows: the wavefront's columns 64 wn + 32 wm ..; the other half of what it summed goes to the
+    // wavefront with the other rows
+    floatx16 v[8];
+    {
+        floatx4 *give = reinterpret_cast<floatx4 *>(L.ring) + w * 16 * 64 + lane;
+        const floatx4 *take = reinterpret_cast<const floatx4 *>(L.ring) + (w ^ 2) * 16 * 64 + lane;
 #pragma unroll
-            for (int ti = 0; ti < 4; ++ti)
+        for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-                for (int tj = 0; tj < 2; ++tj) {
-                    const int cm = wn * 64 + tj * 32 + lr, c = c0 - r0 + cm;     // column of the block = row of its lower triangle
-                    sint4 old[4];
+            for (int g = 0; g < 4; ++g) {
+                floatx4 t;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int m = wm * (S_BM / 2) + ti * 32 + 8 * g + 4 * lg;
-                        const unsigned o = (unsigned)(cm * pr.ldm + m) * 4u;
-                        const bool in = c < nrows && m <= c;
-                        old[g] = __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rm, in && m + 3 <= c ? o : W_OOB, 0, 0));
-                        if (__any(in && m + 3 > c)) {
+                for (int e = 0; e < 4; ++e) t[e] = unscale * (wm ? acc[2 * ti][4 * g + e] : acc[2 * ti + 1][4 * g + e]);
+                give[(ti * 4 + g) * 64] = t;
+                if (g == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+        __syncthreads();
 #pragma unroll
-                            for (int e = 0; e < 3; ++e) {
-                                const int x = __builtin_amdgcn_raw_buffer_load_b32(rm, in && m + 3 > c && m + e <= c ? o + 4u * (unsigned)e : W_OOB, 0, 0);
-                                if (m + 3 > c) old[g][e] = x;
-                            }
-                        }
-                    }
+        for (int ti = 0; ti < 4; ++ti) {
+            floatx16 mine, other;
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int m = wm * (S_BM / 2) + ti * 32 + 8 * g + 4 * lg;
-                        const unsigned o = (unsigned)(c * ld + m) * 4u;
-                        const bool in = c < nrows && m <= c;
-                        floatx4 v;
+            for (int e = 0; e < 16; ++e) mine[e] = unscale * (wm ? acc[2 * ti + 1][e] : acc[2 * ti][e]);
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            v[e] = __builtin_fmaf(-unscale, acc[ti * 2 + tj][4 * g + e], __int_as_float(old[g][e]) + (m + e == c ? damping : 0.f));
-                        // (what lies right of the diagonal is not read: a lane's four columns are stored whole, ld is a multiple of 4)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, v), rt, in ? o : W_OOB, 0, 0);
-                    }
-                }
-            return;
+            for (int g = 0; g < 4; ++g) {
+                const floatx4 t = take[(ti * 4 + g) * 64];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) other[4 * g + e] = t[e];
+            }
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                v[ti][e] = wm ? other[e] : mine[e];
+                v[4 + ti][e] = wm ? mine[e] : other[e];
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        // (see gemm_split_kernel: through LDS, 16 lanes along a row; all loads of a batch ahead of its stores)
-        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(rowk), 0, (int)((long)bs * ld * 4), 0x00020000);
-        const float sign = pass == 0 ? -unscale : unscale;
-        const int col = c0 + wn * 64 + c4;
-        const bool live = wn * 64 + c4 < ncols;              // the pitch is a multiple of 4: a lane's columns exist or do not
-        if (rows > 0) {
+    }
+    // (Rows of V past the edge are rows of the products to come.  They are zero: they come from the columns n .. of T up to a
+    // multiple of 4, which the panels before wrote from nothing but zeros.)
+    const int cw = 64 * wn + 32 * wm;            // first column of this wavefront in the tile
+    {
+        // factor rows: element (m, k) of the lane's row lr of a tile, k = 8 g + 4 lg ..
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(pr.F, 0, CB * CB * 4, 0x00020000);
+        const unsigned xo = (unsigned)(lr * CB + 4 * lg) * 4u;
+        auto rows_of = [&](int t, int s, floatx4 (&f)[4]) {
 #pragma unroll
-            for (int ti = 0; ti < 4; ++ti) {
+            for (int g = 0; g < 4; ++g)
+                f[g] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rx, xo, (unsigned)(32 * t * CB + 32 * s + 8 * g) * 4u, 0));
+        };
+        auto times = [&](const floatx4 (&f)[4], const floatx16 &b, floatx16 c) {
 #pragma unroll
-                for (int tj = 0; tj < 2; ++tj)
+            for (int e = 0; e < 16; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(f[e >> 2][e & 3], b[e], c, 0, 0, 0);
+            return c;
+        };
+        floatx4 f[2][4];
+        rows_of(0, 0, f[0]);
 #pragma unroll
-                    for (int v = 0; v < 16; ++v)
-                        wl[(8 * (v >> 2) + 4 * lg + (v & 3)) * EP + tj * 32 + lr] = acc[ti * 2 + tj][v] * sign;
-                // (LDS operations of one wavefront complete in order: no barrier between these writes and the reads)
+        for (int s = 0, u = 0; s < 8; ++s) {
+            if (32 * s >= bs) break;
 #pragma unroll
-                for (int g = 0; g < 8; ++g) {
-                    const int m = wm * (S_BM / 2) + ti * 32 + 4 * g + rr;
-                    const floatx4 val = *reinterpret_cast<const floatx4 *>(wl + (4 * g + rr) * EP + c4);
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, val), rc, live && m < bs ? (unsigned)(m * ld + col) * 4u : W_OOB, 0, 0);
-                }
+            for (int t = s; t < 8; ++t, ++u) {
+                // the rows of the next product while this one runs
+                if (t < 7) rows_of(t + 1, s, f[(u + 1) & 1]);
+                else if (s < 7) rows_of(s + 1, s + 1, f[(u + 1) & 1]);
+                floatx16 z;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) z[e] = 0.f;
+                if (t == s) v[s] = times(f[u & 1], v[s], z);
+                else if (s == 0) v[t] = times(f[u & 1], v[s], v[t]);
+                else v[t] += times(f[u & 1], v[s], z);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        __syncthreads();                                     // the stores of the workgroup are done, its chunks free
+    }
+    // (see gemm_split_kernel: through LDS, here 8 lanes along a row, four columns each)
+    __syncthreads();
+    constexpr int EP = 36;
+    float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * ld, 0, (int)((long)bs * ld * 4), 0x00020000);
+    const int rr = lane >> 3, c4 = (lane & 7) * 4;
+    const bool live = cw + c4 < ncols;           // the pitch is a multiple of 4: a lane's columns exist or do not
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) wl[(8 * (e >> 2) + 4 * lg + (e & 3)) * EP + lr] = v[t][e];
+        // (LDS operations of one wavefront complete in order: no barrier between these writes and the reads)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int m = 32 * t + 8 * g + rr;
+            const floatx4 val = *reinterpret_cast<const floatx4 *>(wl + (8 * g + rr) * EP + c4);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, val), rc, live && m < bs ? (unsigned)(m * ld + c0 + cw + c4) * 4u : W_OOB, 0, 0);
+        }
     }
 }
 

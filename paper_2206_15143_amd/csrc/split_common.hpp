@@ -123,6 +123,7 @@ struct SplitSrc {
     unsigned va[LAYOUT == kRows ? 1 : 4], vb[LAYOUT == kRows ? 1 : 2];   // byte offset of the column(s), or W_OOB
     unsigned lda4, ldb4;           // kRows: row pitch in bytes
     bool down = false;             // kRows: from the last stage to the first
+    int ahead = 0, back = 0;       // kRows: beginning with stage `ahead`, the ones before it come last, from place `back` on
     int lim_a, lim_b;              // columns of the tile that exist
     int nstages;
     int hw, tpi, img0, kt0, ii, ik;   // kNCHW: image walk
@@ -166,7 +167,7 @@ struct SplitSrc {
         At p;
         p.live = g < nstages;
         if constexpr (LAYOUT == kRows) {
-            const int row = (down ? nstages - 1 - g : g) * S_KT;
+            const int row = (down ? nstages - 1 - g : g < back ? g + ahead : g - back) * S_KT;
             p.sa = p.live ? (unsigned)row * lda4 : 0u;
             p.sb = p.live ? (unsigned)row * ldb4 : 0u;
             p.valid = S_KT;
@@ -232,21 +233,16 @@ struct SplitSrc {
 // multiplies that one (the bias column makes orders of 2^n + 1 the rule here: a tile for a single row would otherwise
 // cost as much power, which is what the full chip is short of, as a whole one); more: all of them.
 //
-// init(acc, unit) leaves what the products are added to: zero, or values times `unit` (the same function is called again for
-// the recomputation, with another unit).
-struct SplitZero {
-    __device__ __forceinline__ void operator()(floatx16 (&acc)[8], float) const
-    {
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
-    }
+// inject(acc, unit) adds values times `unit` to the sums ahead of the last `tail` stages (of all of them if
+// there are fewer), and once more, with another unit, if the tile is computed again.
+struct SplitNone {
+    static constexpr int tail = 0;
+    __device__ __forceinline__ void operator()(floatx16 (&)[8], float) const {}
 };
 
-template <int LAYOUT, bool SHARED, bool MASK, class Init = SplitZero>
+template <int LAYOUT, bool SHARED, bool MASK, class Inject = SplitNone>
 __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, floatx16 (&acc)[8], float (&csum)[4], int boff,
-                                            int rows, int wm, int wn, int tid, const Init &init = Init())
+                                            int rows, int wm, int wn, int tid, const Inject &inject = Inject())
 {
     typedef SplitSrc<LAYOUT> Src;
     typedef SplitLds Lds;
@@ -384,7 +380,10 @@ __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, 
         __syncthreads();
     };
 
-    init(acc, 1.f / kSplitUnscale);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) csum[i] = 0.f;
     src.rewind();
@@ -398,13 +397,23 @@ __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, 
         valid = p.valid;
     }
     __syncthreads();
-    if (rows > 1) {
-        for (int g = 0; g < nstages; ++g) body(std::integral_constant<int, 4>{}, g);
-    } else if (rows == 1) {
-        for (int g = 0; g < nstages; ++g) body(std::integral_constant<int, 1>{}, g);
-    } else {
-        for (int g = 0; g < nstages; ++g) body(std::integral_constant<int, 0>{}, g);
-    }
+    auto all = [&](auto rows_c) {
+        int g = 0;
+        if constexpr (Inject::tail > 0) {
+            const int at = max(0, nstages - Inject::tail);
+            if (nstages == 0) inject(acc, 1.f / kSplitUnscale);
+#pragma unroll 1
+            for (; g < nstages; ++g) {
+                if (g == at) inject(acc, 1.f / kSplitUnscale);
+                body(rows_c, g);
+            }
+        } else {
+            for (; g < nstages; ++g) body(rows_c, g);
+        }
+    };
+    if (Inject::tail > 0 || rows > 1) all(std::integral_constant<int, 4>{});      // (with an injection: one way only, or the ways' sums meet in scratch memory)
+    else if (rows == 1) all(std::integral_constant<int, 1>{});
+    else all(std::integral_constant<int, 0>{});
 
     // Is every result finite?  Rows and columns past the edge of the operands (a 16-byte piece is not split: they may hold
     // anything) have no say.
@@ -426,7 +435,11 @@ __device__ __forceinline__ float split_tile(SplitSrc<LAYOUT> &src, SplitLds &L, 
     __syncthreads();
     if (L.redo == 0) return kSplitUnscale;
     // ---- the fp32 MFMA: rare, written for size ----
-    init(acc, 1.f);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+    inject(acc, 1.f);
     float *xs = reinterpret_cast<float *>(L.ring);           // [16 k][columns of A | of B]
     constexpr int XP = S_BM + S_BN + 8;
     src.rewind();
