@@ -509,7 +509,7 @@ hipError_t CholRun::run()
                  [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
         if (e == hipSuccess)
             e = each(k, [&](int nt) { return chol_next_parts(nt, k); },
-                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(64), 0, q); });
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(256), 0, q); });
     }
     bool thin = false;
     for (int k = 0; k < total; ++k) thin = thin || chol_thin(jobs[idx[k]].n);

@@ -25,7 +25,8 @@
 // begin with the small terms, because every addition cuts: X^T X with the last panel, the sums right of a diagonal block too,
 // the entries of M itself ahead of the first panel (which takes away what is large in them where features are not
 // centred: with the entries behind all panels the error is twice as large there, with them ahead of all a third larger on
-// centred features); sums on the diagonal come in chunks of 32 rows.
+// centred features); sums that go into
+// a diagonal block come in chunks of 16 rows.
 #pragma once
 
 #include "split_common.hpp"
@@ -76,7 +77,7 @@ __host__ __device__ __forceinline__ int chol_class_blocks(int count, int per) { 
 
 // Workgroup -> (matrix, part).  Workgroup i runs on XCD i mod 8.  The matrices of a class up to a multiple of 8 are dealt
 // to the XCDs, all workgroups of a matrix to one, matrix by matrix: they share its panels in that XCD's L2.  The up to 7
-// left over are spread over all of them.
+// left over are spread over all of them, the first (longest) parts of all of them first.
 __device__ __forceinline__ bool chol_locate(const CholSeq &q, int &prob, int &part, int &nt)
 {
     int ci = 0;
@@ -92,10 +93,10 @@ __device__ __forceinline__ bool chol_locate(const CholSeq &q, int &prob, int &pa
         return true;
     }
     off -= full * c.per;
-    const int m = off / c.per;
-    if (m >= c.count - full) return false;
-    prob = c.first + full + m;
-    part = off - m * c.per;
+    const int rest = c.count - full;
+    if (off >= rest * c.per) return false;
+    part = off / rest;
+    prob = c.first + full + off - part * rest;
     return true;
 }
 
@@ -118,62 +119,102 @@ __global__ __launch_bounds__(64) void chol_upload_kernel(const CholUpload u)
 constexpr int CD_WP = 260;                  // LDS pitch of a row of 256 (4 rows are 16 banks apart)
 constexpr int CD_XP = 20;
 
-// X of the 16 x 16 block in `src` (symmetric, pitch CD_XP) -> xs (row-major, zeros above the diagonal), one wavefront.
-// Lane c < 16 holds column c of the block, lanes 16 .. 31 the columns of the identity.  A pivot that is not positive
-// zeroes its row and is reported: 1-based place in the block, or 0.
-__device__ __forceinline__ int chol_leaf(const float *src, float *xs, int lane)
+// Lane (q, n) of the result: lane (G, n) of x[q].
+template <int G>
+__device__ __forceinline__ float chol_rows(const floatx4 &x)
 {
-    float col[16];
-    const int c = lane & 15;
-    {
-        const floatx4 *p = reinterpret_cast<const floatx4 *>(src + c * CD_XP);
+    auto u = [](float f) { return __float_as_uint(f); };
+    const auto h0 = __builtin_amdgcn_permlane32_swap(u(x[0]), u(x[2]), false, false);
+    const auto h1 = __builtin_amdgcn_permlane32_swap(u(x[1]), u(x[3]), false, false);
+    const auto g = __builtin_amdgcn_permlane16_swap(G & 2 ? h0[1] : h0[0], G & 2 ? h1[1] : h1[0], false, false);
+    return __uint_as_float(G & 1 ? g[1] : g[0]);
+}
+
+// Pivots 4 G .. 4 G + 3 of the 16 x 16 block t (MFMA result layout) and of e, which was the identity.  The four rows lie in the
+// same lanes, one register each: they are eliminated there; what they take away from the rows behind them is one MFMA each.
+template <int G>
+__device__ __forceinline__ void chol_pivots(floatx4 &t, floatx4 &e, floatx4 &pivot, int lq, int ln)
+{
+    const bool own = lq == G;
+    float r[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const floatx4 v = p[i];
+    for (int p = 0; p < 4; ++p) {
+        auto lane_of = [&](int v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t[p]), 20 * G + v)); };
+        const float d = lane_of(p);
+        float s[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) col[4 * i + e] = lane < 16 ? v[e] : (4 * i + e == c ? 1.f : 0.f);
+        for (int v = p + 1; v < 4; ++v) s[v] = lane_of(v);
+        float c = __builtin_amdgcn_rcpf(d);
+        c = __builtin_fmaf(__builtin_fmaf(-d, c, 1.f), c, c);
+        r[p] = d > 0.f && d < 0x1p126f ? -c : 0.f;
+        pivot[p] = own ? d : pivot[p];
+        const float mine = own ? r[p] : 0.f;
+#pragma unroll
+        for (int v = p + 1; v < 4; ++v) {
+            const float m = s[v] * mine;
+            t[v] = __builtin_fmaf(m, t[p], t[v]);
+            e[v] = __builtin_fmaf(m, e[p], e[v]);
         }
     }
+    if constexpr (G < 3) {
+        const float bt = chol_rows<G>(t), be = chol_rows<G>(e);
+        const float rq = lq < 2 ? (lq == 0 ? r[0] : r[1]) : (lq == 2 ? r[2] : r[3]);
+        const float at = ln >= 4 * (G + 1) ? bt * rq : 0.f;
+        e = __builtin_amdgcn_mfma_f32_16x16x4f32(at, be, e, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(at, bt, t, 0, 0, 0);
+    }
+}
+
+// X of the 16 x 16 block t (MFMA result layout, from the diagonal up), one wavefront; rows are scaled at the end, so that a
+// pivot waits for one reciprocal and a few multiply-adds of the one before it.  A pivot that is not positive leaves a
+// zero row and is reported: 1-based place in the block, or 0.
+__device__ __forceinline__ int chol_leaf(floatx4 &t, int lane)
+{
+    const int lq = lane >> 4, ln = lane & 15;
+    floatx4 e, pivot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) e[v] = 4 * lq + v == ln ? 1.f : 0.f;
+    chol_pivots<0>(t, e, pivot, lq, ln);
+    chol_pivots<1>(t, e, pivot, lq, ln);
+    chol_pivots<2>(t, e, pivot, lq, ln);
+    chol_pivots<3>(t, e, pivot, lq, ln);
     int fail = 0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(col[i]), i));
-        const bool ok = d > 0.f;
-        if (!ok && fail == 0) fail = i + 1;
-        // 1 / sqrt(d): the instruction's last bit corrected; small pivots are scaled (it takes no denormal numbers)
-        const bool tiny = d < 0x1p-96f;
-        const float ds = tiny ? d * 0x1p64f : d;
-        float r = __builtin_amdgcn_rsqf(ds);
-        const float h = ds * r, e = __builtin_fmaf(-__builtin_fmaf(ds, r, -h), r, __builtin_fmaf(-h, r, 1.f));
-        r = __builtin_fmaf(0.5f * r, e, r);
-        r = tiny ? r * 0x1p32f : r;
-        r = ok && d <= 3.4028235e38f ? r : 0.f;
-        const float w = col[i] * r;
-        col[i] = w;
-#pragma unroll
-        for (int j = i + 1; j < 16; ++j) {
-            const float s = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), j));
-            col[j] = __builtin_fmaf(-s, w, col[j]);
-        }
+    for (int v = 3; v >= 0; --v) {
+        // 1 / sqrt(pivot), the instruction's last bit corrected
+        const float p = pivot[v];
+        float r = __builtin_amdgcn_rsqf(p);
+        const float h = p * r, c = __builtin_fmaf(-__builtin_fmaf(p, r, -h), r, __builtin_fmaf(-h, r, 1.f));
+        r = __builtin_fmaf(0.5f * r, c, r);
+        const bool ok = p > 0.f;
+        t[v] = e[v] * (ok && p < 0x1p126f ? r : 0.f);
+        fail = ok ? fail : 4 * lq + v + 1;
     }
-    if (lane >= 16 && lane < 32) {
+    int first = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) xs[i * CD_XP + c] = col[i];
+    for (int q = 3; q >= 0; --q) {
+        const int f = __builtin_amdgcn_readlane(fail, 16 * q);
+        first = f != 0 ? f : first;
     }
-    return fail;
+    return first;
 }
+
+// (__syncthreads waits for stores to memory too)
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
 {
-    __shared__ floatx4 ws4[16 * CD_WP / 4], xs4[16 * CD_XP / 4], leaf4[16 * CD_XP / 4], diag4[16][64];
+    __shared__ floatx4 ws4[16 * CD_WP / 4], xs4[16 * CD_XP / 4], diag4[16][64];
     __shared__ int bad;
-    float *ws = reinterpret_cast<float *>(ws4), *xs = reinterpret_cast<float *>(xs4), *leaf = reinterpret_cast<float *>(leaf4);
+    float *ws = reinterpret_cast<float *>(ws4), *xs = reinterpret_cast<float *>(xs4);
     const CholProb pr = q.tab[q.c[0].first + blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6), a = w >> 2, b = w & 3;      // tile rows a, a + 2, ..., tile columns b, b + 4, ...
     const int lq = lane >> 4, ln = lane & 15;
     const int p0 = q.step * CB, bs = min(CB, pr.n - p0), nb = (bs + 15) >> 4;
     const bool panel = pr.n > CB;
+    const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * pr.ld + p0, 0, bs * pr.ld * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(pr.F, 0, CB * CB * 4, 0x00020000);
     if (tid == 0) bad = 0;
 
     floatx4 acc[8][4];
@@ -182,37 +223,37 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
         const float *S = first ? pr.M : pr.T + (long)p0 * pr.ld + p0;
         const int pitch = first ? pr.ldm : pr.ld;
         const float damping = first ? (pr.dptr ? *pr.dptr : pr.damping) : 0.f;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(S), 0, ((bs - 1) * pitch + bs) * 4, 0x00020000);
+        auto at = [&](int r, int c) { return (unsigned)(c * pitch + r) * 4u; };
 #pragma unroll
         for (int i = 0; i < 8; ++i)
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int tr = 2 * i + a, tc = 4 * j + b, r = 16 * tr + 4 * lq, c = 16 * tc + ln;
-                typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
-                floatx4 v = {0.f, 0.f, 0.f, 0.f};
-                if (c < bs && r <= c) {
-                    const float *p = S + (long)c * pitch + r;
-                    if (r + 3 <= c) {
-                        v = *reinterpret_cast<const uf4 *>(p);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 3; ++e)
-                            if (r + e <= c) v[e] = p[e];
-                    }
-                }
-                if (tr == tc) {                  // on the diagonal what is taken away is summed by itself
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (r + e == c) v[e] = c < bs ? v[e] + damping : 1.f;          // rows past the edge: the identity
-                    diag4[tr][lane] = v;
-                    v = floatx4{0.f, 0.f, 0.f, 0.f};
-                }
-                acc[i][j] = v;
-                if (j == 3) __builtin_amdgcn_sched_barrier(0);
+                acc[i][j] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, tr < tc && c < bs ? at(r, c) : W_OOB, 0, 0));
             }
+        if (a == (b & 1)) {                      // on the diagonal what is taken away is summed by itself
+            float d[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int r = 16 * (4 * j + b) + 4 * lq + e, c = 16 * (4 * j + b) + ln;
+                    d[j][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, max(r, c) < bs ? at(min(r, c), max(r, c)) : W_OOB, 0, 0));
+                }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int r = 16 * (4 * j + b) + 4 * lq, c = 16 * (4 * j + b) + ln;
+                floatx4 v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = r + e == c ? (c < bs ? d[j][e] + damping : 1.f) : d[j][e];     // past the edge: the identity
+                diag4[4 * j + b][lane] = v;
+            }
+        }
     }
     // Step k forms row k; step -1 only inverts the first diagonal tile.
     for (int k = -1;; ++k) {
-        __syncthreads();
+        lds_barrier();
         if (k >= 0) {
             // the new row: X_kk times the tiles of tile row k
             if (a == (k & 1)) {
@@ -224,68 +265,47 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
 #pragma unroll
                         for (int j = 0; j < 4; ++j) row[j] = acc[i][j];
                     }
+                floatx4 t[4];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int c = 4 * j + b;
-                    floatx4 t = {0.f, 0.f, 0.f, 0.f};
-                    if (c == k) {
+                for (int j = 0; j < 4; ++j) t[j] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int v = 0; v < 4; ++v) t[v] = xs[(4 * lq + v) * CD_XP + ln];
-                    } else {
+                for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[jj], row[j][jj], t, 0, 0, 0);
+                    for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[jj], row[j][jj], t[j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * j + b == k) {        // X_kk itself
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) t[j][v] = xs[(4 * lq + v) * CD_XP + ln];
                     }
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) ws[(4 * lq + v) * CD_WP + 16 * c + ln] = t[v];
-                    if (panel) {
-                        // for the substitution: X in the 32 x 32 blocks on the diagonal, -L below them
-                        const bool same = (c >> 1) == (k >> 1);
-                        if (same && c <= k) {
+                for (int j = 0; j < 4; ++j)
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) pr.F[(16 * k + 4 * lq + v) * CB + 16 * c + ln] = t[v];
-                        } else if (same) {
-                            *reinterpret_cast<floatx4 *>(pr.F + (16 * k + ln) * CB + 16 * c + 4 * lq) = floatx4{0.f, 0.f, 0.f, 0.f};
-                        } else if (c > k) {
-                            *reinterpret_cast<floatx4 *>(pr.F + (16 * c + ln) * CB + 16 * k + 4 * lq) = -t;
-                        }
-                    }
-                }
+                    for (int v = 0; v < 4; ++v) ws[(4 * lq + v) * CD_WP + 16 * (4 * j + b) + ln] = t[j][v];
             }
-            __syncthreads();
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {   // rows w, w + 8 of the new row of X, zeros right of the diagonal
-                const int row = 16 * k + w + 8 * u, c = 4 * lane;
-                if (row < bs && p0 + c < pr.ld) {
-                    const floatx4 v = *reinterpret_cast<const floatx4 *>(ws + (w + 8 * u) * CD_WP + c);
-                    *reinterpret_cast<floatx4 *>(pr.T + (long)(p0 + row) * pr.ld + p0 + c) = c < 16 * (k + 1) ? v : floatx4{0.f, 0.f, 0.f, 0.f};
-                }
-            }
-            if (k + 1 == nb) break;
+            lds_barrier();
         }
+        if (k + 1 < nb) {
         if (a == ((k + 1) & 1) && b == ((k + 1) & 3)) {
-            // the tile that the next step begins with ahead of all others; through LDS, mirrored
+            // the tile that the next step begins with ahead of all others
             floatx4 t;
+            float f[4] = {0.f, 0.f, 0.f, 0.f};
+            if (k >= 0) {
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) f[jj] = ws[(4 * lq + jj) * CD_WP + 16 * (k + 1) + ln];
+            }
 #pragma unroll
             for (int i = 0; i < 8; ++i)
-                if (i == ((k + 1) >> 1)) {
-                    t = acc[i][i >> 1];
-                    if (k >= 0) {
-                        float f[4];
+                if (i == ((k + 1) >> 1)) t = acc[i][i >> 1];
+            floatx4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) f[jj] = ws[(4 * lq + jj) * CD_WP + 16 * (k + 1) + ln];
-#pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) t = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[jj], f[jj], t, 0, 0, 0);
-                    }
-                }
+            for (int jj = 0; jj < 4; ++jj) z = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[jj], f[jj], z, 0, 0, 0);
+            t += z;
             t += diag4[k + 1][lane];
+            const int fail = chol_leaf(t, lane);
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (4 * lq + v <= ln) {
-                    leaf[(4 * lq + v) * CD_XP + ln] = t[v];
-                    leaf[ln * CD_XP + 4 * lq + v] = t[v];
-                }
-            const int f = chol_leaf(leaf, xs, lane);
-            if (lane == 0 && f != 0 && bad == 0) bad = 16 * (k + 1) + f;
+            for (int v = 0; v < 4; ++v) xs[(4 * lq + v) * CD_XP + ln] = t[v];
+            if (lane == 0 && fail != 0 && bad == 0) bad = 16 * (k + 1) + fail;
         }
         if (k < 0) continue;
         __builtin_amdgcn_sched_barrier(0);
@@ -302,16 +322,57 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) ar[jj] = -ws[(4 * lq + jj) * CD_WP + 16 * r + ln];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int c = 4 * j + b;
-                if (c > k && c < r) continue;
-                floatx4 z = {0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < 4; j += 2) {      // two tiles at a time where both are wanted
+                const int c0 = 4 * j + b, c1 = c0 + 4;
+                const bool w0 = c0 <= k || c0 >= r, w1 = c1 <= k || c1 >= r;
+                floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
+                if (w0 && w1) {
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) z = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z, 0, 0, 0);
-                acc[i][j] += z;
+                    for (int jj = 0; jj < 4; ++jj) {
+                        z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z0, 0, 0, 0);
+                        z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j + 1][jj], z1, 0, 0, 0);
+                    }
+                    acc[i][j] += z0;
+                    acc[i][j + 1] += z1;
+                } else if (w0) {
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z0, 0, 0, 0);
+                    acc[i][j] += z0;
+                } else if (w1) {
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j + 1][jj], z1, 0, 0, 0);
+                    acc[i][j + 1] += z1;
+                }
             }
             __builtin_amdgcn_sched_barrier(0);
         }
+        }
+        // to memory, rows and tiles w and w + 8
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int m = w + 8 * u;
+            {   // the new row of X, zeros right of the diagonal
+                const int c = 4 * lane, row = 16 * k + m;
+                const floatx4 v = *reinterpret_cast<const floatx4 *>(ws + m * CD_WP + c);
+                const floatx4 x = c < 16 * (k + 1) ? v : floatx4{0.f, 0.f, 0.f, 0.f};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, x), rt, row < bs && p0 + c < pr.ld ? (unsigned)c * 4u : W_OOB, (unsigned)(row * pr.ld) * 4u, 0);
+            }
+            if (panel) {
+                // for the substitution: X in the 32 x 32 blocks on the diagonal, -L below them
+                if ((m >> 1) == (k >> 1)) {
+                    const int row = lane >> 2, c = 4 * (lane & 3);
+                    const floatx4 v = *reinterpret_cast<const floatx4 *>(ws + row * CD_WP + 16 * m + c);
+                    const floatx4 x = m <= k ? v : floatx4{0.f, 0.f, 0.f, 0.f};
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, x), rf, (unsigned)(row * CB + c) * 4u, (unsigned)(16 * k * CB + 16 * m) * 4u, 0);
+                } else if (m > k) {
+                    floatx4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = -ws[(4 * lq + e) * CD_WP + 16 * m + ln];
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, v), rf, (unsigned)(ln * CB + 4 * lq) * 4u, (unsigned)(16 * m * CB + 16 * k) * 4u, 0);
+                }
+            }
+        }
+        if (k + 1 == nb) break;
     }
     if (tid == 0) {
         if (q.step == 0) *pr.info = bad;
@@ -319,80 +380,128 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
     }
 }
 
-// All diagonal blocks behind block k (lower triangles): what W_k takes away from them.  32 x 32 tiles of the fp32 MFMA, a
-// wavefront each; operands go straight from memory into the registers that the MFMA reads, a chunk of 32 rows ahead, no
-// LDS, no barrier.  Tiles on the diagonal form their sum by itself, the others take it from the block as it was (see the
-// head of this file).
+// All diagonal blocks behind block k (lower triangles): what W_k takes away from them.  64 x 64 tiles; the four wavefronts share
+// the depth of 256 (chunks of 16 in turn), every one computes the whole tile: a lane loads 16 bytes of a row of either
+// operand, which are one column each of four interleaved MFMA tiles, straight into the registers that the MFMA reads, two
+// chunks ahead; no LDS and no barrier until the four sums are added.  A chunk is summed by itself before it is added (see
+// the head of this file).  Bound: fp32 MFMA (48 matrices of order 4096, 15 blocks behind the first: 7200 tiles, 120 us).
 __host__ __device__ __forceinline__ int chol_next_parts(int nt, int k)
 {
     const int left = nt - 2 * (k + 1);                   // column tiles of 128 behind the block
-    return left <= 0 ? 0 : 36 * (left / 2) + (left % 2 ? 10 : 0);
+    return left <= 0 ? 0 : 10 * (left / 2) + (left % 2 ? 3 : 0);
 }
 
-__global__ __launch_bounds__(64, 4) void chol_next_kernel(const CholSeq q)
+__global__ __launch_bounds__(256, 2) void chol_next_kernel(const CholSeq q)
 {
+    __shared__ floatx4 lds[4 * 3 * 4 * 64];
     int prob, part, nt;
     if (!chol_locate(q, prob, part, nt)) return;
     const CholProb pr = q.tab[prob];
-    const int blk = part / 36;
+    const int blk = part / 10;
     int bi, bj;
-    tri_decode(part - 36 * blk, bi, bj);
+    tri_decode(part - 10 * blk, bi, bj);
     const int p0 = q.step * CB, q0 = p0 + CB * (blk + 1), bn = min(CB, pr.n - q0);
-    const int m0 = 32 * bi, n0 = 32 * bj;
+    const int m0 = 64 * bi, n0 = 64 * bj;
     if (m0 >= bn) return;
-    const int lane = threadIdx.x, lr = lane & 31, lg = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lr = lane & 15, lk = lane >> 4;
     const unsigned pitch = (unsigned)pr.ld * 4u;
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * pr.ld + q0, 0, (int)(CB * pitch - 4u * (unsigned)q0), 0x00020000);
-    // columns past the edge repeat the last one: their results are not stored
-    const unsigned ao = (unsigned)min(m0 + lr, bn - 1) * 4u + (unsigned)lg * pitch, bo = (unsigned)min(n0 + lr, bn - 1) * 4u + (unsigned)lg * pitch;
-    float x[2][16], y[2][16];                 // rows 32 g + 2 e + lg
-    auto load = [&](int set, int g) {
+    // a lane whose columns all lie past the edge reads the tile's first ones; a lane past the edge of B, which is on the
+    // diagonal then, reads what is not used
+    const unsigned ao = (unsigned)(m0 + (m0 + 4 * lr < bn ? 4 * lr : 0)) * 4u + (unsigned)(16 * w + lk) * pitch;
+    const unsigned bo = (unsigned)(n0 + (n0 + 4 * lr < bn ? 4 * lr : 0)) * 4u + (unsigned)(16 * w + lk) * pitch;
+    auto load = [&](sint4 (&a)[4], sint4 (&b)[4], int c) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            x[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, ao, (unsigned)(32 * g + 2 * e) * pitch, 0));
-            y[set][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, bo, (unsigned)(32 * g + 2 * e) * pitch, 0));
+        for (int e = 0; e < 4; ++e) {
+            const unsigned ro = (unsigned)(64 * c + 4 * e) * pitch;
+            a[e] = __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rs, ao, ro, 0));
+            b[e] = __builtin_bit_cast(sint4, __builtin_amdgcn_raw_buffer_load_b128(rs, bo, ro, 0));
         }
         __builtin_amdgcn_sched_barrier(0);
     };
-    load(0, 0);
-    // the block as it was: element (m, n) of lane lr = n, m = 8 (v >> 2) + 4 lg + (v & 3)
-    const bool first = q.step == 0, diag = bi == bj;
-    const float *from = first ? pr.M + (long)q0 * pr.ldm + q0 : pr.T + (long)q0 * pr.ld + q0;
-    const int ldf = first ? pr.ldm : pr.ld;
-    const float damping = !first ? 0.f : pr.dptr ? *pr.dptr : pr.damping;
-    const int n = n0 + lr;
-    floatx16 acc, old;
+    floatx4 sum[4][4];
+    auto multiply = [&](const sint4 (&a)[4], const sint4 (&b)[4], bool first) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-        old[v] = m < bn && n <= m ? from[(long)m * ldf + n] : 0.f;
-    }
-    load(1, 1);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = diag ? 0.f : -old[v];
-    floatx16 sum;
+            for (int t = 0; t < 4; ++t) {
+                floatx4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int v = 0; v < 16; ++v) sum[v] = 0.f;
-    auto multiply = [&](int set) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[set][e], y[set][e], acc, 0, 0, 0);
-        sum += acc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_16x16x4f32(__int_as_float(a[e][i]), __int_as_float(b[e][t]), z, 0, 0, 0);
+                sum[i][t] = first ? z : sum[i][t] + z;
+            }
         __builtin_amdgcn_sched_barrier(0);
     };
-#pragma unroll 1
-    for (int g = 0; g < 8; g += 2) {
-        multiply(0);
-        load(0, min(g + 2, 7));               // past the end: the last rows again, not used
-        multiply(1);
-        load(1, min(g + 3, 7));
+    sint4 a0[4], b0[4], a1[4], b1[4];
+    load(a0, b0, 0);
+    load(a1, b1, 1);
+    multiply(a0, b0, true);
+    load(a0, b0, 2);
+    multiply(a1, b1, false);
+    load(a1, b1, 3);
+    multiply(a0, b0, false);
+    multiply(a1, b1, false);
+    // the parts: wavefront t adds MFMA column tile t
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (t != w) {
+            floatx4 *d = lds + ((t * 3 + (w < t ? w : w - 1)) * 4) * 64 + lane;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i * 64] = sum[i][t];
+        }
+    __syncthreads();
+    floatx4 all[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        floatx4 own = sum[i][0];
+#pragma unroll
+        for (int t = 1; t < 4; ++t)
+            if (t == w) own = sum[i][t];
+        all[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ww = 0; ww < 4; ++ww) all[i] += ww == w ? own : lds[((w * 3 + (ww < w ? ww : ww - 1)) * 4 + i) * 64 + lane];
+    }
+    __syncthreads();
+    constexpr int PO = 68;
+    float *o = reinterpret_cast<float *>(lds);          // the tile: row 4 (4 lk + v) + i, column 4 lr + w
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[(4 * (4 * lk + v) + i) * PO + 4 * lr + w] = all[i][v];
+    __syncthreads();
+    // 16 lanes along a row, four columns each; what lies right of the diagonal is not read: whole groups are stored
+    const int mr = tid >> 4, n = n0 + 4 * (tid & 15);
+    const bool first = q.step == 0;
+    const float *from = first ? pr.M + (long)q0 * pr.ldm + q0 : pr.T + (long)q0 * pr.ld + q0;
+    const long ldf = first ? pr.ldm : pr.ld;
+    const float damping = !first ? 0.f : pr.dptr ? *pr.dptr : pr.damping;
+    floatx4 old[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + mr + 16 * r;
+        old[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+        if (m < bn && n <= m) {
+            const float *src = from + (long)m * ldf + n;
+            typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
+            if (n + 3 <= m) old[r] = *reinterpret_cast<const uf4 *>(src);
+            else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (n + e <= m) old[r][e] = src[e];
+            }
+        }
     }
     float *C = pr.T + (long)q0 * pr.ld + q0;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int m = m0 + 8 * (v >> 2) + 4 * lg + (v & 3);
-        if (m < bn && n <= m) C[(long)m * pr.ld + n] = diag ? (old[v] + (m == n ? damping : 0.f)) - sum[v] : -sum[v];
+    for (int r = 0; r < 4; ++r) {
+        const int m = m0 + mr + 16 * r;
+        if (m >= bn || n > m) continue;
+        floatx4 val = *reinterpret_cast<const floatx4 *>(o + (mr + 16 * r) * PO + n - n0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) val[e] = (old[r][e] + (n + e == m ? damping : 0.f)) - val[e];
+        *reinterpret_cast<floatx4 *>(C + (long)m * pr.ld + n) = val;
     }
 }
 
