@@ -391,7 +391,7 @@ int chol_ld(int n)
 }
 size_t chol_ws_floats(int n)
 {
-    return (size_t)n * chol_ld(n) + (n > CB ? (size_t)CB * CB : 0) + align_up(n, 64);
+    return (size_t)n * chol_ld(n) + (n > CB ? (size_t)CB * CB : 0) + 3 * align_up(n, 64);
 }
 size_t fused_ws_floats(int n) { return 4 * (size_t)NB * NB + 2 * (size_t)NB * ((n + 3) / 4 * 4) + 16; }
 // large matrices: two sets of V, W panels, of the pivot block and of its inverse, W and the residual of the next pivot
@@ -474,6 +474,8 @@ hipError_t CholRun::upload(const std::vector<size_t> &offs, void *work)
             p.T = ws;
             p.F = ws + (size_t)j.n * p.ld;
             p.z = p.F + (j.n > CB ? (size_t)CB * CB : 0);
+            p.xd = p.z + align_up(j.n, 64);
+            p.fix = p.xd + align_up(j.n, 64);
         }
         KFAC_LAUNCH(KFAC_K_INV_INIT, s, chol_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
         hipError_t e = hipGetLastError();
@@ -520,6 +522,9 @@ hipError_t CholRun::run()
             e = each(0, [&](int nt) { return 2 * nt; },
                      [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_row_kernel, dim3(blocks), dim3(1024), 0, q); });
     }
+    if (e == hipSuccess)
+        e = each(0, [&](int nt) { return (nt + 1) / 2; },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_diagonal_kernel, dim3(blocks), dim3(256), 0, q); });
     if (e == hipSuccess)
         e = each(0, [&](int nt) { return chol_out_parts(nt); },
                  [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); });

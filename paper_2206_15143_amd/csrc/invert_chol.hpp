@@ -43,6 +43,8 @@ struct CholProb {
     float *out;          // both triangles
     float *F;            // [256, 256] factor of the diagonal block: -L, the inverse of its 32 x 32 blocks on the diagonal
     float *z;            // [n] workspace of the last row (thin)
+    float *xd;           // [n] diagonal of X, ahead of X^T X
+    float *fix;          // [n] 1 / pivot less the square of that
     int *info;
     const float *dptr;   // device-side damping (overrides `damping` when not null)
     float damping;
@@ -70,6 +72,7 @@ struct CholSeq {
     const CholProb *tab;
     int nclass;
     int step;
+    int from;            // blocks whose part of the sums a row block's place in T holds already (chol_ahead_kernel)
     CholClass c[kMaxCholClasses];
 };
 
@@ -167,8 +170,8 @@ __device__ __forceinline__ void chol_pivots(floatx4 &t, floatx4 &e, floatx4 &piv
 
 // X of the 16 x 16 block t (MFMA result layout, from the diagonal up), one wavefront; rows are scaled at the end, so that a
 // pivot waits for one reciprocal and a few multiply-adds of the one before it.  A pivot that is not positive leaves a
-// zero row and is reported: 1-based place in the block, or 0.
-__device__ __forceinline__ int chol_leaf(floatx4 &t, int lane)
+// zero row and is reported: 1-based place in the block, or 0.  fix: 1 / pivot less the square of its rounded root.
+__device__ __forceinline__ int chol_leaf(floatx4 &t, floatx4 &fix, int lane)
 {
     const int lq = lane >> 4, ln = lane & 15;
     floatx4 e, pivot = {0.f, 0.f, 0.f, 0.f};
@@ -186,8 +189,10 @@ __device__ __forceinline__ int chol_leaf(floatx4 &t, int lane)
         float r = __builtin_amdgcn_rsqf(p);
         const float h = p * r, c = __builtin_fmaf(-__builtin_fmaf(p, r, -h), r, __builtin_fmaf(-h, r, 1.f));
         r = __builtin_fmaf(0.5f * r, c, r);
-        const bool ok = p > 0.f;
-        t[v] = e[v] * (ok && p < 0x1p126f ? r : 0.f);
+        const bool ok = p > 0.f, kept = ok && p < 0x1p126f;
+        t[v] = e[v] * (kept ? r : 0.f);
+        const float g = p * r, l = __builtin_fmaf(-__builtin_fmaf(p, r, -g), r, __builtin_fmaf(-g, r, 1.f));
+        fix[v] = kept ? l * r * r : 0.f;
         fail = ok ? fail : 4 * lq + v + 1;
     }
     int first = 0;
@@ -302,7 +307,9 @@ __global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
             for (int jj = 0; jj < 4; ++jj) z = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[jj], f[jj], z, 0, 0, 0);
             t += z;
             t += diag4[k + 1][lane];
-            const int fail = chol_leaf(t, lane);
+            floatx4 fix;
+            const int fail = chol_leaf(t, fix, lane);
+            if (ln == 0) *reinterpret_cast<floatx4 *>(pr.fix + p0 + 16 * (k + 1) + 4 * lq) = fix;
 #pragma unroll
             for (int v = 0; v < 4; ++v) xs[(4 * lq + v) * CD_XP + ln] = t[v];
             if (lane == 0 && fail != 0 && bad == 0) bad = 16 * (k + 1) + fail;
@@ -770,11 +777,26 @@ __global__ __launch_bounds__(1024) void chol_thin_row_kernel(const CholSeq q)
     if (part == 0 && lane == 0) {
         if (!ok && *pr.info == 0) *pr.info = n + 1;
         pr.T[(long)n * pr.ld + n] = x;
-        pr.out[(long)n * pr.ldo + n] = x * x;
+        pr.out[(long)n * pr.ldo + n] = ok ? 1.f / d : 0.f;
     }
 }
 
 // ---- the inverse -----------------------------------------------------------------------------------------------------
+// The products of X^T X with an entry of X's diagonal, the largest of all where M is not far from a diagonal matrix, are
+// left to the epilogue: as terms of the MFMA's sum every one of its six parts is cut to the last place of the
+// result (error of the inverse of a factor near the identity 1.1e-7, 4e-8 with them in fp32 at the end).
+__global__ __launch_bounds__(256) void chol_diagonal_kernel(const CholSeq q)
+{
+    int prob, part, nt;
+    if (!chol_locate(q, prob, part, nt)) return;
+    const CholProb pr = q.tab[prob];
+    const int i = 256 * part + threadIdx.x;
+    if (i >= pr.n) return;
+    float *x = pr.T + (long)i * (pr.ld + 1);
+    pr.xd[i] = *x;
+    *x = 0.f;
+}
+
 // 256 x 128 tiles of X^T X that reach the lower triangle, tile row by tile row: those of the first rows are the deepest
 __host__ __device__ __forceinline__ int chol_out_parts(int nt)
 {
@@ -812,17 +834,44 @@ __global__ __launch_bounds__(256, 2) void chol_out_kernel(const CholSeq q)
     if (rows == 0) return;
     const int ldo = pr.ldo, mw = m0 + wm * (S_BM / 2), nw = n0 + wn * 64;
     const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.out, 0, (int)((long)full * ldo * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(pr.T, 0, (int)((long)n * pr.ld * 4), 0x00020000);
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(pr.xd, 0, n * 4, 0x00020000);
+    float x[2][16];              // X at the places of an MFMA tile, two tiles in turn
+    auto load_x = [&](int u) {
+        const int c = nw + (u & 1) * 32 + lr, m = mw + (u >> 1) * 32 + 4 * lg;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = 8 * (v >> 2) + (v & 3);
+            x[u & 1][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rt, m + r < n && c < n ? (unsigned)((m + r) * pr.ld + c) * 4u : W_OOB, 0, 0));
+        }
+    };
+    load_x(0);
     // the mirror image, straight from the accumulators: a lane's four rows are neighbours there
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ti = 0; ti < 4; ++ti) {
+        float d[16];
 #pragma unroll
-        for (int tj = 0; tj < 2; ++tj)
+        for (int v = 0; v < 16; ++v)
+            d[v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, (unsigned)(mw + ti * 32 + 8 * (v >> 2) + 4 * lg + (v & 3)) * 4u, 0, 0));
+#pragma unroll
+        for (int tj = 0; tj < 2; ++tj) {
+            floatx16 &a = acc[ti * 2 + tj];
+            if (ti * 2 + tj < 7) load_x(ti * 2 + tj + 1);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) a[v] = __builtin_fmaf(d[v], x[tj][v], a[v] * unscale);
+            if (mw + ti * 32 == nw + tj * 32) {
+                const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(pr.fix, 0, n * 4, 0x00020000);
+                const float f = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rf, (unsigned)(nw + tj * 32 + lr) * 4u, 0, 0));
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (8 * (v >> 2) + 4 * lg + (v & 3) == lr) a[v] = __builtin_fmaf(d[v], d[v], a[v] + f);
+            }
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int m = mw + ti * 32 + 8 * g + 4 * lg, c = nw + tj * 32 + lr;
                 floatx4 v;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[ti * 2 + tj][4 * g + e] *= unscale;
+                for (int e = 0; e < 4; ++e) v[e] = a[4 * g + e];
                 const unsigned o = (unsigned)(c * ldo + m) * 4u;
                 const bool all = c < m && m + 3 < n;
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, v), rc, all ? o : W_OOB, 0, 0);
@@ -832,6 +881,9 @@ __global__ __launch_bounds__(256, 2) void chol_out_kernel(const CholSeq q)
                         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[e]), rc, !all && c < m + e && m + e < n ? o + 4u * (unsigned)e : W_OOB, 0, 0);
                 }
             }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
     constexpr int EP = 68;
     float *wl = reinterpret_cast<float *>(L.ring) + w * 32 * EP;
     const int rr = lane >> 4, c4 = (lane & 15) * 4;
