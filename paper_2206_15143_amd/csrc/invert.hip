@@ -410,127 +410,6 @@ int *fused_gate_ptr(float *ws, int n)
 }
 size_t table_bytes(int n) { return align_up((size_t)2 * n * sizeof(InvProbF), 256) + align_up((size_t)n * sizeof(CholProb), 256); }
 
-// The matrices listed in `idx` (sorted by order, largest first) by their triangular factors.
-struct CholRun {
-    const InvertJob *jobs;
-    const std::vector<int> &idx;
-    CholProb *tab;
-    hipStream_t s;
-    std::vector<CholClass> classes;      // equal numbers of column tiles, largest first
-
-    int leading(int k) const { const int n = jobs[idx[k]].n; return n - chol_thin(n); }
-    hipError_t upload(const std::vector<size_t> &offs, void *work);
-    // launches of `parts(nt)` workgroups per matrix, classes with none left out
-    template <class Parts, class Launch>
-    hipError_t each(int step, Parts parts, Launch launch)
-    {
-        CholSeq q;
-        q.tab = tab;
-        q.step = step;
-        q.nclass = 0;
-        long blocks = 0;
-        auto flush = [&]() -> hipError_t {
-            if (q.nclass == 0) return hipSuccess;
-            if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
-            launch(q, (unsigned)blocks);
-            q.nclass = 0;
-            blocks = 0;
-            return hipGetLastError();
-        };
-        for (const CholClass &c : classes) {
-            const int per = parts(c.nt);
-            if (per <= 0) continue;
-            CholClass &d = q.c[q.nclass++];
-            d = c;
-            d.per = per;
-            d.blk_start = (int)blocks;
-            blocks += chol_class_blocks(c.count, per);
-            if (q.nclass == kMaxCholClasses) {
-                hipError_t e = flush();
-                if (e != hipSuccess) return e;
-            }
-        }
-        return flush();
-    }
-    hipError_t run();
-};
-
-hipError_t CholRun::upload(const std::vector<size_t> &offs, void *work)
-{
-    const int total = (int)idx.size();
-    for (int g0 = 0; g0 < total; g0 += kCholUploadMax) {
-        CholUpload u;
-        u.dst = tab + g0;
-        u.count = std::min(kCholUploadMax, total - g0);
-        for (int k = 0; k < u.count; ++k) {
-            const InvertJob &j = jobs[idx[g0 + k]];
-            CholProb &p = u.p[k];
-            float *ws = reinterpret_cast<float *>(static_cast<char *>(work) + offs[idx[g0 + k]]);
-            p.M = j.M; p.out = j.Minv; p.info = j.info; p.damping = j.damping; p.dptr = j.damping_dev;
-            p.thin = chol_thin(j.n); p.n = j.n - p.thin;
-            p.ld = chol_ld(j.n);
-            p.ldm = j.ldm > 0 ? j.ldm : j.n;
-            p.ldo = j.ldo > 0 ? j.ldo : j.n;
-            p.T = ws;
-            p.F = ws + (size_t)j.n * p.ld;
-            p.z = p.F + (j.n > CB ? (size_t)CB * CB : 0);
-            p.xd = p.z + align_up(j.n, 64);
-            p.fix = p.xd + align_up(j.n, 64);
-        }
-        KFAC_LAUNCH(KFAC_K_INV_INIT, s, chol_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    for (int k = 0; k < total; ++k) {
-        const int nt = (leading(k) + S_BN - 1) / S_BN;
-        if (classes.empty() || classes.back().nt != nt) classes.push_back(CholClass{k, 0, nt, 0, 0});
-        ++classes.back().count;
-    }
-    return hipSuccess;
-}
-
-hipError_t CholRun::run()
-{
-    const int total = (int)idx.size();
-    const int steps = (leading(0) + CB - 1) / CB;
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < steps && e == hipSuccess; ++k) {
-        {
-            CholSeq q;
-            q.tab = tab;
-            q.nclass = 1;
-            q.step = k;
-            int active = 0;
-            while (active < total && leading(active) > k * CB) ++active;
-            q.c[0] = CholClass{0, active, 0, 1, 0};
-            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, chol_diag_kernel, dim3(active), dim3(512), 0, q);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        e = each(k, [&](int nt) { return nt > 2 * k ? chol_panel_parts(nt, k) : 0; },
-                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
-        if (e == hipSuccess)
-            e = each(k, [&](int nt) { return chol_next_parts(nt, k); },
-                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(256), 0, q); });
-    }
-    bool thin = false;
-    for (int k = 0; k < total; ++k) thin = thin || chol_thin(jobs[idx[k]].n);
-    if (e == hipSuccess && thin) {
-        e = each(0, [&](int nt) { return 8 * nt; },
-                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_z_kernel, dim3(blocks), dim3(256), 0, q); });
-        if (e == hipSuccess)
-            e = each(0, [&](int nt) { return 2 * nt; },
-                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_row_kernel, dim3(blocks), dim3(1024), 0, q); });
-    }
-    if (e == hipSuccess)
-        e = each(0, [&](int nt) { return (nt + 1) / 2; },
-                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_diagonal_kernel, dim3(blocks), dim3(256), 0, q); });
-    if (e == hipSuccess)
-        e = each(0, [&](int nt) { return chol_out_parts(nt); },
-                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); });
-    return e;
-}
-
 // One-launch-per-step sweep for the matrices listed in `idx` (sorted by order, largest first).
 hipError_t fused_launch(const InvertJob *jobs, const std::vector<int> &idx, const std::vector<size_t> &offs,
                         void *work, InvProbF *dtab, hipStream_t s)
@@ -992,6 +871,164 @@ AuxStreams *aux_streams()
     return &a;
 }
 
+// The matrices listed in `idx` (sorted by order, largest first) by their triangular factors.
+struct CholRun {
+    const InvertJob *jobs;
+    const std::vector<int> &idx;
+    CholProb *tab;
+    hipStream_t s;
+    std::vector<CholClass> classes;      // equal numbers of column tiles, largest first
+
+    int leading(int k) const { const int n = jobs[idx[k]].n; return n - chol_thin(n); }
+    hipError_t upload(const std::vector<size_t> &offs, void *work);
+    // launches of `parts(nt)` workgroups per matrix, classes with none left out
+    template <class Parts, class Launch>
+    hipError_t each(int step, int from, Parts parts, Launch launch)
+    {
+        CholSeq q;
+        q.tab = tab;
+        q.step = step;
+        q.from = from;
+        q.nclass = 0;
+        long blocks = 0;
+        auto flush = [&]() -> hipError_t {
+            if (q.nclass == 0) return hipSuccess;
+            if (blocks > 0x7fffffffl) return hipErrorInvalidValue;
+            launch(q, (unsigned)blocks);
+            q.nclass = 0;
+            blocks = 0;
+            return hipGetLastError();
+        };
+        for (const CholClass &c : classes) {
+            const int per = parts(c.nt);
+            if (per <= 0) continue;
+            CholClass &d = q.c[q.nclass++];
+            d = c;
+            d.per = per;
+            d.blk_start = (int)blocks;
+            blocks += chol_class_blocks(c.count, per);
+            if (q.nclass == kMaxCholClasses) {
+                hipError_t e = flush();
+                if (e != hipSuccess) return e;
+            }
+        }
+        return flush();
+    }
+    bool looks_ahead(int k, const AuxStreams *aux) const;
+    hipError_t run(AuxStreams *aux);
+};
+
+hipError_t CholRun::upload(const std::vector<size_t> &offs, void *work)
+{
+    const int total = (int)idx.size();
+    for (int g0 = 0; g0 < total; g0 += kCholUploadMax) {
+        CholUpload u;
+        u.dst = tab + g0;
+        u.count = std::min(kCholUploadMax, total - g0);
+        for (int k = 0; k < u.count; ++k) {
+            const InvertJob &j = jobs[idx[g0 + k]];
+            CholProb &p = u.p[k];
+            float *ws = reinterpret_cast<float *>(static_cast<char *>(work) + offs[idx[g0 + k]]);
+            p.M = j.M; p.out = j.Minv; p.info = j.info; p.damping = j.damping; p.dptr = j.damping_dev;
+            p.thin = chol_thin(j.n); p.n = j.n - p.thin;
+            p.ld = chol_ld(j.n);
+            p.ldm = j.ldm > 0 ? j.ldm : j.n;
+            p.ldo = j.ldo > 0 ? j.ldo : j.n;
+            p.T = ws;
+            p.F = ws + (size_t)j.n * p.ld;
+            p.z = p.F + (j.n > CB ? (size_t)CB * CB : 0);
+            p.xd = p.z + align_up(j.n, 64);
+            p.fix = p.xd + align_up(j.n, 64);
+        }
+        KFAC_LAUNCH(KFAC_K_INV_INIT, s, chol_upload_kernel, dim3((u.count + 15) / 16), dim3(64), 0, u);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    for (int k = 0; k < total; ++k) {
+        const int nt = (leading(k) + S_BN - 1) / S_BN;
+        if (classes.empty() || classes.back().nt != nt) classes.push_back(CholClass{k, 0, nt, 0, 0});
+        ++classes.back().count;
+    }
+    return hipSuccess;
+}
+
+// Whether the sums of row blocks k + 2 and k + 3 run beside steps k and k + 1: where the launches of a panel leave CUs idle.
+// (ms of a whole update with a limit of 0, 400, 512, 800, 2000, none: 54 layers of a ResNet-50, 3 matrices of order 4609 among them,
+// 12.95, 11.39, 11.33, 11.06, 11.08, 11.7; 24 of 3073 and 120 of 768 / 769 11.0, 11.0, 11.05, 10.66, 10.62, 10.8;
+// 48 of 4097 and 192 of 1025 the same with all.)
+bool CholRun::looks_ahead(int k, const AuxStreams *aux) const
+{
+    if (!aux || k < 2) return false;
+    long blocks = 0;
+    for (const CholClass &c : classes)
+        if (c.nt > 2 * k) blocks += (long)c.count * chol_panel_parts(c.nt, k);
+    return blocks <= tuning().invert_ahead_max;
+}
+
+hipError_t CholRun::run(AuxStreams *aux)
+{
+    const int total = (int)idx.size();
+    const int steps = (leading(0) + CB - 1) / CB;
+    hipError_t e = hipSuccess;
+    int from = 0;                        // panels whose part the present pair of row blocks has from the side stream
+    int due = -1, later = -1;            // first row blocks of the pairs whose sums run there
+    for (int k = 0; k < steps && e == hipSuccess; ++k) {
+        {
+            CholSeq q;
+            q.tab = tab;
+            q.nclass = 1;
+            q.step = k;
+            q.from = 0;
+            int active = 0;
+            while (active < total && leading(active) > k * CB) ++active;
+            q.c[0] = CholClass{0, active, 0, 1, 0};
+            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, chol_diag_kernel, dim3(active), dim3(512), 0, q);
+            e = hipGetLastError();
+            if (e != hipSuccess) break;
+        }
+        if (k % 2 == 0) {
+            from = due == k ? k - 2 : 0;
+            if (due == k && hipStreamWaitEvent(s, aux->ev_ready[k], 0) != hipSuccess) e = hipErrorUnknown;
+            if (due == k) { due = later; later = -1; }
+        }
+        if (e == hipSuccess)
+            e = each(k, from, [&](int nt) { return nt > 2 * k ? chol_panel_parts(nt, k) : 0; },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
+        // Sums of row blocks k + 3 and k + 4 over the panels so far, beside steps k + 1 and k + 2.
+        if (e == hipSuccess && k % 2 == 1 && k + 3 < steps && looks_ahead(k + 1, aux)) {
+            hipStream_t side = aux->chain;
+            if (hipEventRecord(aux->ev_panel[k], s) != hipSuccess || hipStreamWaitEvent(side, aux->ev_panel[k], 0) != hipSuccess) e = hipErrorUnknown;
+            if (e == hipSuccess)
+                e = each(k + 3, k + 1, [&](int nt) { return chol_ahead_parts(nt, k + 3, k + 1); },
+                         [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, side, chol_ahead_kernel, dim3(blocks), dim3(256), 0, q); });
+            if (hipEventRecord(aux->ev_ready[k + 3], side) != hipSuccess) e = hipErrorUnknown;
+            (due < 0 ? due : later) = k + 3;
+        }
+        if (e == hipSuccess)
+            e = each(k, 0, [&](int nt) { return chol_next_parts(nt, k); },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_PANEL, s, chol_next_kernel, dim3(blocks), dim3(256), 0, q); });
+    }
+    if (due >= 0 && e != hipSuccess) {       // always join
+        if (hipEventRecord(aux->ev_panel[0], aux->chain) == hipSuccess) (void)hipStreamWaitEvent(s, aux->ev_panel[0], 0);
+    }
+    bool thin = false;
+    for (int k = 0; k < total; ++k) thin = thin || chol_thin(jobs[idx[k]].n);
+    if (e == hipSuccess && thin) {
+        e = each(0, 0, [&](int nt) { return 8 * nt; },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_z_kernel, dim3(blocks), dim3(256), 0, q); });
+        if (e == hipSuccess)
+            e = each(0, 0, [&](int nt) { return 2 * nt; },
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_thin_row_kernel, dim3(blocks), dim3(1024), 0, q); });
+    }
+    if (e == hipSuccess)
+        e = each(0, 0, [&](int nt) { return (nt + 1) / 2; },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_diagonal_kernel, dim3(blocks), dim3(256), 0, q); });
+    if (e == hipSuccess)
+        e = each(0, 0, [&](int nt) { return chol_out_parts(nt); },
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); });
+    return e;
+}
+
 // One stream: every step in a row.
 hipError_t blocked_serial(BlockedRun &run, hipStream_t s)
 {
@@ -1412,7 +1449,8 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     AuxStreams *aux = nullptr;
     // (with the per-launch event timing on, everything stays on the caller's stream: an event pair around a kernel
     // that waits for another stream's kernel to leave the chip would time the wait as well)
-    if (!large.empty() && tuning().invert_two_streams && !timing_active()) {
+    const bool wide = !chol.empty() && (jobs_in[chol[0]].n + CB - 1) / CB > 5;
+    if ((!large.empty() || wide) && tuning().invert_two_streams && !timing_active()) {
         lock.lock();       // the events are shared by all calls on a device: one call enqueues at a time
         aux = aux_streams();
         if (!aux) lock.unlock();
@@ -1443,7 +1481,7 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     if (e == hipSuccess && !chol.empty()) {
         CholRun run{jobs_in, chol, reinterpret_cast<CholProb *>(static_cast<char *>(work) + align_up((size_t)2 * n_all * sizeof(InvProbF), 256)), s, {}};
         e = run.upload(offs, work);
-        if (e == hipSuccess) e = run.run();
+        if (e == hipSuccess) e = run.run((jobs_in[chol[0]].n + CB - 1) / CB <= AuxStreams::kEvents ? aux : nullptr);
     }
     // always join the side stream, also after an error
     if (side_open && hipStreamWaitEvent(s, aux->side_done, 0) != hipSuccess) return hipErrorUnknown;

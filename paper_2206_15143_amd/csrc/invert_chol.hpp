@@ -562,6 +562,68 @@ struct CholFromM {
     }
 };
 
+// Places (m, c) of a tile of 256 x 128 in memory, MFMA tile by MFMA tile (u = 2 ti + tj): byte offset of element v, or W_OOB.
+struct CholPlaces {
+    int m, c, rows, cols, pitch;       // of the lane's element 0 of MFMA tile 0; the tile's extent; floats
+    __device__ __forceinline__ unsigned operator()(int u, int v) const
+    {
+        const int r = m + (u >> 1) * 32 + 8 * (v >> 2) + (v & 3), k = c + (u & 1) * 32;
+        return r < rows && k < cols ? (unsigned)(r * pitch + k) * 4u : W_OOB;
+    }
+};
+
+// The sums of row blocks `step` and `step` + 1 over the first `from` panels, to the place of these row blocks in T, where
+// chol_panel_kernel finds them: with few matrices a panel of its own has a workgroup on a fraction of the CUs only, and the
+// whole depth in the chain of diagonal blocks, panels and diagonal blocks.  This launch runs beside two steps of that chain.
+__host__ __device__ __forceinline__ int chol_ahead_parts(int nt, int k, int from)
+{
+    if (nt <= 2 * k) return 0;
+    const int r0 = nt - 2 * (k + 1), r1 = nt - 2 * (k + 2);
+    return (r0 > 0 ? r0 + 2 * from : 0) + (r1 > 0 ? r1 : 0) + 2 * from;
+}
+
+__global__ __launch_bounds__(256, 2) void chol_ahead_kernel(const CholSeq q)
+{
+    __shared__ SplitLds L;
+    int prob, part, nt;
+    if (!chol_locate(q, prob, part, nt)) return;
+    const CholProb pr = q.tab[prob];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w >> 1, wn = w & 1;
+    const int lr = lane & 31, lg = lane >> 5;
+    const int n = pr.n, ld = pr.ld, left = 2 * q.from;
+    const int r0 = max(0, nt - 2 * (q.step + 1)), r1 = max(0, nt - 2 * (q.step + 2));
+    const bool is_right = part < r0 + r1;
+    int k = q.step;
+    if (is_right) {
+        if (part >= r0) { ++k; part -= r0; }
+    } else {
+        part -= r0 + r1;
+        if (part >= left) { ++k; part -= left; }
+    }
+    const int p0 = k * CB, bs = min(CB, n - p0);
+    const int c0 = S_BN * part + (is_right ? p0 + bs : 0), ncols = min(S_BN, n - c0);
+    const int kbeg = is_right ? 0 : c0 & ~(CB - 1);
+    const int mleft = bs - wm * (S_BM / 2);
+    const int rows = mleft <= 0 || wn * 64 >= ncols ? 0 : (mleft + 31) / 32;
+    const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.M + (long)c0 * pr.ldm + p0), 0, (int)((long)(ncols - 1) * pr.ldm * 4 + 4 * CB), 0x00020000);
+    const CholFromM inject{rm, pr.ldm, ncols, wm, wn, lr, lg, is_right};
+    SplitSrc<kRows> src;
+    chol_source(src, pr.T + (long)kbeg * ld, ld, p0, bs, pr.T + (long)kbeg * ld, ld, c0, ncols, q.from * CB - kbeg, tid);
+    src.ahead = is_right ? CholFromM::tail : CB / S_KT;
+    src.back = max(0, src.nstages - src.ahead);
+    floatx16 acc[8];
+    float none[4];
+    const float unscale = -split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid, inject);
+    if (rows == 0) return;
+    const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * ld + c0, 0, (bs * ld - c0) * 4, 0x00020000);
+    const CholPlaces at{wm * (S_BM / 2) + 4 * lg, wn * 64 + lr, bs, ncols, ld};
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(unscale * acc[u][v]), rc, at(u, v), 0, 0);
+}
+
 // Row block k: a tile of 256 rows and 128 columns per workgroup, its sum over the panels before it, then the forward
 // substitution with the diagonal block's factor.  Parts of a matrix, longest first: the tiles right of the diagonal
 // block, those left of it (their depth begins at their columns' block).
@@ -583,21 +645,40 @@ __global__ __launch_bounds__(256, 2) void chol_panel_kernel(const CholSeq q)
     const bool is_right = part < right;
     const int c0 = is_right ? p1 + S_BN * part : S_BN * (part - right);
     const int ncols = min(S_BN, (is_right ? n : p0) - c0);
+    const bool begun = c0 < q.from * CB || (is_right && q.from > 0);       // chol_ahead_kernel has begun this tile's sums
     floatx16 acc[8];
     float unscale;
     {
-        const int kbeg = is_right ? 0 : c0 & ~(CB - 1);
+        const int kbeg = begun ? q.from * CB : is_right ? 0 : c0 & ~(CB - 1);
         const int mleft = bs - wm * (S_BM / 2);
         const int rows = mleft <= 0 || wn * 64 >= ncols ? 0 : (mleft + 31) / 32;
         // element (m, n) of the part of M above the diagonal, from below it: m and the three rows after it are neighbours there
         const __amdgpu_buffer_rsrc_t rm = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(pr.M + (long)c0 * pr.ldm + p0), 0, (int)((long)(ncols - 1) * pr.ldm * 4 + 4 * CB), 0x00020000);
-        const CholFromM inject{rm, pr.ldm, ncols, wm, wn, lr, lg, is_right};
+        const CholFromM inject{rm, pr.ldm, ncols, wm, wn, lr, lg, is_right && !begun};
         SplitSrc<kRows> src;
         chol_source(src, pr.T + (long)kbeg * ld, ld, p0, bs, pr.T + (long)kbeg * ld, ld, c0, ncols, p0 - kbeg, tid);
-        src.ahead = is_right ? CholFromM::tail : CB / S_KT;  // the rows with the large terms last
+        src.ahead = begun ? 0 : is_right ? CholFromM::tail : CB / S_KT;  // the rows with the large terms last
         src.back = max(0, src.nstages - src.ahead);
         float none[4];
         unscale = -split_tile<kRows, false, false>(src, L, acc, none, 0, rows, wm, wn, tid, inject);
+    }
+    if (begun) {
+        const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * ld + c0, 0, (bs * ld - c0) * 4, 0x00020000);
+        const CholPlaces at{wm * (S_BM / 2) + 4 * lg, wn * 64 + lr, bs, ncols, ld};
+        float x[2][16];
+        auto load = [&](int u) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) x[u & 1][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rp, at(u, e), 0, 0));
+        };
+        load(0);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            if (u < 7) load(u + 1);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[u][e] = __builtin_fmaf(unscale, acc[u][e], x[u & 1][e]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        unscale = 1.f;
     }
     // V, tile by tile of 32 rows: the wavefront's columns 64 wn + 32 wm ..; the other half of what it summed goes to the
     // wavefront with the other rows
