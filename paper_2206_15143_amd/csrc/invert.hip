@@ -982,7 +982,7 @@ hipError_t CholRun::run(AuxStreams *aux)
             int active = 0;
             while (active < total && leading(active) > k * CB) ++active;
             q.c[0] = CholClass{0, active, 0, 1, 0};
-            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, chol_diag_kernel, dim3(active), dim3(512), 0, q);
+            KFAC_LAUNCH(KFAC_K_INV_PIVOT, s, chol_diag_kernel, dim3(active), dim3(768), 0, q);
             e = hipGetLastError();
             if (e != hipSuccess) break;
         }

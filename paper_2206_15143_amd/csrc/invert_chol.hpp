@@ -112,14 +112,17 @@ __global__ __launch_bounds__(64) void chol_upload_kernel(const CholUpload u)
 }
 
 // ---- diagonal blocks -------------------------------------------------------------------------------------------------
-// X of a diagonal block of up to 256 rows, a workgroup of 8 wavefronts.  The block lives in registers as 16 x 16 tiles of
-// the MFMA result layout, tile (r, c) with wavefront (r mod 2, c mod 4), so that every step keeps all of them busy.  Step k:
-// the rows of tile row k times X_kk, then the rank-16 update of the rows below (of X left of tile column k, of the symmetric
-// rest right of the diagonal).  The operands of the first product are the tiles as they lie (the k of a 16 x 16 x 4 MFMA may
-// come in any order); the new row goes through LDS, from where it is also stored.  The 16 pivots of the next X_kk run in one
-// wavefront beside the update of the others.
-// Bound: the fp32 MFMA of one CU (5440 of 16 x 16 x 4, 18 us at full rate) and the two barriers of a step.
-constexpr int CD_WP = 260;                  // LDS pitch of a row of 256 (4 rows are 16 banks apart)
+// X of a diagonal block of up to 256 rows, a workgroup of 12 wavefronts.  The block lives in registers as 16 x 16 tiles of
+// the MFMA result layout.  Step k: the tiles of row k times X_kk (left of the diagonal they are X's, right of it L^T's), then the
+// rank-16 update of what lies below.  Tile (i, j) above the diagonal is not wanted any more once row i is formed, when tile
+// (j, i) of X below it begins, which is kept transposed: one place for both, 136 in all, those of rows w and w + 8 with wavefront
+// w.  Then every update is place (i, j) less the product of the new row's tiles i (transposed) and j, the first of them in the
+// wavefront's registers.  A row's tiles are operands as they lie (the k of a 16 x 16 x 4 MFMA may come in any order): 16 bytes a
+// lane through LDS, and so do the tiles of the next row, each from the wavefront that has it to the one that forms it.
+// Wavefront 8 runs the 16 pivots of the next X_kk beside the update, the last three store the row.
+// Bound: the chain of the pivots (3300 cycles for 16) against the fp32 MFMA of one CU (5440 of 16 x 16 x 4, 18 us at full
+// rate), and the two barriers of a step.  55 us alone (three
+// matrices at a time; places of 16 x 32 pairs with eight wavefronts that run the pivots and the stores too 72).
 constexpr int CD_XP = 20;
 
 // Lane (q, n) of the result: lane (G, n) of x[q].
@@ -207,183 +210,196 @@ __device__ __forceinline__ int chol_leaf(floatx4 &t, floatx4 &fix, int lane)
 // (__syncthreads waits for stores to memory too)
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-__global__ __launch_bounds__(512, 2) void chol_diag_kernel(const CholSeq q)
+__global__ __launch_bounds__(768) void chol_diag_kernel(const CholSeq q)
 {
-    __shared__ floatx4 ws4[16 * CD_WP / 4], xs4[16 * CD_XP / 4], diag4[16][64];
-    __shared__ int bad;
-    float *ws = reinterpret_cast<float *>(ws4), *xs = reinterpret_cast<float *>(xs4);
+    // tiles of a row, of the next row before the product, on the diagonal, sums of the next two on the diagonal
+    __shared__ floatx4 frag[16][64], raw[16][64], diag[16][64], below[2][64], xf[64], xs4[16 * CD_XP / 4];
+    float *xs = reinterpret_cast<float *>(xs4);
     const CholProb pr = q.tab[q.c[0].first + blockIdx.x];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6), a = w >> 2, b = w & 3;      // tile rows a, a + 2, ..., tile columns b, b + 4, ...
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = wave < 4 ? wave : 11 - wave;     // (wavefronts 4 apart share a SIMD: rows that have equally many places together)
     const int lq = lane >> 4, ln = lane & 15;
     const int p0 = q.step * CB, bs = min(CB, pr.n - p0), nb = (bs + 15) >> 4;
-    const bool panel = pr.n > CB;
-    const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * pr.ld + p0, 0, bs * pr.ld * 4, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(pr.F, 0, CB * CB * 4, 0x00020000);
-    if (tid == 0) bad = 0;
+    const bool panel = pr.n > CB, first = q.step == 0;
+    const float *S = first ? pr.M : pr.T + (long)p0 * pr.ld + p0;
+    const int pitch = first ? pr.ldm : pr.ld;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(S), 0, ((bs - 1) * pitch + bs) * 4, 0x00020000);
 
-    floatx4 acc[8][4];
-    {   // tile (r, c), c >= r: element (16 r + 4 lq + v, 16 c + ln) of the upper triangle, from the lower one
-        const bool first = q.step == 0;
-        const float *S = first ? pr.M : pr.T + (long)p0 * pr.ld + p0;
-        const int pitch = first ? pr.ldm : pr.ld;
-        const float damping = first ? (pr.dptr ? *pr.dptr : pr.damping) : 0.f;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(S), 0, ((bs - 1) * pitch + bs) * 4, 0x00020000);
-        auto at = [&](int r, int c) { return (unsigned)(c * pitch + r) * 4u; };
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int tr = 2 * i + a, tc = 4 * j + b, r = 16 * tr + 4 * lq, c = 16 * tc + ln;
-                acc[i][j] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, tr < tc && c < bs ? at(r, c) : W_OOB, 0, 0));
-            }
-        if (a == (b & 1)) {                      // on the diagonal what is taken away is summed by itself
-            float d[4][4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int r = 16 * (4 * j + b) + 4 * lq + e, c = 16 * (4 * j + b) + ln;
-                    d[j][e] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, max(r, c) < bs ? at(min(r, c), max(r, c)) : W_OOB, 0, 0));
-                }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int r = 16 * (4 * j + b) + 4 * lq, c = 16 * (4 * j + b) + ln;
-                floatx4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = r + e == c ? (c < bs ? d[j][e] + damping : 1.f) : d[j][e];     // past the edge: the identity
-                diag4[4 * j + b][lane] = v;
-            }
-        }
-    }
-    // Step k forms row k; step -1 only inverts the first diagonal tile.
-    for (int k = -1;; ++k) {
+    if (wave == 8) {
+        __builtin_amdgcn_s_setprio(3);
+        int bad = 0;
+        if (lane < 64) below[0][lane] = below[1][lane] = floatx4{0.f, 0.f, 0.f, 0.f};
         lds_barrier();
-        if (k >= 0) {
-            // the new row: X_kk times the tiles of tile row k
-            if (a == (k & 1)) {
-                const floatx4 x = *reinterpret_cast<const floatx4 *>(xs + ln * CD_XP + 4 * lq);
-                floatx4 row[4];
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (i == (k >> 1)) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) row[j] = acc[i][j];
-                    }
-                floatx4 t[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) t[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[jj], row[j][jj], t[j], 0, 0, 0);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (4 * j + b == k) {        // X_kk itself
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) t[j][v] = xs[(4 * lq + v) * CD_XP + ln];
-                    }
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) ws[(4 * lq + v) * CD_WP + 16 * (4 * j + b) + ln] = t[j][v];
-            }
-            lds_barrier();
-        }
-        if (k + 1 < nb) {
-        if (a == ((k + 1) & 1) && b == ((k + 1) & 3)) {
-            // the tile that the next step begins with ahead of all others
-            floatx4 t;
-            float f[4] = {0.f, 0.f, 0.f, 0.f};
+        for (int k = -1;; ++k) {
             if (k >= 0) {
-#pragma unroll
-                for (int jj = 0; jj < 4; ++jj) f[jj] = ws[(4 * lq + jj) * CD_WP + 16 * (k + 1) + ln];
+                lds_barrier();
+                lds_barrier();
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                if (i == ((k + 1) >> 1)) t = acc[i][i >> 1];
+            if (k + 1 == nb) break;
             floatx4 z = {0.f, 0.f, 0.f, 0.f};
+            if (k >= 0) {
+                const floatx4 f = frag[k + 1][lane];
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) z = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[jj], f[jj], z, 0, 0, 0);
-            t += z;
-            t += diag4[k + 1][lane];
-            floatx4 fix;
+                for (int e = 0; e < 4; ++e) z = __builtin_amdgcn_mfma_f32_16x16x4f32(-f[e], f[e], z, 0, 0, 0);
+            }
+            floatx4 t = below[(k + 1) & 1][lane] + z, fix;     // what is taken away is summed by itself
+            t += diag[k + 1][lane];
             const int fail = chol_leaf(t, fix, lane);
-            if (ln == 0) *reinterpret_cast<floatx4 *>(pr.fix + p0 + 16 * (k + 1) + 4 * lq) = fix;
 #pragma unroll
             for (int v = 0; v < 4; ++v) xs[(4 * lq + v) * CD_XP + ln] = t[v];
-            if (lane == 0 && fail != 0 && bad == 0) bad = 16 * (k + 1) + fail;
+            xf[lane] = t;
+            if (ln == 0) *reinterpret_cast<floatx4 *>(pr.fix + p0 + 16 * (k + 1) + 4 * lq) = fix;
+            if (fail != 0 && bad == 0) bad = 16 * (k + 1) + fail;
         }
-        if (k < 0) continue;
-        __builtin_amdgcn_sched_barrier(0);
-        float br[4][4];
+        if (lane == 0) {
+            if (first) *pr.info = bad;
+            else if (bad != 0 && *pr.info == 0) *pr.info = p0 + bad;
+        }
+        return;
+    }
+
+    if (wave > 8) {
+        const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(pr.T + (long)p0 * pr.ld + p0, 0, bs * pr.ld * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rf = __builtin_amdgcn_make_buffer_rsrc(pr.F, 0, CB * CB * 4, 0x00020000);
+        lds_barrier();
+        for (int k = 0; k < nb; ++k) {
+            lds_barrier();
+            lds_barrier();
+            for (int m = wave - 9; m < 16; m += 3) {
+                const floatx4 f = m < nb ? frag[m][lane] : floatx4{0.f, 0.f, 0.f, 0.f};
+                const floatx4 x = m <= k ? f : floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+                for (int v = 0; v < 4; ++v) {    // the row of X, zeros right of the diagonal
+                    const int row = 16 * k + 4 * lq + v, col = 16 * m + ln;
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[v]), rt, row < bs && p0 + col < pr.ld ? (unsigned)(row * pr.ld + col) * 4u : W_OOB, 0, 0);
+                }
+                if (!panel) continue;            // for the substitution: X in the 32 x 32 blocks on the diagonal, -L below them
+                if ((m >> 1) == (k >> 1)) {
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) br[j][jj] = ws[(4 * lq + jj) * CD_WP + 16 * (4 * j + b) + ln];
+                    for (int v = 0; v < 4; ++v)
+                        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[v]), rf, (unsigned)((16 * k + 4 * lq + v) * CB + 16 * m + ln) * 4u, 0, 0);
+                } else if (m > k && m < nb) {
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, -f), rf, (unsigned)((16 * m + ln) * CB + 16 * k + 4 * lq) * 4u, 0, 0);
+                }
+            }
+        }
+        return;
+    }
+
+    // place (i, j), i <= j: of row w in acc[j], of row w + 8 in acc[j + 8]
+    floatx4 acc[24];
+    {   // tiles above the diagonal, element (16 i + 4 lq + v, 16 j + ln), from below it
+        const float damping = first ? (pr.dptr ? *pr.dptr : pr.damping) : 0.f;
+        auto at = [&](int r, int c) { return (unsigned)(c * pitch + r) * 4u; };
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = 2 * i + a;
-            if (r <= k) continue;
-            float ar[4];
+        for (int u = 0; u < 24; ++u) {
+            const int i = u < 16 ? w : w + 8, j = u < 16 ? u : u - 8, c = 16 * j + ln;
+            acc[u] = __builtin_bit_cast(floatx4, __builtin_amdgcn_raw_buffer_load_b128(rs, i < j && c < bs ? at(16 * i + 4 * lq, c) : W_OOB, 0, 0));
+        }
+        float d[2][4];
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) ar[jj] = -ws[(4 * lq + jj) * CD_WP + 16 * r + ln];
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int j = 0; j < 4; j += 2) {      // two tiles at a time where both are wanted
-                const int c0 = 4 * j + b, c1 = c0 + 4;
-                const bool w0 = c0 <= k || c0 >= r, w1 = c1 <= k || c1 >= r;
-                floatx4 z0 = {0.f, 0.f, 0.f, 0.f}, z1 = z0;
-                if (w0 && w1) {
+            for (int v = 0; v < 4; ++v) {
+                const int r = 16 * (w + 8 * u) + 4 * lq + v, c = 16 * (w + 8 * u) + ln;
+                d[u][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, max(r, c) < bs ? at(min(r, c), max(r, c)) : W_OOB, 0, 0));
+            }
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z0, 0, 0, 0);
-                        z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j + 1][jj], z1, 0, 0, 0);
+        for (int u = 0; u < 2; ++u) {
+            const int r = 16 * (w + 8 * u) + 4 * lq, c = 16 * (w + 8 * u) + ln;
+            floatx4 t;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] = r + v == c ? (c < bs ? d[u][v] + damping : 1.f) : d[u][v];      // past the edge: the identity
+            diag[w + 8 * u][lane] = t;
+        }
+        if (w == 0) {
+#pragma unroll
+            for (int j = 1; j < 16; ++j) raw[j][lane] = acc[j];
+        }
+        // all loads are waited for here, not in the loop
+#pragma unroll
+        for (int u = 0; u < 24; ++u) asm volatile("" : "+v"(acc[u]));
+    }
+    lds_barrier();
+    const floatx4 none = {0.f, 0.f, 0.f, 0.f};
+    // where this lane's part of a tile of row k + 1 goes that is kept transposed: element (ln, 4 lq + v)
+    float *const turned = reinterpret_cast<float *>(raw) + (16 * (ln >> 2) + 4 * lq) * 4 + (ln & 3);
+    for (int k = 0;; ++k) {
+        lds_barrier();
+        // tiles w and w + 8 of row k
+        floatx4 f0 = none, f1 = none;
+        {
+            const floatx4 x = *reinterpret_cast<const floatx4 *>(xs + ln * CD_XP + 4 * lq), r0 = raw[w][lane], r1 = raw[w + 8][lane];
+            const floatx4 own = xf[lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                f0 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], r0[e], f0, 0, 0, 0);
+                f1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], r1[e], f1, 0, 0, 0);
+            }
+            f0 = k == w ? own : f0;
+            f1 = k == w + 8 ? own : f1;
+            frag[w][lane] = f0;
+            frag[w + 8][lane] = f1;
+        }
+        lds_barrier();
+        if (k + 1 == nb) break;
+        if (k == w) {                            // row w is done: X begins
+#pragma unroll
+            for (int u = 0; u < 16; ++u) acc[u] = none;
+        }
+        if (k == w + 8) {
+#pragma unroll
+            for (int u = 16; u < 24; ++u) acc[u] = none;
+        }
+        // One bit per column: places of row w and of row w + 8 that the step changes, places that the next step looks for elsewhere.
+        const unsigned present = (1u << nb) - 1u;
+        unsigned m0 = (0xffffffffu << max(w, k + 1)) & present, m1 = (0xffffffffu << max(w + 8, k + 1)) & present;
+        unsigned pass = (w == k + 1 ? m0 : 0u) | (w + 8 == k + 1 ? m1 : 0u) | (2u << k) | (w == k + 2 || w + 8 == k + 2 ? 4u << k : 0u);
+        asm volatile("" : "+s"(m0), "+s"(m1), "+s"(pass));
+        auto pass_on = [&](const floatx4 &a, int i, int j) {
+            if (i == k + 1) raw[j][lane] = a;    // the next row
+            if (j == k + 1 && i <= k) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) turned[i * 256 + 4 * v] = a[v];
+            }
+            if (i == j && j == k + 2) below[j & 1][lane] = a;
+        };
+        floatx4 op[4];
+        auto column = [&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const floatx4 o = op[j & 3];
+            if (j + 3 < 16) op[(j + 3) & 3] = frag[j + 3][lane];
+            __builtin_amdgcn_sched_barrier(0);
+            if (m0 & (1u << j)) {
+                floatx4 z0 = none, z1 = none;
+                if (j >= 8 && (m1 & (1u << j))) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(f0[e], o[e], z0, 0, 0, 0);
+                        z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(f1[e], o[e], z1, 0, 0, 0);
                     }
-                    acc[i][j] += z0;
-                    acc[i][j + 1] += z1;
-                } else if (w0) {
+                    acc[j < 8 ? j : j + 8] -= z1;
+                } else {
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j][jj], z0, 0, 0, 0);
-                    acc[i][j] += z0;
-                } else if (w1) {
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[jj], br[j + 1][jj], z1, 0, 0, 0);
-                    acc[i][j + 1] += z1;
+                    for (int e = 0; e < 4; ++e) z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(f0[e], o[e], z0, 0, 0, 0);
+                }
+                acc[j] -= z0;
+                if (pass & (1u << j)) {
+                    pass_on(acc[j], w, j);
+                    if (j >= 8 && (m1 & (1u << j))) pass_on(acc[j < 8 ? j : j + 8], w + 8, j);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
-        }
-        }
-        // to memory, rows and tiles w and w + 8
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int m = w + 8 * u;
-            {   // the new row of X, zeros right of the diagonal
-                const int c = 4 * lane, row = 16 * k + m;
-                const floatx4 v = *reinterpret_cast<const floatx4 *>(ws + m * CD_WP + c);
-                const floatx4 x = c < 16 * (k + 1) ? v : floatx4{0.f, 0.f, 0.f, 0.f};
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, x), rt, row < bs && p0 + c < pr.ld ? (unsigned)c * 4u : W_OOB, (unsigned)(row * pr.ld) * 4u, 0);
-            }
-            if (panel) {
-                // for the substitution: X in the 32 x 32 blocks on the diagonal, -L below them
-                if ((m >> 1) == (k >> 1)) {
-                    const int row = lane >> 2, c = 4 * (lane & 3);
-                    const floatx4 v = *reinterpret_cast<const floatx4 *>(ws + row * CD_WP + 16 * m + c);
-                    const floatx4 x = m <= k ? v : floatx4{0.f, 0.f, 0.f, 0.f};
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, x), rf, (unsigned)(row * CB + c) * 4u, (unsigned)(16 * k * CB + 16 * m) * 4u, 0);
-                } else if (m > k) {
-                    floatx4 v;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = -ws[(4 * lq + e) * CD_WP + 16 * m + ln];
-                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(suint4, v), rf, (unsigned)(ln * CB + 4 * lq) * 4u, (unsigned)(16 * m * CB + 16 * k) * 4u, 0);
-                }
-            }
-        }
-        if (k + 1 == nb) break;
+        };
+        // columns right of tile column k
+#define KFAC_CHOL_COLUMNS(J)                                                                                                  \
+    if (k < J + 3 && J < nb) {                                                                                                \
+        for (int u = J; u < J + 3; ++u) op[u & 3] = frag[u][lane];                                                            \
+        column(std::integral_constant<int, J>{}); column(std::integral_constant<int, J + 1>{});                               \
+        column(std::integral_constant<int, J + 2>{}); column(std::integral_constant<int, J + 3>{});                           \
     }
-    if (tid == 0) {
-        if (q.step == 0) *pr.info = bad;
-        else if (bad != 0 && *pr.info == 0) *pr.info = p0 + bad;
+        KFAC_CHOL_COLUMNS(0) KFAC_CHOL_COLUMNS(4) KFAC_CHOL_COLUMNS(8) KFAC_CHOL_COLUMNS(12)
+#undef KFAC_CHOL_COLUMNS
     }
 }
 
