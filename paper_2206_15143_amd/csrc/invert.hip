@@ -380,7 +380,8 @@ __global__ __launch_bounds__(256) void sweep_finish_kernel(const InvTable tab)
 }
 
 namespace {
-bool takes_chol(int n) { return n > tuning().invert_chol_min_n && n <= kCholMaxOrder; }
+// (invert_refine = 0 asks for the sweep without its refinements)
+bool takes_chol(int n) { return n > tuning().invert_chol_min_n && n <= kCholMaxOrder && tuning().invert_refine; }
 bool takes_fused(int n) { return !takes_chol(n) && n <= tuning().invert_fused_max_n; }
 int chol_thin(int n) { return n > CB && n % CB == 1; }
 // row pitch of T: whole cache lines, and not a multiple of 2 KB (a column of tiles would come from few memory channels)
@@ -398,10 +399,10 @@ size_t fused_ws_floats(int n) { return 4 * (size_t)NB * NB + 2 * (size_t)NB * ((
 // block's columns, the workspace of the nested pivot-block inversion, its status and gate words
 size_t job_ws_floats(int n)
 {
-    if (takes_chol(n)) return chol_ws_floats(n);
-    if (takes_fused(n)) return fused_ws_floats(n);
+    // enough for either method: a workspace stays good when the tuning changes
+    const size_t chol = n > tuning().invert_chol_min_n && n <= kCholMaxOrder ? chol_ws_floats(n) : 0;
     const size_t PB = (size_t)outer_block();
-    return 5 * PB * ((n + 3) / 4 * 4) + 6 * PB * PB + fused_ws_floats((int)PB) + 64;
+    return std::max(chol, n <= tuning().invert_fused_max_n ? fused_ws_floats(n) : 5 * PB * ((n + 3) / 4 * 4) + 6 * PB * PB + fused_ws_floats((int)PB) + 64);
 }
 // the three flags at the end of a matrix's one-launch-per-step workspace: gate of either step parity, sticky flag
 int *fused_gate_ptr(float *ws, int n)
@@ -1394,7 +1395,7 @@ bool takes_border(int n)
 {
     return tuning().invert_border && !takes_chol(n) && n > 64 && n % 64 == 1 && takes_fused(n - 1) && n - 1 <= 1280;   // 1280: the LDS vectors of the two kernels
 }
-size_t border_ws_floats(int n) { return takes_border(n) ? 3 * (size_t)((n - 1 + 63) / 64 * 64) : 0; }
+size_t border_ws_floats(int n) { return n > 64 && n % 64 == 1 && n <= 1281 ? 3 * (size_t)((n - 1 + 63) / 64 * 64) : 0; }
 }  // namespace
 
 size_t invert_workspace_bytes(const InvertJob *jobs, int n)
