@@ -239,85 +239,148 @@ __global__ __launch_bounds__(T::NT) void syrk_partial_kernel(const SyrkTable tab
 // block row for the border).  Fixed summation order over the splits.
 constexpr int kRedChunk = 256;
 constexpr int kRedGroup = 4;   // sub-tiles per block
+constexpr int kRedWide = 64;   // 256-wide tiles: a block owns 64 x 64, or 16 x 64 where more slices are to be added than this
+constexpr int kRedWideSplits = 8;
+__host__ __device__ constexpr int red_rows(int splits) { return splits <= kRedWideSplits ? kRedWide : 16; }
+__host__ __device__ constexpr int red_blocks(int bm, int splits)   // blocks per tile
+{
+    return bm == 256 ? (256 / red_rows(splits)) * (256 / kRedWide) : ((bm * bm + kRedChunk - 1) / kRedChunk + kRedGroup - 1) / kRedGroup;
+}
 
 // NATIVE: the partial tiles are stored as the MFMA accumulators lie in registers (per 16x16 tile
 // [lane][4], tiles row-major inside the 144-wide macro tile), which lets the wave kernels store
 // 16 bytes per lane; element e of a macro tile then maps to row / column as decoded below.
+// 256-wide tiles (the kernels on the bf16 MFMA: the factors with the most slices), ROWS x 64 of one per block: 16 lanes along
+// a row, 16 bytes each (rows of F begin at any multiple of 4), up to two groups of 16 rows at a time with eight slices of both and
+// the old values in flight.  The mirror image goes through LDS, so that it too is written as long pieces of rows: 256 bytes of 64
+// rows.  (The partial tiles are allocated whole: a vector that straddles the diagonal or the edge of the factor reads defined
+// or stale words, and only live elements are used.)
+// Bound: HBM.  16 rows of 64 with a load and four stores of 4 bytes a lane for the old and the new values before; us per update: 24
+// factors of order 3073 and 120 of 768 / 769, one slice each, 703 -> 545; thirteen 3x3 convolutions up to 4608 columns 407 -> 317;
+// 54 layers of a ResNet-50 in bf16 1018 -> 746.  64 rows a block with all slice counts: 142 -> 400 where 50 slices meet in 36 tiles.
+template <int ROWS>
+__device__ __forceinline__ void syrk_reduce_wide(const SyrkProb &pr, int local, float *lds)
+{
+    typedef float uf4 __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int P = kRedWide + 1, S = 256 / kRedWide, Q = ROWS >= 32 ? 2 : 1;
+    constexpr int GPT = (256 / ROWS) * S;
+    const int nblk = pr.nb * (pr.nb + 1) / 2;
+    const int dF = pr.d + pr.has_bias;
+    const float wnew = (1.0f - pr.decay) * pr.scale;
+    const int tile = local / GPT;
+    const int grp = local - tile * GPT;
+    int bi, bj;
+    tri_decode(tile, bi, bj);
+    const int ur = (grp / S) * ROWS, vc = (grp % S) * kRedWide;     // in the tile
+    const int u0 = bi * 256 + ur, v0 = bj * 256 + vc;
+    if (u0 >= pr.d || v0 > u0 + ROWS - 1) return;
+    const float *src = pr.partial + (long)tile * (256 * 256);
+    const long sstride = (long)nblk * (256 * 256);
+    const int t = threadIdx.x;
+    const int r = t >> 4, c4 = (t & 15) * 4, v = v0 + c4;
+#pragma unroll
+    for (int h = 0; h < ROWS / (16 * Q); ++h) {
+        floatx4 sum[Q], old[Q], a[Q][8];
+        int e[Q], u[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int row = 16 * (Q * h + q) + r;
+            u[q] = u0 + row;
+            e[q] = (ur + row) * 256 + vc + c4;
+            old[q] = floatx4{0.f, 0.f, 0.f, 0.f};
+            const float *f = pr.F + (long)u[q] * dF + v;
+            if (u[q] < pr.d && v <= u[q]) {
+                if (v + 3 <= u[q]) old[q] = *reinterpret_cast<const uf4 *>(f);
+                else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (v + i <= u[q]) old[q][i] = f[i];
+                }
+            }
+        }
+        if (pr.splits == 1) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) sum[q] = *reinterpret_cast<const floatx4 *>(src + e[q]);
+        } else {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a[q][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+            const int last = pr.splits - 1;
+            for (int k = 0; k <= last; k += 8)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float *s = src + (long)min(k + j, last) * sstride;       // (no condition on a load)
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const floatx4 x = *reinterpret_cast<const floatx4 *>(s + e[q]);
+                        a[q][j] += k + j <= last ? x : floatx4{0.f, 0.f, 0.f, 0.f};
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+#pragma unroll
+                for (int s = 4; s > 0; s >>= 1)
+#pragma unroll
+                    for (int j = 0; j < s; ++j) a[q][j] += a[q][j + s];
+                sum[q] = a[q][0];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            floatx4 out;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                out[i] = pr.decay * old[q][i] + wnew * sum[q][i];
+                lds[(16 * (Q * h + q) + r) * P + c4 + i] = out[i];
+            }
+            float *f = pr.F + (long)u[q] * dF + v;
+            if (u[q] < pr.d && v <= u[q]) {
+                if (v + 3 <= u[q]) *reinterpret_cast<uf4 *>(f) = out;
+                else {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        if (v + i <= u[q]) f[i] = out[i];
+                }
+            }
+        }
+    }
+    __syncthreads();
+    constexpr int LP = ROWS / 4, RP = 256 / LP;          // lanes along a row of the mirror image, rows at a time
+    const int r4 = (t % LP) * 4, u2 = u0 + r4;
+#pragma unroll
+    for (int j = 0; j < kRedWide / RP; ++j) {
+        const int cc = t / LP + RP * j, v2 = v0 + cc;
+        floatx4 out;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) out[i] = lds[(r4 + i) * P + cc];
+        float *f = pr.F + (long)v2 * dF + u2;
+        if (v2 < u2 && u2 + 3 < pr.d) *reinterpret_cast<uf4 *>(f) = out;
+        else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (u2 + i < pr.d && v2 < u2 + i) f[i] = out[i];
+        }
+    }
+}
+
 template <class T, bool NATIVE>
-__device__ __forceinline__ void syrk_reduce_body(const SyrkProb &pr, int local, float (*mir)[16][17])
+__device__ __forceinline__ void syrk_reduce_body(const SyrkProb &pr, int local, float *lds)
 {
     const int nblk = pr.nb * (pr.nb + 1) / 2;
     const int dF = pr.d + pr.has_bias;
     const float wnew = (1.0f - pr.decay) * pr.scale;
     constexpr int TILE = T::BM * T::BM;
     constexpr int CPT = (TILE + kRedChunk - 1) / kRedChunk;   // chunks per tile
-
-    constexpr int GPT = (CPT + kRedGroup - 1) / kRedGroup;    // blocks per tile
+    const int GPT = red_blocks(T::BM, pr.splits);
     if constexpr (T::BM == 256 && !NATIVE) {
-        // 256-wide tiles (the bf16 MFMA kernels: the factors with the most slices).  The kRedGroup sub-tiles of a
-        // block lie side by side, 16 rows x 64 columns of the tile: thread t takes four consecutive columns of
-        // row t / 16, so a slice is read with 16 bytes per lane and 256 contiguous bytes per row, eight slices
-        // in flight.  (The partial tiles are allocated whole: a vector that straddles the diagonal or the edge
-        // of the factor reads defined or stale words, and only live elements are used.)
         if (local < nblk * GPT) {
-            static_assert(kRedGroup == 4 && kRedChunk == 256, "the strip of a block is 16 x 64");
-            float(*tr)[65] = reinterpret_cast<float(*)[65]>(&mir[0][0][0]);    // 16 x 65 <= 4 x 16 x 17
-            const int tile = local / GPT;
-            const int grp = local - tile * GPT;
-            int bi, bj;
-            tri_decode(tile, bi, bj);
-            const float *src = pr.partial + (long)tile * TILE;
-            const long sstride = (long)nblk * TILE;
-            const int t = threadIdx.x;
-            const int r = t >> 4, c4 = (t & 15) * 4;
-            const int sr = grp >> 2, c0 = (grp & 3) * 64;
-            const int u = bi * 256 + sr * 16 + r, v0 = bj * 256 + c0 + c4;
-            const int e = (sr * 16 + r) * 256 + c0 + c4;
-            const bool any = u < pr.d && v0 <= u;         // some element of the four is in the lower triangle
-            floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-            if (any) {
-                if (pr.splits == 1) {
-                    sum = *reinterpret_cast<const floatx4 *>(src + e);
-                } else {
-                    floatx4 a[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) a[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-                    int k = 0;
-                    for (; k + 8 <= pr.splits; k += 8) {
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) a[j] += *reinterpret_cast<const floatx4 *>(src + (k + j) * sstride + e);
-                    }
-                    for (; k < pr.splits; ++k) a[0] += *reinterpret_cast<const floatx4 *>(src + k * sstride + e);
-#pragma unroll
-                    for (int h = 4; h > 0; h >>= 1)
-#pragma unroll
-                        for (int j = 0; j < h; ++j) a[j] += a[j + h];
-                    sum = a[0];
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int v = v0 + i;
-                float out = 0.f;
-                if (any && v <= u) {
-                    out = pr.decay * pr.F[(long)u * dF + v] + wnew * sum[i];
-                    pr.F[(long)u * dF + v] = out;
-                }
-                tr[r][c4 + i] = out;
-            }
-            __syncthreads();
-            // the mirror image, along rows of F: thread t writes row (column of the strip) t / 16 + 16 j
-            const int r2 = t & 15;
-            const int u2 = bi * 256 + sr * 16 + r2;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int cc = (t >> 4) + 16 * j;
-                const int v2 = bj * 256 + c0 + cc;
-                if (u2 < pr.d && v2 < u2) pr.F[(long)v2 * dF + u2] = tr[r2][cc];
-            }
+            if (red_rows(pr.splits) == kRedWide) syrk_reduce_wide<kRedWide>(pr, local, lds);
+            else syrk_reduce_wide<16>(pr, local, lds);
             return;
         }
     }
+    float(*mir)[16][17] = reinterpret_cast<float(*)[16][17]>(lds);
     if (local < nblk * GPT) {
         // kRedGroup 16 x 16 sub-tiles per block: thread t holds one element of each; all loads are issued
         // before the first store.  The mirror image goes through LDS so that both stores run along rows of F.
@@ -448,7 +511,8 @@ struct RedTable {
 
 __global__ __launch_bounds__(256) void syrk_reduce_kernel(const RedTable tab)
 {
-    __shared__ float mir[kRedGroup][16][17];
+    __shared__ float lds[kRedWide * (kRedWide + 1)];
+    static_assert(kRedGroup * 16 * 17 <= kRedWide * (kRedWide + 1), "the narrow tiles use it too");
     int pi = 0, hi = tab.count - 1;
     while (pi < hi) {
         const int mid = (pi + hi + 1) >> 1;
@@ -458,12 +522,12 @@ __global__ __launch_bounds__(256) void syrk_reduce_kernel(const RedTable tab)
     const SyrkProb &pr = tab.p[pi];
     const int local = blockIdx.x - tab.starts[pi];
     switch (tab.kind[pi]) {
-        case 0: syrk_reduce_body<Tile<4, 2>, false>(pr, local, mir); break;
-        case 1: syrk_reduce_body<Tile<3, 3>, false>(pr, local, mir); break;
-        case 2: syrk_reduce_body<Tile<2, 2>, false>(pr, local, mir); break;
-        case 3: syrk_reduce_body<Tile<1, 2>, false>(pr, local, mir); break;
-        case 4: syrk_reduce_body<Tile<3, 3>, true>(pr, local, mir); break;    // 144-wide tiles in accumulator order
-        default: syrk_reduce_body<Tile<8, 2>, false>(pr, local, mir); break;
+        case 0: syrk_reduce_body<Tile<4, 2>, false>(pr, local, lds); break;
+        case 1: syrk_reduce_body<Tile<3, 3>, false>(pr, local, lds); break;
+        case 2: syrk_reduce_body<Tile<2, 2>, false>(pr, local, lds); break;
+        case 3: syrk_reduce_body<Tile<1, 2>, false>(pr, local, lds); break;
+        case 4: syrk_reduce_body<Tile<3, 3>, true>(pr, local, lds); break;    // 144-wide tiles in accumulator order
+        default: syrk_reduce_body<Tile<8, 2>, false>(pr, local, lds); break;
     }
 }
 
@@ -1102,9 +1166,7 @@ hipError_t syrk_launch(const FactorJob *jobs, int n, void *work, size_t work_byt
             blocks += pl[j].bps * pl[j].splits;
             {
                 const int bm = kCfgs[pl[j].cfg].bm;
-                const int cpt = (bm * bm + kRedChunk - 1) / kRedChunk;
-                const int gpt = (cpt + kRedGroup - 1) / kRedGroup;
-                red_n[k] = pl[j].nblk * gpt + (job.has_bias ? pl[j].nb : 0);
+                red_n[k] = pl[j].nblk * red_blocks(bm, pl[j].splits) + (job.has_bias ? pl[j].nb : 0);
             }
         }
         const int cfg = pl[g[0]].cfg;
