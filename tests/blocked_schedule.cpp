@@ -3,7 +3,8 @@
 // and that neither the order of a stream nor an event puts in an order.  Compiled and run by test_blocked_schedule.py; needs no GPU:
 // the calls of the runtime that the host code makes are answered here and only noted down, no kernel runs.
 //
-//   blocked_schedule REFINE ORDER...      two calls in a row on one stream, with the same buffers
+//   blocked_schedule REFINE ORDER...      two calls in a row on one stream, with the same buffers; by the sweep with or without its
+//                                         refinements (1, 0), or by triangular factors (2)
 #include "../paper_2206_15143_amd/csrc/common.hpp"
 
 #include <algorithm>
@@ -140,6 +141,62 @@ static void touch_product(Access &a, const float *A, const float *B, float *C, l
         a.wr.put(row + p1, 4 * (size_t)std::max(0l, end - p1));
     }
 }
+static std::map<const CholProb *, CholProb> chol_table;
+
+// A step of the inversion by triangular factors: rows of T are panels, its diagonal blocks and what is left and right of them.
+static void touch_chol(Access &a, const std::string &kernel, const CholSeq &q)
+{
+    auto is = [&](const char *s) { return kernel.find(s) != std::string::npos; };
+    for (int c = 0; c < q.nclass; ++c)
+        for (int k = q.c[c].first; k < q.c[c].first + q.c[c].count; ++k) {
+            a.rd.put(q.tab + k, sizeof(CholProb));
+            const CholProb &p = chol_table.at(q.tab + k);
+            const long n = p.n, p0 = (long)q.step * CB, p1 = std::min<long>(n, p0 + CB), all = n + p.thin;
+            auto rows = [&](Set &s, long from, long to, long col, long end) { if (from < to && col < end) s.mat(p.T + from * p.ld + col, p.ld, to - from, end - col); };
+            if (is("chol_diag_kernel")) {
+                if (q.step == 0) a.rd.lower(p.M, p.ldm, n);
+                rows(a.wr, p0, p1, p0, p1);
+                a.wr.put(p.F, n > CB ? 4 * CB * CB : 0);
+                a.wr.put(p.fix + p0, 4 * (p1 - p0));
+                a.wr.put(p.info, 4);
+            } else if (is("chol_panel_kernel") || is("chol_ahead_kernel")) {
+                const bool ahead = is("chol_ahead_kernel");
+                a.rd.lower(p.M, p.ldm, n);
+                rows(a.rd, 0, ahead ? (long)q.from * CB : p0, 0, n);
+                if (!ahead) a.rd.put(p.F, 4 * CB * CB);
+                for (long r = p0; r < n && r < p0 + (ahead ? 2 : 1) * CB; r += CB) {
+                    const long e = std::min<long>(n, r + CB);
+                    rows(a.wr, r, e, 0, ahead ? (long)q.from * CB : r);
+                    rows(a.wr, r, e, e, n);
+                }
+            } else if (is("chol_next_kernel")) {
+                if (q.step == 0) a.rd.lower(p.M, p.ldm, n);
+                rows(a.rd, p0, p1, p1, n);
+                for (long r = p1; r < n; r += CB) rows(a.wr, r, std::min<long>(n, r + CB), r, std::min<long>(n, r + CB));
+            } else if (is("chol_thin_z_kernel")) {
+                rows(a.rd, 0, n, 0, n);
+                a.rd.put(p.M + n * p.ldm, 4 * n);
+                a.wr.put(p.z, 4 * n);
+            } else if (is("chol_thin_row_kernel")) {
+                rows(a.rd, 0, n, 0, n);
+                a.rd.put(p.z, 4 * n);
+                rows(a.wr, n, all, 0, all);
+                a.wr.mat(p.out, p.ldo, all, all);
+                a.wr.put(p.info, 4);
+            } else if (is("chol_diagonal_kernel")) {
+                for (long i = 0; i < n; ++i) a.wr.put(p.T + i * (p.ld + 1), 4);
+                a.wr.put(p.xd, 4 * n);
+            } else if (is("chol_out_kernel")) {
+                rows(a.rd, 0, all, 0, all);
+                a.rd.put(p.xd, 4 * n);
+                a.rd.put(p.fix, 4 * n);
+                a.wr.mat(p.out, p.ldo, n, n);
+            } else {
+                fprintf(stderr, "unknown kernel %s\n", kernel.c_str());
+                abort();
+            }
+        }
+}
 template <class T>
 static const T &arg(const Node &n, int i = 0) { if (n.args.at(i).size() != sizeof(T)) abort(); return *reinterpret_cast<const T *>(n.args[i].data()); }
 
@@ -168,6 +225,12 @@ static Access touched(const Node &n)
         const InvUpload &u = arg<InvUpload>(n);
         for (int k = 0; k < u.count; ++k) device_table[u.dst + k] = u.p[k];
         a.wr.put(u.dst, u.count * sizeof(InvProbF));
+    } else if (is("chol_upload_kernel")) {
+        const CholUpload &u = arg<CholUpload>(n);
+        for (int k = 0; k < u.count; ++k) chol_table[u.dst + k] = u.p[k];
+        a.wr.put(u.dst, u.count * sizeof(CholProb));
+    } else if (is("chol_")) {
+        touch_chol(a, n.kernel, arg<CholSeq>(n));
     } else if (is("fsweep_pivot0_kernel")) {
         const bool own = n.args.at(1).size() > sizeof(InvProbF);
         touch_nested(a, arg<InvSeq>(n), own ? reinterpret_cast<const InvProbF *>(n.args[1].data()) : nullptr);
@@ -239,7 +302,8 @@ static Access touched(const Node &n)
 
 int main(int argc, char **argv)
 {
-    tuning().invert_refine = atoi(argv[1]);
+    tuning().invert_refine = atoi(argv[1]) != 0;
+    if (atoi(argv[1]) < 2) tuning().invert_chol_min_n = 1l << 30;
     std::vector<InvertJob> jobs;
     char *at = reinterpret_cast<char *>(uintptr_t(1) << 40);          // addresses only: nothing is read or written
     auto take = [&](size_t bytes) { char *p = at; at += align_up(bytes, 256); return p; };

@@ -37,3 +37,17 @@ def test_launches_that_share_memory_are_ordered(program, orders, refine):
     # not vacuous: the caller's stream and the library's two or three, with launches that may run side by side
     assert streams == (4 if min(orders) <= 1280 else 3) and free > launches
     assert len(lines) == 1, "\n".join(lines[:10])
+
+
+@pytest.mark.parametrize("orders", [(1281,), (1793, 1537, 1536, 1300), (1301, 2049, 1536, 700, 577, 1793, 64, 65, 2304),
+                                    (4609, 4609, 2049, 1025, 129)])
+def test_launches_of_the_triangular_factors_that_share_memory_are_ordered(program, orders):
+    r = subprocess.run([program, "2"] + [str(n) for n in orders], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    lines = r.stdout.splitlines()
+    print(lines[-1])
+    counts = lines[-1].split()
+    launches, streams, free = int(counts[1]), int(counts[3]), int(counts[6])
+    # the caller's stream, the sums of the row blocks to come beside it, the small orders beside both
+    assert streams == (3 if min(orders) <= 128 else 2) and free > 0 and launches > 0
+    assert len(lines) == 1, "\n".join(lines[:10])
