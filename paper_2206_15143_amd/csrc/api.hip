@@ -285,7 +285,7 @@ std::vector<Chunk> make_chunks(const std::vector<Geo> &geo, const kfac_layer_des
             // a long run of equal layers gets chunks of its own, cut into equal parts
             flush();
             const size_t pb = patch_bytes(geo[order[r0]]) + geo[order[r0]].corr_bytes;
-            int per = cap;
+            int per = pb > 0 ? cap : kMaxSyrk / 2;      // (nothing to be found in the cache: as many as a table takes)
             if (pb > 0) per = (int)std::max<size_t>(1, std::min<size_t>(cap, budget / pb));
             const int parts = (cnt + per - 1) / per;
             const int each = (cnt + parts - 1) / parts;

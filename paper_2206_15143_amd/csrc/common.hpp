@@ -15,6 +15,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kMaxProblems = 40;   // problems per grouped launch (table travels as a kernel argument)
+constexpr int kMaxSyrk = 128;      // the same for factors (15 KB): both of 64 linear layers
 
 enum Layout : int {
     kRows = 0,   // X is [K, ld] row-major: element (k, c) at k*ld + c

@@ -805,7 +805,8 @@ void plan_all(const FactorJob *jobs, int n, std::vector<Planned> &pl, std::vecto
         for (int i = 0; i < n; ++i) {
             if (keys[i] != key) continue;
             cur.push_back(i);
-            if ((int)cur.size() == kMaxProblems) { groups.push_back(cur); cur.clear(); }
+            const bool corr = is_corr3_cfg(pl[i].cfg) || pl[i].cfg == kCorrWCfg;     // (tables of their own)
+            if ((int)cur.size() == (corr ? kMaxProblems : kMaxSyrk)) { groups.push_back(cur); cur.clear(); }
         }
         if (!cur.empty()) groups.push_back(cur);
     }

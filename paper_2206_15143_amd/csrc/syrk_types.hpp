@@ -25,8 +25,8 @@ struct SyrkProb {
 
 struct SyrkTable {
     int count;
-    int starts[kMaxProblems];   // blk_start of every problem, compact: searched by bisection
-    SyrkProb p[kMaxProblems];
+    int starts[kMaxSyrk];       // blk_start of every problem, compact: searched by bisection
+    SyrkProb p[kMaxSyrk];
 };
 
 }  // namespace kfac
