@@ -167,7 +167,8 @@ __device__ __forceinline__ void sweep16_pivot(float (&d)[4], int lr, int lk, int
     const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d[K & 3]), K + 16 * (K >> 2)));
     if (!(p > 0.f) && fail == 0) fail = c0 + K + 1;
     const float ip = __builtin_amdgcn_rcpf(p);   // 1 ulp reciprocal: far below the fp32 error of the sweep
-    // column element D[i][K] = D[K][i]: element i of the row, held by lane i + 16*(i>>2) in register i & 3
+    // column element D[i][K] = D[K][i]: element i of the row, held by lane i + 16*(i>>2) in register i & 3.  (The column itself, equal
+    // up to rounding, would come without the LDS round trip of a bpermute; at a condition of 1e5 the error was 0.4 then.)
     float mine = rk[0];
     mine = (lr & 3) == 1 ? rk[1] : mine;
     mine = (lr & 3) == 2 ? rk[2] : mine;
@@ -307,6 +308,7 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
     const InvProbG pr = N > 0 ? load_prob(own.p[prob]) : load_prob(q.tab[prob]);
     if (local > 0) {
         const int g0 = local * FNB;
+#pragma unroll
         for (int e = tid; e < FNB * FNB; e += 256) {
             const int c = e >> 6, k = e & 63;
             tile[c][k] = (g0 + c < pr.n) ? pr.M[(long)(g0 + c) * pr.ldm + k] : 0.f;
@@ -323,17 +325,24 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
     const float damping = pr.dptr ? *pr.dptr : pr.damping;
     const bool test = q.refine_cond >= 0.f;
     float colsum = 0.f;
-    for (int e = tid; e < FNB * FNB; e += 256) {
-        const int i = e >> 6, j = e & 63;
-        float v = (i == j) ? 1.f : 0.f;
-        const bool in = i < bs && j < bs;
-        if (in) {
-            const int a = max(i, j), b = min(i, j);
-            v = pr.M[a * ldm + b] + (a == b ? damping : 0.f);
-            colsum += fabsf(v);
+    const float edge = pr.border ? pr.M[64 * ldm + (tid & 63)] : 0.f, corner = pr.border ? pr.M[64 * ldm + 64] : 0.f;     // the row behind the block
+    {
+        // all loads ahead of the first store (S may be any memory: one iteration would wait for the other)
+        float x[FNB * FNB / 256];
+#pragma unroll
+        for (int u = 0; u < FNB * FNB / 256; ++u) {
+            const int i = (tid >> 6) + 4 * u, j = tid & 63;
+            x[u] = pr.M[min(max(i, j), bs - 1) * ldm + min(min(i, j), bs - 1)];
         }
-        sbuf[i * SW_PITCH + j] = v;
-        if (test) pr.S[i * FNB + j] = in ? v : 0.f;
+#pragma unroll
+        for (int u = 0; u < FNB * FNB / 256; ++u) {
+            const int i = (tid >> 6) + 4 * u, j = tid & 63;
+            const bool in = i < bs && j < bs;
+            const float v = in ? x[u] + (i == j ? damping : 0.f) : (i == j ? 1.f : 0.f);
+            colsum += in ? fabsf(v) : 0.f;
+            sbuf[i * SW_PITCH + j] = v;
+            if (test) pr.S[i * FNB + j] = in ? v : 0.f;
+        }
     }
     nrm[tid] = colsum;
     __syncthreads();
@@ -362,9 +371,8 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
         // thread (i, part) sums a quarter of row i.  y, r, z, b in pw.
         float *yv = pw, *rv = pw + 64, *zv = pw + 128, *bv = pw + 192, *red = pw + 256;
         const int i = tid & 63, part = tid >> 6;
-        const long lastrow = 64 * ldm;
         __syncthreads();                                     // the sweep has been read, pw is free
-        if (tid < 64) bv[i] = pr.M[lastrow + i];
+        if (tid < 64) bv[i] = edge;
         nrm[tid] = colsum;
         __syncthreads();
         if (part == 1 && test) norm_fold(nrm, 1, i);
@@ -393,11 +401,14 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
             red[i] = term * yv[i];
         }
         __syncthreads();
-        for (int h = 32; h > 0; h >>= 1) {
-            if (tid < h) red[tid] += red[tid + h];
-            __syncthreads();
+        if (tid < 64) {
+            float x = red[tid];
+#pragma unroll
+            for (int h = 32; h > 0; h >>= 1) x += __shfl_down(x, h);
+            if (tid == 0) red[0] = x;
         }
-        const float sp = pr.M[lastrow + 64] + damping - red[0];
+        __syncthreads();
+        const float sp = corner + damping - red[0];
         const float is = 1.0f / sp;
         if (tid < 64) {
             if (fix) yv[i] += zv[i];
