@@ -26,6 +26,7 @@
 // table of distinct sizes.
 #pragma once
 
+#include "chol_leaf.hpp"
 #include "tn_engine.hpp"
 
 namespace kfac {
@@ -155,42 +156,10 @@ __device__ __forceinline__ bool seq_locate(const InvSeq &q, int blk, int &prob, 
     return true;
 }
 
-// One pivot of the in-register 16 x 16 sweep (see sweep64_blocked): lane (lr, lk) holds D[lr][4lk..4lk+3].
-template <int K>
-__device__ __forceinline__ void sweep16_pivot(float (&d)[4], int lr, int lk, int c0, int &fail)
-{
-    float rk[4];
-#pragma unroll
-    for (int m = 0; m < 4; ++m)
-        rk[m] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(d[m]), 0x150 + K, 0xf, 0xf, false));
-    // the pivot D[K][K] sits in lane K + 16*(K>>2), register K & 3
-    const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d[K & 3]), K + 16 * (K >> 2)));
-    if (!(p > 0.f) && fail == 0) fail = c0 + K + 1;
-    const float ip = __builtin_amdgcn_rcpf(p);   // 1 ulp reciprocal: far below the fp32 error of the sweep
-    // column element D[i][K] = D[K][i]: element i of the row, held by lane i + 16*(i>>2) in register i & 3.  (The column itself, equal
-    // up to rounding, would come without the LDS round trip of a bpermute; at a condition of 1e5 the error was 0.4 then.)
-    float mine = rk[0];
-    mine = (lr & 3) == 1 ? rk[1] : mine;
-    mine = (lr & 3) == 2 ? rk[2] : mine;
-    mine = (lr & 3) == 3 ? rk[3] : mine;
-    const float ci = __int_as_float(__builtin_amdgcn_ds_bpermute((lr + 16 * (lr >> 2)) * 4, __float_as_int(mine)));
-    const float cip = ci * ip;
-    const bool prow = (lr == K);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const float upd = __builtin_fmaf(-cip, rk[m], d[m]);
-        const float onr = rk[m] * ip;
-        float v = prow ? onr : upd;
-        if (m == (K & 3)) v = (lk == (K >> 2)) ? (prow ? -ip : cip) : v;
-        d[m] = v;
-    }
-}
-
 // Sweep of a 64 x 64 pivot block held in LDS (full symmetric storage, row pitch
 // SW_PITCH; blocks smaller than 64 are padded with the identity by the caller).  Four sub-steps of 16
-// pivots.  Per sub-step: wavefront 0 sweeps the 16 x 16 pivot block inside its registers (lane (i, q)
-// holds D[i][4q..4q+3]; the pivot row reaches the lanes by DPP row broadcast, the pivot column, equal to
-// the row by symmetry, by one ds_bpermute: no barrier inside the 16 pivots); then all four wavefronts
+// pivots.  Per sub-step: wavefront 0 inverts the 16 x 16 pivot block inside its registers, P = X^T X with its triangular inverse
+// X (chol_leaf.hpp; 2300 cycles of the 6600 of a sub-step); then all four wavefronts
 // form W = V P and the rank-16 update of the other blocks on the MFMA units and write the new panel.
 // On exit S holds the swept block (-inverse).  Pb: [16][17], Wb: [64][17] scratch.
 // Returns 0 or the 1-based index (within the block) of the first non-positive pivot (valid in wave 0).
@@ -206,70 +175,56 @@ __device__ __forceinline__ int sweep64_blocked(float *S, float *Pb, float *Wb, i
         const int c0 = kb * 16;
         if (w == 0) {
             // ---- the 16 x 16 pivot block, in registers ----
-            float d[4];
-            {
-                const floatx4 v = *reinterpret_cast<const floatx4 *>(S + (c0 + lr) * SW_PITCH + c0 + 4 * lk);
-                d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-            }
-            sweep16_pivot<0>(d, lr, lk, c0, fail);
-            sweep16_pivot<1>(d, lr, lk, c0, fail);
-            sweep16_pivot<2>(d, lr, lk, c0, fail);
-            sweep16_pivot<3>(d, lr, lk, c0, fail);
-            sweep16_pivot<4>(d, lr, lk, c0, fail);
-            sweep16_pivot<5>(d, lr, lk, c0, fail);
-            sweep16_pivot<6>(d, lr, lk, c0, fail);
-            sweep16_pivot<7>(d, lr, lk, c0, fail);
-            sweep16_pivot<8>(d, lr, lk, c0, fail);
-            sweep16_pivot<9>(d, lr, lk, c0, fail);
-            sweep16_pivot<10>(d, lr, lk, c0, fail);
-            sweep16_pivot<11>(d, lr, lk, c0, fail);
-            sweep16_pivot<12>(d, lr, lk, c0, fail);
-            sweep16_pivot<13>(d, lr, lk, c0, fail);
-            sweep16_pivot<14>(d, lr, lk, c0, fail);
-            sweep16_pivot<15>(d, lr, lk, c0, fail);
-            // P = -swept block
+            floatx4 x = *reinterpret_cast<const floatx4 *>(S + (c0 + lr) * SW_PITCH + c0 + 4 * lk), fix, p = {0.f, 0.f, 0.f, 0.f};
+            const int f = chol_leaf(x, fix, lane);
+            if (f != 0 && fail == 0) fail = c0 + f;
 #pragma unroll
-            for (int m = 0; m < 4; ++m) Pb[lr * 17 + 4 * lk + m] = -d[m];
+            for (int m = 0; m < 4; ++m) p = __builtin_amdgcn_mfma_f32_16x16x4f32(x[m], x[m], p, 0, 0, 0);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) Pb[(4 * lk + m) * 17 + lr] = p[m] + (4 * lk + m == lr ? fix[m] : 0.f);
         }
         __syncthreads();
-        // ---- W = V P for the row tile of this wavefront (rows 16w..16w+15) ----
+        // ---- rows 16w .. 16w + 15, a wavefront's own: W = V P, then S_ij -= W_i V_j^T for the three blocks outside the pivot row
+        // and column, their chains side by side ----
+        floatx4 wt = {0.f, 0.f, 0.f, 0.f};
         if (w != kb) {
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            float b[3][4], old[3][4];
 #pragma unroll
-            for (int s4 = 0; s4 < 4; ++s4) {
-                const float a = S[(16 * w + lr) * SW_PITCH + c0 + 4 * s4 + lk];
-                const float b = Pb[(4 * s4 + lk) * 17 + lr];
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+            for (int s4 = 0; s4 < 4; ++s4)
+                wt = __builtin_amdgcn_mfma_f32_16x16x4f32(S[(16 * w + lr) * SW_PITCH + c0 + 4 * s4 + lk], Pb[(4 * s4 + lk) * 17 + lr], wt, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const int bj = r + (r >= kb ? 1 : 0);
+#pragma unroll
+                for (int s4 = 0; s4 < 4; ++s4) b[r][s4] = S[(16 * bj + lr) * SW_PITCH + c0 + 4 * s4 + lk];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) old[r][v] = S[(16 * w + 4 * lk + v) * SW_PITCH + 16 * bj + lr];
             }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Wb[(16 * w + 4 * lk + v) * 17 + lr] = acc[v];
-        }
-        __syncthreads();
-        // ---- S_ij -= W_i V_j^T for the nine blocks outside the pivot row and column ----
-        for (int t = w; t < 9; t += 4) {
-            const int r3 = t / 3, c3 = t - 3 * r3;
-            const int bi = r3 + (r3 >= kb ? 1 : 0), bj = c3 + (c3 >= kb ? 1 : 0);
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+            for (int v = 0; v < 4; ++v) Wb[(16 * w + 4 * lk + v) * 17 + lr] = wt[v];
+            floatx4 acc[3];
+#pragma unroll
+            for (int r = 0; r < 3; ++r) acc[r] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
-                const float a = Wb[(16 * bi + lr) * 17 + 4 * s4 + lk];
-                const float b = S[(16 * bj + lr) * SW_PITCH + c0 + 4 * s4 + lk];
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+                const float x = Wb[(16 * w + lr) * 17 + 4 * s4 + lk];
+#pragma unroll
+                for (int r = 0; r < 3; ++r) acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b[r][s4], acc[r], 0, 0, 0);
             }
 #pragma unroll
-            for (int v = 0; v < 4; ++v) S[(16 * bi + 4 * lk + v) * SW_PITCH + 16 * bj + lr] -= acc[v];
+            for (int r = 0; r < 3; ++r)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) S[(16 * w + 4 * lk + v) * SW_PITCH + 16 * (r + (r >= kb ? 1 : 0)) + lr] = old[r][v] - acc[r][v];
         }
         __syncthreads();
         // ---- new panel (both triangles) and pivot block ----
-        for (int e = tid; e < 64 * 16; e += 256) {
-            const int i = e >> 4, c = e & 15;
-            if ((i >> 4) != kb) {
-                const float wv = Wb[i * 17 + c];
-                S[i * SW_PITCH + c0 + c] = wv;
-                S[(c0 + c) * SW_PITCH + i] = wv;
-            } else {
-                S[i * SW_PITCH + c0 + c] = -Pb[(i - c0) * 17 + c];
-            }
+        if (w != kb) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(16 * w + 4 * lk + v) * SW_PITCH + c0 + lr] = wt[v];
+            *reinterpret_cast<floatx4 *>(S + (c0 + lr) * SW_PITCH + 16 * w + 4 * lk) = wt;
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) S[(c0 + 4 * lk + v) * SW_PITCH + c0 + lr] = -Pb[(4 * lk + v) * 17 + lr];
         }
         __syncthreads();
     }
@@ -351,20 +306,28 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
     const bool whole = pr.nblk == 1;   // the block is the matrix: store the result itself, both triangles
     const bool border = whole && pr.border;
     colsum = 0.f;
-    for (int e = tid; e < FNB * FNB; e += 256) {
-        const int i = e >> 6, j = e & 63;
-        const bool in = (i < bs && j < bs);
-        const float v = sbuf[i * SW_PITCH + j];
-        if (in) colsum += fabsf(v);
-        if (whole) {
-            if (in && j <= i && !border) {
-                pr.W[i * ldw + j] = -v;
-                pr.W[j * ldw + i] = -v;
-            }
-            continue;
+    {
+        float x[FNB * FNB / 256];
+#pragma unroll
+        for (int u = 0; u < FNB * FNB / 256; ++u) {
+            const int i = (tid >> 6) + 4 * u, j = tid & 63;
+            x[u] = sbuf[i * SW_PITCH + j];
+            colsum += i < bs && j < bs ? fabsf(x[u]) : 0.f;
         }
-        pr.P[i * FNB + j] = in ? -v : 0.f;
-        if (in && j <= i) pr.W[i * ldw + j] = v;
+        if (!border) {
+#pragma unroll
+            for (int u = 0; u < FNB * FNB / 256; ++u) {
+                const int i = (tid >> 6) + 4 * u, j = tid & 63;
+                const bool in = i < bs && j < bs;
+                if (whole) {
+                    // row i from the lower triangle, which is stored as both
+                    if (in) pr.W[i * ldw + j] = -(j <= i ? x[u] : sbuf[j * SW_PITCH + i]);
+                } else {
+                    pr.P[i * FNB + j] = in ? -x[u] : 0.f;
+                    if (in && j <= i) pr.W[i * ldw + j] = x[u];
+                }
+            }
+        }
     }
     if (border) {
         // The last row and column by bordering, as the kernels of larger orders do it (invert.hip has the formulas):
@@ -417,11 +380,14 @@ __global__ __launch_bounds__(256) void fsweep_pivot0_kernel(const InvSeq q, cons
             pr.W[i * ldw + 64] = e;
         }
         __syncthreads();
-        for (int e = tid; e < FNB * FNB; e += 256) {
-            const int a = e >> 6, b = e & 63;
-            const int hi = max(a, b), lo = min(a, b);
-            pr.W[a * ldw + b] = -sbuf[hi * SW_PITCH + lo] + (yv[hi] * yv[lo]) * is;
+        float x[FNB * FNB / 256];
+#pragma unroll
+        for (int u = 0; u < FNB * FNB / 256; ++u) {
+            const int a = (tid >> 6) + 4 * u, b = tid & 63, hi = max(a, b), lo = min(a, b);
+            x[u] = -sbuf[hi * SW_PITCH + lo] + (yv[hi] * yv[lo]) * is;
         }
+#pragma unroll
+        for (int u = 0; u < FNB * FNB / 256; ++u) pr.W[((tid >> 6) + 4 * u) * ldw + (tid & 63)] = x[u];
         if (tid == 0) {
             pr.W[64 * ldw + 64] = is;
             *pr.info = fail != 0 ? fail : (sp > 0.f ? 0 : 65);
