@@ -126,15 +126,23 @@ def load_library():
     return lib
 
 
+_SIZES = (1, 2, 4)
+
+
 def _addr(t) -> int:
     """Device address of a tensor, after the two checks a raw pointer cannot make for itself: the library
     assumes dense row-major storage, and knows 4-byte (fp32, int32), 2-byte (bfloat16) and byte (workspace)
     elements only, so a strided view or a float64 tensor is refused here instead of being misread there."""
+    try:
+        if t.is_contiguous() and t.element_size() in _SIZES:      # a tensor that passes: three calls and no more
+            return t.data_ptr()
+    except AttributeError:
+        pass
     contiguous = getattr(t, "is_contiguous", None)
     if contiguous is not None and not contiguous():
         raise ValueError(f"tensor of shape {tuple(t.shape)} is not contiguous: the library takes dense row-major buffers")
     size = getattr(t, "element_size", None)
-    if size is not None and size() not in (1, 2, 4):
+    if size is not None and size() not in _SIZES:
         raise TypeError(f"tensor of dtype {getattr(t, 'dtype', '?')}: the library takes fp32 / int32, bfloat16 or byte buffers")
     return int(t.data_ptr())
 
@@ -153,10 +161,25 @@ def _nbytes(t) -> int:
     return int(t.numel() * t.element_size())
 
 
+_current = None
+
+
+def _current_stream():
+    """The function that gives the handle of the current stream: without a Stream object on the way where torch has that."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return lambda: int(torch.cuda.current_stream().cuda_stream)
+    device = torch.cuda.current_device
+    return lambda: raw(device())
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        import torch
-        return int(torch.cuda.current_stream().cuda_stream) or None
+        global _current
+        if _current is None:
+            _current = _current_stream()
+        return _current() or None
     if isinstance(stream, int):
         return stream or None
     return int(stream.cuda_stream) or None
