@@ -43,6 +43,7 @@ CLASSES = {
     "gemm_wave": ("gemm_wave_kernel", "mfma", "f32", False),
     "gemm_split": ("gemm_split_kernel", "mfma", "bf16", False),
     "inv_step": ("fsweep_step_kernel", "mfma", "f32", False),
+    "inv_chol": ("chol_panel_kernel and chol_out_kernel", "mfma", "bf16", False),
 }
 # launches without which a factor is not complete: counted in the KF-GEMM time
 KF_GEMM_EXTRA = ("syrk_reduce", "corr3_assemble")

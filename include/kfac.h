@@ -129,15 +129,13 @@ kfac_status kfac_update_factors(const kfac_layer_desc *desc, const void *d_act, 
 
 /* Damped inverses (section 5.2, matrix-inversion variant with the damping of
  * each factor given explicitly).  d_info: 2 ints (A, G).
- * The inversion works in place in the output buffer: d_A_inv / d_G_inv must not alias the running factors, and
+ * d_A_inv / d_G_inv must not alias the running factors (orders up to 128 work in place in the output buffer), and
  * the inverse of a factor that is reported as not positive definite holds whatever the elimination had reached
  * (see Conventions); the running factor itself is never modified.
- * Accuracy: fp32 elimination, relative error of the order of a few hundredths of cond(M) * 2^-24.  The panel
- * products of ill-conditioned pivot blocks are refined once and the bordering step of orders 64 k + 1 corrected
- * to second order (both decided on the device from the condition number of the pivot block), which keeps the
- * result within a factor two of an fp32 LAPACK Cholesky inverse up to condition numbers of a few 1e5.
- * Streams: when a call has a factor of order above 1280, part of the work (the short dependent kernels of every
- * elimination step, and the factors of order up to 1280) runs on the three library streams named under
+ * Accuracy: fp32 elimination, relative error of the order of a few hundredths of cond(M) * 2^-24, within a factor
+ * two of an fp32 LAPACK Cholesky inverse up to condition numbers of a few 1e5.
+ * Streams: when a call has a factor of order above 1280, part of the work (sums of the row blocks to come, and the
+ * smallest factors) runs on the three library streams named under
  * Conventions, forked from and joined back to hip_stream by events inside the call: ordering on hip_stream is
  * as if everything ran there, and the call may be captured into a HIP graph like any other. */
 kfac_status kfac_invert(const kfac_layer_desc *desc, const float *d_A_run, const float *d_G_run,

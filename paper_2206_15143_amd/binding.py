@@ -272,7 +272,7 @@ def kfac_tune(key: str, value: int) -> None:
         raise KeyError(key)
 
 
-KFAC_K_COUNT = 21
+KFAC_K_COUNT = 22
 
 
 def kfac_profile_copy(dst, src, nbytes: int, stream=None) -> None:

@@ -941,7 +941,7 @@ const char *kfac_timing_class_name(int cls)
                                               "inv_pivot", "inv_panel", "inv_finish", "gemm_tn",
                                               "syrk_wave", "syrk_conv3", "syrk_small", "inv_step",
                                               "syrk_bf16", "gemm_wave", "eig_init", "eig_round", "eig_final",
-                                              "syrk_corr3", "corr3_assemble", "gemm_split", "syrk_split"};
+                                              "syrk_corr3", "corr3_assemble", "gemm_split", "syrk_split", "inv_chol"};
     return (cls >= 0 && cls < KFAC_K_COUNT) ? names[cls] : "?";
 }
 

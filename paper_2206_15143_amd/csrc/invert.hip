@@ -1,6 +1,8 @@
 // Damped inverse of the Kronecker factors, (M + damping I)^{-1} (section 5.2 of
 // the DP-KFAC paper, matrix-inversion variant).
 //
+// Orders above invert_chol_min_n (128) up to 23000 go by their triangular factor (invert_chol.hpp, CholRun below).  The rest:
+//
 // Method: blocked symmetric Gauss-Jordan ("sweep") on the lower triangle,
 // batched over matrices.  Sweeping the pivot block K of a symmetric matrix does
 //     P      = M_KK^{-1}
@@ -915,6 +917,8 @@ struct CholRun {
         }
         return flush();
     }
+    // flops of the definition: of the panels of step k (of their sums alone), which have all panels before them there while launches are timed; k < 0: of X^T X
+    double work(const CholSeq &q, int k, bool sums = false) const;
     bool looks_ahead(int k, const AuxStreams *aux) const;
     hipError_t run(AuxStreams *aux);
 };
@@ -966,6 +970,18 @@ bool CholRun::looks_ahead(int k, const AuxStreams *aux) const
     return blocks <= tuning().invert_ahead_max;
 }
 
+double CholRun::work(const CholSeq &q, int k, bool sums) const
+{
+    if (!timing_active()) return 0.0;
+    double w = 0.0;
+    for (int c = 0; c < q.nclass; ++c)
+        for (int i = q.c[c].first; i < q.c[c].first + q.c[c].count; ++i) {
+            const double n = leading(i), p0 = (double)CB * k, bs = std::min<double>(CB, n - p0);
+            w += k < 0 ? n * n * n / 3.0 : bs * (2.0 * p0 * (n - p0 - bs) + p0 * (p0 + CB)) + (sums ? 0.0 : bs * bs * (n - bs));
+        }
+    return w;
+}
+
 hipError_t CholRun::run(AuxStreams *aux)
 {
     const int total = (int)idx.size();
@@ -994,14 +1010,14 @@ hipError_t CholRun::run(AuxStreams *aux)
         }
         if (e == hipSuccess)
             e = each(k, from, [&](int nt) { return nt > 2 * k ? chol_panel_parts(nt, k) : 0; },
-                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); });
+                     [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_CHOL, s, chol_panel_kernel, dim3(blocks), dim3(256), 0, q); timing_work(work(q, k), 6.0 * work(q, k, true)); });
         // Sums of row blocks k + 3 and k + 4 over the panels so far, beside steps k + 1 and k + 2.
         if (e == hipSuccess && k % 2 == 1 && k + 3 < steps && looks_ahead(k + 1, aux)) {
             hipStream_t side = aux->chain;
             if (hipEventRecord(aux->ev_panel[k], s) != hipSuccess || hipStreamWaitEvent(side, aux->ev_panel[k], 0) != hipSuccess) e = hipErrorUnknown;
             if (e == hipSuccess)
                 e = each(k + 3, k + 1, [&](int nt) { return chol_ahead_parts(nt, k + 3, k + 1); },
-                         [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_STEP, side, chol_ahead_kernel, dim3(blocks), dim3(256), 0, q); });
+                         [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_CHOL, side, chol_ahead_kernel, dim3(blocks), dim3(256), 0, q); });
             if (hipEventRecord(aux->ev_ready[k + 3], side) != hipSuccess) e = hipErrorUnknown;
             (due < 0 ? due : later) = k + 3;
         }
@@ -1026,7 +1042,7 @@ hipError_t CholRun::run(AuxStreams *aux)
                  [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_diagonal_kernel, dim3(blocks), dim3(256), 0, q); });
     if (e == hipSuccess)
         e = each(0, 0, [&](int nt) { return chol_out_parts(nt); },
-                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_FINISH, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); });
+                 [&](const CholSeq &q, unsigned blocks) { KFAC_LAUNCH(KFAC_K_INV_CHOL, s, chol_out_kernel, dim3(blocks), dim3(256), 0, q); timing_work(work(q, -1), 6.0 * work(q, -1)); });
     return e;
 }
 
