@@ -26,7 +26,6 @@
 // table of distinct sizes.
 #pragma once
 
-#include "chol_leaf.hpp"
 #include "tn_engine.hpp"
 
 namespace kfac {
@@ -156,10 +155,43 @@ __device__ __forceinline__ bool seq_locate(const InvSeq &q, int blk, int &prob, 
     return true;
 }
 
+// One pivot of the in-register 16 x 16 sweep (see sweep64_blocked): lane (lr, lk) holds D[lr][4lk..4lk+3].
+template <int K>
+__device__ __forceinline__ void sweep16_pivot(float (&d)[4], int lr, int lk, int c0, int &fail)
+{
+    float rk[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+        rk[m] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(d[m]), 0x150 + K, 0xf, 0xf, false));
+    // the pivot D[K][K] sits in lane K + 16*(K>>2), register K & 3
+    const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d[K & 3]), K + 16 * (K >> 2)));
+    if (!(p > 0.f) && fail == 0) fail = c0 + K + 1;
+    const float ip = __builtin_amdgcn_rcpf(p);   // 1 ulp reciprocal: far below the fp32 error of the sweep
+    // column element D[i][K] = D[K][i]: element i of the row, held by lane i + 16*(i>>2) in register i & 3.  (The column itself, equal
+    // up to rounding, would come without the LDS round trip of a bpermute; at a condition of 1e5 the error was 0.4 then.)
+    float mine = rk[0];
+    mine = (lr & 3) == 1 ? rk[1] : mine;
+    mine = (lr & 3) == 2 ? rk[2] : mine;
+    mine = (lr & 3) == 3 ? rk[3] : mine;
+    const float ci = __int_as_float(__builtin_amdgcn_ds_bpermute((lr + 16 * (lr >> 2)) * 4, __float_as_int(mine)));
+    const float cip = ci * ip;
+    const bool prow = (lr == K);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const float upd = __builtin_fmaf(-cip, rk[m], d[m]);
+        const float onr = rk[m] * ip;
+        float v = prow ? onr : upd;
+        if (m == (K & 3)) v = (lk == (K >> 2)) ? (prow ? -ip : cip) : v;
+        d[m] = v;
+    }
+}
+
 // Sweep of a 64 x 64 pivot block held in LDS (full symmetric storage, row pitch
 // SW_PITCH; blocks smaller than 64 are padded with the identity by the caller).  Four sub-steps of 16
-// pivots.  Per sub-step: wavefront 0 inverts the 16 x 16 pivot block inside its registers, P = X^T X with its triangular inverse
-// X (chol_leaf.hpp; 2300 cycles of the 6600 of a sub-step); then all four wavefronts
+// pivots.  Per sub-step: wavefront 0 sweeps the 16 x 16 pivot block inside its registers (lane (i, q)
+// holds D[i][4q..4q+3]; the pivot row reaches the lanes by DPP row broadcast, the pivot column, equal to
+// the row by symmetry, by one ds_bpermute: no barrier inside the 16 pivots; P = X^T X with its triangular inverse X takes half
+// the time, but at order 129 and a condition of 1e5 the error was 3.3e-2 then, below 9e-3 with this); then all four wavefronts
 // form W = V P and the rank-16 update of the other blocks on the MFMA units and write the new panel.
 // On exit S holds the swept block (-inverse).  Pb: [16][17], Wb: [64][17] scratch.
 // Returns 0 or the 1-based index (within the block) of the first non-positive pivot (valid in wave 0).
@@ -175,13 +207,30 @@ __device__ __forceinline__ int sweep64_blocked(float *S, float *Pb, float *Wb, i
         const int c0 = kb * 16;
         if (w == 0) {
             // ---- the 16 x 16 pivot block, in registers ----
-            floatx4 x = *reinterpret_cast<const floatx4 *>(S + (c0 + lr) * SW_PITCH + c0 + 4 * lk), fix, p = {0.f, 0.f, 0.f, 0.f};
-            const int f = chol_leaf(x, fix, lane);
-            if (f != 0 && fail == 0) fail = c0 + f;
+            float d[4];
+            {
+                const floatx4 v = *reinterpret_cast<const floatx4 *>(S + (c0 + lr) * SW_PITCH + c0 + 4 * lk);
+                d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+            }
+            sweep16_pivot<0>(d, lr, lk, c0, fail);
+            sweep16_pivot<1>(d, lr, lk, c0, fail);
+            sweep16_pivot<2>(d, lr, lk, c0, fail);
+            sweep16_pivot<3>(d, lr, lk, c0, fail);
+            sweep16_pivot<4>(d, lr, lk, c0, fail);
+            sweep16_pivot<5>(d, lr, lk, c0, fail);
+            sweep16_pivot<6>(d, lr, lk, c0, fail);
+            sweep16_pivot<7>(d, lr, lk, c0, fail);
+            sweep16_pivot<8>(d, lr, lk, c0, fail);
+            sweep16_pivot<9>(d, lr, lk, c0, fail);
+            sweep16_pivot<10>(d, lr, lk, c0, fail);
+            sweep16_pivot<11>(d, lr, lk, c0, fail);
+            sweep16_pivot<12>(d, lr, lk, c0, fail);
+            sweep16_pivot<13>(d, lr, lk, c0, fail);
+            sweep16_pivot<14>(d, lr, lk, c0, fail);
+            sweep16_pivot<15>(d, lr, lk, c0, fail);
+            // P = -swept block
 #pragma unroll
-            for (int m = 0; m < 4; ++m) p = __builtin_amdgcn_mfma_f32_16x16x4f32(x[m], x[m], p, 0, 0, 0);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) Pb[(4 * lk + m) * 17 + lr] = p[m] + (4 * lk + m == lr ? fix[m] : 0.f);
+            for (int m = 0; m < 4; ++m) Pb[lr * 17 + 4 * lk + m] = -d[m];
         }
         __syncthreads();
         // ---- rows 16w .. 16w + 15, a wavefront's own: W = V P, then S_ij -= W_i V_j^T for the three blocks outside the pivot row
