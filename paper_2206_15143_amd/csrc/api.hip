@@ -1000,6 +1000,7 @@ int kfac_tune(const char *key, long value)
     else if (k == "update_bm") t.update_bm = value;
     else if (k == "use_small_kernel") t.use_small_kernel = value;
     else if (k == "invert_ahead_max") t.invert_ahead_max = value;
+    else if (k == "invert_factors") t.invert_factors = value;
     else if (k == "invert_chol_min_n") t.invert_chol_min_n = value;
     else if (k == "invert_fused_max_n") t.invert_fused_max_n = value;
     else if (k == "use_corr3") t.use_corr3 = value;

@@ -1,7 +1,8 @@
 // Damped inverse of the Kronecker factors, (M + damping I)^{-1} (section 5.2 of
 // the DP-KFAC paper, matrix-inversion variant).
 //
-// Orders above invert_chol_min_n (128) up to 23000 go by their triangular factor (invert_chol.hpp, CholRun below).  The rest:
+// Orders from 1281 to 23000, and from 129 on where the work of a call makes it the faster way (choose_factors), go by their
+// triangular factor (invert_chol.hpp, CholRun below).  The rest:
 //
 // Method: blocked symmetric Gauss-Jordan ("sweep") on the lower triangle,
 // batched over matrices.  Sweeping the pivot block K of a symmetric matrix does
@@ -382,9 +383,36 @@ __global__ __launch_bounds__(256) void sweep_finish_kernel(const InvTable tab)
 }
 
 namespace {
-// (invert_refine = 0 asks for the sweep without its refinements)
-bool takes_chol(int n) { return n > tuning().invert_chol_min_n && n <= kCholMaxOrder && tuning().invert_refine; }
-bool takes_fused(int n) { return !takes_chol(n) && n <= tuning().invert_fused_max_n; }
+constexpr int kSweepMaxOrder = 1280;         // orders above this go by their triangular factor whatever else is in the call
+// `factors`: the call's choice for the orders up to that.  (invert_refine = 0 asks for the sweep without its refinements)
+bool may_chol(int n) { return n > tuning().invert_chol_min_n && n <= kCholMaxOrder && tuning().invert_refine; }
+bool takes_chol(int n, bool factors) { return may_chol(n) && (factors || n > kSweepMaxOrder); }
+bool takes_fused(int n, bool factors) { return !takes_chol(n, factors) && n <= tuning().invert_fused_max_n; }
+
+// Whether the orders up to 1280 of a call go by triangular factors.  They do beside larger ones, which they share the launches with.
+// By themselves it is a chain of launches for the largest order against the work of all: a step of the sweep is 20 us for 64 rows
+// (20 more for a last row by itself, and 1.8 for every matrix that has one), a pivot block 100 to 150 us for 256; an operation of the
+// sweep costs two and a half times as much.  Measured, us for 2, 16 and 100 matrices, sweep / factors: order 130 60 / 51, 59 / 51, 73 / 54; 256 80 / 90, 82 / 92, 115 / 101;
+// 384 119 / 200, 134 / 200, 222 / 234; 577 203 / 334, 267 / 338, 751 / 552; 768 239 / 403, 331 / 407, 1139 / 751;
+// 1024 344 / 569, 535 / 584; 1280 438 / 749, 895 / 826; 257 97 / 98, 116 / 100, 273 / 114.
+bool choose_factors(const InvertJob *jobs, int n)
+{
+    if (tuning().invert_factors >= 0) return tuning().invert_factors != 0;
+    int top = 0, rows = 0;
+    double cubes = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const double d = jobs[i].n;
+        if (!may_chol(jobs[i].n)) continue;
+        if (jobs[i].n > kSweepMaxOrder) return true;
+        top = std::max(top, jobs[i].n);
+        cubes += d * d * d;
+        rows += jobs[i].n % 64 == 1;
+    }
+    const int row = top % 64 == 1;
+    const double sweep = 20.0 * ((top - row + 63) / 64 + row) + 1.8 * rows + 2e-8 * cubes;
+    const double factors = (top <= 257 ? 95.0 : 0.58 * top) + 0.8e-8 * cubes;
+    return factors < sweep;
+}
 int chol_thin(int n) { return n > CB && n % CB == 1; }
 // row pitch of T: whole cache lines, and not a multiple of 2 KB (a column of tiles would come from few memory channels)
 int chol_ld(int n)
@@ -1407,9 +1435,9 @@ hipError_t border_launch(const InvertJob *jobs, const std::vector<int> &idx, con
 }
 
 // orders the sweep hands to the bordering: 64 k + 1 inside the range of the one-launch-per-step path
-bool takes_border(int n)
+bool takes_border(int n, bool factors)
 {
-    return tuning().invert_border && !takes_chol(n) && n > 64 && n % 64 == 1 && takes_fused(n - 1) && n - 1 <= 1280;   // 1280: the LDS vectors of the two kernels
+    return tuning().invert_border && !takes_chol(n, factors) && n > 64 && n % 64 == 1 && takes_fused(n - 1, factors) && n - 1 <= 1280;   // 1280: the LDS vectors of the two kernels
 }
 size_t border_ws_floats(int n) { return n > 64 && n % 64 == 1 && n <= 1281 ? 3 * (size_t)((n - 1 + 63) / 64 * 64) : 0; }
 }  // namespace
@@ -1425,6 +1453,7 @@ size_t invert_workspace_bytes(const InvertJob *jobs, int n)
 hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t work_bytes, hipStream_t s)
 {
     if (invert_workspace_bytes(jobs_in, n_all) > work_bytes) return hipErrorInvalidValue;
+    const bool factors = choose_factors(jobs_in, n_all);
     std::vector<size_t> offs(n_all);
     size_t off = table_bytes(n_all);
     // bordered orders: the sweep sees the leading block (same storage, same pitches), the last row and column
@@ -1436,7 +1465,7 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     for (int i = 0; i < n_all; ++i) {
         offs[i] = off;
         const int n = jobs_in[i].n;
-        if (takes_border(n)) {
+        if (takes_border(n, factors)) {
             inner[i].n = n - 1;
             inner[i].ldm = jobs_in[i].ldm > 0 ? jobs_in[i].ldm : n;
             inner[i].ldo = jobs_in[i].ldo > 0 ? jobs_in[i].ldo : n;
@@ -1454,7 +1483,7 @@ hipError_t invert_launch(const InvertJob *jobs_in, int n_all, void *work, size_t
     const InvertJob *jobs = inner.data();
     // largest matrices first so that the matrices still active at a step form a prefix
     std::vector<int> large, fused, chol;
-    for (int i = 0; i < n_all; ++i) (takes_chol(jobs_in[i].n) ? chol : takes_fused(jobs[i].n) ? fused : large).push_back(i);
+    for (int i = 0; i < n_all; ++i) (takes_chol(jobs_in[i].n, factors) ? chol : takes_fused(jobs[i].n, factors) ? fused : large).push_back(i);
     auto by_size = [&](int a, int b) { return jobs[a].n > jobs[b].n; };
     std::stable_sort(large.begin(), large.end(), by_size);
     std::stable_sort(fused.begin(), fused.end(), by_size);

@@ -1,0 +1,130 @@
+"""Inversion by triangular factors (orders above 128) at the edges of its tiles (16), column tiles (128) and pivot blocks (256), orders
+256 k + 1, whose last row goes by itself, orders whose sums run ahead beside the chain (six blocks and more, the last pair of row blocks
+whole, of one, ragged), several matrices of an order (dealt eight at a time, the rest spread); and the factor reduction with slice counts
+on either side of where a workgroup's share changes.  Against float64."""
+import numpy as np
+import pytest
+import torch
+
+import gpu_util as gu
+import paper_2206_15143_amd as kf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _by_factors():
+    kf.kfac_tune("invert_factors", 1)
+    yield
+    kf.kfac_tune("invert_factors", -1)
+
+
+def _spd(n, cond, seed):
+    """Eigenvalues from 1 / cond to 1, evenly spaced logarithms; a product of reflections as the vectors (no O(n^3) in numpy)."""
+    g = torch.Generator(device=gu.DEV)
+    g.manual_seed(seed)
+    m = torch.diag(torch.logspace(0, -np.log10(cond), n, dtype=torch.float64, device=gu.DEV))
+    for _ in range(3):
+        v = torch.randn(n, 1, generator=g, dtype=torch.float64, device=gu.DEV)
+        v /= v.norm()
+        m = m - 2 * v @ (v.T @ m)
+        m = m - 2 * (m @ v) @ v.T
+    return ((m + m.T) / 2).float()
+
+
+def _invert(mats, damping):
+    """Pairs (A, G); the part above the diagonal is not to be read."""
+    n = len(mats)
+    descs = [kf.LayerDesc.linear(a.shape[0] - 1, g.shape[0], True, kf.KFAC_F32) for a, g in mats]
+    low = lambda m: torch.where(torch.ones_like(m).tril() > 0, m, torch.full_like(m, float("nan"))).contiguous()  # noqa: E731
+    A, G = [low(a) for a, _ in mats], [low(g) for _, g in mats]
+    Ai, Gi = [torch.full_like(a, float("nan")) for a in A], [torch.full_like(g, float("nan")) for g in G]
+    info = torch.full((2 * n,), -1, dtype=torch.int32, device=gu.DEV)
+    ws = gu.workspace(kf.kfac_workspace_bytes_batched(descs, [1] * n, [1] * n, [1] * n))
+    kf.kfac_invert_batched(descs, A, G, damping, damping, Ai, Gi, info, ws)
+    torch.cuda.synchronize()
+    return Ai, Gi, info.cpu().numpy()
+
+
+def _check(m, x, damping, cond):
+    d = m.double() + damping * torch.eye(len(m), dtype=torch.float64, device=gu.DEV)
+    ref = torch.cholesky_inverse(torch.linalg.cholesky(d))
+    err = ((x.double() - ref).norm() / ref.norm()).item()
+    print(len(m), f"{err:.2e}", flush=True)
+    # elimination in fp32: cond * 2^-24 times a small factor (measured 0.02 to 0.3)
+    assert err < 1.5 * cond * 2.0 ** -24 + 2.0 ** -22
+    assert torch.equal(x, x.T)
+
+
+@pytest.mark.parametrize("n", [129, 130, 144, 145, 255, 256, 257, 258, 271, 273, 383, 384, 385, 511, 512, 513, 514, 769, 1025])
+@pytest.mark.parametrize("cond", [10.0, 1e4])
+def test_orders_at_edges(n, cond):
+    a, g = _spd(n, cond, n), _spd(n + 1, cond, n + 1)
+    Ai, Gi, info = _invert([(a, g)], 0.0)
+    assert not info.any()
+    _check(a, Ai[0], 0.0, cond)
+    _check(g, Gi[0], 0.0, cond)
+
+
+@pytest.mark.parametrize("orders", [(1281, 1282), (1536, 1537), (1553, 1792), (1793, 2049), (2177, 700)])
+def test_sums_ahead_of_the_chain(orders):
+    a, g = _spd(orders[0], 1e3, 1), _spd(orders[1], 1e3, 2)
+    for _ in range(2):                       # the second call on the streams of the first
+        Ai, Gi, info = _invert([(a, g)], 1e-3)
+        assert not info.any()
+        _check(a, Ai[0], 1e-3, 1e3)
+        _check(g, Gi[0], 1e-3, 1e3)
+
+
+@pytest.mark.parametrize("count", [3, 9])
+def test_matrices_of_several_orders(count):
+    """Two classes of column tiles of `count` matrices, one of them with and without a last row, small orders beside them."""
+    mats = [(_spd(513 if i % 2 else 400, 100.0, i), _spd(300 if i % 3 else 70, 100.0, 50 + i)) for i in range(count)]
+    Ai, Gi, info = _invert(mats, 0.01)
+    assert not info.any()
+    for (a, g), x, y in zip(mats, Ai, Gi):
+        _check(a, x, 0.01, 100.0)
+        _check(g, y, 0.01, 100.0)
+
+
+@pytest.mark.parametrize("bad", [0, 15, 16, 255, 256, 511, 512])
+def test_first_pivot_that_is_not_positive(bad):
+    """Order 513: a negative entry on the diagonal of a nearly diagonal matrix, in a tile, at its ends, in the last row."""
+    m = _spd(513, 10.0, 3) * 0.01 + torch.eye(513, device=gu.DEV)
+    m[bad, bad] = -1.0
+    _, _, info = _invert([(m, _spd(200, 10.0, 4))], 0.0)
+    assert list(info) == [bad + 1, 0]
+
+
+@pytest.mark.parametrize("orders", [[130], [200], [256], [257], [320], [577], [577] * 60, [1153] * 20, [769, 577, 300, 145, 129] * 2])
+def test_either_method_of_a_call(orders):
+    """Calls on either side of the rule that chooses for the orders up to 1280: both methods give the inverse, and so does the choice."""
+    mats = [(_spd(n, 100.0, i), _spd(8, 10.0, i)) for i, n in enumerate(orders)]
+    for way in (-1, 0, 1):
+        kf.kfac_tune("invert_factors", way)
+        Ai, Gi, info = _invert(mats, 0.01)
+        assert not info.any()
+        for (a, g), x, y in list(zip(mats, Ai, Gi))[::7]:
+            _check(a, x, 0.01, 100.0)
+            _check(g, y, 0.01, 100.0)
+
+
+@pytest.mark.parametrize("d", [255, 256, 257, 320, 321, 513])
+@pytest.mark.parametrize("rows", [512, 1024, 4096, 4608, 9000])
+def test_reduction_of_slices(d, rows):
+    """Slices of 512 rows: 1, 2, 8, 9, 18 of them."""
+    g = torch.Generator(device=gu.DEV)
+    g.manual_seed(d + rows)
+    x, y = torch.randn(rows, d, generator=g, device=gu.DEV), torch.randn(rows, 8, generator=g, device=gu.DEV)
+    desc = kf.LayerDesc.linear(d, 8, True, kf.KFAC_F32)
+    A = torch.randn(d + 1, d + 1, generator=g, device=gu.DEV)
+    A = (A + A.T) / 2
+    old, G = A.clone(), torch.zeros(8, 8, device=gu.DEV)
+    ws = gu.workspace(kf.kfac_workspace_bytes(desc, rows, 1, 1))
+    kf.kfac_update_factors(desc, x, y, rows, 1, 1, 1.0 / rows, 1.0 / rows, 0.95, A, G, ws)
+    torch.cuda.synchronize()
+    z = torch.cat([x, torch.ones(rows, 1, device=gu.DEV)], 1).double()
+    ref = float(np.float32(0.95)) * old.double() + float(1 - np.float32(0.95)) * (z.T @ z) / rows
+    assert torch.equal(A, A.T)
+    # sums of `rows` products in fp32, rounded 32 stages at a time
+    assert ((A.double() - ref).norm() / ref.norm()).item() < 1e-6
